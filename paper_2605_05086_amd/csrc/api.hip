@@ -761,6 +761,7 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
   D.rb_c8 = nullptr;
   D.rb_seg = nullptr;
   D.rb_nxb = 0;
+  D.rb_rows = kResGroupRows;
   if (D.row_c8 && P->x_small && P->exact_incremental && m > 0 && n > 0) {
     // int32 row sums: |a| <= 127 and |x| <= 128, so sum |a| < 2^24 bounds them
     bool fits = true;
@@ -770,22 +771,31 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       fits = mag < 16777216.0;
     }
     if (fits) {
-      const int32_t ng = (m + kResGroupRows - 1) / kResGroupRows;
+      // rows per workgroup: as few as still leave at most one workgroup per CU
+      // (each sweeps all of x, so more of them than CUs would only add sweeps)
+      int dev = 0, cus = 0;
+      if (hipGetDevice(&dev) != hipSuccess ||
+          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+      int32_t gr = kResGroupMin;
+      while (gr < kResGroupRows && ((int64_t)m + gr - 1) / gr > cus) gr *= 2;
+      const int32_t ng = (m + gr - 1) / gr;
+      D.rb_rows = gr;
       const int32_t nxb = (int32_t)(((int64_t)n + kResXBlock - 1) / kResXBlock);
       std::vector<int32_t> seg((size_t)ng * nxb + 1, 0);
       for (int32_t i = 0; i < m; ++i)
         for (int32_t e = rptr[i]; e < rptr[i + 1]; ++e)
-          ++seg[(size_t)(i / kResGroupRows) * nxb + rcol[e] / kResXBlock + 1];
+          ++seg[(size_t)(i / gr) * nxb + rcol[e] / kResXBlock + 1];
       for (size_t k = 1; k < seg.size(); ++k) seg[k] += seg[k - 1];
       std::vector<int32_t> fill(seg.begin(), seg.end() - 1);
       std::vector<uint32_t> ent(rcol.size());
       std::vector<int8_t> c8(rcol.size());
       for (int32_t i = 0; i < m; ++i) {
-        const int32_t g = i / kResGroupRows;
+        const int32_t g = i / gr;
         for (int32_t e = rptr[i]; e < rptr[i + 1]; ++e) {
           const int32_t b = rcol[e] / kResXBlock;
           const int32_t at = fill[(size_t)g * nxb + b]++;
-          ent[at] = ((uint32_t)(i - g * kResGroupRows) << 17) | (uint32_t)(rcol[e] - b * kResXBlock);
+          ent[at] = ((uint32_t)(i - g * gr) << 17) | (uint32_t)(rcol[e] - b * kResXBlock);
           c8[at] = (int8_t)rval[e];
         }
       }
@@ -799,6 +809,19 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       D.rb_c8 = d_c8b;
       D.rb_seg = d_seg;
       D.rb_nxb = nxb;
+    }
+  }
+  D.long_rows = nullptr;
+  D.n_long_rows = 0;
+  if (!D.rb_ent) {
+    std::vector<int32_t> lr;
+    for (int32_t i = 0; i < m; ++i)
+      if (rptr[i + 1] - rptr[i] > kResLongRow) lr.push_back(i);
+    if (!lr.empty()) {
+      int32_t* d_lr;
+      CHAP_HIP(A.upload(&d_lr, lr));
+      D.long_rows = d_lr;
+      D.n_long_rows = (int32_t)lr.size();
     }
   }
   if (!packs.empty()) {

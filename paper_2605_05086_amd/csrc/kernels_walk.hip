@@ -116,9 +116,8 @@ struct ObjState {
 // (coefficients from the int8 row copy when the instance has one), with the
 // row's products summed one after another in the row's stored
 // order (the order of the caller's CSR, as the definition is written). A
-// group of kResidualLanes lanes owns kResidualRows consecutive rows, read
-// side by side so that more loads are in flight: for each row the lanes
-// load consecutive entries and form their products (coalesced row reads),
+// group of kResidualLanes lanes owns a row: the lanes load consecutive
+// entries and form their products (coalesced row reads),
 // and every lane of the group then adds the products in entry order from
 // its neighbours' registers, so the sum is the sequential one bit for bit. On
 // instances whose row activities are exact integers (P.sums_exact) the
@@ -132,94 +131,111 @@ struct ObjState {
 // weight (the cutoff's included) does not fit.
 constexpr int kResidualLanes = 8;
 constexpr int kResidualSteps = 4;
-constexpr int kResidualRows = 1;  // consecutive rows per group (4 measured no faster: 98 against 94 us)
-static_assert(kResidualRows <= kResidualLanes, "a lane of the group writes each row");
 enum { kWeightsKeep = 0, kWeightsUnit = 1, kWeightsScatter = 2 };
 
 constexpr int kResidualRound = kResidualLanes * kResidualSteps;
 
-// Sums of the products of one group's kResidualRows rows: where the row
-// activities are exact (P.sums_exact) each lane's share, added up by the
-// caller; otherwise the whole sequential sum on every lane of the group.
-// kResidualSteps entries of each row per lane in flight, every load of a
-// round issued before its products are summed. kSmall: int8 coefficients
-// and the byte copy of x, whose products are exact integers, summed in any
-// order (instances with exact row activities); otherwise the FP64 values
-// (the byte copy of x when xc is given) and, unless P.sums_exact, the
-// sequential order within each row.
+// One row's sum by a group of kResidualLanes lanes, [rb, re) its entries:
+// where the row activities are exact (P.sums_exact) each lane's share, added
+// up by the caller; otherwise the whole sequential sum on every lane of the
+// group. kResidualSteps entries per lane in flight, every load of a round
+// issued before its products are summed. kSmall: int8 coefficients and the
+// byte copy of x, whose products are exact integers (instances with exact row
+// activities); otherwise the FP64 values (the byte copy of x when xc is
+// given) and, unless P.sums_exact, the sequential order within the row.
 template <bool kSmall>
-__device__ __forceinline__ void residual_rounds(const DevProblem& P, const double* x, const int8_t* xc, int g,
-                                                const int* beg, const int* end, int rounds, double* acc) {
-  constexpr int R = kResidualRows, S = kResidualSteps;
+__device__ __forceinline__ double residual_rounds(const DevProblem& P, const double* x, const int8_t* xc, int g,
+                                                  int rb, int re) {
+  constexpr int S = kResidualSteps;
   const gptr<const double> val = gmem(P.row_val);
   const gptr<const int8_t> c8 = gmem(P.row_c8);
   const gptr<const int32_t> col = gmem(P.row_col);
   const gptr<const double> xg = gmem(x);
   const gptr<const int8_t> xcg = gmem(xc);
-#pragma unroll
-  for (int rr = 0; rr < R; ++rr) acc[rr] = 0.0;
-  for (int t0 = 0; t0 < rounds; ++t0) {
-    int c[R][S];
+  double sum = 0.0;
+  for (int e0 = rb; e0 < re; e0 += kResidualRound) {
+    int c[S];
     if constexpr (kSmall) {
-      int a[R][S];
+      int a[S];
 #pragma unroll
-      for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-        for (int u = 0; u < S; ++u) {
-          const int e = beg[rr] + t0 * kResidualRound + u * kResidualLanes + g;
-          const bool in = e < end[rr];
-          c[rr][u] = in ? col[e] : 0;
-          a[rr][u] = in ? (int)c8[e] : 0;
-        }
-#pragma unroll
-      for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-        for (int u = 0; u < S; ++u) acc[rr] = acc[rr] + (double)(a[rr][u] * (int)xcg[c[rr][u]]);
-    }
-  }
-  if constexpr (!kSmall) {
-    // one row after another: the FP64 path keeps the register count of a
-    // single row in flight
-#pragma unroll 1
-    for (int rr = 0; rr < R; ++rr) {
-      // register arrays indexed by a loop variable would go to scratch:
-      // this row's range by selection
-      int rb = 0, re = 0;
-#pragma unroll
-      for (int t = 0; t < R; ++t)
-        if (t == rr) {
-          rb = beg[t];
-          re = end[t];
-        }
-      double sum = 0.0;
-      for (int e0 = rb; e0 < re; e0 += kResidualRound) {
-        int c[S];
-        double a[S], prod[S];
-#pragma unroll
-        for (int u = 0; u < S; ++u) {
-          const int e = e0 + u * kResidualLanes + g;
-          const bool in = e < re;
-          c[u] = in ? col[e] : 0;
-          a[u] = in ? val[e] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < S; ++u) prod[u] = a[u] * (xc ? (double)xcg[c[u]] : xg[c[u]]);
-        if (P.sums_exact) {
-#pragma unroll
-          for (int u = 0; u < S; ++u) sum = sum + prod[u];
-        } else {
-#pragma unroll
-          for (int u = 0; u < S; ++u) {
-            const int cnt = min(kResidualLanes, re - (e0 + u * kResidualLanes));
-            for (int t = 0; t < cnt; ++t) sum = sum + __shfl(prod[u], t, kResidualLanes);
-          }
-        }
+      for (int u = 0; u < S; ++u) {
+        const int e = e0 + u * kResidualLanes + g;
+        const bool in = e < re;
+        c[u] = in ? col[e] : 0;
+        a[u] = in ? (int)c8[e] : 0;
       }
 #pragma unroll
-      for (int t = 0; t < R; ++t)
-        if (t == rr) acc[t] = sum;
+      for (int u = 0; u < S; ++u) sum = sum + (double)(a[u] * (int)xcg[c[u]]);
+    } else {
+      double a[S], prod[S];
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const int e = e0 + u * kResidualLanes + g;
+        const bool in = e < re;
+        c[u] = in ? col[e] : 0;
+        a[u] = in ? val[e] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < S; ++u) prod[u] = a[u] * (xc ? (double)xcg[c[u]] : xg[c[u]]);
+      if (P.sums_exact) {
+#pragma unroll
+        for (int u = 0; u < S; ++u) sum = sum + prod[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+          const int cnt = min(kResidualLanes, re - (e0 + u * kResidualLanes));
+          for (int t = 0; t < cnt; ++t) sum = sum + __shfl(prod[u], t, kResidualLanes);
+        }
+      }
     }
   }
+  return sum;
+}
+
+// The sequential sum of one row's products by a whole wavefront, [rb, re) its
+// entries (uniform). The products of kWaveSteps x 64 entries are formed side
+// by side, every load issued before any is used; each is then read from its
+// lane into a scalar register and added in entry order, which costs an add
+// and no exchange through LDS. jmoved, xn: the value column jmoved has from
+// now on (a move being applied); -1 for none.
+constexpr int kWaveSteps = 4;
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const unsigned long long u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ double wave_row_sum(const DevProblem& P, const double* x, int rb, int re, int jmoved,
+                                               double xn) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const gptr<const double> val = gmem(P.row_val);
+  const gptr<const int32_t> col = gmem(P.row_col);
+  const gptr<const double> xg = gmem(x);
+  double sum = 0.0;
+  for (int e0 = rb; e0 < re; e0 += kWaveSteps * kWave) {
+    int c[kWaveSteps];
+    double a[kWaveSteps], prod[kWaveSteps];
+#pragma unroll
+    for (int u = 0; u < kWaveSteps; ++u) {
+      const int e = e0 + u * kWave + lane;
+      const bool in = e < re;
+      c[u] = in ? col[e] : 0;
+      a[u] = in ? val[e] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kWaveSteps; ++u) prod[u] = a[u] * (c[u] == jmoved ? xn : xg[c[u]]);
+#pragma unroll
+    for (int u = 0; u < kWaveSteps; ++u) {
+      const int cnt = min(kWave, re - (e0 + u * kWave));
+      int t = 0;
+      for (; t + 8 <= cnt; t += 8)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum = sum + read_lane(prod[u], t + k);
+      for (; t < cnt; ++t) sum = sum + read_lane(prod[u], t);
+    }
+  }
+  return sum;
 }
 
 // Writes row i's residual r and weights (kWeightsKeep: r only; Unit: 1 and
@@ -262,64 +278,63 @@ __device__ __forceinline__ void write_residual(int64_t i, double r, float w0, fl
   }
 }
 
+// Rows of more than kResLongRow entries are left to the grid's last
+// workgroups, one wavefront per row of P.long_rows: with eight lanes the
+// longest rows set the kernel's time (general instance of 100k columns and
+// rows of up to 346 entries: 32 us before).
 template <int kWeights>
-__global__ __launch_bounds__(256) void k_residual(DevProblem P, const double* __restrict__ x,
+__global__ __launch_bounds__(256) void k_residual(DevProblem P, int32_t group_blocks, const double* __restrict__ x,
                                                   const int8_t* __restrict__ xc, const WalkState* st,
                                                   uint32_t epoch, RowState* __restrict__ rs,
                                                   const int32_t* __restrict__ nidx, const uint8_t* __restrict__ pair,
                                                   const float* __restrict__ w, GatherRow* __restrict__ grow) {
-  constexpr int R = kResidualRows;
   WalkState* st_w = const_cast<WalkState*>(st);
-  const int g = threadIdx.x & (kResidualLanes - 1);
-  const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kResidualLanes * R;
-  if (i0 >= P.ms) return;  // whole groups leave together
   const bool small = xc != nullptr && st->x_misfit != epoch;
-  // lane g < R owns row i0 + g's right-hand side and weights: loaded first,
-  // they arrive while the entries are read
-  const int64_t mine = i0 + g;
-  const bool owner = g < R && mine < P.ms;
+  const bool wave = (int)blockIdx.x >= group_blocks;
+  const int lanes = wave ? kWave : kResidualLanes;
+  const int g = threadIdx.x & (lanes - 1);
+  int64_t i = ((int64_t)(blockIdx.x - (wave ? group_blocks : 0)) * blockDim.x + threadIdx.x) / lanes;
+  if (wave) {
+    if (i >= P.n_long_rows) return;  // whole wavefronts leave together
+    i = __builtin_amdgcn_readfirstlane(P.long_rows[i]);
+  }
+  if (i >= P.ms) return;  // whole groups leave together
+  const int rb = P.row_ptr[i], re = P.row_ptr[i + 1];
+  if (!wave && P.long_rows && re - rb > kResLongRow) return;
+  // lane 0 writes the row: its right-hand side and weights are loaded first
+  // and arrive while the entries are read
   double rhs = 0.0;
   float w0 = 1.0f, w1 = -1.0f;
   bool twin = false;
-  if (owner) {
-    rhs = P.row_rhs[mine];
-    if constexpr (kWeights != kWeightsKeep) twin = pair[mine] != 0;
+  if (g == 0) {
+    rhs = P.row_rhs[i];
+    if constexpr (kWeights != kWeightsKeep) twin = pair[i] != 0;
     if constexpr (kWeights == kWeightsScatter) {
-      const int k = nidx[mine];
+      const int k = nidx[i];
       w0 = w[k];
       if (twin) w1 = w[k + 1];
     }
   }
-  int beg[R], end[R], rounds = 0;
+  double sum;
+  if (wave && !P.sums_exact) {
+    sum = wave_row_sum(P, x, __builtin_amdgcn_readfirstlane(rb), __builtin_amdgcn_readfirstlane(re), -1, 0.0);
+  } else if (wave) {
+    sum = 0.0;
+    for (int e = rb + g; e < re; e += kWave) sum = sum + P.row_val[e] * x[P.row_col[e]];
 #pragma unroll
-  for (int rr = 0; rr < R; ++rr) {
-    const int64_t i = i0 + rr;
-    beg[rr] = i < P.ms ? P.row_ptr[i] : 0;
-    end[rr] = i < P.ms ? P.row_ptr[i + 1] : 0;
+    for (int o = 1; o < kWave; o <<= 1) sum = sum + __shfl_xor(sum, o, kWave);
+  } else {
+    sum = (P.row_c8 && small && P.sums_exact) ? residual_rounds<true>(P, x, xc, g, rb, re)
+                                              : residual_rounds<false>(P, x, small ? xc : nullptr, g, rb, re);
+    if (P.sums_exact) {
+#pragma unroll
+      for (int o = 1; o < kResidualLanes; o <<= 1) sum = sum + __shfl_xor(sum, o, kResidualLanes);
+    }
   }
-#pragma unroll
-  for (int rr = 0; rr < R; ++rr) rounds = max(rounds, (end[rr] - beg[rr] + kResidualRound - 1) / kResidualRound);
-  double acc[R];
-  if (P.row_c8 && small && P.sums_exact)
-    residual_rounds<true>(P, x, xc, g, beg, end, rounds, acc);
-  else
-    residual_rounds<false>(P, x, small ? xc : nullptr, g, beg, end, rounds, acc);
-  if (P.sums_exact) {
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-      for (int o = 1; o < kResidualLanes; o <<= 1) acc[rr] = acc[rr] + __shfl_xor(acc[rr], o, kResidualLanes);
-  }
-  // every lane of the group holds every row's sum; lane g writes row i0 + g
-  double sum = 0.0;
-#pragma unroll
-  for (int rr = 0; rr < R; ++rr)
-    if (g == rr) sum = acc[rr];
-  if (!owner) return;
-  write_residual<kWeights>(mine, sum - rhs, w0, w1, twin, rs, grow, st_w);
+  if (g == 0) write_residual<kWeights>(i, sum - rhs, w0, w1, twin, rs, grow, st_w);
 }
 
-// Row sums of one workgroup's kResGroupRows rows with x held in LDS: the
+// Row sums of one workgroup's P.rb_rows rows with x held in LDS: the
 // byte copy of x is swept in kResXBlock-column blocks (the next block's
 // bytes loaded into registers while the current one is used), and the
 // group's entries of each block (int8 coefficient, word = row in group and
@@ -338,8 +353,8 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
   __shared__ int32_t acc[kResGroupRows];
   __shared__ __align__(16) int8_t xs[kResXBlock];
   WalkState* st_w = const_cast<WalkState*>(st);
-  const int64_t i0 = (int64_t)blockIdx.x * kResGroupRows;
-  const int rows = (int)min((int64_t)kResGroupRows, (int64_t)P.ms - i0);
+  const int64_t i0 = (int64_t)blockIdx.x * P.rb_rows;
+  const int rows = (int)min((int64_t)P.rb_rows, (int64_t)P.ms - i0);
   const bool small = st->x_misfit != epoch;
   if (small) {
     constexpr int kV = kResXBlock / 16 / kResBlockedThreads;  // 16-byte words of a block per thread
@@ -350,26 +365,32 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
     const gptr<const int8_t> c8 = gmem(P.rb_c8);
     const int nxb = P.rb_nxb;
     const int32_t* seg = P.rb_seg + (int64_t)blockIdx.x * nxb;
-    for (int t = threadIdx.x; t < kResGroupRows; t += kResBlockedThreads) acc[t] = 0;
-    // block b's bytes: whole 16-byte words below n, single bytes past the
-    // last whole word
+    for (int t = threadIdx.x; t < rows; t += kResBlockedThreads) acc[t] = 0;
+    // block b's bytes below n: whole 16-byte words, then the single bytes of
+    // the last one (words past n are neither loaded nor read)
     int4 pre[kV];
     auto load_block = [&](int b) {
       const int64_t c0 = (int64_t)b * kResXBlock;
-      const int64_t words = ((int64_t)P.n - c0) / 16;
+      const int bytes = (int)min((int64_t)kResXBlock, (int64_t)P.n - c0);
 #pragma unroll
       for (int v = 0; v < kV; ++v) {
         const int t = threadIdx.x + v * kResBlockedThreads;
-        if (t < words) {
+        if (16 * t + 16 <= bytes) {
           pre[v] = xv[c0 / 16 + t];
-        } else {
+        } else if (16 * t < bytes) {
           int32_t part[4] = {0, 0, 0, 0};
-          for (int k = 0; k < 16; ++k) {
-            const int64_t c = c0 + 16 * (int64_t)t + k;
-            if (c < P.n) part[k >> 2] |= (int32_t)(uint8_t)xb[c] << (8 * (k & 3));
-          }
+          for (int k = 0; 16 * t + k < bytes; ++k)
+            part[k >> 2] |= (int32_t)(uint8_t)xb[c0 + 16 * t + k] << (8 * (k & 3));
           pre[v] = make_int4(part[0], part[1], part[2], part[3]);
         }
+      }
+    };
+    auto store_block = [&](int b) {
+      const int bytes = (int)min((int64_t)kResXBlock, (int64_t)P.n - (int64_t)b * kResXBlock);
+#pragma unroll
+      for (int v = 0; v < kV; ++v) {
+        const int t = threadIdx.x + v * kResBlockedThreads;
+        if (16 * t < bytes) ((int4*)xs)[t] = pre[v];
       }
     };
     int b = 0;
@@ -379,8 +400,7 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
       int nb = b + 1;
       while (nb < nxb && seg[nb] == seg[nb + 1]) ++nb;
       __syncthreads();  // the previous block's readers are done
-#pragma unroll
-      for (int v = 0; v < kV; ++v) ((int4*)xs)[threadIdx.x + v * kResBlockedThreads] = pre[v];
+      store_block(b);
       if (nb < nxb) load_block(nb);  // in flight while this block is used
       __syncthreads();
       const int e_end = seg[b + 1];
@@ -418,12 +438,9 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
     const int g = threadIdx.x & (kResidualLanes - 1);
     for (int t = threadIdx.x / kResidualLanes; t < rows; t += kResBlockedThreads / kResidualLanes) {
       const int64_t i = i0 + t;
-      const int beg[1] = {P.row_ptr[i]}, end[1] = {P.row_ptr[i + 1]};
-      const int rounds = (end[0] - beg[0] + kResidualRound - 1) / kResidualRound;
-      double sum[1];
-      residual_rounds<false>(P, x, nullptr, g, beg, end, rounds, sum);
+      double sum = residual_rounds<false>(P, x, nullptr, g, P.row_ptr[i], P.row_ptr[i + 1]);
 #pragma unroll
-      for (int o = 1; o < kResidualLanes; o <<= 1) sum[0] = sum[0] + __shfl_xor(sum[0], o, kResidualLanes);
+      for (int o = 1; o < kResidualLanes; o <<= 1) sum = sum + __shfl_xor(sum, o, kResidualLanes);
       if (g != 0) continue;
       float w0 = 1.0f, w1 = -1.0f;
       bool twin = false;
@@ -433,7 +450,7 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
         w0 = w[k];
         if (twin) w1 = w[k + 1];
       }
-      write_residual<kWeights>(i, sum[0] - P.row_rhs[i], w0, w1, twin, rs, grow, st_w);
+      write_residual<kWeights>(i, sum - P.row_rhs[i], w0, w1, twin, rs, grow, st_w);
     }
   }
 }
@@ -942,32 +959,46 @@ __global__ __launch_bounds__(256) void k_apply(const WalkCtx* __restrict__ walks
   const int gs = C.apply_blocks * blockDim.x;
   long long dv = 0;
   if (jstar >= 0 && recompute) {
-    // kResidualLanes lanes per touched row: the row is summed again in its
-    // stored order (products side by side, added in entry order)
+    // every touched row is summed again in its stored order (products side by
+    // side, added in entry order): by a wavefront while there is one per row
+    // (long rows are the likelier ones to be touched, and the longest sets
+    // the time), else by kResidualLanes lanes
     const double xn = st->mv_new;
     const int beg = P.col_ptr[jstar], end = P.col_ptr[jstar + 1];
     const int g = gt & (kResidualLanes - 1);
-    for (int e = beg + gt / kResidualLanes; e < end; e += gs / kResidualLanes) {
-      const int i = P.col_row[e];
-      double acc = 0.0;
-      const int rb = P.row_ptr[i], re = P.row_ptr[i + 1];
-      for (int e0 = rb; e0 < re; e0 += kResidualLanes) {
-        const int f = e0 + g;
-        double prod = 0.0;
-        if (f < re) {
-          const int c = P.row_col[f];
-          prod = P.row_val[f] * ((c == jstar) ? xn : x[c]);
-        }
-        const int cnt = min(kResidualLanes, re - e0);
-        for (int t = 0; t < cnt; ++t) acc = acc + __shfl(prod, t, kResidualLanes);
+    const bool wave = end - beg <= gs / kWave;
+    auto update = [&](int i, double acc) {
+      const RowState q = rs[i];
+      const double r2 = acc - P.row_rhs[i];
+      rs[i].r = r2;
+      if (C.grow) C.grow[i].r = (int32_t)r2;
+      dv += viol_change(q.r, r2, eps);
+      if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
+    };
+    if (wave) {
+      const int e = __builtin_amdgcn_readfirstlane(beg + gt / kWave);
+      if (e < end) {
+        const int i = __builtin_amdgcn_readfirstlane(P.col_row[e]);
+        const double acc = wave_row_sum(P, x, __builtin_amdgcn_readfirstlane(P.row_ptr[i]),
+                                        __builtin_amdgcn_readfirstlane(P.row_ptr[i + 1]), jstar, xn);
+        if ((threadIdx.x & (kWave - 1)) == 0) update(i, acc);
       }
-      if (g == 0) {
-        const RowState q = rs[i];
-        const double r2 = acc - P.row_rhs[i];
-        rs[i].r = r2;
-        if (C.grow) C.grow[i].r = (int32_t)r2;
-        dv += viol_change(q.r, r2, eps);
-        if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
+    } else {
+      for (int e = beg + gt / kResidualLanes; e < end; e += gs / kResidualLanes) {
+        const int i = P.col_row[e];
+        double acc = 0.0;
+        const int rb = P.row_ptr[i], re = P.row_ptr[i + 1];
+        for (int e0 = rb; e0 < re; e0 += kResidualLanes) {
+          const int f = e0 + g;
+          double prod = 0.0;
+          if (f < re) {
+            const int c = P.row_col[f];
+            prod = P.row_val[f] * ((c == jstar) ? xn : x[c]);
+          }
+          const int cnt = min(kResidualLanes, re - e0);
+          for (int t = 0; t < cnt; ++t) acc = acc + __shfl(prod, t, kResidualLanes);
+        }
+        if (g == 0) update(i, acc);
       }
     }
     dv = block_sum_ll(dv, red);
@@ -1504,16 +1535,19 @@ __global__ void k_restart_fix(WalkState* st, RestartKeep keep) {
 
 namespace {
 
-inline dim3 residual_grid(int32_t ms) {
-  const int64_t groups = ((int64_t)ms + kResidualRows - 1) / kResidualRows;
-  return dim3((unsigned)((groups * kResidualLanes + 255) / 256));
+inline int32_t residual_groups(int32_t ms) { return (int32_t)(((int64_t)ms * kResidualLanes + 255) / 256); }
+
+// k_residual's workgroups: the rows' lane groups, then the long rows' wavefronts
+inline dim3 residual_grid(const DevProblem& P) {
+  return dim3((unsigned)(residual_groups(P.ms) + (P.n_long_rows + 3) / 4));
 }
 
 }  // namespace
 
 hipError_t launch_residual(const DevProblem& P, const double* x, RowState* rs, hipStream_t stream) {
   if (P.ms > 0)
-    hipLaunchKernelGGL(k_residual<kWeightsKeep>, residual_grid(P.ms), dim3(256), 0, stream, P, x, nullptr, nullptr,
+    hipLaunchKernelGGL(k_residual<kWeightsKeep>, residual_grid(P), dim3(256), 0, stream, P,
+                       residual_groups(P.ms), x, nullptr, nullptr,
                        0u, rs, nullptr, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
@@ -1522,16 +1556,19 @@ hipError_t launch_residual(const DevProblem& P, const double* x, RowState* rs, h
 // a byte copy of x (its own fallback covers a point that does not fit).
 inline bool residual_blocked(const DevProblem& P, const int8_t* xc) { return P.rb_ent != nullptr && xc != nullptr; }
 
-inline dim3 residual_blocked_grid(int32_t ms) { return dim3((unsigned)((ms + kResGroupRows - 1) / kResGroupRows)); }
+inline dim3 residual_blocked_grid(const DevProblem& P) {
+  return dim3((unsigned)(((int64_t)P.ms + P.rb_rows - 1) / P.rb_rows));
+}
 
 hipError_t launch_residual_unit(const DevProblem& P, const uint8_t* pair, const double* x, const int8_t* xc,
                                 const WalkState* st, uint32_t epoch, RowState* rs, GatherRow* grow,
                                 hipStream_t stream) {
   if (P.ms > 0 && residual_blocked(P, xc))
-    hipLaunchKernelGGL(k_residual_blocked<kWeightsUnit>, residual_blocked_grid(P.ms), dim3(kResBlockedThreads), 0,
+    hipLaunchKernelGGL(k_residual_blocked<kWeightsUnit>, residual_blocked_grid(P), dim3(kResBlockedThreads), 0,
                        stream, P, x, xc, st, epoch, rs, nullptr, pair, nullptr, grow);
   else if (P.ms > 0)
-    hipLaunchKernelGGL(k_residual<kWeightsUnit>, residual_grid(P.ms), dim3(256), 0, stream, P, x, xc, st, epoch, rs,
+    hipLaunchKernelGGL(k_residual<kWeightsUnit>, residual_grid(P), dim3(256), 0, stream, P,
+                       residual_groups(P.ms), x, xc, st, epoch, rs,
                        nullptr, pair, nullptr, grow);
   return hipGetLastError();
 }
@@ -1540,10 +1577,11 @@ hipError_t launch_residual_scatter(const DevProblem& P, const int32_t* nidx, con
                                    const double* x, const int8_t* xc, const WalkState* st, uint32_t epoch,
                                    RowState* rs, hipStream_t stream, GatherRow* grow) {
   if (P.ms > 0 && residual_blocked(P, xc))
-    hipLaunchKernelGGL(k_residual_blocked<kWeightsScatter>, residual_blocked_grid(P.ms), dim3(kResBlockedThreads), 0,
+    hipLaunchKernelGGL(k_residual_blocked<kWeightsScatter>, residual_blocked_grid(P), dim3(kResBlockedThreads), 0,
                        stream, P, x, xc, st, epoch, rs, nidx, pair, w, grow);
   else if (P.ms > 0)
-    hipLaunchKernelGGL(k_residual<kWeightsScatter>, residual_grid(P.ms), dim3(256), 0, stream, P, x, xc, st, epoch,
+    hipLaunchKernelGGL(k_residual<kWeightsScatter>, residual_grid(P), dim3(256), 0, stream, P,
+                       residual_groups(P.ms), x, xc, st, epoch,
                        rs, nidx, pair, w, grow);
   return hipGetLastError();
 }
