@@ -57,8 +57,10 @@ typedef struct chap_run chap_run;
 typedef struct {
   double feas_tol;      /* eps; default 1e-6 */
   int32_t graph_iters;  /* tabu iterations recorded per HIP graph; 0 = 64 */
-  int32_t short_max;    /* normalised entries up to which a column is scored
-                           by one lane (1..8); 0 = 8 */
+  int32_t short_max;    /* normalised entries up to which a column of the
+                           row-staged form (row_stage) is scored by one lane
+                           (1..8); 0 = 8. Other columns of at most 64 entries
+                           take a group of lanes whatever this is */
   int32_t chunk_min;    /* entries above which an integer column with at most
                            64 values is split over workgroups; 0 = 4096 */
   int32_t chunk_len;    /* nonzeros per workgroup chunk for those columns;

@@ -51,7 +51,7 @@ hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* 
   if (nw > 1) {
     std::vector<int64_t> work(nw, 0);
     for (size_t w = 0; w < nw; ++w)
-      for (int k = KS_SHORT; k <= KS_STAGE_SCORE; ++k) work[w] += kernel_blocks(ctx[w], k);
+      for (int k = KS_GROUP; k <= KS_STAGE_SCORE; ++k) work[w] += kernel_blocks(ctx[w], k);
     std::vector<int32_t> by(nw);
     std::iota(by.begin(), by.end(), 0);
     std::stable_sort(by.begin(), by.end(), [&](int32_t a, int32_t b) { return work[a] > work[b]; });
@@ -349,9 +349,9 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
   }
   // ---- column classes and the internal column order ----------------------
   // Every kernel of the pass scores one contiguous range of internal
-  // columns: short binaries (by degree), short non-binary columns by stored
-  // degree D = 0..8, long binaries, narrow columns, chunked narrow columns,
-  // general columns by LDS sort capacity, very long general columns.
+  // columns: lane-group columns by class (binaries, then others, by width),
+  // long binaries, narrow columns, chunked narrow columns, general columns by
+  // LDS sort capacity, very long general columns.
   enum Cls { BIN, NARROW, GENERAL };
   std::vector<uint8_t> cls(n);
   for (int32_t j = 0; j < n; ++j) {
@@ -378,24 +378,31 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     stage = amax < 4194304.0 && lmax * amax <= P->eps * 17592186044416.0 &&  // 2^22, 2^44
             (int64_t)m <= (int64_t)kStageMaxRb * kStageRowBlock;
   }
-  std::vector<std::vector<int32_t>> short_seg(kShortMax + 2), sortl(kSortCaps);
+  // Lane groups (k_group) take every unstaged column of at most kGroupMax
+  // stored entries, except the narrow ones above chunk_min: one lane per
+  // entry and no sort beat the one-lane, one-wavefront and LDS-bin kernels
+  // they replace at every length up to there.
+  std::vector<std::vector<int32_t>> group(kGroupClasses), sortl(kSortCaps);
   std::vector<int32_t> flip, narrow, chunked, longg, sshort, sone;
+  auto width_class = [&](int32_t d) {
+    int c = 0;
+    while ((kGroupMin << c) < d) ++c;
+    return c;
+  };
   for (int32_t j = 0; j < n; ++j) {
-    if (ne[j] <= o.short_max) {
-      if (stage && cls[j] == NARROW && deg[j] == 1)
-        sone.push_back(j);
-      else if (stage && cls[j] == NARROW)
-        sshort.push_back(j);
-      else
-        short_seg[cls[j] == BIN ? 0 : 1 + deg[j]].push_back(j);
+    const bool is_short = ne[j] <= o.short_max;
+    if (stage && cls[j] == NARROW && is_short) {
+      (deg[j] == 1 ? sone : sshort).push_back(j);
+    } else if (cls[j] == NARROW && !is_short && ne[j] > o.chunk_min) {
+      chunked.push_back(j);
+    } else if (stage && cls[j] == NARROW) {
+      narrow.push_back(j);
+    } else if (deg[j] <= kGroupMax) {
+      group[(cls[j] == BIN ? 0 : kGroupWidths) + width_class(deg[j])].push_back(j);
     } else if (cls[j] == BIN) {
       flip.push_back(j);
     } else if (cls[j] == NARROW) {
-      if (ne[j] <= o.chunk_min) {
-        narrow.push_back(j);
-      } else {
-        chunked.push_back(j);
-      }
+      narrow.push_back(j);
     } else {
       const int32_t entries = ne[j] + 2;
       int c = 0;
@@ -406,20 +413,20 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
         longg.push_back(j);
     }
   }
-  std::stable_sort(short_seg[0].begin(), short_seg[0].end(), [&](int32_t a, int32_t b) { return deg[a] < deg[b]; });
-  std::stable_sort(flip.begin(), flip.end(), [&](int32_t a, int32_t b) { return deg[a] < deg[b]; });
   PassPlan& L = P->plan;
   std::vector<int32_t> perm;
   perm.reserve(n);
   auto append = [&](const std::vector<int32_t>& v) { perm.insert(perm.end(), v.begin(), v.end()); };
-  L.short_seg[0] = 0;
-  for (int g = 0; g < kShortMax + 2; ++g) {
-    append(short_seg[g]);
-    L.short_seg[g + 1] = (int32_t)perm.size();
+  // within a class by degree: the wavefronts of short columns end early
+  for (int g = 0; g < kGroupClasses; ++g) {
+    std::stable_sort(group[g].begin(), group[g].end(), [&](int32_t a, int32_t b) { return deg[a] < deg[b]; });
+    L.grp_col[g] = (int32_t)perm.size();
+    append(group[g]);
   }
-  L.flip_begin = (int32_t)perm.size();
+  std::stable_sort(flip.begin(), flip.end(), [&](int32_t a, int32_t b) { return deg[a] < deg[b]; });
+  L.grp_col[kGroupClasses] = (int32_t)perm.size();
   append(flip);
-  L.flip_end = (int32_t)perm.size();
+  L.grp_col[kGroupClasses + 1] = (int32_t)perm.size();
   std::vector<PackTask> packs;
   {
     int32_t q = (int32_t)perm.size();
@@ -494,6 +501,32 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     }
   }
   for (int32_t& c : rcol) c = inv[c];
+  // lane-group entries: each column's entries side by side in its lanes
+  std::vector<int32_t> grow;
+  std::vector<double> gval;
+  {
+    int32_t blocks = 0;
+    int64_t elems = 0;
+    for (int g = 0; g < kGroupClasses; ++g) {
+      const int64_t cnt = (int64_t)(L.grp_col[g + 1] - L.grp_col[g]) * (kGroupMin << (g % kGroupWidths));
+      L.grp_blk[g] = blocks;
+      L.grp_off[g] = elems;
+      blocks += (int32_t)((cnt + 255) / 256);
+      elems += (cnt + 255) / 256 * 256;
+    }
+    grow.assign((size_t)elems, -1);
+    gval.assign((size_t)elems, 1.0);
+    for (int g = 0; g < kGroupClasses; ++g) {
+      const int32_t width = kGroupMin << (g % kGroupWidths);
+      for (int32_t q = L.grp_col[g]; q < L.grp_col[g + 1]; ++q) {
+        const size_t at = (size_t)L.grp_off[g] + (size_t)(q - L.grp_col[g]) * width;
+        std::copy(crow.begin() + cptr[q], crow.begin() + cptr[q + 1], grow.begin() + at);
+        std::copy(cval.begin() + cptr[q], cval.begin() + cptr[q + 1], gval.begin() + at);
+      }
+    }
+    L.grp_blk[kGroupClasses] = blocks;
+    L.grp_blk[kGroupClasses + 1] = blocks + ((int32_t)flip.size() + 3) / 4;
+  }
   // chunk tasks of long narrow columns: each column's entries are cut at the
   // kXcds row-range boundaries and into pieces of chunk_len; the task list
   // interleaves the ranges so that task t gathers from range t mod kXcds
@@ -810,6 +843,14 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       D.rb_seg = d_seg;
       D.rb_nxb = nxb;
     }
+  }
+  if (!grow.empty()) {
+    int32_t* dr;
+    double* dv;
+    CHAP_HIP(A.upload(&dr, grow));
+    CHAP_HIP(A.upload(&dv, gval));
+    L.grp_row = dr;
+    L.grp_val = dv;
   }
   D.long_rows = nullptr;
   D.n_long_rows = 0;
@@ -1409,28 +1450,26 @@ int slot_setup(const chap_problem* p, WalkSlot& S) {
     // with the affected columns of each iteration (or with all columns)
     const int32_t n = p->n;
     const int32_t cap = p->opt.rescore_cap;
-    const int32_t* seg = p->plan.short_seg;
+    const int32_t g0 = p->plan.grp_col[0], g1 = p->plan.grp_col[kGroupClasses];  // lane-group columns
     AffLists& F = S.aff;
     CHAP_HIP(S.A.alloc(&F.stamp, (size_t)std::max<int32_t>(n, 1)));
-    CHAP_HIP(S.A.alloc(&F.slist, (size_t)cap + (size_t)kWave * kAffClasses));
+    CHAP_HIP(S.A.alloc(&F.slist, (size_t)cap));
     CHAP_HIP(S.A.alloc(&F.olist, (size_t)cap));
     CHAP_HIP(S.A.alloc(&F.ooff, (size_t)cap + 1));
     CHAP_HIP(S.A.alloc(&F.run, 1));
     CHAP_HIP(hipMemset(F.run, 0, sizeof(AffRun)));
     F.cap = cap;
-    // all columns, split as an iteration's list is, when every column outside
-    // the short range has a subset form
+    // the columns outside the lane-group range, when each has a subset form
     bool all = n > 0;
-    std::vector<int32_t> sl, ol, oo(1, 0);
-    for (int c = 0; c < kAffClasses; ++c) {
-      const int32_t lo = seg[c], hi = seg[c + 1];
-      for (int32_t q = lo; q < hi; ++q) sl.push_back(q);
-      while (sl.size() % kWave) sl.push_back(-1);
-    }
+    std::vector<int32_t> ol, oo(1, 0);
+    S.aff_general = 0;
+    S.aff_other = 0;
     for (int32_t q = 0; q < n; ++q) {
-      if (q >= seg[0] && q < seg[kShortMax + 2]) continue;
+      if (q >= g0 && q < g1) continue;
       const uint8_t cl = p->sub_cls[q];
       if (cl == SUB_NONE) all = false;
+      if (cl == SUB_GENERAL) S.aff_general = 1;
+      S.aff_other = 1;
       ol.push_back(q);
       const int32_t c = (cl == SUB_GENERAL || cl == SUB_NONE)
                             ? 0
@@ -1439,14 +1478,11 @@ int slot_setup(const chap_problem* p, WalkSlot& S) {
     }
     int64_t sub_cap = p->nnz / kSubsetChunk + cap + 1;
     if (all) {
-      int32_t *d_sl = nullptr, *d_ol = nullptr, *d_oo = nullptr;
-      CHAP_HIP(S.A.upload(&d_sl, sl.empty() ? std::vector<int32_t>(1, -1) : sl));
+      int32_t *d_ol = nullptr, *d_oo = nullptr;
       CHAP_HIP(S.A.upload(&d_ol, ol.empty() ? std::vector<int32_t>(1, 0) : ol));
       CHAP_HIP(S.A.upload(&d_oo, oo));
-      F.full_slist = d_sl;
       F.full_olist = d_ol;
       F.full_ooff = d_oo;
-      F.n_full_s = (int32_t)sl.size();
       F.n_full_o = (int32_t)ol.size();
       F.full_chunks = oo.back();
       sub_cap = std::max<int64_t>(sub_cap, oo.back());
@@ -1457,7 +1493,7 @@ int slot_setup(const chap_problem* p, WalkSlot& S) {
     uint8_t* d_cls;
     CHAP_HIP(S.A.upload(&d_cls, p->sub_cls));
     L.cls = d_cls;
-    L.short_lane = 1;
+    L.group_role = 1;
     L.K[0] = cap;
     L.sel[0] = F.olist;
     L.sub_off = F.ooff;
@@ -1467,8 +1503,6 @@ int slot_setup(const chap_problem* p, WalkSlot& S) {
     CHAP_HIP(hipMemset(L.ls, 0, sizeof(LearnState)));
     CHAP_HIP(S.A.alloc(&S.aff_L, 1));
     CHAP_HIP(hipMemcpy(S.aff_L, &L, sizeof(LearnCtx), hipMemcpyHostToDevice));
-    S.aff_general = 0;
-    for (uint8_t c : p->sub_cls) S.aff_general |= (c == SUB_GENERAL) ? 1 : 0;
   }
   return CHAP_OK;
 }
@@ -1484,17 +1518,16 @@ int slot_graph(WalkSlot& S, int64_t K, int compact, hipGraphExec_t* out) {
   CHAP_HIP(hipStreamBeginCapture(S.s, hipStreamCaptureModeThreadLocal));
   hipError_t cap_err = hipSuccess;
   const AffLists& F = S.aff;
-  const int32_t n = S.ctx.P.n;
   for (int64_t q = 0; q < K && cap_err == hipSuccess; ++q) {
     if (S.aff_L) {
       // affected rescoring: the lists, the full pass only where no split of
-      // all columns exists, the short columns by lanes, the rest by the
+      // all columns exists, the lane-group columns by groups, the rest by the
       // subset kernels
       cap_err = launch_affected(S.L.walks, S.aff_L, F, S.s);
-      if (cap_err == hipSuccess && !F.full_slist) cap_err = launch_pass(S.L, S.s, &S.ps, true);
+      if (cap_err == hipSuccess && !F.full_olist) cap_err = launch_pass(S.L, S.s, &S.ps, true);
       if (cap_err == hipSuccess) {
-        const int g[4] = {std::min(1024, (n + 255) / 256), S.aff_general ? std::min(256, (n + 3) / 4) : 0,
-                          std::min(256, F.sub_cap), S.aff_general ? 32 : 0};
+        const int g[3] = {std::min(1024, std::max(1, S.ctx.plan.grp_blk[kGroupClasses])),
+                          S.aff_other ? std::min(256, F.sub_cap) : 0, S.aff_general ? 32 : 0};
         cap_err = launch_aff_score(S.L.walks, S.aff_L, F.run, g, 64, compact, S.s);
       }
     } else {

@@ -98,8 +98,15 @@ constexpr int kXcds = 8;           // L2 domains (XCDs) of an MI355X; chunks are
 constexpr int kWave = 64;          // lanes of a gfx950 wavefront
 constexpr int kNarrowBins = 64;
 constexpr int32_t kStageUnitMask = 0x0FFFFFFF;    // values of a narrow integer column
-constexpr int kSortCaps = 4;       // LDS sort capacities: 64, 256, 1024, 4096
-constexpr int kSortCap[kSortCaps] = {64, 256, 1024, 4096};
+constexpr int kSortCaps = 3;       // LDS sort capacities: 256, 1024, 4096
+constexpr int kSortCap[kSortCaps] = {256, 1024, 4096};
+// columns of at most kGroupMax stored entries outside the staged tasks are
+// scored by groups of 4, 8, 16, 32 or 64 lanes: classes 0..4 hold binaries,
+// 5..9 other columns, by that width
+constexpr int kGroupWidths = 5;
+constexpr int kGroupClasses = 2 * kGroupWidths;
+constexpr int kGroupMin = 4;
+constexpr int kGroupMax = 64;
 constexpr int kResGroupRows = 4096;  // most rows per workgroup of the x-block residual kernel
 constexpr int kResGroupMin = 64;     // fewest (an instance's own count: DevProblem::rb_rows)
 constexpr int kResLongRow = 32;      // entries above which a wavefront sums a row (k_residual)
@@ -319,10 +326,17 @@ struct LongTask {
 // order in which each kernel's columns form one contiguous range of internal
 // indices.
 struct PassPlan {
-  // short columns: binaries [short_seg[0], short_seg[1]), then non-binary
-  // columns with D stored entries [short_seg[1+D], short_seg[2+D])
-  int32_t short_seg[kShortMax + 3] = {0};
-  int32_t flip_begin = 0, flip_end = 0;
+  // lane-group columns: class c holds the internal columns [grp_col[c],
+  // grp_col[c + 1]) and the workgroups [grp_blk[c], grp_blk[c + 1]) of the
+  // group kernel; then the binaries of more than kGroupMax entries, a
+  // wavefront each. Entry l of the class's i-th column is element grp_off[c] +
+  // i * width + l of grp_row (-1: none) and grp_val, so a lane reads its entry
+  // without the column's offset
+  int32_t grp_col[kGroupClasses + 2] = {0};
+  int32_t grp_blk[kGroupClasses + 2] = {0};
+  int64_t grp_off[kGroupClasses] = {0};
+  const int32_t* grp_row = nullptr;
+  const double* grp_val = nullptr;
   // packs of whole narrow columns
   const PackTask* packs = nullptr;
   int32_t n_packs = 0;
@@ -399,8 +413,7 @@ struct WalkCtx {
 
 // Kernels of one iteration; each has its own per-walk block counts.
 enum KernelSlot {
-  KS_SHORT = 0,
-  KS_FLIP,
+  KS_GROUP = 0,
   KS_PACK,
   KS_CHUNK,
   KS_COMBINE,
@@ -458,21 +471,21 @@ __device__ __forceinline__ int block_walk(const int32_t* __restrict__ off, int n
   return lo;
 }
 
-// Side streams on which the pass kernels run beside the main stream (they
-// write disjoint columns): fork and join events order them with the main
-// stream, also under graph capture.
+// Side stream on which the long-column kernels of unstaged columns run
+// beside the main stream (they write disjoint columns): fork and join events
+// order it with the main stream, also under graph capture.
 struct PassStreams {
-  hipStream_t side[2] = {nullptr, nullptr};
+  hipStream_t side = nullptr;
   hipEvent_t fork = nullptr;
-  hipEvent_t join[2] = {nullptr, nullptr};
+  hipEvent_t join = nullptr;
   hipError_t create();
   void destroy();
 };
 
 // ---- launchers (kernels_pass.hip) -----------------------------------------
 // One exact best-shift pass over all columns of every walk of the batch;
-// with `ps`, the short-column and long-column kernels run on side streams
-// beside the pack kernel. With defer_combine, a pass for which
+// with `ps`, the long-column kernels of unstaged columns run on its side
+// stream. With defer_combine, a pass for which
 // pass_defers_combine(L) holds leaves the long narrow columns' partial bins
 // uncombined: the move selection that follows (launch_walk_choose with
 // combine) scores them while it scans.
@@ -651,9 +664,9 @@ struct LearnCtx {
   const uint8_t* cls;        // SUB_* per internal column
   const int32_t* elig_list;  // internal indices of proposable columns
   int32_t n_elig;
-  // 1: listed short columns (the plan's short range) are scored one per lane
-  // by k_aff_score's lane role, and the subset kernels leave them alone
-  int32_t short_lane;
+  // 1: listed columns of the plan's lane-group range are scored by
+  // k_aff_score's group role, and the subset kernels leave them alone
+  int32_t group_role;
   int32_t mp;                // normalised rows (for the violated fraction)
   double c_max;              // max |c_j| (0 when c = 0)
   // row refresh work: short proposable columns, chunks of long ones
@@ -758,31 +771,27 @@ hipError_t launch_subset_grids(const WalkCtx* C, const LearnCtx* L, int chunk_gr
                                int has_general, int compact, hipStream_t s);
 
 // The lists of affected rescoring. The affected columns of an iteration are
-// split into its short columns (slist: grouped by short class, binaries then
-// D = 0..8 stored entries, each class padded with -1 to a multiple of 64 so
-// that a wavefront holds one class) and the rest (olist, with the subset
-// chunk offsets ooff). When every column has a subset form, the same split
-// of all columns (full_*) serves iterations that must score every column.
+// split into its lane-group columns (slist) and the rest (olist, with the
+// subset chunk offsets ooff). When every column outside the lane-group range
+// has a subset form, iterations that must score every column take the whole
+// range and the list of all others (full_*) instead of the full pass.
 struct AffRun {
-  const int32_t* slist;  // short columns of this iteration (-1: padding)
-  int32_t n_s;           // entries of slist, padding included
+  const int32_t* slist;  // lane-group columns of this iteration
+  int32_t n_s;           // entries of slist; -1: the whole lane-group range
   int32_t pad_;
 };
-constexpr int kAffClasses = kShortMax + 2;  // binaries, then D = 0..kShortMax
 constexpr int kAffRows = 256;  // rows of a moved column up to which its affected columns are listed
 
 struct AffLists {
   int32_t* stamp = nullptr;  // n
-  int32_t* slist = nullptr;  // cap + 64 kAffClasses
+  int32_t* slist = nullptr;  // cap
   int32_t* olist = nullptr;  // cap
   int32_t* ooff = nullptr;   // cap + 1
   AffRun* run = nullptr;     // 1
   int32_t cap = 0;
   int32_t sub_cap = 0;
-  const int32_t* full_slist = nullptr;  // null: those iterations run the full pass
-  const int32_t* full_olist = nullptr;
+  const int32_t* full_olist = nullptr;  // null: those iterations run the full pass
   const int32_t* full_ooff = nullptr;
-  int32_t n_full_s = 0;
   int32_t n_full_o = 0;
   int32_t full_chunks = 0;
 };
@@ -825,10 +834,11 @@ hipError_t launch_hamming(const HamTask* tasks, int32_t ntasks, int32_t* dist, h
 // record.
 hipError_t launch_restart_fix(WalkState* st, const RestartKeep& keep, hipStream_t s);
 // The whole scoring of an affected-rescoring iteration: one launch whose
-// workgroups take four roles: the short columns by lanes (g[0]), general
-// columns of at most 64 breakpoints by wavefronts (g[1]), the subset chunks
-// (g[2]) and the subset general columns (g[3]); then the subset combine.
-hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[4], int combine_grid,
+// workgroups take two roles: the lane-group columns (g[0]) and the subset
+// chunks (g[1]); then, with g[2] > 0 workgroups, the subset general columns
+// (their LDS sort would keep the other roles at one workgroup per CU); then
+// the subset combine.
+hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[3], int combine_grid,
                             int compact, hipStream_t s);
 // Move choice over the proposal set and the stored-row update of its move
 // (kernels_walk.hip).
@@ -975,7 +985,8 @@ struct WalkSlot {
   AffLists aff{};
   LearnCtx* aff_L = nullptr;     // device record for the subset pass
   LearnCtx aff_Lh{};             // its host copy
-  int aff_general = 0;           // the problem has general columns
+  int aff_other = 0;             // the problem has columns outside the lane-group range
+  int aff_general = 0;           // the problem has general columns outside the lane-group range
   WalkSlot() = default;
   WalkSlot(const WalkSlot&) = delete;
   WalkSlot& operator=(const WalkSlot&) = delete;

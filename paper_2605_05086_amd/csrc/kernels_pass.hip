@@ -5,18 +5,21 @@
 // variable, and for every other variable the result of Algorithm 1 ("Best
 // Shift via Sort-Scan-Argmax"). Columns are routed by class and length:
 //
-//   k_short        one lane per column with at most 8 normalised entries;
-//                  scores every candidate position directly (bounds and
-//                  breakpoints, incumbent excluded) from the penalty
-//                  definition written in breakpoint form.
-//   k_flip_wave    one wavefront per longer binary column (flip score).
-//   k_narrow_pack  integer columns with <= 64 values, packed whole into
+//   k_group        columns with at most 64 stored entries: 4, 8, 16, 32 or 64
+//                  lanes per column, one stored entry each. Binaries: the flip
+//                  score, summed across the group. Others: every candidate
+//                  position (bounds and breakpoints, incumbent excluded) is
+//                  scored directly from the penalty definition written in
+//                  breakpoint form, each lane scoring its own entry's
+//                  candidates against all entries. Longer binaries: one
+//                  wavefront per column.
+//   k_narrow_pack  longer integer columns with <= 64 values, packed whole into
 //                  workgroups: the sort of Algorithm 1 becomes a counting sort
 //                  into 64 LDS bins per column, the scan a wavefront prefix
 //                  sum, the argmax a wavefront reduction over candidate bins.
 //   k_narrow_chunk the same for long columns split over many workgroups by
 //                  row range; k_narrow_combine adds the partial bins.
-//   k_sort_block   one workgroup per general column: LDS bitonic sort of the
+//   k_sort_block   one workgroup per longer general column: LDS bitonic sort of the
 //                  breakpoints, block scan, block argmax.
 //   k_sort_long    general columns beyond the LDS capacity: the same steps in
 //                  global scratch memory.
@@ -199,259 +202,262 @@ __device__ __forceinline__ unsigned long long wave_or(unsigned long long v) {
 
 
 // ---------------------------------------------------------------------------
-// k_short: one lane per column (at most 8 normalised entries).
+// k_group: a group of lanes per column (at most kGroupMax stored entries).
+//
+// Bound: latency. The columns are short, so the kernel is one chain of loads
+// (row index and coefficient of the lane's entry, its row state) followed by a
+// few hundred instructions; a lane per entry makes every load of a column one
+// request, starts all chains at once and needs one division per lane where a
+// lane per column needs one per entry. On the general instance of 100k
+// columns it replaces three kernels on forked streams (one lane per column of
+// at most 8 normalised entries 25-30 us, one wavefront per longer binary
+// 5-15 us, a bitonic sort across a wavefront per longer general column 30 us,
+// and the events between them).
 // ---------------------------------------------------------------------------
 
-template <typename Rows>
-__device__ __forceinline__ void flip_column(const DevProblem& P, const double* x, const Rows& rs,
-                                            const WalkState* st, double* xhat, double* sc, int q) {
+// One normalised entry in breakpoint form: satisfied at p when p <= t (a > 0)
+// or p >= t (a < 0); what it adds to the score where it is satisfied, and
+// where it is not on either side of xbar.
+struct GroupTerm {
+  double t;
+  float sat;    // satisfied
+  float left;   // not satisfied, p < xbar
+  float right;  // not satisfied, p > xbar
+  uint32_t ap;  // a > 0
+};
+
+struct GroupSmem {
+  GroupTerm term[2][256];  // a lane's row and its twin
+};
+
+__device__ __forceinline__ GroupTerm group_term(double t, bool ap, float w, double xb) {
+  GroupTerm g;
+  const bool s0 = ap ? (xb <= t) : (xb >= t);
+  g.t = t;
+  g.ap = ap ? 1u : 0u;
+  g.sat = s0 ? 0.0f : w;
+  g.left = s0 ? -w : (ap ? 0.5f * w : -0.5f * w);
+  g.right = s0 ? -w : (ap ? -0.5f * w : 0.5f * w);
+  return g;
+}
+
+__device__ __forceinline__ double term_at(const GroupTerm& g, double p, bool right) {
+  const float sat = g.sat, left = g.left, rgt = g.right;  // values, not addresses, to select from
+  const bool le = p <= g.t, ge = p >= g.t;
+  const bool s1 = g.ap ? le : ge;
+  const float off = right ? rgt : left;
+  return (double)(s1 ? sat : off);
+}
+
+// Orders the LDS writes and reads of one wavefront.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Column q by the G lanes of its group; row, a: this lane's stored entry (row
+// < 0: none; a column's entries fill its first lanes). Groups without a column
+// (in = false) take part in the exchanges and write nothing.
+template <int G, bool kFlip, typename Rows>
+__device__ __forceinline__ void score_group(const WalkCtx& C, const Rows& rs, const WalkState* st, int q, bool in,
+                                            int row, double a, GroupSmem& S) {
+  const DevProblem& P = C.P;
+  const int tid = threadIdx.x, g = tid & (G - 1);
   const double eps = P.eps;
-  const double xb = x[q];
+  const bool has = row >= 0;
+  const double xb = gmem((const double*)C.x)[q];
+  const double c = st->cut_active ? gmem(P.obj)[q] : 0.0;
+  RowState r{0.0, 0.0f, -1.0f};
+  if (has) r = rs[row];
+  if constexpr (kFlip) {
+    const double xn = 1.0 - xb, d = xn - xb;
+    double s = 0.0;
+    if (has) {
+      const double r2 = r.r + a * d;
+      s = penalty(r.r, r2, (double)r.w0, eps);
+      if (r.w1 >= 0.0f) s += penalty(-r.r, -r2, (double)r.w1, eps);
+    }
+    if (g == 0 && c != 0.0) s += penalty(st->rc, st->rc + c * d, (double)st->wc, eps);
+#pragma unroll
+    for (int o = 1; o < G; o <<= 1) s += __shfl_xor(s, o, kWave);
+    if (g == 0 && in) write_result(gmem(C.xhat), gmem(C.s), q, true, s, xn, xb);
+    return;
+  }
+  const bool isint = gmem(P.is_int)[q] != 0;
+  const double l = gmem(P.lb)[q], u = gmem(P.ub)[q];
+  const bool twin = has && r.w1 >= 0.0f;
+  const GroupTerm g0 = group_term(has ? breakpoint(xb, r.r, a, eps, isint) : 0.0, a > 0.0, r.w0, xb);
+  const GroupTerm g1 = group_term(twin ? breakpoint(xb, -r.r, -a, eps, isint) : 0.0, !(a > 0.0),
+                                  twin ? r.w1 : 0.0f, xb);
+  const bool any_twin = __any(twin);
+  S.term[0][tid] = g0;
+  if (any_twin) S.term[1][tid] = g1;
+  wave_sync();
+  GroupTerm gc{0.0, 0.0f, 0.0f, 0.0f, 0u};
+  if (c != 0.0) gc = group_term(breakpoint(xb, st->rc, c, eps, isint), c > 0.0, st->wc, xb);
+  // this lane's candidates: its entry's breakpoints, and a bound (lanes 0 and
+  // 1) or the cutoff row's breakpoint (lane 2)
+  const double none = HUGE_VAL;  // never inside finite bounds, excluded by isfinite otherwise
+  double p[3];
+  p[0] = has ? g0.t : none;
+  p[1] = twin ? g1.t : none;
+  p[2] = g == 0 ? l : (g == 1 ? u : ((g == 2 && c != 0.0) ? gc.t : none));
+  bool right[3];
+  double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) right[k] = p[k] > xb;
+  // entries fill the first lanes of every group: the wavefront runs to the
+  // longest of its columns
+  unsigned long long m = __ballot(has);
+#pragma unroll
+  for (int o = 32; o >= G; o >>= 1) m |= m >> o;
+  if constexpr (G < kWave) m &= (1ull << (G & 63)) - 1ull;
+  const int cnt = 64 - __builtin_clzll(m | 1ull) - (m == 0ull ? 1 : 0);
+  const int base = tid & ~(G - 1);
+  if (any_twin) {
+    for (int e = 0; e < cnt; ++e) {
+      const GroupTerm t0 = S.term[0][base + e], t1 = S.term[1][base + e];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        v[k] += term_at(t0, p[k], right[k]);
+        v[k] += term_at(t1, p[k], right[k]);
+      }
+    }
+  } else {
+    for (int e = 0; e < cnt; ++e) {
+      const GroupTerm t0 = S.term[0][base + e];
+      v[0] += term_at(t0, p[0], right[0]);
+      v[2] += term_at(t0, p[2], right[2]);
+    }
+  }
+  double best = -HUGE_VAL, at = HUGE_VAL;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (!(p[k] >= l && p[k] <= u) || p[k] == xb || !isfinite(p[k])) continue;
+    const double val = v[k] + term_at(gc, p[k], right[k]);
+    if (val > best || (val == best && p[k] < at)) {
+      best = val;
+      at = p[k];
+    }
+  }
+#pragma unroll
+  for (int o = 1; o < G; o <<= 1) {
+    const double ov = __shfl_xor(best, o, kWave), op = __shfl_xor(at, o, kWave);
+    if (ov > best || (ov == best && op < at)) {
+      best = ov;
+      at = op;
+    }
+  }
+  if (g == 0 && in) write_result(gmem(C.xhat), gmem(C.s), q, best > -HUGE_VAL, best, at, xb);
+}
+
+template <int G, bool kFlip, typename Rows>
+__device__ __forceinline__ void group_block(const WalkCtx& C, const Rows& rs, const WalkState* st, int cls, int b,
+                                            GroupSmem& S) {
+  const PassPlan& L = C.plan;
+  const int64_t t = L.grp_off[cls] + (int64_t)b * 256 + (int)threadIdx.x;
+  const int row = gmem(L.grp_row)[t];
+  const double a = gmem(L.grp_val)[t];
+  const int q = L.grp_col[cls] + b * (256 / G) + (int)threadIdx.x / G, end = L.grp_col[cls + 1];
+  score_group<G, kFlip, Rows>(C, rs, st, min(q, end - 1), q < end, row, a, S);
+}
+
+// A binary column of any length by one wavefront.
+template <typename Rows>
+__device__ __forceinline__ void flip_wave(const WalkCtx& C, const Rows& rs, const WalkState* st, int q) {
+  const DevProblem& P = C.P;
+  const int lane = threadIdx.x & (kWave - 1);
+  const double eps = P.eps;
+  const double xb = gmem((const double*)C.x)[q];
   const double xn = 1.0 - xb;
   const double d = xn - xb;
   double s = 0.0;
-  const int beg = P.col_ptr[q], end = P.col_ptr[q + 1];
-  // at most kShortMax entries here: every gather is issued before any is used
-  RowState rr[kShortMax];
-  double av[kShortMax];
-#pragma unroll
-  for (int k = 0; k < kShortMax; ++k) {
-    if (beg + k < end) {
-      av[k] = P.col_val[beg + k];
-      rr[k] = rs[P.col_row[beg + k]];
-    }
+  const int beg = gmem(P.col_ptr)[q], end = gmem(P.col_ptr)[q + 1];
+  for (int e = beg + lane; e < end; e += kWave) {
+    const RowState r = rs[gmem(P.col_row)[e]];
+    const double r2 = r.r + gmem(P.col_val)[e] * d;
+    s += penalty(r.r, r2, (double)r.w0, eps);
+    if (r.w1 >= 0.0f) s += penalty(-r.r, -r2, (double)r.w1, eps);
   }
-#pragma unroll
-  for (int k = 0; k < kShortMax; ++k) {
-    if (beg + k < end) {
-      const RowState& r = rr[k];
-      const double r2 = r.r + av[k] * d;
-      s += penalty(r.r, r2, (double)r.w0, eps);
-      if (r.w1 >= 0.0f) s += penalty(-r.r, -r2, (double)r.w1, eps);
-    }
+  if (lane == 0 && st->cut_active) {
+    const double c = gmem(P.obj)[q];
+    if (c != 0.0) s += penalty(st->rc, st->rc + c * d, (double)st->wc, eps);
   }
-  if (st->cut_active) {
-    const double c = P.obj[q];
-    if (c != 0.0) {
-      const double r2 = st->rc + c * d;
-      s += penalty(st->rc, r2, (double)st->wc, eps);
-    }
-  }
-  write_result(xhat, sc, q, true, s, xn, xb);
+  s = wave_sum(s);
+  if (lane == 0) write_result(gmem(C.xhat), gmem(C.s), q, true, s, xn, xb);
 }
 
-// Normalised entries of a short column held in compile-time indexed slots.
-struct ShortSlots {
-  double tau[kShortMax];
-  double w[kShortMax];
-  uint32_t apos = 0, sat0 = 0;
-  int ns = 0;
-  __device__ __forceinline__ void push(double t, double wt, bool ap, double xb) {
-#pragma unroll
-    for (int k = 0; k < kShortMax; ++k)
-      if (k == ns) {
-        tau[k] = t;
-        w[k] = wt;
-      }
-    const bool s0 = ap ? (xb <= t) : (xb >= t);
-    apos |= (ap ? 1u : 0u) << ns;
-    sat0 |= (s0 ? 1u : 0u) << ns;
-    ns += 1;
-  }
-};
-
-// Scores every candidate position of a short column (both bounds and the
-// breakpoints inside [l, u], xbar excluded) from the penalty definition: the
-// largest score, the smallest position on ties.
-__device__ __forceinline__ void short_best(const ShortSlots& S, double l, double u, double xb, bool& found,
-                                           double& best, double& bestp) {
-  found = false;
-  best = 0.0;
-  bestp = xb;
-  auto consider = [&](double p) {
-    if (!(p >= l && p <= u) || p == xb || !isfinite(p)) return;
-    double v = 0.0;
-#pragma unroll
-    for (int k = 0; k < kShortMax; ++k) {
-      if (k < S.ns) {
-        const bool ap = (S.apos >> k) & 1u;
-        const bool s0 = (S.sat0 >> k) & 1u;
-        const bool s1 = ap ? (p <= S.tau[k]) : (p >= S.tau[k]);
-        double c;
-        if (s0)
-          c = s1 ? 0.0 : -S.w[k];
-        else if (s1)
-          c = S.w[k];
-        else
-          c = (ap ? (p < xb) : (p > xb)) ? 0.5 * S.w[k] : -0.5 * S.w[k];
-        v += c;
-      }
-    }
-    if (!found || v > best || (v == best && p < bestp)) {
-      found = true;
-      best = v;
-      bestp = p;
-    }
-  };
-  consider(l);
-  consider(u);
-#pragma unroll
-  for (int k = 0; k < kShortMax; ++k)
-    if (k < S.ns) consider(S.tau[k]);
-}
-
-template <int D, typename Rows>
-__device__ __forceinline__ void short_general(const DevProblem& P, const double* x, const Rows& rs,
-                                              const WalkState* st, double* xhat, double* sc, int q) {
-  const double eps = P.eps;
-  const double xb = x[q];
-  const bool isint = P.is_int[q] != 0;
-  const double l = P.lb[q], u = P.ub[q];
-  const int beg = P.col_ptr[q];
-  ShortSlots S;
-#pragma unroll
-  for (int k = 0; k < kShortMax; ++k) {
-    S.tau[k] = 0.0;
-    S.w[k] = 0.0;
-  }
-  // loads of all D entries first (independent), then the breakpoints
-  RowState rr[D > 0 ? D : 1];
-  double av[D > 0 ? D : 1];
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    av[k] = P.col_val[beg + k];
-    rr[k] = rs[P.col_row[beg + k]];
-  }
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const double a = av[k];
-    S.push(breakpoint(xb, rr[k].r, a, eps, isint), (double)rr[k].w0, a > 0.0, xb);
-    if (rr[k].w1 >= 0.0f) S.push(breakpoint(xb, -rr[k].r, -a, eps, isint), (double)rr[k].w1, -a > 0.0, xb);
-  }
-  if (st->cut_active) {
-    const double c = P.obj[q];
-    if (c != 0.0) S.push(breakpoint(xb, st->rc, c, eps, isint), (double)st->wc, c > 0.0, xb);
-  }
-  bool found;
-  double best, bestp;
-  short_best(S, l, u, xb, found, best, bestp);
-  write_result(xhat, sc, q, found, best, bestp, xb);
-}
-
-// Short columns occupy the internal range [seg[0], seg[10]): binaries in
-// [seg[0], seg[1]), then non-binary columns with D stored entries in
-// [seg[1 + D], seg[2 + D]) for D = 0..8.
+// Workgroup b of the lane-group columns.
 template <typename Rows>
-__global__ __launch_bounds__(256) void k_short(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
+__device__ __forceinline__ void group_task(const WalkCtx& C, const Rows& rs, const WalkState* st, int b,
+                                           GroupSmem& S) {
+  const int32_t* blk = C.plan.grp_blk;
+  int c = 0;
+#pragma unroll
+  for (int k = 1; k <= kGroupClasses; ++k)
+    if (b >= blk[k]) c = k;
+  b -= blk[c];
+  switch (c) {
+    case 0: group_block<4, true, Rows>(C, rs, st, 0, b, S); break;
+    case 1: group_block<8, true, Rows>(C, rs, st, 1, b, S); break;
+    case 2: group_block<16, true, Rows>(C, rs, st, 2, b, S); break;
+    case 3: group_block<32, true, Rows>(C, rs, st, 3, b, S); break;
+    case 4: group_block<64, true, Rows>(C, rs, st, 4, b, S); break;
+    case 5: group_block<4, false, Rows>(C, rs, st, 5, b, S); break;
+    case 6: group_block<8, false, Rows>(C, rs, st, 6, b, S); break;
+    case 7: group_block<16, false, Rows>(C, rs, st, 7, b, S); break;
+    case 8: group_block<32, false, Rows>(C, rs, st, 8, b, S); break;
+    case 9: group_block<64, false, Rows>(C, rs, st, 9, b, S); break;
+    default: {
+      const int q = C.plan.grp_col[kGroupClasses] + b * 4 + (int)(threadIdx.x >> 6);
+      if (q < C.plan.grp_col[kGroupClasses + 1]) flip_wave(C, rs, st, q);
+    }
+  }
+}
+
+template <typename Rows>
+__global__ __launch_bounds__(256) void k_group(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
                                                int32_t nw) {
   int lb;
   const int w_ = block_walk(off, nw, lb);
   if (w_ < 0) return;
   const WalkCtx& C = walks[w_];
+  const WalkState* st = C.st;
+  if (st->k >= st->iters || st->pass_skip) return;
+  __shared__ GroupSmem S;
   const Rows rs = rows_of<Rows>(C);
-  if (C.st->k >= C.st->iters || C.st->pass_skip) return;
-  const int32_t* seg = C.plan.short_seg;
-  const int q = seg[0] + lb * 256 + threadIdx.x;
-  if (q >= seg[kShortMax + 2]) return;
-  if (q < seg[1]) {
-    flip_column(C.P, C.x, rs, C.st, C.xhat, C.s, q);
+  group_task<Rows>(C, rs, st, lb, S);
+}
+
+// The lane-group columns of an affected-rescoring iteration (b of nb
+// workgroups): the listed ones, a wavefront each, or all of them.
+template <typename Rows>
+__device__ __forceinline__ void aff_group_body(const WalkCtx& C, const AffRun* run, int b, int nb, GroupSmem& S) {
+  const WalkState* st = C.st;
+  if (st->k >= st->iters) return;
+  const Rows rs = rows_of<Rows>(C);
+  const int count = run->n_s;
+  if (count < 0) {
+    for (int t = b; t < C.plan.grp_blk[kGroupClasses]; t += nb) group_task<Rows>(C, rs, st, t, S);
     return;
   }
-  int D = 0;
-#pragma unroll
-  for (int k = 1; k <= kShortMax; ++k)
-    if (q >= seg[1 + k]) D = k;
-  switch (D) {
-    case 0: short_general<0>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 1: short_general<1>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 2: short_general<2>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 3: short_general<3>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 4: short_general<4>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 5: short_general<5>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 6: short_general<6>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    case 7: short_general<7>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    default: short_general<8>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-  }
-}
-
-// The short columns of an affected-rescoring iteration, one lane each
-// (grid-stride over the list; classes padded to whole wavefronts, -1 marks
-// padding), with the full pass's per-column code.
-// b, nb: this workgroup's index among the nb workgroups of the role.
-template <typename Rows>
-__device__ __forceinline__ void aff_short_body(const WalkCtx& C, const AffRun* run, int b, int nb) {
-  if (C.st->k >= C.st->iters) return;
-  const Rows rs = rows_of<Rows>(C);
-  const int32_t* seg = C.plan.short_seg;
-  const int count = run->n_s;
-  const int32_t* list = run->slist;
-  for (int i = b * (int)blockDim.x + (int)threadIdx.x; i < count; i += nb * (int)blockDim.x) {
-    const int q = list[i];
-    if (q < 0) continue;
-    if (q < seg[1]) {
-      flip_column(C.P, C.x, rs, C.st, C.xhat, C.s, q);
-      continue;
-    }
-    int D = 0;
-#pragma unroll
-    for (int k = 1; k <= kShortMax; ++k)
-      if (q >= seg[1 + k]) D = k;
-    switch (D) {
-      case 0: short_general<0>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 1: short_general<1>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 2: short_general<2>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 3: short_general<3>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 4: short_general<4>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 5: short_general<5>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 6: short_general<6>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      case 7: short_general<7>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-      default: short_general<8>(C.P, C.x, rs, C.st, C.xhat, C.s, q); break;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// k_flip_wave: one wavefront per longer binary column.
-// ---------------------------------------------------------------------------
-
-template <typename Rows>
-__global__ __launch_bounds__(256) void k_flip_wave(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
-                                                   int32_t nw) {
-  int lb;
-  const int w_ = block_walk(off, nw, lb);
-  if (w_ < 0) return;
-  const WalkCtx& C = walks[w_];
-  const DevProblem& P = C.P;
-  const double* x = C.x;
-  const Rows rs = rows_of<Rows>(C);
-  const WalkState* st = C.st;
-  double* xhat = C.xhat;
-  double* sc = C.s;
-  if (st->k >= st->iters || st->pass_skip) return;
   const int lane = threadIdx.x & (kWave - 1);
-  const int q = C.plan.flip_begin + lb * 4 + (threadIdx.x >> 6);
-  if (q >= C.plan.flip_end) return;
-  const double eps = P.eps;
-  const double xb = x[q];
-  const double xn = 1.0 - xb;
-  const double d = xn - xb;
-  double s = 0.0;
-  const int beg = P.col_ptr[q], end = P.col_ptr[q + 1];
-  for (int e = beg + lane; e < end; e += kWave) {
-    const RowState r = rs[P.col_row[e]];
-    const double r2 = r.r + P.col_val[e] * d;
-    s += penalty(r.r, r2, (double)r.w0, eps);
-    if (r.w1 >= 0.0f) s += penalty(-r.r, -r2, (double)r.w1, eps);
-  }
-  if (lane == 0 && st->cut_active) {
-    const double c = P.obj[q];
-    if (c != 0.0) {
-      const double r2 = st->rc + c * d;
-      s += penalty(st->rc, r2, (double)st->wc, eps);
+  const int n_flip = C.plan.grp_col[kGroupWidths];
+  for (int i = b * 4 + (int)(threadIdx.x >> 6); i < count; i += nb * 4) {
+    const int q = __builtin_amdgcn_readfirstlane(run->slist[i]);
+    const int beg = C.P.col_ptr[q], deg = C.P.col_ptr[q + 1] - beg;
+    int row = -1;
+    double a = 1.0;
+    if (lane < deg) {
+      row = gmem(C.P.col_row)[beg + lane];
+      a = gmem(C.P.col_val)[beg + lane];
     }
+    if (q < n_flip)
+      score_group<kWave, true, Rows>(C, rs, st, q, true, row, a, S);
+    else
+      score_group<kWave, false, Rows>(C, rs, st, q, true, row, a, S);
   }
-  s = wave_sum(s);
-  if (lane == 0) write_result(xhat, sc, q, true, s, xn, xb);
 }
 
 // ---------------------------------------------------------------------------
@@ -1745,173 +1751,6 @@ __device__ __forceinline__ void scan_argmax(PosT pos, MarkT mk, DelT dl, int cap
   bestp = found ? pos[bk] : xb;
 }
 
-// General columns with at most 64 breakpoint slots: one wavefront per column
-// (four per workgroup), one slot per lane. Phase 1 emits the entries into
-// the wavefront's LDS slots by a ballot prefix count, the bitonic sort runs
-// across lanes with exchanges between partner lanes (no barriers), then a
-// wavefront scan and argmax.
-struct WaveSortSmem {
-  double pos[4][kWave];
-  double del[4][kWave];
-  int32_t mk[4][kWave];
-};
-
-// Inclusive prefix sum across the wavefront.
-__device__ __forceinline__ double wave_inclusive(double v, int lane) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const double y = __shfl_up(v, o, kWave);
-    if (lane >= o) v += y;
-  }
-  return v;
-}
-
-// Algorithm 1 for general column j with at most 64 breakpoints (bounds and
-// cutoff included), by one wavefront: entries and breakpoints in registers,
-// a bitonic sort across the lanes, wavefront scan and argmax. Every lane of
-// the wavefront calls it with the same j; wv is the wavefront's slot in S.
-template <typename Rows>
-__device__ __forceinline__ void sort_wave_column(const WalkCtx& C, const Rows& rs, int j, WaveSortSmem& S, int wv) {
-  const DevProblem& P = C.P;
-  const WalkState* st = C.st;
-  const int lane = threadIdx.x & (kWave - 1);
-  const double eps = P.eps;
-  const double xb = gmem((const double*)C.x)[j];
-  const bool isint = P.is_int[j] != 0;
-  const int beg = P.col_ptr[j], end = P.col_ptr[j + 1];
-  double beta = 0.0, alpha = 0.0;
-  // up to two entries per lane (a row and its twin), lane 0 adds the bounds
-  // and the cutoff row; the class guarantees at most 64 in all
-  BkEntry en[2];
-  int ne = 0;
-  const int e = beg + lane;
-  if (e < end) {
-    const RowState q = rs[P.col_row[e]];
-    const double a = P.col_val[e];
-    en[0] = phase1(xb, q.r, a, (double)q.w0, eps, isint, beta, alpha);
-    if (en[0].has) ne = 1;
-    if (q.w1 >= 0.0f) {
-      const BkEntry b1 = phase1(xb, -q.r, -a, (double)q.w1, eps, isint, beta, alpha);
-      if (b1.has) en[ne++] = b1;
-    }
-  }
-  BkEntry ex[3];
-  int nx = 0;
-  if (lane == 0) {
-    const double l = P.lb[j], u = P.ub[j];
-    if (isfinite(l)) ex[nx++] = BkEntry{l, 0.0, -1, true};
-    if (isfinite(u)) ex[nx++] = BkEntry{u, 0.0, -1, true};
-    if (st->cut_active) {
-      const double c = P.obj[j];
-      if (c != 0.0) {
-        const BkEntry b2 = phase1(xb, st->rc, c, (double)st->wc, eps, isint, beta, alpha);
-        if (b2.has) ex[nx++] = b2;
-      }
-    }
-  }
-  // slot of each lane's first entry: exclusive prefix count of entries
-  const int cnt_lane = ne + nx;
-  int incl = cnt_lane;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(incl, o, kWave);
-    if (lane >= o) incl += y;
-  }
-  const int total = __shfl(incl, kWave - 1, kWave);
-  int slot = incl - cnt_lane;
-  for (int k = 0; k < ne; ++k, ++slot) {
-    S.pos[wv][slot] = en[k].t + 0.0;
-    S.mk[wv][slot] = en[k].marker;
-    S.del[wv][slot] = en[k].delta;
-  }
-  for (int k = 0; k < nx; ++k, ++slot) {
-    S.pos[wv][slot] = ex[k].t + 0.0;
-    S.mk[wv][slot] = ex[k].marker;
-    S.del[wv][slot] = ex[k].delta;
-  }
-  // the slots written by other lanes of this wavefront become visible
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  double p = HUGE_VAL, d = 0.0;
-  int m = kPadMarker;
-  if (lane < total) {
-    p = S.pos[wv][lane];
-    m = S.mk[wv][lane];
-    d = S.del[wv][lane];
-  }
-  // bitonic sort of (position, marker) across the lanes; both lanes of a
-  // pair take the same decision from the lower lane's point of view
-#pragma unroll
-  for (int size = 2; size <= kWave; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const double po = __shfl_xor(p, stride, kWave);
-      const int mo = __shfl_xor(m, stride, kWave);
-      const double dlo = __shfl_xor(d, stride, kWave);
-      const bool lower = (lane & stride) == 0;
-      const bool up = (lane & size) == 0;
-      const double pl = lower ? p : po, ph = lower ? po : p;
-      const int ml = lower ? m : mo, mh = lower ? mo : m;
-      const bool swap = up ? key_greater(pl, ml, ph, mh) : key_greater(ph, mh, pl, ml);
-      if (swap) {
-        p = po;
-        m = mo;
-        d = dlo;
-      }
-    }
-  }
-  beta = wave_sum(beta);
-  alpha = wave_sum(alpha);
-  const double inc = wave_inclusive(d, lane);
-  const double prefix = inc - d;
-  double bv = -DBL_MAX;
-  int bk = INT_MAX;
-  const double l = P.lb[j], u = P.ub[j];
-  if (m != kPadMarker && isfinite(p) && p >= l && p <= u && p != xb) {
-    bv = beta + ((m < 0) ? inc : prefix) + ((p > xb) ? alpha : 0.0);
-    bk = lane;
-  }
-  wave_argmax(bv, bk);
-  const bool found = bk != INT_MAX;
-  const double bestp = __shfl(p, found ? bk : 0, kWave);
-  if (lane == 0) write_result(C.xhat, C.s, j, found, bv, found ? bestp : xb, xb);
-}
-
-template <typename Rows>
-__global__ __launch_bounds__(256) void k_sort_wave(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
-                                                   int32_t nw) {
-  int lb;
-  const int w_ = block_walk(off, nw, lb);
-  if (w_ < 0) return;
-  const WalkCtx& C = walks[w_];
-  const WalkState* st = C.st;
-  if (st->k >= st->iters || st->pass_skip) return;
-  __shared__ WaveSortSmem S;
-  const int wv = threadIdx.x >> 6;
-  const int j = C.plan.sort_begin[0] + lb * 4 + wv;
-  if (j >= C.plan.sort_begin[1]) return;  // whole wavefronts leave together
-  const Rows rs = rows_of<Rows>(C);
-  sort_wave_column<Rows>(C, rs, j, S, wv);
-}
-
-// The listed general columns of the wave-sort class (at most 64
-// breakpoints) in an affected-rescoring iteration: one wavefront each
-// (grid-stride over the subset list).
-template <typename Rows>
-__device__ __forceinline__ void aff_wave_body(const WalkCtx& C, const LearnCtx& L, int b, int nb, WaveSortSmem& S) {
-  if (C.st->k >= C.st->iters || L.ls->idle) return;
-  const int wv = threadIdx.x >> 6;
-  const Rows rs = rows_of<Rows>(C);
-  const int count = L.ls->tk[0].count;
-  const int q0 = C.plan.sort_begin[0], q1 = C.plan.sort_begin[1];
-  for (int i = b * 4 + wv; i < count; i += nb * 4) {
-    const int q = L.sel[0][i];
-    if (q < q0 || q >= q1) continue;  // uniform across the wavefront
-    sort_wave_column<Rows>(C, rs, q, S, wv);
-  }
-}
-
 template <int CAP, typename Rows>
 __global__ __launch_bounds__(256) void k_sort_block(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
                                                     int32_t nw) {
@@ -2149,7 +1988,7 @@ __global__ __launch_bounds__(256) void k_subset_combine(const WalkCtx* __restric
     const int q = L.sel[0][i];
     const uint8_t cl = L.cls[q];
     if (cl == SUB_GENERAL) continue;
-    if (L.short_lane && q >= C.plan.short_seg[0] && q < C.plan.short_seg[kShortMax + 2]) continue;
+    if (L.group_role && q >= C.plan.grp_col[0] && q < C.plan.grp_col[kGroupClasses]) continue;
     const int c0 = L.sub_off[i], c1 = L.sub_off[i + 1];
     const double xb = C.x[q];
     if (cl == SUB_FLIP) {
@@ -2203,10 +2042,7 @@ __device__ __forceinline__ void subset_general_body(const WalkCtx& C, const Lear
   for (int i = b; i < count; i += nb) {
     const int q = L.sel[0][i];
     if (L.cls[q] != SUB_GENERAL) continue;
-    // affected rescoring: short columns go to lanes, the wave-sort class to wavefronts (k_aff_score)
-    if (L.short_lane && ((q >= C.plan.short_seg[0] && q < C.plan.short_seg[kShortMax + 2]) ||
-                         (q >= C.plan.sort_begin[0] && q < C.plan.sort_begin[1])))
-      continue;
+    if (L.group_role && q >= C.plan.grp_col[0] && q < C.plan.grp_col[kGroupClasses]) continue;
     const double xb = C.x[q];
     if (tid == 0) scount = 0;
     __syncthreads();
@@ -2247,29 +2083,22 @@ __global__ __launch_bounds__(256) void k_subset_general(const WalkCtx* __restric
 }
 
 // The scoring of an affected-rescoring iteration in one launch: workgroups
-// [0, g[0]) score the short columns by lanes, the next g[1] the wave-sort
-// class, the next g[2] the subset chunks and the last g[3] the other general
-// columns (each role strides over its own work).
+// [0, g0) score the lane-group columns, the other g1 the subset chunks (each
+// role strides over its own work).
 template <typename Rows>
 __global__ __launch_bounds__(256) void k_aff_score(const WalkCtx* __restrict__ walks,
                                                    const LearnCtx* __restrict__ lc, const AffRun* __restrict__ run,
-                                                   int g0, int g1, int g2, int g3) {
+                                                   int g0, int g1) {
   __shared__ union {
-    WaveSortSmem w;
+    GroupSmem s;
     SubsetChunkSmem c;
-    SubsetGeneralSmem g;
   } U;
   const WalkCtx& C = walks[0];
   const int b = (int)blockIdx.x;
-  if (b < g0) {
-    aff_short_body<Rows>(C, run, b, g0);
-  } else if (b < g0 + g1) {
-    aff_wave_body<Rows>(C, *lc, b - g0, g1, U.w);
-  } else if (b < g0 + g1 + g2) {
-    subset_chunks_body<Rows>(C, *lc, b - g0 - g1, g2, U.c);
-  } else if (b < g0 + g1 + g2 + g3) {
-    subset_general_body(C, *lc, b - g0 - g1 - g2, g3, U.g);
-  }
+  if (b < g0)
+    aff_group_body<Rows>(C, run, b, g0, U.s);
+  else
+    subset_chunks_body<Rows>(C, *lc, b - g0, g1, U.c);
 }
 
 }  // namespace
@@ -2286,14 +2115,17 @@ hipError_t launch_subset_grids(const WalkCtx* C, const LearnCtx* L, int chunk_gr
   return hipGetLastError();
 }
 
-hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[4], int combine_grid,
+hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[3], int combine_grid,
                             int compact, hipStream_t s) {
-  const unsigned total = (unsigned)(g[0] + g[1] + g[2] + g[3]);
+  const unsigned total = (unsigned)(g[0] + g[1]);
   if (compact)
-    hipLaunchKernelGGL(k_aff_score<CompactRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1], g[2], g[3]);
+    hipLaunchKernelGGL(k_aff_score<CompactRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1]);
   else
-    hipLaunchKernelGGL(k_aff_score<FullRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1], g[2], g[3]);
-  hipLaunchKernelGGL(k_subset_combine, dim3((unsigned)std::max(combine_grid, 1)), dim3(256), 0, s, C, L);
+    hipLaunchKernelGGL(k_aff_score<FullRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1]);
+  if (g[2] > 0) hipLaunchKernelGGL(k_subset_general, dim3((unsigned)g[2]), dim3(256), 0, s, C, L);
+  // without columns outside the lane-group range there is nothing to combine
+  if (g[1] > 0)
+    hipLaunchKernelGGL(k_subset_combine, dim3((unsigned)std::max(combine_grid, 1)), dim3(256), 0, s, C, L);
   return hipGetLastError();
 }
 
@@ -2307,8 +2139,7 @@ hipError_t launch_subset_pass(const WalkCtx* C, const LearnCtx* L, const LearnCt
 int32_t kernel_blocks(const WalkCtx& c, int slot) {
   const PassPlan& p = c.plan;
   switch (slot) {
-    case KS_SHORT: return (p.short_seg[kShortMax + 2] - p.short_seg[0] + 255) / 256;
-    case KS_FLIP: return (p.flip_end - p.flip_begin + 3) / 4;
+    case KS_GROUP: return p.grp_blk[kGroupClasses + 1];
     case KS_PACK: return p.n_packs;
     case KS_CHUNK: return p.stage ? 0 : p.n_chunks;  // a staged pass scores its chunks in k_stage_score
     case KS_COMBINE: return (p.n_chunk_cols + 3) / 4;
@@ -2320,31 +2151,25 @@ int32_t kernel_blocks(const WalkCtx& c, int slot) {
     case KS_APPLY: return c.apply_blocks;
     case KS_FINISH: return 1;
     default:
-      if (slot == KS_SORT0) return (p.sort_begin[1] - p.sort_begin[0] + 3) / 4;  // a wavefront per column
-      if (slot > KS_SORT0 && slot < KS_SORT0 + kSortCaps)
+      if (slot >= KS_SORT0 && slot < KS_SORT0 + kSortCaps)
         return p.sort_begin[slot - KS_SORT0 + 1] - p.sort_begin[slot - KS_SORT0];
       return 0;
   }
 }
 
 hipError_t PassStreams::create() {
-  for (int k = 0; k < 2; ++k) {
-    hipError_t e = hipStreamCreateWithFlags(&side[k], hipStreamNonBlocking);
-    if (e != hipSuccess) return e;
-    e = hipEventCreateWithFlags(&join[k], hipEventDisableTiming);
-    if (e != hipSuccess) return e;
-  }
-  return hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+  hipError_t e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+  return e;
 }
 
 void PassStreams::destroy() {
-  for (int k = 0; k < 2; ++k) {
-    if (side[k]) (void)hipStreamDestroy(side[k]);
-    if (join[k]) (void)hipEventDestroy(join[k]);
-    side[k] = nullptr;
-    join[k] = nullptr;
-  }
+  if (side) (void)hipStreamDestroy(side);
+  if (join) (void)hipEventDestroy(join);
   if (fork) (void)hipEventDestroy(fork);
+  side = nullptr;
+  join = nullptr;
   fork = nullptr;
 }
 
@@ -2365,23 +2190,18 @@ hipError_t launch_pass_rows(const BatchLaunch& L, hipStream_t stream, const Pass
     const hipError_t le = hipGetLastError();
     if (first == hipSuccess) first = le;
   };
-  // the staged scoring is one launch on the main stream; the side streams
-  // carry the short, flip, chunk and long-sort kernels of unstaged columns
-  const bool fork = ps && (L.total[KS_SHORT] > 0 || L.total[KS_FLIP] > 0 || L.total[KS_LONG] > 0 ||
-                           L.total[KS_CHUNK] > 0);
-  hipStream_t s_short = stream, s_long = stream;
+  // the side stream carries the chunks and the long sorts of unstaged columns
+  const bool fork = ps && (L.total[KS_LONG] > 0 || L.total[KS_CHUNK] > 0);
+  hipStream_t s_long = stream;
   hipError_t e = hipSuccess;
   if (fork) {
     e = hipEventRecord(ps->fork, stream);
-    for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipStreamWaitEvent(ps->side[k], ps->fork, 0);
+    if (e == hipSuccess) e = hipStreamWaitEvent(ps->side, ps->fork, 0);
     if (e != hipSuccess) return e;
-    s_short = ps->side[0];
-    s_long = ps->side[1];
+    s_long = ps->side;
   }
-  if (L.total[KS_SHORT] > 0)
-    CHAP_LAUNCH(k_short<Rows>, grid(KS_SHORT), dim3(256), 0, s_short, L.walks, L.off[KS_SHORT], nw);
-  if (L.total[KS_FLIP] > 0)
-    CHAP_LAUNCH(k_flip_wave<Rows>, grid(KS_FLIP), dim3(256), 0, s_short, L.walks, L.off[KS_FLIP], nw);
+  if (L.total[KS_GROUP] > 0)
+    CHAP_LAUNCH(k_group<Rows>, grid(KS_GROUP), dim3(256), 0, stream, L.walks, L.off[KS_GROUP], nw);
   // staged columns: the records (alone: they are bound by HBM), then the
   // scoring of every staged task and long-column chunk
   if (L.total[KS_STAGE] > 0)
@@ -2409,23 +2229,18 @@ hipError_t launch_pass_rows(const BatchLaunch& L, hipStream_t stream, const Pass
   if (L.total[KS_PACK] > 0)
     CHAP_LAUNCH(k_narrow_pack<Rows>, grid(KS_PACK), dim3(256), 0, stream, L.walks, L.off[KS_PACK], nw);
   if (L.total[KS_SORT0] > 0)
-    CHAP_LAUNCH(k_sort_wave<Rows>, grid(KS_SORT0), dim3(256), 0, stream, L.walks, L.off[KS_SORT0], nw);
+    CHAP_LAUNCH((k_sort_block<256, Rows>), grid(KS_SORT0), dim3(256), 0, stream, L.walks, L.off[KS_SORT0], nw);
   if (L.total[KS_SORT0 + 1] > 0)
-    CHAP_LAUNCH((k_sort_block<256, Rows>), grid(KS_SORT0 + 1), dim3(256), 0, stream, L.walks,
-                       L.off[KS_SORT0 + 1], nw);
+    CHAP_LAUNCH((k_sort_block<1024, Rows>), grid(KS_SORT0 + 1), dim3(256), 0, stream, L.walks,
+                L.off[KS_SORT0 + 1], nw);
   if (L.total[KS_SORT0 + 2] > 0)
-    CHAP_LAUNCH((k_sort_block<1024, Rows>), grid(KS_SORT0 + 2), dim3(256), 0, stream, L.walks,
-                       L.off[KS_SORT0 + 2], nw);
-  if (L.total[KS_SORT0 + 3] > 0)
-    CHAP_LAUNCH((k_sort_block<4096, Rows>), grid(KS_SORT0 + 3), dim3(256), 0, stream, L.walks,
-                       L.off[KS_SORT0 + 3], nw);
+    CHAP_LAUNCH((k_sort_block<4096, Rows>), grid(KS_SORT0 + 2), dim3(256), 0, stream, L.walks,
+                L.off[KS_SORT0 + 2], nw);
   check();
   e = first;
-  if (fork) {
-    for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-      e = hipEventRecord(ps->join[k], ps->side[k]);
-      if (e == hipSuccess) e = hipStreamWaitEvent(stream, ps->join[k], 0);
-    }
+  if (fork && e == hipSuccess) {
+    e = hipEventRecord(ps->join, ps->side);
+    if (e == hipSuccess) e = hipStreamWaitEvent(stream, ps->join, 0);
   }
   if (e == hipSuccess && combine_after_join) {
     hipLaunchKernelGGL(k_narrow_combine, grid(KS_COMBINE), dim3(256), 0, stream, L.walks, L.off[KS_COMBINE], nw);

@@ -1291,35 +1291,21 @@ inline int blocks_for(int64_t work, int cap) {
 // only x_j* and the columns sharing one of those rows need a new score.
 // ---------------------------------------------------------------------------
 
-// Short class of internal column q: 0 for a short binary, 1 + D for a short
-// non-binary column with D stored entries, -1 for a column outside the
-// short range.
-__device__ __forceinline__ int aff_class(const int32_t* seg, int q) {
-  if (q < seg[0] || q >= seg[kShortMax + 2]) return -1;
-  if (q < seg[1]) return 0;
-  int c = 1;
-#pragma unroll
-  for (int k = 1; k <= kShortMax; ++k)
-    if (q >= seg[1 + k]) c = 1 + k;
-  return c;
-}
-
-// One workgroup: lists the affected columns, splits the list into its short columns (grouped by
-// class, each class padded to whole wavefronts) and the rest, with the rest's
-// subset chunk offsets (ceil(entries / kSubsetChunk) chunks per binary or
-// narrow column, none for a general one), and skips the full pass. When the
-// step was not a plain move, the list is longer than cap, a listed column
-// has no subset form, or the chunks exceed sub_cap, the iteration scores
-// every column: through the split of all columns when there is one, else
-// through the full pass. Points the subset record and the lane list at the
-// lists it takes and clears the count.
+// One workgroup: lists the affected columns, splits the list into its
+// lane-group columns and the rest, with the rest's subset chunk offsets
+// (ceil(entries / kSubsetChunk) chunks per binary or narrow column, none for a
+// general one), and skips the full pass. When the step was not a plain move,
+// the list is longer than cap, a listed column has no subset form, or the
+// chunks exceed sub_cap, the iteration scores every column: through the
+// split of all columns when there is one, else through the full pass. Points
+// the subset record and the group list at the lists it takes and clears the
+// count.
 __global__ __launch_bounds__(256) void k_aff_plan(const WalkCtx* __restrict__ walks, LearnCtx* __restrict__ lc,
                                                   AffLists A) {
   const WalkCtx& C = walks[0];
   WalkState* st = C.st;
   LearnCtx& L = *lc;
   if (st->k >= st->iters) return;
-  __shared__ int ccount[kAffClasses], cfill[kAffClasses], cbase[kAffClasses];
   __shared__ int wsum[4];
   __shared__ int carry, bad, n_other, n_s, n_mark;
   const int tid = threadIdx.x;
@@ -1332,7 +1318,7 @@ __global__ __launch_bounds__(256) void k_aff_plan(const WalkCtx* __restrict__ wa
   __shared__ int rpre[kAffRows + 1];
   __shared__ int rrow[kAffRows];
   __shared__ int lst[kRescoreCapMax];  // the affected list
-  __shared__ int olst[kRescoreCapMax];  // its columns outside the short range
+  __shared__ int olst[kRescoreCapMax];  // its columns outside the lane-group range
   if (tid == 0) n_mark = 0;
   __syncthreads();
   if (st->aff_ok) {
@@ -1388,11 +1374,7 @@ __global__ __launch_bounds__(256) void k_aff_plan(const WalkCtx* __restrict__ wa
   __syncthreads();
   const int n_list = st->aff_ok ? n_mark : 0;
   const bool listed = st->aff_ok && n_list <= A.cap;
-  const int32_t* seg = C.plan.short_seg;
-  if (tid < kAffClasses) {
-    ccount[tid] = 0;
-    cfill[tid] = 0;
-  }
+  const int g0 = C.plan.grp_col[0], g1 = C.plan.grp_col[kGroupClasses];
   if (tid == 0) {
     carry = 0;
     bad = 0;
@@ -1403,9 +1385,8 @@ __global__ __launch_bounds__(256) void k_aff_plan(const WalkCtx* __restrict__ wa
   if (listed) {
     for (int i = tid; i < n_list; i += 256) {
       const int q = lst[i];
-      const int c = aff_class(seg, q);
-      if (c >= 0) {
-        atomicAdd(&ccount[c], 1);
+      if (q >= g0 && q < g1) {
+        A.slist[atomicAdd(&n_s, 1)] = q;
       } else {
         if (L.cls[q] == SUB_NONE) bad = 1;
         const int k = atomicAdd(&n_other, 1);
@@ -1414,24 +1395,6 @@ __global__ __launch_bounds__(256) void k_aff_plan(const WalkCtx* __restrict__ wa
       }
     }
     __syncthreads();
-    if (tid == 0) {
-      int base = 0;
-      for (int c = 0; c < kAffClasses; ++c) {
-        cbase[c] = base;
-        base += (ccount[c] + kWave - 1) / kWave * kWave;
-      }
-      n_s = base;
-    }
-    __syncthreads();
-    for (int i = tid; i < n_list; i += 256) {
-      const int q = lst[i];
-      const int c = aff_class(seg, q);
-      if (c >= 0) A.slist[cbase[c] + atomicAdd(&cfill[c], 1)] = q;
-    }
-    for (int c = 0; c < kAffClasses; ++c) {
-      const int end = (ccount[c] + kWave - 1) / kWave * kWave;
-      for (int t = ccount[c] + tid; t < end; t += 256) A.slist[cbase[c] + t] = -1;
-    }
     const int n_o = n_other;
     const int lane = tid & 63, wv = tid >> 6;
     for (int base = 0; base < n_o; base += 256) {
@@ -1472,14 +1435,13 @@ __global__ __launch_bounds__(256) void k_aff_plan(const WalkCtx* __restrict__ wa
     A.run->n_s = n_s;
     st->pass_skip = 1;
     st->aff_iters += 1;
-  } else if (A.full_slist) {
+  } else if (A.full_olist) {
     L.sel[0] = const_cast<int32_t*>(A.full_olist);
     L.sub_off = const_cast<int32_t*>(A.full_ooff);
     L.ls->tk[0].count = A.n_full_o;
     L.ls->tk[0].chunks = A.full_chunks;
     L.ls->idle = 0;
-    A.run->slist = A.full_slist;
-    A.run->n_s = A.n_full_s;
+    A.run->n_s = -1;
     st->pass_skip = 1;
   } else {
     L.ls->tk[0].count = 0;
