@@ -1051,14 +1051,20 @@ hipError_t build_perm_plan(const std::vector<int32_t>& dest, DeviceArena& A, Per
   return hipSuccess;
 }
 
-int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx& c) {
+int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx& c, bool scan_all,
+               int32_t extra_rec) {
   const int32_t n = p->n;
   c = WalkCtx{};
   c.P = p->dev;
   c.plan = p->plan;
-  c.argmax_blocks = blocks_for_host(n, kArgmaxBlocks);
+  // the lane-group columns' best moves come from the kernel that scores them
+  const int32_t grouped = scan_all ? 0 : p->plan.grp_col[kGroupClasses + 1];
+  c.group_rec = grouped > 0 ? p->plan.grp_blk[kGroupClasses + 1] : 0;
+  c.scan_from = grouped;
+  c.argmax_blocks = (n > grouped || c.group_rec == 0) ? blocks_for_host(n - grouped, kArgmaxBlocks) : 0;
   c.argmax_comb = p->plan.stage ? (p->plan.n_chunk_cols + 3) / 4 : 0;
-  c.apply_blocks = blocks_for_host(std::max(p->m, p->max_col_deg), 256);
+  c.apply_blocks = (int32_t)std::max<int64_t>(
+      1, std::min<int64_t>(((int64_t)std::max(p->m, p->max_col_deg) + kStepRows - 1) / kStepRows, kStepBlocks));
   c.recompute = p->exact_incremental ? 0 : 1;
   CHAP_HIP(A.alloc(&c.x, (size_t)n));
   CHAP_HIP(A.alloc(&c.xhat, (size_t)n));
@@ -1068,7 +1074,7 @@ int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx
   CHAP_HIP(A.alloc(&c.rs, (size_t)p->m));
   CHAP_HIP(A.alloc(&c.st, 1));
   if (trace_cap > 0) CHAP_HIP(A.alloc(&c.trace, (size_t)trace_cap));
-  CHAP_HIP(A.alloc(&c.argmax_partial, (size_t)kArgmaxRecord * (c.argmax_blocks + c.argmax_comb)));
+  CHAP_HIP(A.alloc(&c.best, (size_t)std::max(c.group_rec + c.argmax_blocks + c.argmax_comb, extra_rec)));
   CHAP_HIP(A.alloc(&c.partials, (size_t)p->plan.n_partials));
   CHAP_HIP(A.alloc(&c.long_pos, (size_t)p->plan.long_scratch));
   CHAP_HIP(A.alloc(&c.long_delta, (size_t)p->plan.long_scratch));
@@ -1117,8 +1123,8 @@ int init_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, const WalkCtx
 }
 
 int prepare_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, DeviceArena& A, WalkCtx& c, double* partial,
-                 uint32_t* ticket, hipStream_t s, int compact) {
-  int rc = alloc_walk(spec.p, std::max<int64_t>(iters, 1), A, c);
+                 uint32_t* ticket, hipStream_t s, int compact, bool scan_all, int32_t extra_rec) {
+  int rc = alloc_walk(spec.p, std::max<int64_t>(iters, 1), A, c, scan_all, extra_rec);
   if (rc != CHAP_OK) return rc;
   if (!compact) c.grow = nullptr;
   rc = init_walk(spec, iters, tenure, c, partial, ticket, s);
@@ -1433,7 +1439,7 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
 
 // Buffers, launch table and streams of a new walk slot for problem p.
 int slot_setup(const chap_problem* p, WalkSlot& S) {
-  int rc = alloc_walk(p, 0, S.A, S.ctx);
+  int rc = alloc_walk(p, 0, S.A, S.ctx, p->opt.rescore_cap > 0);
   if (rc != CHAP_OK) return rc;
   S.grow_buf = S.ctx.grow;
   S.ctx.grow = nullptr;

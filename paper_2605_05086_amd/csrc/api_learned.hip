@@ -124,10 +124,8 @@ hipError_t capture_block(const BatchLaunch& BL, const WalkCtx* C, const LearnCtx
   if (e == hipSuccess) e = launch_pass(BL, s, ps);
   if (e == hipSuccess && Lh.n_elig > 0) e = launch_learn_propose(C, L, Lh, M, n, 1, s);
   if (e == hipSuccess && Lh.n_elig > 0) e = launch_learn_train(C, L, Lh, M, n, o.train_steps, o.lr, s);
-  if (e == hipSuccess) e = launch_walk_choose(BL, s);
+  if (e == hipSuccess) e = launch_walk_step(BL, s);
   if (e == hipSuccess) e = launch_learn_judge(C, L, s);
-  if (e == hipSuccess) e = launch_walk_apply(BL, s);
-  if (e == hipSuccess) e = launch_walk_finish(BL, s);
   if (e == hipSuccess) e = launch_learn_refresh(C, L, Lh, s);
   // proposal iterations: a new set from the network every refresh_every of
   // them (the scoring kernel also copies a pending incumbent); otherwise the
@@ -140,10 +138,9 @@ hipError_t capture_block(const BatchLaunch& BL, const WalkCtx* C, const LearnCtx
       e = launch_copy_best_batch(BL, s);
       if (e == hipSuccess && Lh.n_elig > 0) e = launch_learn_keep_set(C, L, s);
     }
-    if (e == hipSuccess && Lh.n_elig > 0) e = launch_subset_pass(C, L, Lh, has_general, BL.compact, s);
-    if (e == hipSuccess) e = launch_subset_select(C, L, s);
-    if (e == hipSuccess) e = launch_walk_apply(BL, s);
-    if (e == hipSuccess) e = launch_walk_finish(BL, s);
+    if (e == hipSuccess)
+      e = Lh.n_elig > 0 ? launch_subset_pass(C, L, Lh, has_general, BL.compact, s) : launch_subset_none(C, L, s);
+    if (e == hipSuccess) e = launch_subset_step(BL, L, Lh.n_elig > 0 ? subset_records(Lh, has_general) : 0, s);
   }
   return e;
 }
@@ -210,7 +207,8 @@ int chap_learned_run(chap_problem* p, chap_model* m, const chap_learned_options*
   CHAP_HIP(hipStreamWaitEvent(s, e_user, 0));
   WalkCtx c;
   const int compact = compact_walks({WalkSpec{p, seed, x0}}, iters);
-  rc = prepare_walk(WalkSpec{p, seed, x0}, iters, tenure, A, c, partial, ticket, s, compact);
+  rc = prepare_walk(WalkSpec{p, seed, x0}, iters, tenure, A, c, partial, ticket, s, compact, true,
+                    (kTopkMax + 3) / 4 + kSubsetGeneralGrid);
   if (rc != CHAP_OK) return rc;
   BatchLaunch BL;
   std::vector<WalkCtx> one{c};

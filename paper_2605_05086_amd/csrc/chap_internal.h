@@ -112,7 +112,9 @@ constexpr int kResGroupMin = 64;     // fewest (an instance's own count: DevProb
 constexpr int kResLongRow = 32;      // entries above which a wavefront sums a row (k_residual)
 constexpr int kResXBlock = 131072;   // columns of x (bytes) per LDS block of that kernel
 constexpr int kArgmaxBlocks = 256;  // workgroups of the move-selection reduction
-constexpr int kArgmaxRecord = 8;     // doubles per workgroup record of that reduction
+constexpr int kStepThreads = 1024;   // threads per workgroup of the move kernel
+constexpr int kStepRows = 4096;      // rows per workgroup of the move kernel (reweights)
+constexpr int kStepBlocks = 256;     // most workgroups of the move kernel
 constexpr int kInitBlocks = 256;     // workgroups of the walk state initialisation
 // its scratch in doubles: (f, V) per workgroup, then the workgroups' exact
 // objective sums (kExactLimbs 64-bit limbs each)
@@ -182,6 +184,15 @@ struct DevProblem {
   int32_t pad_;
 };
 
+// Best moves of one scoring or scanning workgroup: the best positive score
+// overall and among the columns not tabu, with its original and internal
+// column (score 0 and index -1: none).
+struct __align__(16) MoveRecord {
+  double s_all, s_free;
+  int32_t j_all, q_all;
+  int32_t j_free, q_free;
+};
+
 // Mutable state of one walk (also used, with k = 0 and iters = 1, by a single
 // best-shift pass). Lives in device memory.
 struct __align__(16) WalkState {
@@ -198,20 +209,18 @@ struct __align__(16) WalkState {
   int64_t V;     // violated normalised rows (cutoff included when active)
   int32_t has_best;
   int32_t copy_best;
-  // selection (original indices)
-  int32_t j_all;
-  int32_t j_nt;
-  double s_all;
-  double s_nt;
+  // iteration and violated rows of the move selection under way (-1: none);
+  // written by the kernel before it (see snapshot())
+  int64_t sel_k;
+  int64_t sel_V;
   // chosen step (internal column index)
   int32_t mv_j;
   int32_t mv_kind;
   double mv_old;
   double mv_new;
-  double mv_delta;
-  double mv_score;
-  unsigned long long dV;  // two's complement accumulator of violation changes
-  int32_t skip;           // learned walks: this iteration does nothing (block idle)
+  // workgroups of the move kernel that are done (low 16 bits) and, above, the
+  // sum of their violation changes (two's complement)
+  unsigned long long dV;
   int32_t compact_rows;   // single passes: the compact row copy is exact for these weights
   // the call (epoch) whose point did not fit the byte copy of x (see
   // launch_stage_x); 0 after the state is cleared
@@ -228,7 +237,6 @@ struct __align__(16) WalkState {
   // affected rescoring: this iteration's full pass does nothing (the
   // affected columns are scored by the subset pass instead)
   int32_t pass_skip;
-  int32_t pad2_;
   int64_t aff_iters;  // iterations scored by the subset pass (affected rescoring)
 };
 
@@ -390,7 +398,9 @@ struct WalkCtx {
   GatherRow* grow;  // compact copy of rs kept by the walk kernels, or null
   WalkState* st;
   chap_trace_record* trace;
-  double* argmax_partial;
+  // best moves of the group kernel's workgroups (group_rec of them; 0: it
+  // records none), then of the move selection's scanning workgroups
+  MoveRecord* best;
   ChunkPartial* partials;
   double* long_pos;
   double* long_delta;
@@ -402,7 +412,9 @@ struct WalkCtx {
   // byte copy of x for residuals from scratch (problems whose variables are
   // all integers with bounds in [-128, 127]), or null
   int8_t* xc;
-  int32_t argmax_blocks;
+  int32_t group_rec;
+  int32_t scan_from;      // first internal column the scanning workgroups look at
+  int32_t argmax_blocks;  // scanning workgroups
   // further move-selection workgroups, one wavefront per long narrow column:
   // they combine those columns' partial bins when the pass leaves that to
   // the move selection, else they only write empty records
@@ -422,9 +434,8 @@ enum KernelSlot {
   KS_STAGE,
   KS_STAGE_SCORE,
   KS_ARGMAX,
-  KS_SELECT,
-  KS_APPLY,
-  KS_FINISH,
+  KS_STEP,
+  KS_COPY,
   KS_COUNT
 };
 
@@ -454,7 +465,11 @@ int32_t kernel_blocks(const WalkCtx& c, int slot);
 // walk's row states stay in one L2.
 __device__ __forceinline__ int block_walk(const int32_t* __restrict__ off, int nw, int& local) {
   int b = blockIdx.x;
-  if (nw > 1) {
+  if (nw == 1) {  // no table to read
+    local = b;
+    return 0;
+  }
+  {
     const int x = b % kXcds, s = b / kXcds;
     if (s >= off[nw + 1 + kXcds + x]) return -1;
     b = off[nw + 1 + x] + s;
@@ -482,12 +497,14 @@ struct PassStreams {
   void destroy();
 };
 
+struct LearnCtx;
+
 // ---- launchers (kernels_pass.hip) -----------------------------------------
 // One exact best-shift pass over all columns of every walk of the batch;
 // with `ps`, the long-column kernels of unstaged columns run on its side
 // stream. With defer_combine, a pass for which
 // pass_defers_combine(L) holds leaves the long narrow columns' partial bins
-// uncombined: the move selection that follows (launch_walk_choose with
+// uncombined: the move selection that follows (launch_walk_step with
 // combine) scores them while it scans.
 hipError_t launch_pass(const BatchLaunch& L, hipStream_t stream, const PassStreams* ps = nullptr,
                        bool defer_combine = false);
@@ -572,6 +589,12 @@ hipError_t launch_gather2(const int32_t* inv, const double* a, const double* b, 
 // Move selection, application and iteration end for every walk of the batch
 // (combine: after a pass launched with defer_combine).
 hipError_t launch_walk_step(const BatchLaunch& L, hipStream_t stream, bool combine = false);
+// The same for a proposal iteration over its proposal set, whose nrec best
+// records and snapshot the subset pass wrote.
+hipError_t launch_subset_step(const BatchLaunch& L, const LearnCtx* lc, int32_t nrec, hipStream_t stream);
+// The snapshot of a proposal iteration without a subset pass (no proposable
+// columns).
+hipError_t launch_subset_none(const WalkCtx* C, const LearnCtx* L, hipStream_t s);
 // Final copy of an incumbent found by a walk's last iteration.
 hipError_t launch_copy_best_batch(const BatchLaunch& L, hipStream_t stream);
 
@@ -727,7 +750,10 @@ hipError_t launch_learn_judge(const WalkCtx* C, const LearnCtx* L, hipStream_t s
 // Materialised inputs of every column at the walk's state (original order).
 hipError_t launch_learn_features_out(const WalkCtx* C, const LearnCtx* L, int32_t n, int64_t k, int64_t k_last_full,
                                      uint16_t* out, hipStream_t s);
-// Exact best shift of the proposal set (kernels_pass.hip).
+// Exact best shift of the proposal set (kernels_pass.hip), the best moves of
+// its workgroups and the iteration's snapshot; subset_records() of them.
+constexpr int kSubsetGeneralGrid = 1024;  // most workgroups of the subset sort kernel
+int32_t subset_records(const LearnCtx& Lh, int has_general);
 hipError_t launch_subset_pass(const WalkCtx* C, const LearnCtx* L, const LearnCtx& Lh, int has_general, int compact,
                               hipStream_t s);
 // Jump values (kernels_jump.hip): one wavefront task of a longer column (its
@@ -766,10 +792,6 @@ hipError_t launch_jump(const DevProblem& P, const double* x, const RowState* rs,
                        int32_t n_plain_tasks, const JumpBinTask* btasks, int32_t nbtasks, const JumpCol* cols,
                        int32_t ncols, int32_t n_plain_cols, int32_t n_chunk_cols, double* part, long long* bpart,
                        double* jv, double* js, hipStream_t s);
-// The same kernels with explicit grids (each kernel strides over its work).
-hipError_t launch_subset_grids(const WalkCtx* C, const LearnCtx* L, int chunk_grid, int combine_grid, int general_grid,
-                               int has_general, int compact, hipStream_t s);
-
 // The lists of affected rescoring. The affected columns of an iteration are
 // split into its lane-group columns (slist) and the rest (olist, with the
 // subset chunk offsets ooff). When every column outside the lane-group range
@@ -840,9 +862,6 @@ hipError_t launch_restart_fix(WalkState* st, const RestartKeep& keep, hipStream_
 // the subset combine.
 hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[3], int combine_grid,
                             int compact, hipStream_t s);
-// Move choice over the proposal set and the stored-row update of its move
-// (kernels_walk.hip).
-hipError_t launch_subset_select(const WalkCtx* C, const LearnCtx* L, hipStream_t s);
 
 }  // namespace chap
 
@@ -1072,8 +1091,11 @@ struct WalkSpec {
 };
 
 // Allocates one walk's buffers in A (a trace of trace_cap records when
-// trace_cap > 0; the compact row copy when the problem allows it).
-int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx& c);
+// trace_cap > 0; the compact row copy when the problem allows it). scan_all:
+// the move selection scans every column's kept score (walks that do not
+// score every column in every iteration), and has room for extra_rec records.
+int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx& c, bool scan_all = false,
+               int32_t extra_rec = 0);
 // Start point (seeded on the device, or the caller's x0) and the set-up
 // kernels of a walk on stream s: tabu list, residuals with unit weights (and
 // c.grow when set), state, incumbent check.
@@ -1081,7 +1103,7 @@ int init_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, const WalkCtx
               uint32_t* ticket, hipStream_t s);
 // alloc_walk + init_walk (the compact copy only when `compact`).
 int prepare_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, DeviceArena& A, WalkCtx& c, double* partial,
-                 uint32_t* ticket, hipStream_t s, int compact);
+                 uint32_t* ticket, hipStream_t s, int compact, bool scan_all = false, int32_t extra_rec = 0);
 // 1 when every walk of a run may keep the compact GatherRow copy.
 int compact_walks(const std::vector<WalkSpec>& specs, int64_t iters);
 // Copies a finished walk back into R (host order).
@@ -1090,10 +1112,4 @@ int collect_walk(const chap_problem* p, const WalkCtx& c, int64_t iters, double 
 // is reordered by XCD (order[i]: caller's index of ctx[i]; may be null).
 hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* L, std::vector<int32_t>* order);
 int blocks_for_host(int64_t work, int cap);
-// The parts of launch_walk_step: argmax + selection, application, end of
-// iteration.
-hipError_t launch_walk_choose(const BatchLaunch& L, hipStream_t stream, bool combine = false);
-hipError_t launch_walk_apply(const BatchLaunch& L, hipStream_t stream);
-hipError_t launch_walk_finish(const BatchLaunch& L, hipStream_t stream);
-
 }  // namespace chap

@@ -237,7 +237,6 @@ __global__ void k_learn_begin(const WalkCtx* __restrict__ walks, const LearnCtx*
   LearnState* ls = lc->ls;
   if (threadIdx.x != 0) return;
   WalkState* st = C.st;
-  st->skip = 0;
   if (st->k < st->iters) {
     ls->idle = 0;
     ls->train_active = 1;
@@ -705,17 +704,17 @@ __global__ __launch_bounds__(256) void k_learn_pairs(const WalkCtx* __restrict__
 }
 
 // Judge of a full evaluation (was its move in the network's proposal set?)
-// and the stored-row update of the move.
+// and the stored-row update of the move. Runs after the iteration's end.
 __global__ void k_learn_judge(const WalkCtx* __restrict__ walks, const LearnCtx* __restrict__ lc) {
   const WalkCtx& C = walks[0];
   const LearnCtx& L = *lc;
   const WalkState* st = C.st;
-  if (threadIdx.x != 0 || st->k >= st->iters) return;
+  if (threadIdx.x != 0 || st->sel_k < 0) return;
   LearnState* ls = L.ls;
   ls->evals += 1;
   const int q = st->mv_j;
   if (q < 0) return;
-  after_move(C, L);
+  after_move(C, L, q, st->mv_new, st->sel_k);
   const int32_t* set = L.sel[0];
   int lo = 0, hi = ls->tk[0].count - 1;
   while (lo <= hi) {

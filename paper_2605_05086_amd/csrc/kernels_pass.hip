@@ -50,6 +50,7 @@
 #include <type_traits>
 
 #include "chap_internal.h"
+#include "move_best.h"
 #include "narrow_finish.h"
 
 namespace chap {
@@ -216,25 +217,39 @@ __device__ __forceinline__ unsigned long long wave_or(unsigned long long v) {
 // ---------------------------------------------------------------------------
 
 // One normalised entry in breakpoint form: satisfied at p when p <= t (a > 0)
-// or p >= t (a < 0); what it adds to the score where it is satisfied, and
-// where it is not on either side of xbar.
+// or p >= t (a < 0), kept as p' <= t' with the sign of both flipped for a < 0;
+// what it adds to the score where it is satisfied, and where it is not on
+// either side of xbar.
 struct GroupTerm {
   double t;
-  float sat;    // satisfied
-  float left;   // not satisfied, p < xbar
-  float right;  // not satisfied, p > xbar
-  uint32_t ap;  // a > 0
+  float sat;      // satisfied
+  float left;     // not satisfied, p < xbar
+  float right;    // not satisfied, p > xbar
+  uint32_t flip;  // sign bit to flip
 };
 
+// A wavefront's columns: the terms of a column side by side in entry order
+// (a row, then its twin; the cutoff row last), its candidate positions
+// likewise with the bounds after them. Both lists are dense, so that columns
+// with few equality rows cost neither terms nor candidates for the twins that
+// they do not have.
+constexpr int kGroupTerms = 144;  // most of any width: 64 / G columns of 2 G + 1
+constexpr int kGroupCands = 176;  // 64 / G columns of 2 G + 3
 struct GroupSmem {
-  GroupTerm term[2][256];  // a lane's row and its twin
+  GroupTerm term[4][kGroupTerms];
+  double cand[4][kGroupCands];
 };
+
+__device__ __forceinline__ double flip_sign(double v, uint32_t flip) {
+  const unsigned long long u = __double_as_longlong(v);
+  return __longlong_as_double(u ^ ((unsigned long long)flip << 32));
+}
 
 __device__ __forceinline__ GroupTerm group_term(double t, bool ap, float w, double xb) {
   GroupTerm g;
   const bool s0 = ap ? (xb <= t) : (xb >= t);
-  g.t = t;
-  g.ap = ap ? 1u : 0u;
+  g.flip = ap ? 0u : 0x80000000u;
+  g.t = flip_sign(t, g.flip);
   g.sat = s0 ? 0.0f : w;
   g.left = s0 ? -w : (ap ? 0.5f * w : -0.5f * w);
   g.right = s0 ? -w : (ap ? -0.5f * w : 0.5f * w);
@@ -243,10 +258,8 @@ __device__ __forceinline__ GroupTerm group_term(double t, bool ap, float w, doub
 
 __device__ __forceinline__ double term_at(const GroupTerm& g, double p, bool right) {
   const float sat = g.sat, left = g.left, rgt = g.right;  // values, not addresses, to select from
-  const bool le = p <= g.t, ge = p >= g.t;
-  const bool s1 = g.ap ? le : ge;
   const float off = right ? rgt : left;
-  return (double)(s1 ? sat : off);
+  return (double)(flip_sign(p, g.flip) <= g.t ? sat : off);
 }
 
 // Orders the LDS writes and reads of one wavefront.
@@ -258,9 +271,10 @@ __device__ __forceinline__ void wave_sync() {
 
 // Column q by the G lanes of its group; row, a: this lane's stored entry (row
 // < 0: none; a column's entries fill its first lanes). Groups without a column
-// (in = false) take part in the exchanges and write nothing.
+// (in = false) take part in the exchanges and write nothing. Returns the
+// column's kept score on the group's first lane, 0 on the others.
 template <int G, bool kFlip, typename Rows>
-__device__ __forceinline__ void score_group(const WalkCtx& C, const Rows& rs, const WalkState* st, int q, bool in,
+__device__ __forceinline__ double score_group(const WalkCtx& C, const Rows& rs, const WalkState* st, int q, bool in,
                                             int row, double a, GroupSmem& S) {
   const DevProblem& P = C.P;
   const int tid = threadIdx.x, g = tid & (G - 1);
@@ -281,63 +295,73 @@ __device__ __forceinline__ void score_group(const WalkCtx& C, const Rows& rs, co
     if (g == 0 && c != 0.0) s += penalty(st->rc, st->rc + c * d, (double)st->wc, eps);
 #pragma unroll
     for (int o = 1; o < G; o <<= 1) s += __shfl_xor(s, o, kWave);
-    if (g == 0 && in) write_result(gmem(C.xhat), gmem(C.s), q, true, s, xn, xb);
-    return;
+    if (g != 0 || !in) return 0.0;
+    write_result(gmem(C.xhat), gmem(C.s), q, true, s, xn, xb);
+    return fmax(s, 0.0);
   }
   const bool isint = gmem(P.is_int)[q] != 0;
   const double l = gmem(P.lb)[q], u = gmem(P.ub)[q];
   const bool twin = has && r.w1 >= 0.0f;
-  const GroupTerm g0 = group_term(has ? breakpoint(xb, r.r, a, eps, isint) : 0.0, a > 0.0, r.w0, xb);
-  const GroupTerm g1 = group_term(twin ? breakpoint(xb, -r.r, -a, eps, isint) : 0.0, !(a > 0.0),
-                                  twin ? r.w1 : 0.0f, xb);
-  const bool any_twin = __any(twin);
-  S.term[0][tid] = g0;
-  if (any_twin) S.term[1][tid] = g1;
+  // the column's terms and candidates: slots by the entries and twins before
+  const int lane = tid & (kWave - 1), col = lane / G;
+  const unsigned long long mine = (G < kWave ? (1ull << (G & 63)) - 1ull : ~0ull) << (lane & ~(G - 1) & 63);
+  const unsigned long long bt = __ballot(twin) & mine;
+  const int deg = __popcll(__ballot(has) & mine), tw = __popcll(bt);
+  const int slot = g + __popcll(bt & ((1ull << lane) - 1ull));
+  const int nt = deg + tw + (c != 0.0 ? 1 : 0), nc = nt + 2;
+  GroupTerm* term = S.term[tid >> 6] + col * (2 * G + 1);
+  double* cand = S.cand[tid >> 6] + col * (2 * G + 3);
+  if (has) {
+    const double t = breakpoint(xb, r.r, a, eps, isint);
+    term[slot] = group_term(t, a > 0.0, r.w0, xb);
+    cand[slot] = t;
+  }
+  if (twin) {
+    const double t = breakpoint(xb, -r.r, -a, eps, isint);
+    term[slot + 1] = group_term(t, !(a > 0.0), r.w1, xb);
+    cand[slot + 1] = t;
+  }
+  if (g == 0) {
+    if (c != 0.0) {
+      const double t = breakpoint(xb, st->rc, c, eps, isint);
+      term[nt - 1] = group_term(t, c > 0.0, st->wc, xb);
+      cand[nt - 1] = t;
+    }
+    cand[nc - 2] = l;
+    cand[nc - 1] = u;
+  }
   wave_sync();
-  GroupTerm gc{0.0, 0.0f, 0.0f, 0.0f, 0u};
-  if (c != 0.0) gc = group_term(breakpoint(xb, st->rc, c, eps, isint), c > 0.0, st->wc, xb);
-  // this lane's candidates: its entry's breakpoints, and a bound (lanes 0 and
-  // 1) or the cutoff row's breakpoint (lane 2)
-  const double none = HUGE_VAL;  // never inside finite bounds, excluded by isfinite otherwise
-  double p[3];
-  p[0] = has ? g0.t : none;
-  p[1] = twin ? g1.t : none;
-  p[2] = g == 0 ? l : (g == 1 ? u : ((g == 2 && c != 0.0) ? gc.t : none));
-  bool right[3];
-  double v[3] = {0.0, 0.0, 0.0};
+  // candidates g, g + G (and g + 2 G where a column of the wavefront has that
+  // many) against every term of the column
+  constexpr int kC = 3;
+  const bool third = __any(nc > 2 * G);
+  double p[kC], v[kC];
+  bool right[kC];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) right[k] = p[k] > xb;
-  // entries fill the first lanes of every group: the wavefront runs to the
-  // longest of its columns
-  unsigned long long m = __ballot(has);
+  for (int k = 0; k < kC; ++k) {
+    p[k] = (g + k * G < nc) ? cand[g + k * G] : HUGE_VAL;
+    right[k] = p[k] > xb;
+    v[k] = 0.0;
+  }
+  if (third) {
+    for (int e = 0; e < nt; ++e) {
+      const GroupTerm t = term[e];
 #pragma unroll
-  for (int o = 32; o >= G; o >>= 1) m |= m >> o;
-  if constexpr (G < kWave) m &= (1ull << (G & 63)) - 1ull;
-  const int cnt = 64 - __builtin_clzll(m | 1ull) - (m == 0ull ? 1 : 0);
-  const int base = tid & ~(G - 1);
-  if (any_twin) {
-    for (int e = 0; e < cnt; ++e) {
-      const GroupTerm t0 = S.term[0][base + e], t1 = S.term[1][base + e];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        v[k] += term_at(t0, p[k], right[k]);
-        v[k] += term_at(t1, p[k], right[k]);
-      }
+      for (int k = 0; k < kC; ++k) v[k] += term_at(t, p[k], right[k]);
     }
   } else {
-    for (int e = 0; e < cnt; ++e) {
-      const GroupTerm t0 = S.term[0][base + e];
-      v[0] += term_at(t0, p[0], right[0]);
-      v[2] += term_at(t0, p[2], right[2]);
+    for (int e = 0; e < nt; ++e) {
+      const GroupTerm t = term[e];
+      v[0] += term_at(t, p[0], right[0]);
+      v[1] += term_at(t, p[1], right[1]);
     }
   }
   double best = -HUGE_VAL, at = HUGE_VAL;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < kC; ++k) {
     if (!(p[k] >= l && p[k] <= u) || p[k] == xb || !isfinite(p[k])) continue;
-    const double val = v[k] + term_at(gc, p[k], right[k]);
-    if (val > best || (val == best && p[k] < at)) {
-      best = val;
+    if (v[k] > best || (v[k] == best && p[k] < at)) {
+      best = v[k];
       at = p[k];
     }
   }
@@ -349,23 +373,47 @@ __device__ __forceinline__ void score_group(const WalkCtx& C, const Rows& rs, co
       at = op;
     }
   }
-  if (g == 0 && in) write_result(gmem(C.xhat), gmem(C.s), q, best > -HUGE_VAL, best, at, xb);
+  if (g != 0 || !in) return 0.0;
+  write_result(gmem(C.xhat), gmem(C.s), q, best > -HUGE_VAL, best, at, xb);
+  return fmax(best, 0.0);
+}
+
+// What a workgroup of the group kernel hands to the move selection: the
+// column of this lane and its kept score (0: none).
+struct GroupScore {
+  double s = 0.0;
+  int q = -1;
+  int j = 0;           // its original index
+  bool tabu = false;
+};
+
+// The move selection's data of column q, loaded ahead of the scoring.
+__device__ __forceinline__ void group_ids(const WalkCtx& C, const WalkState* st, bool first, int q, GroupScore& o) {
+  if (C.group_rec == 0 || !first) return;
+  o.j = gmem(C.P.perm)[q];
+  o.tabu = st->k <= (int64_t)gmem((const int32_t*)C.tabu)[q];
 }
 
 template <int G, bool kFlip, typename Rows>
-__device__ __forceinline__ void group_block(const WalkCtx& C, const Rows& rs, const WalkState* st, int cls, int b,
-                                            GroupSmem& S) {
+__device__ __forceinline__ GroupScore group_block(const WalkCtx& C, const Rows& rs, const WalkState* st, int cls,
+                                                  int b, GroupSmem& S) {
   const PassPlan& L = C.plan;
   const int64_t t = L.grp_off[cls] + (int64_t)b * 256 + (int)threadIdx.x;
   const int row = gmem(L.grp_row)[t];
   const double a = gmem(L.grp_val)[t];
-  const int q = L.grp_col[cls] + b * (256 / G) + (int)threadIdx.x / G, end = L.grp_col[cls + 1];
-  score_group<G, kFlip, Rows>(C, rs, st, min(q, end - 1), q < end, row, a, S);
+  const int end = L.grp_col[cls + 1];
+  const int qt = L.grp_col[cls] + b * (256 / G) + (int)threadIdx.x / G;
+  const int q = min(qt, end - 1);
+  GroupScore o;
+  group_ids(C, st, ((int)threadIdx.x & (G - 1)) == 0, q, o);
+  o.s = score_group<G, kFlip, Rows>(C, rs, st, q, qt < end, row, a, S);
+  o.q = qt < end ? q : -1;
+  return o;
 }
 
 // A binary column of any length by one wavefront.
 template <typename Rows>
-__device__ __forceinline__ void flip_wave(const WalkCtx& C, const Rows& rs, const WalkState* st, int q) {
+__device__ __forceinline__ double flip_wave(const WalkCtx& C, const Rows& rs, const WalkState* st, int q) {
   const DevProblem& P = C.P;
   const int lane = threadIdx.x & (kWave - 1);
   const double eps = P.eps;
@@ -385,12 +433,14 @@ __device__ __forceinline__ void flip_wave(const WalkCtx& C, const Rows& rs, cons
     if (c != 0.0) s += penalty(st->rc, st->rc + c * d, (double)st->wc, eps);
   }
   s = wave_sum(s);
-  if (lane == 0) write_result(gmem(C.xhat), gmem(C.s), q, true, s, xn, xb);
+  if (lane != 0) return 0.0;
+  write_result(gmem(C.xhat), gmem(C.s), q, true, s, xn, xb);
+  return fmax(s, 0.0);
 }
 
 // Workgroup b of the lane-group columns.
 template <typename Rows>
-__device__ __forceinline__ void group_task(const WalkCtx& C, const Rows& rs, const WalkState* st, int b,
+__device__ __forceinline__ GroupScore group_task(const WalkCtx& C, const Rows& rs, const WalkState* st, int b,
                                            GroupSmem& S) {
   const int32_t* blk = C.plan.grp_blk;
   int c = 0;
@@ -399,19 +449,25 @@ __device__ __forceinline__ void group_task(const WalkCtx& C, const Rows& rs, con
     if (b >= blk[k]) c = k;
   b -= blk[c];
   switch (c) {
-    case 0: group_block<4, true, Rows>(C, rs, st, 0, b, S); break;
-    case 1: group_block<8, true, Rows>(C, rs, st, 1, b, S); break;
-    case 2: group_block<16, true, Rows>(C, rs, st, 2, b, S); break;
-    case 3: group_block<32, true, Rows>(C, rs, st, 3, b, S); break;
-    case 4: group_block<64, true, Rows>(C, rs, st, 4, b, S); break;
-    case 5: group_block<4, false, Rows>(C, rs, st, 5, b, S); break;
-    case 6: group_block<8, false, Rows>(C, rs, st, 6, b, S); break;
-    case 7: group_block<16, false, Rows>(C, rs, st, 7, b, S); break;
-    case 8: group_block<32, false, Rows>(C, rs, st, 8, b, S); break;
-    case 9: group_block<64, false, Rows>(C, rs, st, 9, b, S); break;
+    case 0: return group_block<4, true, Rows>(C, rs, st, 0, b, S);
+    case 1: return group_block<8, true, Rows>(C, rs, st, 1, b, S);
+    case 2: return group_block<16, true, Rows>(C, rs, st, 2, b, S);
+    case 3: return group_block<32, true, Rows>(C, rs, st, 3, b, S);
+    case 4: return group_block<64, true, Rows>(C, rs, st, 4, b, S);
+    case 5: return group_block<4, false, Rows>(C, rs, st, 5, b, S);
+    case 6: return group_block<8, false, Rows>(C, rs, st, 6, b, S);
+    case 7: return group_block<16, false, Rows>(C, rs, st, 7, b, S);
+    case 8: return group_block<32, false, Rows>(C, rs, st, 8, b, S);
+    case 9: return group_block<64, false, Rows>(C, rs, st, 9, b, S);
     default: {
+      GroupScore o;
       const int q = C.plan.grp_col[kGroupClasses] + b * 4 + (int)(threadIdx.x >> 6);
-      if (q < C.plan.grp_col[kGroupClasses + 1]) flip_wave(C, rs, st, q);
+      if (q < C.plan.grp_col[kGroupClasses + 1]) {
+        group_ids(C, st, (threadIdx.x & 63) == 0, q, o);
+        o.s = flip_wave(C, rs, st, q);
+        o.q = q;
+      }
+      return o;
     }
   }
 }
@@ -424,10 +480,19 @@ __global__ __launch_bounds__(256) void k_group(const WalkCtx* __restrict__ walks
   if (w_ < 0) return;
   const WalkCtx& C = walks[w_];
   const WalkState* st = C.st;
-  if (st->k >= st->iters || st->pass_skip) return;
+  const bool rec = C.group_rec > 0;
+  const bool active = st->k < st->iters && !st->pass_skip;
+  if (rec && lb == 0 && threadIdx.x == 0) snapshot(C.st, active);
+  if (!active) return;
   __shared__ GroupSmem S;
   const Rows rs = rows_of<Rows>(C);
-  group_task<Rows>(C, rs, st, lb, S);
+  const GroupScore o = group_task<Rows>(C, rs, st, lb, S);
+  if (!rec) return;
+  // the walk's move selection: this workgroup's best moves, and the pending
+  // copy of a new incumbent (flagged by the previous iteration, before this
+  // iteration's move changes x)
+  if (st->copy_best && o.q >= 0) gmem(C.best_x)[o.q] = gmem((const double*)C.x)[o.q];
+  block_record_one<4>(o.s, o.j, o.q, o.tabu, C.best + lb);
 }
 
 // The lane-group columns of an affected-rescoring iteration (b of nb
@@ -1975,13 +2040,21 @@ __global__ __launch_bounds__(256) void k_subset_chunks(const WalkCtx* __restrict
 
 // One wavefront per selected binary or narrow column (grid-stride): its
 // chunks in order, then the flip score or the bins' scan and argmax.
+// With rec (proposal iterations), also the iteration's snapshot and the best
+// moves of every workgroup.
 __global__ __launch_bounds__(256) void k_subset_combine(const WalkCtx* __restrict__ walks,
-                                                        const LearnCtx* __restrict__ lc) {
+                                                        const LearnCtx* __restrict__ lc, int32_t rec) {
   const WalkCtx& C = walks[0];
   const LearnCtx& L = *lc;
   const DevProblem& P = C.P;
   const WalkState* st = C.st;
-  if (st->k >= st->iters || L.ls->idle) return;
+  const bool active = st->k < st->iters && !L.ls->idle;
+  if (rec && blockIdx.x == 0 && threadIdx.x == 0) snapshot(C.st, active);
+  if (!active) return;
+  BestPair best_pair;
+  auto offer = [&](int q, bool found, double v) {
+    if (rec && found && v > 0.0) best_pair.offer(v, C.P.perm[q], q, st->k <= (int64_t)C.tabu[q]);
+  };
   const int count = L.ls->tk[0].count;
   const int lane = threadIdx.x & 63;
   for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < count; i += gridDim.x * 4) {
@@ -1994,7 +2067,10 @@ __global__ __launch_bounds__(256) void k_subset_combine(const WalkCtx* __restric
     if (cl == SUB_FLIP) {
       double v = 0.0;
       for (int c = c0; c < c1; ++c) v += L.sub_parts[c].beta;
-      if (lane == 0) write_result(C.xhat, C.s, q, true, v, 1.0 - xb, xb);
+      if (lane == 0) {
+        write_result(C.xhat, C.s, q, true, v, 1.0 - xb, xb);
+        offer(q, true, v);
+      }
       continue;
     }
     double bv = 0.0, b = 0.0, a = 0.0;
@@ -2011,8 +2087,12 @@ __global__ __launch_bounds__(256) void k_subset_combine(const WalkCtx* __restric
     bool found;
     double best, bestp;
     narrow_finish(bv, b, a, cand, xb, l, W, lane, found, best, bestp);
-    if (lane == 0) write_result(C.xhat, C.s, q, found, best, bestp, xb);
+    if (lane == 0) {
+      write_result(C.xhat, C.s, q, found, best, bestp, xb);
+      offer(q, found, best);
+    }
   }
+  if (rec) block_record<4>(best_pair, C.best + blockIdx.x);
 }
 
 // One workgroup per selected general column (grid-stride; Algorithm 1 with
@@ -2026,8 +2106,9 @@ struct SubsetGeneralSmem {
   int redk[8];
 };
 
+// out: this workgroup's best moves, or null.
 __device__ __forceinline__ void subset_general_body(const WalkCtx& C, const LearnCtx& L, int b, int nb,
-                                                    SubsetGeneralSmem& SM) {
+                                                    SubsetGeneralSmem& SM, MoveRecord* out) {
   const DevProblem& P = C.P;
   const WalkState* st = C.st;
   if (st->k >= st->iters || L.ls->idle) return;
@@ -2039,6 +2120,7 @@ __device__ __forceinline__ void subset_general_body(const WalkCtx& C, const Lear
   int* redk = SM.redk;
   const int tid = threadIdx.x;
   const int count = L.ls->tk[0].count;
+  BestPair best_pair;
   for (int i = b; i < count; i += nb) {
     const int q = L.sel[0][i];
     if (L.cls[q] != SUB_GENERAL) continue;
@@ -2070,16 +2152,21 @@ __device__ __forceinline__ void subset_general_body(const WalkCtx& C, const Lear
     bool found;
     double best, bestp;
     scan_argmax(spos, smk, sdel, cap, beta, alpha, xb, P.lb[q], P.ub[q], red, redk, found, best, bestp);
-    if (tid == 0) write_result(C.xhat, C.s, q, found, best, bestp, xb);
+    if (tid == 0) {
+      write_result(C.xhat, C.s, q, found, best, bestp, xb);
+      if (out && found && best > 0.0) best_pair.offer(best, P.perm[q], q, st->k <= (int64_t)C.tabu[q]);
+    }
     // every reader of this column's LDS arrays is done before the next one
     __syncthreads();
   }
+  if (out && tid == 0) *out = best_pair.record();
 }
 
 __global__ __launch_bounds__(256) void k_subset_general(const WalkCtx* __restrict__ walks,
-                                                        const LearnCtx* __restrict__ lc) {
+                                                        const LearnCtx* __restrict__ lc, int32_t rec_from) {
   __shared__ SubsetGeneralSmem SM;
-  subset_general_body(walks[0], *lc, (int)blockIdx.x, (int)gridDim.x, SM);
+  subset_general_body(walks[0], *lc, (int)blockIdx.x, (int)gridDim.x, SM,
+                      rec_from >= 0 ? walks[0].best + rec_from + blockIdx.x : nullptr);
 }
 
 // The scoring of an affected-rescoring iteration in one launch: workgroups
@@ -2103,18 +2190,6 @@ __global__ __launch_bounds__(256) void k_aff_score(const WalkCtx* __restrict__ w
 
 }  // namespace
 
-hipError_t launch_subset_grids(const WalkCtx* C, const LearnCtx* L, int chunk_grid, int combine_grid, int general_grid,
-                               int has_general, int compact, hipStream_t s) {
-  const dim3 grid((unsigned)std::max(chunk_grid, 1));
-  if (compact)
-    hipLaunchKernelGGL(k_subset_chunks<CompactRows>, grid, dim3(256), 0, s, C, L);
-  else
-    hipLaunchKernelGGL(k_subset_chunks<FullRows>, grid, dim3(256), 0, s, C, L);
-  hipLaunchKernelGGL(k_subset_combine, dim3((unsigned)std::max(combine_grid, 1)), dim3(256), 0, s, C, L);
-  if (has_general) hipLaunchKernelGGL(k_subset_general, dim3((unsigned)std::max(general_grid, 1)), dim3(256), 0, s, C, L);
-  return hipGetLastError();
-}
-
 hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[3], int combine_grid,
                             int compact, hipStream_t s) {
   const unsigned total = (unsigned)(g[0] + g[1]);
@@ -2122,18 +2197,31 @@ hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* r
     hipLaunchKernelGGL(k_aff_score<CompactRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1]);
   else
     hipLaunchKernelGGL(k_aff_score<FullRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1]);
-  if (g[2] > 0) hipLaunchKernelGGL(k_subset_general, dim3((unsigned)g[2]), dim3(256), 0, s, C, L);
+  if (g[2] > 0) hipLaunchKernelGGL(k_subset_general, dim3((unsigned)g[2]), dim3(256), 0, s, C, L, -1);
   // without columns outside the lane-group range there is nothing to combine
   if (g[1] > 0)
-    hipLaunchKernelGGL(k_subset_combine, dim3((unsigned)std::max(combine_grid, 1)), dim3(256), 0, s, C, L);
+    hipLaunchKernelGGL(k_subset_combine, dim3((unsigned)std::max(combine_grid, 1)), dim3(256), 0, s, C, L, 0);
   return hipGetLastError();
+}
+
+static int subset_general_grid(const LearnCtx& Lh) { return std::min(Lh.K[0], kSubsetGeneralGrid); }
+
+int32_t subset_records(const LearnCtx& Lh, int has_general) {
+  return (Lh.K[0] + 3) / 4 + (has_general ? subset_general_grid(Lh) : 0);
 }
 
 hipError_t launch_subset_pass(const WalkCtx* C, const LearnCtx* L, const LearnCtx& Lh, int has_general, int compact,
                               hipStream_t s) {
-  const int K = Lh.K[0];
-  return launch_subset_grids(C, L, std::min(kSubsetGrid, std::max(Lh.sub_cap, 1)), (K + 3) / 4, K, has_general,
-                             compact, s);
+  const dim3 chunks((unsigned)std::min(kSubsetGrid, std::max(Lh.sub_cap, 1)));
+  const int combine = (Lh.K[0] + 3) / 4;
+  if (compact)
+    hipLaunchKernelGGL(k_subset_chunks<CompactRows>, chunks, dim3(256), 0, s, C, L);
+  else
+    hipLaunchKernelGGL(k_subset_chunks<FullRows>, chunks, dim3(256), 0, s, C, L);
+  hipLaunchKernelGGL(k_subset_combine, dim3((unsigned)combine), dim3(256), 0, s, C, L, 1);
+  if (has_general)
+    hipLaunchKernelGGL(k_subset_general, dim3((unsigned)subset_general_grid(Lh)), dim3(256), 0, s, C, L, combine);
+  return hipGetLastError();
 }
 
 int32_t kernel_blocks(const WalkCtx& c, int slot) {
@@ -2147,9 +2235,8 @@ int32_t kernel_blocks(const WalkCtx& c, int slot) {
     case KS_STAGE: return p.n_stage_rtasks;
     case KS_STAGE_SCORE: return p.n_stage_units * kXcds;
     case KS_ARGMAX: return c.argmax_blocks + c.argmax_comb;
-    case KS_SELECT: return 1;
-    case KS_APPLY: return c.apply_blocks;
-    case KS_FINISH: return 1;
+    case KS_STEP: return c.apply_blocks;
+    case KS_COPY: return blocks_for_host(c.P.n, 256);
     default:
       if (slot >= KS_SORT0 && slot < KS_SORT0 + kSortCaps)
         return p.sort_begin[slot - KS_SORT0 + 1] - p.sort_begin[slot - KS_SORT0];

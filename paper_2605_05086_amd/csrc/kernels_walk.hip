@@ -14,6 +14,7 @@
 #include "chap_internal.h"
 #include "exact_sum.h"
 #include "learned_rows.h"
+#include "move_best.h"
 #include "narrow_finish.h"
 
 namespace chap {
@@ -621,8 +622,7 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
   st->iters = iters;
   st->tenure = tenure;
   o.store(st);
-  st->j_all = -1;
-  st->j_nt = -1;
+  st->sel_k = -1;
   st->mv_j = -1;
   st->mv_kind = 2;
   st->dV = 0ull;
@@ -630,40 +630,16 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
   // half weights only when it is an integer below 2^16 (the rows are
   // checked where the copy is written)
   st->compact_rows = (o.wc == floorf(o.wc) && o.wc >= 0.0f && o.wc < 65535.0f) ? 1 : 0;
-  st->skip = 0;
   st->aff_ok = 0;
   st->pass_skip = 0;
   st->aff_iters = 0;
 }
 
-__device__ __forceinline__ bool better(double sa, int ja, double sb, int jb) {
-  return sa > sb || (sa == sb && ja < jb);
-}
-
-// Running best (score desc, original index asc) with the internal index.
-struct Best {
-  double s = 0.0;
-  int j = INT_MAX;  // original index
-  int q = -1;       // internal index
-  __device__ __forceinline__ void offer(double s2, int j2, int q2) {
-    if (better(s2, j2, s, j)) {
-      s = s2;
-      j = j2;
-      q = q2;
-    }
-  }
-  __device__ __forceinline__ void wave_reduce() {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) offer(__shfl_xor(s, o, kWave), __shfl_xor(j, o, kWave), __shfl_xor(q, o, kWave));
-  }
-};
-
-constexpr int kPartialStride = kArgmaxRecord;
-
-// Best positive score overall and among non-tabu variables, ties to the
-// lowest original index; one partial record per workgroup. The pending copy
-// of a new incumbent (flagged by the previous iteration, before this
-// iteration's move changes x) is done here too.
+// Best positive score overall and among non-tabu variables of the columns the
+// pass did not record itself (from C.scan_from on), ties to the lowest
+// original index; one record per workgroup. The pending copy of a new
+// incumbent (flagged by the previous iteration, before this iteration's move
+// changes x) is done here too for those columns.
 //
 // With `combine` the long narrow columns' scores are not in s yet: the
 // workgroups past argmax_blocks combine their partial bins, one wavefront
@@ -682,13 +658,13 @@ __global__ __launch_bounds__(256) void k_argmax(const WalkCtx* __restrict__ walk
   const gptr<const double> x = gmem((const double*)C.x);
   const gptr<double> best_x = gmem(C.best_x);
   const int32_t n = C.P.n;
-  if (st->k >= st->iters) return;
-  __shared__ double sa_s[4], sn_s[4];
-  __shared__ int ja_s[4], jn_s[4], qa_s[4], qn_s[4];
+  const bool active = st->k < st->iters;
+  if (lb == 0 && threadIdx.x == 0) snapshot(C.st, active);
+  if (!active) return;
   const int64_t k = st->k;
   const bool copy = st->copy_best != 0;
-  Best ba, bn;
-  const int gt = lb * blockDim.x + threadIdx.x;
+  BestPair best;
+  const int gt = C.scan_from + lb * blockDim.x + threadIdx.x;
   const int gs = C.argmax_blocks * blockDim.x;
   const int ncc = combine ? C.plan.n_chunk_cols : 0;
   const int cq0 = ncc > 0 ? C.plan.chunk_cols[0].col : 0;
@@ -697,23 +673,19 @@ __global__ __launch_bounds__(256) void k_argmax(const WalkCtx* __restrict__ walk
     if (idx < ncc) {
       int q;
       const double v = combine_col(C, idx, threadIdx.x & 63, &q);
-      if ((threadIdx.x & 63) == 0 && v > 0.0) {
-        const int j = perm[q];
-        ba.offer(v, j, q);
-        if (k > (int64_t)tabu[q]) bn.offer(v, j, q);
-      }
+      if ((threadIdx.x & 63) == 0 && v > 0.0) best.offer(v, perm[q], q, k <= (int64_t)tabu[q]);
     }
   } else {
     if (copy)
       for (int q = gt; q < n; q += gs) best_x[q] = x[q];
     // kU columns per thread and step, every load issued before any is used
     constexpr int kU = 8;
-    for (int q0 = gt; q0 < n; q0 += kU * gs) {
+    for (int64_t q0 = gt; q0 < n; q0 += (int64_t)kU * gs) {
       double v[kU];
       int j[kU], tb[kU];
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const int q = q0 + u * gs;
+        const int64_t q = q0 + (int64_t)u * gs;
         v[u] = 0.0;
         if (q < n) {
           v[u] = s[q];
@@ -723,267 +695,318 @@ __global__ __launch_bounds__(256) void k_argmax(const WalkCtx* __restrict__ walk
       }
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const int q = q0 + u * gs;
-        if (q < n && v[u] > 0.0 && (unsigned)(q - cq0) >= (unsigned)ncc) {
-          ba.offer(v[u], j[u], q);
-          if (k > (int64_t)tb[u]) bn.offer(v[u], j[u], q);
-        }
+        const int64_t q = q0 + (int64_t)u * gs;
+        if (q < n && v[u] > 0.0 && (uint64_t)(q - cq0) >= (uint64_t)ncc)
+          best.offer(v[u], j[u], (int)q, k <= (int64_t)tb[u]);
       }
     }
   }
-  ba.wave_reduce();
-  bn.wave_reduce();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) {
-    sa_s[wv] = ba.s;
-    ja_s[wv] = ba.j;
-    qa_s[wv] = ba.q;
-    sn_s[wv] = bn.s;
-    jn_s[wv] = bn.j;
-    qn_s[wv] = bn.q;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) {
-      ba.offer(sa_s[w], ja_s[w], qa_s[w]);
-      bn.offer(sn_s[w], jn_s[w], qn_s[w]);
-    }
-    double* rec = C.argmax_partial + kPartialStride * lb;
-    rec[0] = ba.s;
-    rec[1] = (double)ba.j;
-    rec[2] = (double)ba.q;
-    rec[3] = bn.s;
-    rec[4] = (double)bn.j;
-    rec[5] = (double)bn.q;
-  }
+  block_record<4>(best, C.best + C.group_rec + lb);
 }
 
-// Reduces the per-thread bests of a workgroup (every thread gets the result).
-__device__ __forceinline__ void block_best(Best& ba, Best& bn) {
-  __shared__ double sa_s[4], sn_s[4];
-  __shared__ int ja_s[4], jn_s[4], qa_s[4], qn_s[4];
-  ba.wave_reduce();
-  bn.wave_reduce();
+// ---------------------------------------------------------------------------
+// k_step: the rest of an iteration in one launch.
+//
+// Selection: every workgroup reduces the iteration's best-move records (a few
+// hundred to a few thousand of 32 bytes) for itself, so that no kernel boundary
+// stands between the choice and its application. Every input of the choice is
+// left alone until the walk's last workgroup ends the iteration: the records,
+// the snapshot of the iteration and its violated rows, x, xhat and s.
+//
+// Tabu/aspiration: a tabu overall best is taken only if its move leaves no
+// violated row; since a move changes at most one violation per normalised
+// entry of its column, that is impossible while V exceeds the column's entry
+// count, and the column is only scanned otherwise, then by workgroup 0, which
+// also does the rest alone (the others must not change rows it still reads).
+//
+// Application: the move's rows, or the weights of every violated row (a
+// reweight), over as many workgroups as their number asks for; the others
+// leave. With recompute = 0 the rows are updated as r += a_ij d, exact on
+// all-integer data; otherwise each touched row is summed again from scratch so
+// the kept residual equals its definition bit for bit.
+//
+// End of the iteration (objective, cutoff row, incumbent rule, trace, k + 1)
+// by one wavefront of the workgroup that finishes last, found by one 64-bit
+// atomic that counts workgroups and sums their violation changes; a move of
+// one workgroup needs no atomic. No fence: the last workgroup reads nothing
+// that another one wrote except that word.
+//
+// Bound: latency. One launch replaces four (5 us each at the least in a graph:
+// selection, application, end, and the scan of s where the pass records its
+// best moves itself).
+// ---------------------------------------------------------------------------
+
+constexpr int kStepWaves = kStepThreads / kWave;
+
+struct StepSmem {
+  MoveRecord rec[kStepWaves];
+  int red[kStepWaves];
+  long long total;
+  int last;
+};
+
+// Sum over the workgroup (a thread's violation changes fit 32 bits, and so do
+// a wavefront's).
+__device__ __forceinline__ long long step_sum(int v, StepSmem& S) {
+  v = wave_sum_int(v);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) {
-    sa_s[wv] = ba.s;
-    ja_s[wv] = ba.j;
-    qa_s[wv] = ba.q;
-    sn_s[wv] = bn.s;
-    jn_s[wv] = bn.j;
-    qn_s[wv] = bn.q;
-  }
+  if (lane == 0) S.red[wv] = v;
   __syncthreads();
-  for (int w = 0; w < 4; ++w) {
-    ba.offer(sa_s[w], ja_s[w], qa_s[w]);
-    bn.offer(sn_s[w], jn_s[w], qn_s[w]);
-  }
+  long long t = 0;
+#pragma unroll
+  for (int w = 0; w < kStepWaves; ++w) t += S.red[w];
+  return t;
 }
 
-// Tabu/aspiration decision of one workgroup from the best positive score
-// overall (ba) and among non-tabu columns (bn). A tabu overall best is taken
-// only if its move leaves no violated row; since a move changes at most one
-// violation per normalised entry of its column, that is impossible while V
-// exceeds the column's entry count, and the column is only scanned
-// otherwise. Without a move the kind is `none_kind` (a reweight for the full
-// pass); moves get `kind_offset` added. Writes the chosen step and trace
-// record; returns the kind.
-__device__ int decide(const WalkCtx& C, const Best& ba, const Best& bn, int none_kind, int kind_offset) {
-  __shared__ long long red[4];
+// Violation change of column q moved by d, one workgroup.
+__device__ long long step_violations(const WalkCtx& C, int q, double d, StepSmem& S) {
   const DevProblem& P = C.P;
-  const double* x = C.x;
-  const double* xhat = C.xhat;
-  const double* s = C.s;
-  const RowState* rs = C.rs;
-  WalkState* st = C.st;
+  const WalkState* st = C.st;
   const double eps = P.eps;
-  const int64_t k = st->k;
-  const int qa = (ba.j == INT_MAX) ? -1 : ba.q;
-  const int qn = (bn.j == INT_MAX) ? -1 : bn.q;
-  int qstar = -1, jstar = -1, kind = none_kind;
-  if (qa >= 0 && k > (int64_t)C.tabu[qa]) {
-    qstar = qa;
-    jstar = ba.j;
-    kind = 0;
-  } else if (qa >= 0) {
-    const int beg = P.col_ptr[qa], end = P.col_ptr[qa + 1];
-    const int64_t bound = 2 * (int64_t)(end - beg) + 1;
-    long long dv = 0;
-    if (st->V <= bound) {
-      const double d = xhat[qa] - x[qa];
-      for (int e = beg + threadIdx.x; e < end; e += blockDim.x) {
-        const RowState r = rs[P.col_row[e]];
-        const double r2 = r.r + P.col_val[e] * d;
-        dv += viol_change(r.r, r2, eps);
-        if (r.w1 >= 0.0f) dv += viol_change(-r.r, -r2, eps);
-      }
-      dv = block_sum_ll(dv, red);
-      if (st->cut_active) {
-        const double c = P.obj[qa];
-        if (c != 0.0) dv += viol_change(st->rc, st->rc + c * d, eps);
-      }
-    }
-    if (st->V <= bound && st->V + dv == 0) {
-      qstar = qa;
-      jstar = ba.j;
-      kind = 1;
-    } else if (qn >= 0) {
-      qstar = qn;
-      jstar = bn.j;
-      kind = 0;
-    }
+  int mine = 0;
+  for (int e = P.col_ptr[q] + (int)threadIdx.x; e < P.col_ptr[q + 1]; e += kStepThreads) {
+    const RowState r = C.rs[P.col_row[e]];
+    const double r2 = r.r + P.col_val[e] * d;
+    mine += viol_change(r.r, r2, eps);
+    if (r.w1 >= 0.0f) mine += viol_change(-r.r, -r2, eps);
   }
-  if (qstar >= 0) kind += kind_offset;
-  if (threadIdx.x != 0) return kind;
-  st->j_all = (qa >= 0) ? ba.j : -1;
-  st->s_all = ba.s;
-  st->j_nt = (qn >= 0) ? bn.j : -1;
-  st->s_nt = bn.s;
-  st->copy_best = 0;
-  st->mv_j = qstar;
-  st->mv_kind = kind;
-  chap_trace_record* t = C.trace + k;
-  t->iter = k;
-  t->var = jstar;
-  t->kind = kind;
-  if (qstar >= 0) {
-    const double xo = x[qstar], xn = xhat[qstar];
-    st->mv_old = xo;
-    st->mv_new = xn;
-    st->mv_delta = xn - xo;
-    st->mv_score = s[qstar];
-    t->x_old = xo;
-    t->x_new = xn;
-    t->score = s[qstar];
-  } else {
-    st->mv_delta = 0.0;
-    t->x_old = 0.0;
-    t->x_new = 0.0;
-    t->score = 0.0;
+  long long dv = step_sum(mine, S);
+  if (st->cut_active) {
+    const double c = P.obj[q];
+    if (c != 0.0) dv += viol_change(st->rc, st->rc + c * d, eps);
   }
-  return kind;
+  return dv;
 }
 
-// One workgroup per walk: finishes the argmax over the partial records, then
-// the tabu/aspiration decision.
-__global__ __launch_bounds__(256) void k_select(const WalkCtx* __restrict__ walks) {
-  const WalkCtx& C = walks[blockIdx.x];
-  const double* partial = C.argmax_partial;
-  const int32_t nparts = C.argmax_blocks + C.argmax_comb;
-  if (C.st->k >= C.st->iters) return;
-  Best ba, bn;
-  const gptr<const double> pg = gmem(partial);
-  // all of a thread's records are loaded before any is compared
-  constexpr int kU = 4;
-  for (int b0 = threadIdx.x; b0 < nparts; b0 += kU * blockDim.x) {
-    double r[kU][6];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int b = b0 + u * blockDim.x;
-      if (b < nparts)
-#pragma unroll
-        for (int f = 0; f < 6; ++f) r[u][f] = pg[kPartialStride * b + f];
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-      if (b0 + u * (int)blockDim.x < nparts) {
-        ba.offer(r[u][0], (int)r[u][1], (int)r[u][2]);
-        bn.offer(r[u][3], (int)r[u][4], (int)r[u][5]);
-      }
-  }
-  block_best(ba, bn);
-  decide(C, ba, bn, 2, 0);
-}
+struct StepMove {
+  int64_t k;
+  int q, j, kind;  // internal and original column (-1: none), trace kind
+  double x_old, x_new, score;
+  double c;  // objective coefficient of the moved column
+};
 
-// Move choice of a proposal iteration over the proposal set, same rules as
-// k_select. Without an admissible move the iteration is a stall (no
-// reweight) and the block's remaining proposal iterations do nothing.
-__global__ __launch_bounds__(256) void k_subset_select(const WalkCtx* __restrict__ walks,
-                                                       const LearnCtx* __restrict__ lc) {
-  const WalkCtx& C = walks[0];
-  const LearnCtx& L = *lc;
+// What the end of the iteration needs of the state as it was before it, read
+// by wavefront 0 of every workgroup while the records arrive (nobody changes
+// it before the last workgroup of the walk does).
+struct StepState {
+  ObjState o;
+  WaveExact acc;
+  long long inf_V;
+  int tenure;
+};
+
+// Ends the iteration, one wavefront (the exact objective sum is spread over
+// its lanes); lane 0 writes. dV: violation change of the rows.
+__device__ __forceinline__ void step_finish(const WalkCtx& C, const StepMove& M, long long dV, StepState& T) {
   WalkState* st = C.st;
-  if (st->k >= st->iters) return;
-  if (L.ls->idle) {
-    if (threadIdx.x == 0) st->skip = 1;
-    return;
+  const int lane = threadIdx.x & (kWave - 1);
+  const double eps = C.P.eps;
+  ObjState& o = T.o;
+  o.copy_best = 0;  // a pending copy was done by the kernels before
+  o.V += dV;
+  const bool exact = C.objacc != nullptr;
+  WaveExact& acc = T.acc;
+  const double c = M.c;
+  if (M.q >= 0) {
+    if (c != 0.0) {
+      double r2 = 0.0;
+      if (exact) {
+        double p, e;
+        exact_product(c, M.x_new, p, e);
+        acc.add(p);
+        acc.add(e);
+        exact_product(c, M.x_old, p, e);
+        acc.add(-p);
+        acc.add(-e);
+        acc.normalize();
+        acc.store(C.objacc);
+        o.f = acc.round_nearest();
+        if (o.cut_active) r2 = o.cutoff_residual(&acc);
+      } else {
+        const double d = M.x_new - M.x_old;
+        r2 = o.rc + c * d;
+        o.f = o.f + c * d;
+      }
+      if (o.cut_active) {
+        o.V += viol_change(o.rc, r2, eps);
+        o.rc = r2;
+      }
+    }
+  } else if (M.kind != kStallKind && o.cut_active && o.rc > eps) {
+    o.wc = o.wc + 1.0f;
   }
-  const int64_t k = st->k;
-  const int cnt = L.ls->tk[0].count;
-  Best ba, bn;
-  for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-    const int q = L.sel[0][i];
-    const double v = C.s[q];
-    if (!(v > 0.0)) continue;
-    const int j = C.P.perm[q];
-    ba.offer(v, j, q);
-    if (k > (int64_t)C.tabu[q]) bn.offer(v, j, q);
-  }
-  block_best(ba, bn);
-  const int kind = decide(C, ba, bn, kStallKind, kProposalKind);
-  if (threadIdx.x == 0) {
-    st->skip = 0;
-    if (kind == kStallKind) {
-      L.ls->stalls += 1;
-      L.ls->idle = 1;
-    } else {
-      learned::after_move(C, L);
+  const long long V = o.V;
+  const double f = o.f;
+  const long long v_orig = V - ((o.cut_active && o.rc > eps) ? 1 : 0);
+  // the next iteration may rescore only the columns of the moved column's
+  // rows when this step changed nothing else the scores depend on: no
+  // reweight, no cutoff residual change, no incumbent (which moves the
+  // cutoff row)
+  const int aff = (M.q >= 0 && !(o.cut_active && c != 0.0) && V != 0) ? 1 : 0;
+  o.incumbent_check(eps, exact ? &acc : nullptr);
+  if (lane != 0) return;
+  chap_trace_record* t = C.trace + M.k;
+  t->iter = M.k;
+  t->var = M.j;
+  t->kind = M.kind;
+  t->x_old = M.x_old;
+  t->x_new = M.x_new;
+  t->score = M.score;
+  t->viol = V;
+  t->obj = f;
+  if (M.q >= 0) {
+    C.x[M.q] = M.x_new;
+    C.tabu[M.q] = (int32_t)(M.k + T.tenure);
+    if (v_orig > 0 && v_orig < T.inf_V) {
+      st->inf_V = v_orig;
+      st->inf_k = M.k;
     }
   }
+  o.store(st);
+  st->mv_j = M.q;
+  st->mv_kind = M.kind;
+  st->mv_old = M.x_old;
+  st->mv_new = M.x_new;
+  st->aff_ok = aff;
+  st->dV = 0ull;
+  st->k = M.k + 1;
 }
 
-
-// Applies the chosen move to the rows of one column, or the weight update to
-// every violated row; violation changes are summed into st->dV (read by
-// k_finish after this kernel). With recompute = 0 the rows are updated as
-// r += a_ij d, exact on all-integer data; otherwise each touched row is
-// summed again from scratch so the kept residual equals its definition bit
-// for bit.
-__global__ __launch_bounds__(256) void k_apply(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
-                                               int32_t nw) {
+// lc: null for an iteration over every column (no admissible move: a
+// reweight); else a proposal iteration over nrec records (no admissible move:
+// a stall, which makes no reweight and idles the rest of its block).
+__global__ __launch_bounds__(kStepThreads) void k_step(const WalkCtx* __restrict__ walks,
+                                                       const int32_t* __restrict__ off, int32_t nw,
+                                                       const LearnCtx* lc, int32_t nrec) {
   int lb;
   const int w_ = block_walk(off, nw, lb);
   if (w_ < 0) return;
   const WalkCtx& C = walks[w_];
   const DevProblem& P = C.P;
-  const double* x = C.x;
-  RowState* rs = C.rs;
   WalkState* st = C.st;
-  const int32_t recompute = C.recompute;
-  if (st->k >= st->iters || st->skip || st->mv_kind == kStallKind) return;
-  __shared__ long long red[4];
+  const int64_t k = st->sel_k;
+  if (k < 0) return;
+  __shared__ StepSmem S;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
   const double eps = P.eps;
-  const int jstar = st->mv_j;
-  const int gt = lb * blockDim.x + threadIdx.x;
-  const int gs = C.apply_blocks * blockDim.x;
-  long long dv = 0;
-  if (jstar >= 0 && recompute) {
+  // ---- selection
+  if (!lc) nrec = C.group_rec + C.argmax_blocks + C.argmax_comb;
+  StepState T;
+  if (wv == 0) {
+    T.o.load(st);
+    if (C.objacc) T.acc.load(C.objacc);
+    T.inf_V = st->inf_V;
+    T.tenure = st->tenure;
+  }
+  BestPair b;
+  {
+    const gptr<const MoveRecord> rec = gmem((const MoveRecord*)C.best);
+    // kU records per thread and step, every load issued before any is used
+    constexpr int kU = 4;
+    for (int i0 = tid; i0 < nrec; i0 += kU * kStepThreads) {
+      MoveRecord r[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int i = min(i0 + u * kStepThreads, nrec - 1);
+        r[u].s_all = rec[i].s_all;
+        r[u].s_free = rec[i].s_free;
+        r[u].j_all = rec[i].j_all;
+        r[u].q_all = rec[i].q_all;
+        r[u].j_free = rec[i].j_free;
+        r[u].q_free = rec[i].q_free;
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) b.offer(r[u]);  // the last record may be offered again
+    }
+    // wavefronts without a record (and their slots) hold none
+    const int used = min(kStepWaves, (nrec + kWave - 1) / kWave);
+    if (wv < used) {
+      b.wave_reduce();
+      if (lane == 0) S.rec[wv] = b.record();
+    }
+    __syncthreads();
+    b = BestPair();
+    if (lane < used) b.offer(S.rec[lane]);
+    b.wave_reduce();
+  }
+  StepMove M{k, -1, -1, lc ? kStallKind : 2, 0.0, 0.0, 0.0, 0.0};
+  const int qa = b.all.q;
+  const gptr<const double> x = gmem((const double*)C.x), xhat = gmem((const double*)C.xhat),
+                           sc = gmem((const double*)C.s);
+  bool solo = false;
+  if (qa >= 0 && b.all.j == b.free.j) {
+    M.q = qa;
+    M.j = b.all.j;
+    M.kind = 0;
+  } else if (qa >= 0) {
+    const int64_t V = st->sel_V;
+    const int64_t bound = 2 * (int64_t)(P.col_ptr[qa + 1] - P.col_ptr[qa]) + 1;
+    bool aspire = false;
+    if (V <= bound) {
+      if (lb != 0) return;
+      solo = true;
+      aspire = V + step_violations(C, qa, xhat[qa] - x[qa], S) == 0;
+    }
+    if (aspire) {
+      M.q = qa;
+      M.j = b.all.j;
+      M.kind = 1;
+    } else if (b.free.q >= 0) {
+      M.q = b.free.q;
+      M.j = b.free.j;
+      M.kind = 0;
+    }
+  }
+  if (M.q >= 0 && lc) M.kind += kProposalKind;
+  // ---- application
+  int beg = 0, end = 0;
+  if (M.q >= 0) {  // one round of loads
+    beg = P.col_ptr[M.q];
+    end = P.col_ptr[M.q + 1];
+    M.x_old = x[M.q];
+    M.x_new = xhat[M.q];
+    M.score = sc[M.q];
+    M.c = gmem(P.obj)[M.q];
+  }
+  const int deg = end - beg;
+  const bool resum = M.q >= 0 && C.recompute;
+  // a row summed again: by a wavefront while that leaves few rounds, else by
+  // kResidualLanes lanes (a short row leaves most of a wavefront idle)
+  const bool by_wave = resum && deg <= C.apply_blocks * kStepWaves * 2;
+  int nb = C.apply_blocks;
+  if (M.q >= 0) {
+    const int per = resum ? (by_wave ? kStepWaves : kStepThreads / kResidualLanes) : kStepThreads;
+    nb = max(1, min(nb, (deg + per - 1) / per));
+  } else if (M.kind == kStallKind) {
+    nb = 1;
+  }
+  if (solo) nb = 1;
+  if (lb >= nb) return;
+  const int gt = lb * kStepThreads + tid, gs = nb * kStepThreads;
+  RowState* rs = C.rs;
+  int dv = 0;  // this thread's violation changes
+  if (resum) {
     // every touched row is summed again in its stored order (products side by
-    // side, added in entry order): by a wavefront while there is one per row
-    // (long rows are the likelier ones to be touched, and the longest sets
-    // the time), else by kResidualLanes lanes
-    const double xn = st->mv_new;
-    const int beg = P.col_ptr[jstar], end = P.col_ptr[jstar + 1];
-    const int g = gt & (kResidualLanes - 1);
-    const bool wave = end - beg <= gs / kWave;
-    auto update = [&](int i, double acc) {
-      const RowState q = rs[i];
-      const double r2 = acc - P.row_rhs[i];
+    // side, added in entry order); its state and right-hand side q, rhs
+    auto update = [&](int i, RowState q, double rhs, double acc) {
+      const double r2 = acc - rhs;
       rs[i].r = r2;
       if (C.grow) C.grow[i].r = (int32_t)r2;
       dv += viol_change(q.r, r2, eps);
       if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
     };
-    if (wave) {
-      const int e = __builtin_amdgcn_readfirstlane(beg + gt / kWave);
-      if (e < end) {
+    if (by_wave) {
+      for (int e = __builtin_amdgcn_readfirstlane(beg + gt / kWave); e < end; e += gs / kWave) {
         const int i = __builtin_amdgcn_readfirstlane(P.col_row[e]);
-        const double acc = wave_row_sum(P, x, __builtin_amdgcn_readfirstlane(P.row_ptr[i]),
-                                        __builtin_amdgcn_readfirstlane(P.row_ptr[i + 1]), jstar, xn);
-        if ((threadIdx.x & (kWave - 1)) == 0) update(i, acc);
+        const RowState q = rs[i];
+        const double rhs = P.row_rhs[i];
+        const double acc = wave_row_sum(P, C.x, __builtin_amdgcn_readfirstlane(P.row_ptr[i]),
+                                        __builtin_amdgcn_readfirstlane(P.row_ptr[i + 1]), M.q, M.x_new);
+        if (lane == 0) update(i, q, rhs, acc);
       }
     } else {
+      const int g = gt & (kResidualLanes - 1);
       for (int e = beg + gt / kResidualLanes; e < end; e += gs / kResidualLanes) {
         const int i = P.col_row[e];
         double acc = 0.0;
@@ -993,19 +1016,16 @@ __global__ __launch_bounds__(256) void k_apply(const WalkCtx* __restrict__ walks
           double prod = 0.0;
           if (f < re) {
             const int c = P.row_col[f];
-            prod = P.row_val[f] * ((c == jstar) ? xn : x[c]);
+            prod = P.row_val[f] * ((c == M.q) ? M.x_new : x[c]);
           }
           const int cnt = min(kResidualLanes, re - e0);
           for (int t = 0; t < cnt; ++t) acc = acc + __shfl(prod, t, kResidualLanes);
         }
-        if (g == 0) update(i, acc);
+        if (g == 0) update(i, rs[i], P.row_rhs[i], acc);
       }
     }
-    dv = block_sum_ll(dv, red);
-    if (threadIdx.x == 0 && dv != 0) atomicAdd(&st->dV, (unsigned long long)dv);
-  } else if (jstar >= 0) {
-    const double d = st->mv_delta;
-    const int beg = P.col_ptr[jstar], end = P.col_ptr[jstar + 1];
+  } else if (M.q >= 0) {
+    const double d = M.x_new - M.x_old;
     for (int e = beg + gt; e < end; e += gs) {
       const int i = P.col_row[e];
       const RowState q = rs[i];
@@ -1015,98 +1035,58 @@ __global__ __launch_bounds__(256) void k_apply(const WalkCtx* __restrict__ walks
       dv += viol_change(q.r, r2, eps);
       if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
     }
-    dv = block_sum_ll(dv, red);
-    if (threadIdx.x == 0 && dv != 0) atomicAdd(&st->dV, (unsigned long long)dv);
-  } else {
-    for (int i = gt; i < P.ms; i += gs) {
-      const RowState q = rs[i];
-      if (q.r > eps) {
-        rs[i].w0 = q.w0 + 1.0f;
-        if (C.grow) C.grow[i].w0 = (uint16_t)(q.w0 + 1.0f);
+  } else if (M.kind != kStallKind) {
+    constexpr int kU = 4;  // rows per thread and step, loaded before any is used
+    for (int64_t i0 = gt; i0 < P.ms; i0 += (int64_t)kU * gs) {
+      RowState q[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t i = i0 + (int64_t)u * gs;
+        q[u] = i < P.ms ? rs[i] : RowState{0.0, 0.0f, -1.0f};
       }
-      if (q.w1 >= 0.0f && -q.r > eps) {
-        rs[i].w1 = q.w1 + 1.0f;
-        if (C.grow) C.grow[i].w1 = (uint16_t)(q.w1 + 1.0f);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t i = i0 + (int64_t)u * gs;
+        if (q[u].r > eps) {
+          rs[i].w0 = q[u].w0 + 1.0f;
+          if (C.grow) C.grow[i].w0 = (uint16_t)(q[u].w0 + 1.0f);
+        }
+        if (q[u].w1 >= 0.0f && -q[u].r > eps) {
+          rs[i].w1 = q[u].w1 + 1.0f;
+          if (C.grow) C.grow[i].w1 = (uint16_t)(q[u].w1 + 1.0f);
+        }
       }
+    }
+  }
+  // ---- the last workgroup ends the iteration
+  long long dV = step_sum(dv, S);
+  if (nb > 1) {
+    if (tid == 0) {
+      const unsigned long long mine = ((unsigned long long)dV << 16) + 1ull;
+      const unsigned long long sum = atomicAdd(&st->dV, mine) + mine;
+      S.last = (int)(sum & 0xFFFFull) == nb;
+      S.total = (long long)sum >> 16;
+    }
+    __syncthreads();
+    if (!S.last) return;
+    dV = S.total;
+  }
+  if (wv != 0) return;
+  step_finish(C, M, dV, T);
+  if (lc && lane == 0) {
+    if (M.q >= 0) {
+      learned::after_move(C, *lc, M.q, M.x_new, k);
+    } else {
+      lc->ls->stalls += 1;
+      lc->ls->idle = 1;
     }
   }
 }
 
-// Ends the iteration: objective, cutoff row, incumbent rule, trace, k + 1.
-// One wavefront per walk (the exact objective sum is spread over its lanes);
-// lane 0 writes.
-__global__ __launch_bounds__(64) void k_finish(const WalkCtx* __restrict__ walks) {
-  const WalkCtx& C = walks[blockIdx.x];
-  const DevProblem& P = C.P;
-  WalkState* st = C.st;
-  if (st->k >= st->iters || st->skip) return;
-  const int lane = threadIdx.x;
-  const double eps = P.eps;
-  const int64_t k = st->k;
-  const int jstar = st->mv_j;
-  ObjState o;
-  o.load(st);
-  o.V += (long long)st->dV;
-  const bool exact = C.objacc != nullptr;
-  WaveExact acc;
-  if (exact) acc.load(C.objacc);
-  if (jstar >= 0) {
-    const double c = P.obj[jstar];
-    const double xo = st->mv_old, xn = st->mv_new;
-    if (c != 0.0) {
-      double r2 = 0.0;
-      if (exact) {
-        double p, e;
-        exact_product(c, xn, p, e);
-        acc.add(p);
-        acc.add(e);
-        exact_product(c, xo, p, e);
-        acc.add(-p);
-        acc.add(-e);
-        acc.normalize();
-        acc.store(C.objacc);
-        o.f = acc.round_nearest();
-        if (o.cut_active) r2 = o.cutoff_residual(&acc);
-      } else {
-        const double d = st->mv_delta;
-        r2 = o.rc + c * d;
-        o.f = o.f + c * d;
-      }
-      if (o.cut_active) {
-        o.V += viol_change(o.rc, r2, eps);
-        o.rc = r2;
-      }
-    }
-    if (lane == 0) {
-      C.x[jstar] = xn;
-      C.tabu[jstar] = (int32_t)(k + st->tenure);
-    }
-  } else if (st->mv_kind != kStallKind && o.cut_active && o.rc > eps) {
-    o.wc = o.wc + 1.0f;
-  }
-  if (lane == 0) {
-    C.trace[k].viol = o.V;
-    C.trace[k].obj = o.f;
-    if (jstar >= 0) {
-      const long long v_orig = o.V - ((o.cut_active && o.rc > eps) ? 1 : 0);
-      if (v_orig > 0 && v_orig < st->inf_V) {
-        st->inf_V = v_orig;
-        st->inf_k = k;
-      }
-    }
-  }
-  // the next iteration may rescore only the columns of the moved column's
-  // rows when this step changed nothing else the scores depend on: no
-  // reweight, no cutoff residual change, no incumbent (which moves the
-  // cutoff row)
-  int aff = (jstar >= 0 && !(o.cut_active && P.obj[jstar] != 0.0)) ? 1 : 0;
-  if (o.V == 0) aff = 0;
-  o.incumbent_check(eps, exact ? &acc : nullptr);
-  if (lane != 0) return;
-  o.store(st);
-  st->aff_ok = aff;
-  st->dV = 0ull;
-  st->k = k + 1;
+__global__ __launch_bounds__(64) void k_subset_none(const WalkCtx* __restrict__ walks,
+                                                    const LearnCtx* __restrict__ lc) {
+  WalkState* st = walks[0].st;
+  if (threadIdx.x == 0) snapshot(st, st->k < st->iters && !lc->ls->idle);
 }
 
 __global__ __launch_bounds__(256) void k_copy_best(const double* __restrict__ x, double* __restrict__ best_x,
@@ -1116,14 +1096,16 @@ __global__ __launch_bounds__(256) void k_copy_best(const double* __restrict__ x,
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gs) best_x[j] = x[j];
 }
 
+__device__ __forceinline__ int copy_blocks(int32_t n) { return max(1, min((int)(((int64_t)n + 255) / 256), 256)); }
+
 __global__ __launch_bounds__(256) void k_copy_best_batch(const WalkCtx* __restrict__ walks,
                                                          const int32_t* __restrict__ off, int32_t nw) {
   int lb;
   const int w_ = block_walk(off, nw, lb);
   if (w_ < 0) return;
   const WalkCtx& C = walks[w_];
-  if (!C.st->copy_best || lb >= C.argmax_blocks) return;
-  const int gs = C.argmax_blocks * blockDim.x;
+  if (!C.st->copy_best) return;
+  const int gs = copy_blocks(C.P.n) * blockDim.x;
   for (int q = lb * blockDim.x + threadIdx.x; q < C.P.n; q += gs) C.best_x[q] = C.x[q];
 }
 
@@ -1574,30 +1556,26 @@ hipError_t launch_state_init(const DevProblem& P, const double* x, const RowStat
   return hipGetLastError();
 }
 
-hipError_t launch_walk_choose(const BatchLaunch& L, hipStream_t stream, bool combine) {
+hipError_t launch_walk_step(const BatchLaunch& L, hipStream_t stream, bool combine) {
   const int nw = L.nw;
   const int32_t comb = (combine && pass_defers_combine(L)) ? 1 : 0;
-  hipLaunchKernelGGL(k_argmax, dim3((unsigned)L.grid[KS_ARGMAX]), dim3(256), 0, stream, L.walks, L.off[KS_ARGMAX], nw,
-                     comb);
-  hipLaunchKernelGGL(k_select, dim3((unsigned)nw), dim3(256), 0, stream, L.walks);
+  if (L.total[KS_ARGMAX] > 0)
+    hipLaunchKernelGGL(k_argmax, dim3((unsigned)L.grid[KS_ARGMAX]), dim3(256), 0, stream, L.walks, L.off[KS_ARGMAX],
+                       nw, comb);
+  hipLaunchKernelGGL(k_step, dim3((unsigned)L.grid[KS_STEP]), dim3(kStepThreads), 0, stream, L.walks, L.off[KS_STEP],
+                     nw, nullptr, 0);
   return hipGetLastError();
 }
 
-hipError_t launch_walk_apply(const BatchLaunch& L, hipStream_t stream) {
-  hipLaunchKernelGGL(k_apply, dim3((unsigned)L.grid[KS_APPLY]), dim3(256), 0, stream, L.walks, L.off[KS_APPLY], L.nw);
+hipError_t launch_subset_step(const BatchLaunch& L, const LearnCtx* lc, int32_t nrec, hipStream_t stream) {
+  hipLaunchKernelGGL(k_step, dim3((unsigned)L.grid[KS_STEP]), dim3(kStepThreads), 0, stream, L.walks, L.off[KS_STEP],
+                     L.nw, lc, nrec);
   return hipGetLastError();
 }
 
-hipError_t launch_walk_finish(const BatchLaunch& L, hipStream_t stream) {
-  hipLaunchKernelGGL(k_finish, dim3((unsigned)L.nw), dim3(64), 0, stream, L.walks);
+hipError_t launch_subset_none(const WalkCtx* C, const LearnCtx* L, hipStream_t s) {
+  hipLaunchKernelGGL(k_subset_none, dim3(1), dim3(64), 0, s, C, L);
   return hipGetLastError();
-}
-
-hipError_t launch_walk_step(const BatchLaunch& L, hipStream_t stream, bool combine) {
-  hipError_t e = launch_walk_choose(L, stream, combine);
-  if (e == hipSuccess) e = launch_walk_apply(L, stream);
-  if (e == hipSuccess) e = launch_walk_finish(L, stream);
-  return e;
 }
 
 hipError_t launch_affected(const WalkCtx* C, LearnCtx* L, const AffLists& A, hipStream_t s) {
@@ -1620,14 +1598,9 @@ hipError_t launch_restart_fix(WalkState* st, const RestartKeep& keep, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_subset_select(const WalkCtx* C, const LearnCtx* L, hipStream_t s) {
-  hipLaunchKernelGGL(k_subset_select, dim3(1), dim3(256), 0, s, C, L);
-  return hipGetLastError();
-}
-
 hipError_t launch_copy_best_batch(const BatchLaunch& L, hipStream_t stream) {
-  hipLaunchKernelGGL(k_copy_best_batch, dim3((unsigned)L.grid[KS_ARGMAX]), dim3(256), 0, stream, L.walks,
-                     L.off[KS_ARGMAX], L.nw);
+  hipLaunchKernelGGL(k_copy_best_batch, dim3((unsigned)L.grid[KS_COPY]), dim3(256), 0, stream, L.walks,
+                     L.off[KS_COPY], L.nw);
   return hipGetLastError();
 }
 

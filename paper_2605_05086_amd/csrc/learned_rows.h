@@ -36,20 +36,15 @@ __device__ __forceinline__ void set_last_move(uint16_t* row, int32_t k) {
   row[13] = (uint16_t)((uint32_t)k >> 16);
 }
 
-// Stored-row update after the walk moved column st->mv_j at iteration st->k
-// (one thread, before the iteration ends).
-__device__ __forceinline__ void after_move(const WalkCtx& C, const LearnCtx& L) {
-  const WalkState* st = C.st;
-  const int q = st->mv_j;
-  if (q < 0) return;
+// Stored-row update of column q, moved to xn at iteration k (one thread).
+__device__ __forceinline__ void after_move(const WalkCtx& C, const LearnCtx& L, int q, double xn, int64_t k) {
   uint16_t* row = L.feat + (int64_t)q * 16;
   const int32_t mv = L.moves[q] + 1;
   L.moves[q] = mv;
-  const double xn = st->mv_new;
   row[7] = d2bf(position(xn, C.P.lb[q], C.P.ub[q]));
   row[11] = d2bf(sign_of(L.xhat_last[q] - xn));
   row[15] = d2bf(log2(1.0 + (double)mv));
-  set_last_move(row, (int32_t)st->k);
+  set_last_move(row, (int32_t)k);
 }
 
 }  // namespace learned
