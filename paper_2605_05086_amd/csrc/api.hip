@@ -607,8 +607,16 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
           ent_rb[rb].push_back((uint64_t)(i - rb * kStageRowBlock) | (lc << 16) | (a24 << 24));
         }
       }
+      // a pack's segments hold whole pairs of records, at even positions: its
+      // workgroup reads two records at a time
+      if ((int32_t)t < npk)
+        for (auto& v : ent_rb)
+          if (v.size() & 1) v.push_back((uint64_t)kStagePadSlot << 16 | (uint64_t)1 << 24);
     }
-    for (int32_t rb = 0; rb < nrb; ++rb) sseg[T * nrb + rb] = (int32_t)ent_rb[rb].size();
+    for (int32_t rb = 0; rb < nrb; ++rb) {
+      sseg[T * nrb + rb] = (int32_t)ent_rb[rb].size();
+      if (ent_rb[rb].size() & 1) ent_rb[rb].push_back((uint64_t)kStagePadSlot << 16 | (uint64_t)1 << 24);
+    }
     std::vector<std::vector<StageRowTask>> per_xcd(kXcds);
     // slices per row block: at most one per kStageSlice entries, and at most
     // the block's share of the workgroups the device holds at once, so that
@@ -621,9 +629,10 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         cus = 256;
       for (const auto& v : ent_rb) staged += (int64_t)v.size();
+      staged += L.stage_one_end - L.stage_one_begin;
       resident = (int64_t)kStageRowsPerCu * cus;
     }
-    int32_t qone = L.stage_one_begin;
+    int32_t qone = L.stage_one_begin, slices = 0;
     for (int32_t rb = 0; rb < nrb; ++rb) {
       const int32_t e0 = (int32_t)sent.size();
       for (size_t t = 0; t <= T; ++t) sseg[t * nrb + rb] += e0;
@@ -632,9 +641,14 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       const int32_t c0 = qone;
       while (qone < L.stage_one_end && crow[cptr[qone]] < (rb + 1) * kStageRowBlock) ++qone;
       const int32_t c1 = qone;
+      // slices: the block's share of the resident workgroups by its entries and
+      // single-entry columns, but none below kStageSlice entries (or
+      // kStageSliceCols columns) while there are fewer
       const int32_t by_e = (e1 - e0 + kStageSlice - 1) / kStageSlice;
-      const int32_t share = (int32_t)std::max<int64_t>(1, resident * (e1 - e0) / std::max<int64_t>(staged, 1));
-      const int32_t ns = std::max(std::min(by_e, share), (c1 - c0 + kStageSliceCols - 1) / kStageSliceCols);
+      const int32_t by_c = (c1 - c0 + kStageSliceCols - 1) / kStageSliceCols;
+      const int64_t work = (int64_t)(e1 - e0) + (c1 - c0);
+      const int32_t share = (int32_t)std::max<int64_t>(1, resident * work / std::max<int64_t>(staged, 1));
+      const int32_t ns = std::min(std::max(by_e, by_c), share);
       if (ns == 0) continue;
       const int32_t se = (e1 - e0 + ns - 1) / ns, sc = (c1 - c0 + ns - 1) / ns;
       for (int32_t k = 0; k < ns; ++k) {
@@ -644,7 +658,9 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
         rt.e_end = std::min(e1, e0 + (k + 1) * se);
         rt.c_beg = std::min(c1, c0 + k * sc);
         rt.c_end = std::min(c1, c0 + (k + 1) * sc);
-        per_xcd[rb % kXcds].push_back(rt);
+        // the slices of one row block share an XCD's L2 while there are blocks
+        // for every XCD; with few blocks their slices take all XCDs in turn
+        per_xcd[(nrb >= 8 * kXcds ? rb : slices++) % kXcds].push_back(rt);
       }
     }
     // per task: segment starts, then prefix counts of its records
@@ -779,16 +795,14 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
   P->d_pair = d_pair;
   P->d_nidx = d_nidx;
   D.row_c8 = nullptr;
-  {
-    bool fits = true;
-    for (double a : rval) fits = fits && a == std::nearbyint(a) && std::fabs(a) <= 127.0;
-    if (fits && !rval.empty()) {
-      std::vector<int8_t> c8(rval.size());
-      for (size_t e = 0; e < rval.size(); ++e) c8[e] = (int8_t)rval[e];
-      int8_t* d_c8;
-      CHAP_HIP(A.upload(&d_c8, c8));
-      D.row_c8 = d_c8;
-    }
+  bool fits8 = !rval.empty();
+  for (double a : rval) fits8 = fits8 && a == std::nearbyint(a) && std::fabs(a) <= 127.0;
+  if (fits8) {
+    std::vector<int8_t> c8(rval.size());
+    for (size_t e = 0; e < rval.size(); ++e) c8[e] = (int8_t)rval[e];
+    int8_t* d_c8;
+    CHAP_HIP(A.upload(&d_c8, c8));
+    D.row_c8 = d_c8;
   }
   D.rb_ent = nullptr;
   D.rb_c8 = nullptr;
@@ -874,15 +888,60 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
   if (L.stage) {
     StageTask* dt;
     int32_t* dseg;
-    uint64_t* dent;
     StageRowTask* drt;
     CHAP_HIP(A.upload(&dt, stasks));
     CHAP_HIP(A.upload(&dseg, sseg));
-    CHAP_HIP(A.upload(&dent, sent));
     CHAP_HIP(A.upload(&drt, srtasks));
+    if (fits8) {
+      L.stage_packed = 1;
+      std::vector<uint32_t> s32(sent.size());
+      for (size_t e = 0; e < sent.size(); ++e)
+        s32[e] = (uint32_t)(sent[e] & 0x1FFFu) | ((uint32_t)((sent[e] >> 16) & 0xFFu) << 13) |
+                 ((uint32_t)((sent[e] >> 24) & 0xFFu) << 21);
+      uint32_t* d32;
+      CHAP_HIP(A.upload(&d32, s32));
+      L.stage_ent32 = d32;
+    } else {
+      uint64_t* dent;
+      CHAP_HIP(A.upload(&dent, sent));
+      L.stage_ent = dent;
+    }
+    static_assert((int64_t)kStageMaxRb * kStageRowBlock <= (1 << 24), "rows of a staged instance fit 24 bits");
+    if (fits8 && L.stage_one_end > L.stage_one_begin) {
+      std::vector<uint32_t> one((size_t)(L.stage_one_end - L.stage_one_begin));
+      for (int32_t q = L.stage_one_begin; q < L.stage_one_end; ++q)
+        one[(size_t)(q - L.stage_one_begin)] =
+            (uint32_t)(crow[cptr[q]] % kStageRowBlock) | ((uint32_t)(uint8_t)(int8_t)cval[cptr[q]] << 16);
+      uint32_t* d_one;
+      CHAP_HIP(A.upload(&d_one, one));
+      L.stage_one = d_one;
+    }
+    {
+      bool fit = true;
+      for (int32_t j = 0; j < n && fit; ++j)
+        fit = cls[j] != NARROW || (P->lb[j] >= -32768.0 && P->ub[j] <= 32767.0);
+      if (fit) {
+        std::vector<uint32_t> lu((size_t)n, 0u);
+        for (int32_t q = 0; q < n; ++q)
+          if (cls[perm[q]] == NARROW)
+            lu[q] = (uint32_t)(uint16_t)(int16_t)lbq[q] | ((uint32_t)(uint16_t)(int16_t)ubq[q] << 16);
+        uint32_t* d_lu;
+        CHAP_HIP(A.upload(&d_lu, lu));
+        L.stage_lu = d_lu;
+      }
+    }
+    if (fits8 && !chunked.empty()) {
+      const int32_t e0 = cptr[chunk_begin], e1 = cptr[chunk_begin + (int32_t)chunked.size()];
+      std::vector<uint32_t> ce((size_t)(e1 - e0));
+      for (int32_t e = e0; e < e1; ++e)
+        ce[(size_t)(e - e0)] = ((uint32_t)crow[e] << 8) | (uint32_t)(uint8_t)(int8_t)cval[e];
+      uint32_t* d_ce;
+      CHAP_HIP(A.upload(&d_ce, ce));
+      L.chunk_ent = d_ce;
+      L.chunk_e0 = e0;
+    }
     L.stage_tasks = dt;
     L.stage_seg = dseg;
-    L.stage_ent = dent;
     L.stage_rtasks = drt;
     if (!sunits.empty()) {
       int32_t* du;

@@ -286,18 +286,24 @@ struct __align__(16) ChunkPartial {
 // needs no column data.
 //
 // Staged entry (uint64): bits 0..15 row inside its block, 16..23 column
-// slot inside its task, 24..47 coefficient (24-bit two's complement).
-// Record (uint64): bits 0..7 column slot, bit 8 coefficient > 0, bit 9 twin
-// row present, bits 10..17 and 18..25 the offsets of the row and of its twin
-// plus 64 (clamped to [-64, 64]); bits 32..63 the weights w0 | w1 << 16 when
-// the walk keeps compact rows, else the stored row.
+// slot inside its task, 24..47 coefficient (24-bit two's complement); where
+// every coefficient fits int8, uint32: bits 0..12 row, 13..20 slot, 21..28
+// coefficient.
+// Record (uint64): bits 0..7 column slot; 8..12 and 20..24 four times the
+// phase-1 case of the row and of its twin (see kCoefBeta), 13..19 and 25..31
+// the offsets of their breakpoints from xbar (two's complement, below -64
+// clamped to -64; an offset above 63 is a case of its own, offset 0; a row
+// without a twin has case 6 there, which adds nothing); bits 32..63 the
+// weights w0 | w1 << 16 (w1 = 0: no twin) when the walk keeps compact rows,
+// else the stored row.
 constexpr int kStageRowBlock = 8192;  // stored rows per block (64 KB of LDS)
-constexpr int kStageSlice = 16384;    // staged entries per workgroup of k_stage_rows (fewest)
+constexpr int kStageSlice = 1024;     // staged entries per workgroup of k_stage_rows (fewest)
+constexpr int kStagePadSlot = 255;    // column slot of a pack's padding entries (every segment holds whole pairs)
 constexpr int kStageRowsPerCu = 2;    // k_stage_rows workgroups resident per CU (64 KB of LDS each)
 constexpr int kStageShort = 256;      // short narrow columns per scoring task
 constexpr int kStageClamp = 64;       // offsets beyond +-64 leave every narrow column
 constexpr int kStageMaxRb = 256;      // row blocks a scoring workgroup can index in LDS
-constexpr int kStageSliceCols = 4096; // single-entry columns per workgroup of k_stage_rows
+constexpr int kStageSliceCols = 2048; // single-entry columns per workgroup of k_stage_rows (fewest)
 constexpr int kStagePackCols = 64;    // columns per staged pack (one lane each in the final scan)
 constexpr int kStagePackEntries = 3072;  // target stored entries per staged pack
 
@@ -373,6 +379,18 @@ struct PassPlan {
   const int32_t* stage_seg = nullptr;
   const StageRowTask* stage_rtasks = nullptr;
   const uint64_t* stage_ent = nullptr;
+  const uint32_t* stage_ent32 = nullptr;  // instead, where every coefficient fits int8
+  // the chunked columns' entries (internal entries from chunk_e0 on) as
+  // row << 8 | int8 coefficient, where every coefficient fits; else null
+  const uint32_t* chunk_ent = nullptr;
+  int32_t chunk_e0 = 0;
+  // single-entry column stage_one_begin + i: row inside its block | int8
+  // coefficient << 16 (null unless packed)
+  const uint32_t* stage_one = nullptr;
+  // bounds of every internal column as int16 l | u << 16, where those of all
+  // narrow columns fit (others hold anything); else null
+  const uint32_t* stage_lu = nullptr;
+  int32_t stage_packed = 0;  // every coefficient fits int8: stage_ent32, chunk_ent
   int32_t n_stage_ent = 0;
   int32_t stage_short_begin = 0, stage_short_end = 0;
   int32_t stage_one_begin = 0, stage_one_end = 0;  // single-entry short narrow columns

@@ -673,27 +673,67 @@ __device__ __forceinline__ int cutoff_offset(double xb, const WalkState* st, dou
   return (int)fmin(fmax(t - xb, -(double)kStageClamp), (double)kStageClamp);
 }
 
-// Coefficients, in half weights, of beta, alpha and delta of a row for the
-// six cases of phase1() (index 3 [a > 0] + sign(d) + 1): 4-bit fields.
-constexpr uint32_t pack6(int c0, int c1, int c2, int c3, int c4, int c5) {
+// The cases of phase1() in offset form (coefficient sign ap, breakpoint t =
+// xbar + d): 3 [a > 0] + sign(d) + 1, and two for a breakpoint above every
+// narrow column (d > 63), whose delta never applies and which is no
+// candidate: 6 for a > 0, 7 for a < 0. Tables of 4-bit fields: the
+// coefficients, in half weights, of what the row adds to beta, alpha and (from
+// its breakpoint on, or after it where kCaseAfter is 1) delta.
+constexpr uint32_t pack8(int c0, int c1, int c2, int c3, int c4, int c5, int c6, int c7) {
   return (uint32_t)(c0 & 15) | (uint32_t)(c1 & 15) << 4 | (uint32_t)(c2 & 15) << 8 | (uint32_t)(c3 & 15) << 12 |
-         (uint32_t)(c4 & 15) << 16 | (uint32_t)(c5 & 15) << 20;
+         (uint32_t)(c4 & 15) << 16 | (uint32_t)(c5 & 15) << 20 | (uint32_t)(c6 & 15) << 24 |
+         (uint32_t)(c7 & 15) << 28;
 }
-constexpr uint32_t kCoefBeta = pack6(-2, -2, -1, 2, 0, 0);
-constexpr uint32_t kCoefAlpha = pack6(0, 2, 2, -2, -2, 0);
-constexpr uint32_t kCoefDelta = pack6(2, 0, 1, -1, 0, -2);
-__device__ __forceinline__ int row_coef(uint32_t packed, int cs) { return ((int)(packed << (28 - 4 * cs))) >> 28; }
+constexpr uint32_t kCoefBeta = pack8(-2, -2, -1, 2, 0, 0, 0, -1);
+constexpr uint32_t kCoefAlpha = pack8(0, 2, 2, -2, -2, 0, 0, 2);
+constexpr uint32_t kCoefDelta = pack8(2, 0, 1, -1, 0, -2, 0, 0);
+constexpr uint32_t kCaseAfter = pack8(0, 0, 0, 1, 1, 1, 1, 0);
+constexpr int kCaseNone = 24;  // four times case 6
+// Field `at` (four times the case) of a table: one bit-field extract.
+__device__ __forceinline__ int row_coef(uint32_t table, int at) { return __builtin_amdgcn_sbfe((int)table, at, 4); }
+// Four times the case of a row with offset d in [-64, 64] (64: above).
+__device__ __forceinline__ int row_case(bool ap, int d) {
+  const int at = (ap ? 16 : 4) + 4 * min(max(d, -1), 1);
+  return d >= kStageClamp ? (ap ? 24 : 28) : at;
+}
+
+// Offsets of a row with integer residual r and coefficient a != 0, clamped to
+// [-64, 64]: *d0 of the row, *d1 of its negated twin. With A = |a|, f =
+// floor(-r / A) and c = ceil(-r / A), they are f and c for a > 0 and -f and -c
+// for a < 0. kSmall (A <= 127): the quotient is a float product with the
+// reciprocal, within 1.2e-5 of -r / A where |r / A| <= 65 (one ulp of the
+// reciprocal, half of one of the sum); 1/512 moves an integer quotient past its
+// own floor, and any other lies at least 1/127 from an integer, so floor and
+// ceil are exact; larger quotients are clamped whatever their rounding. 12
+// instructions against about 40 of the FP64 division with its clamps.
+template <bool kSmall>
+__device__ __forceinline__ void row_offsets(int r, int a, int* d0, int* d1) {
+  int f, c;
+  if constexpr (kSmall) {
+    constexpr float kBias = 1.0f / 512.0f, kLim = (float)kStageClamp;
+    const float n = -(float)r;
+    const float rc = __builtin_amdgcn_rcpf(fabsf((float)a));
+    f = (int)__builtin_amdgcn_fmed3f(floorf(__builtin_fmaf(n, rc, kBias)), -kLim, kLim);
+    c = (int)__builtin_amdgcn_fmed3f(ceilf(__builtin_fmaf(n, rc, -kBias)), -kLim, kLim);
+  } else {
+    const double q = -(double)r / fabs((double)a);
+    f = (int)fmin(fmax(floor(q), -(double)kStageClamp), (double)kStageClamp);
+    c = (int)fmin(fmax(ceil(q), -(double)kStageClamp), (double)kStageClamp);
+  }
+  *d0 = a > 0 ? f : -f;
+  *d1 = a > 0 ? c : -c;
+}
 
 // One row of a long column (one column per workgroup) in half weights:
 // beta, alpha and the candidate mask summed by the caller, delta into the
-// bins (the cases of phase1() in offset form, as add_row).
+// bins. half = w/2 in value units (a weight below 2^16).
 __device__ __forceinline__ void add_row_reg(bool ap, int d, int32_t half, int k0, int W, int32_t* bins,
                                             int32_t& beta, int32_t& alpha, unsigned long long& cand) {
-  const int cs = (ap ? 4 : 1) + (d > 0 ? 1 : 0) - (d < 0 ? 1 : 0);
-  beta += row_coef(kCoefBeta, cs) * half;
-  alpha += row_coef(kCoefAlpha, cs) * half;
+  const int at = (ap ? 16 : 4) + 4 * min(max(d, -1), 1);
+  beta += __mul24(row_coef(kCoefBeta, at), half);
+  alpha += __mul24(row_coef(kCoefAlpha, at), half);
   if (d == 0) return;
-  const int32_t dl = row_coef(kCoefDelta, cs) * half;
+  const int32_t dl = __mul24(row_coef(kCoefDelta, at), half);
   const int k = k0 + d;
   if (k < 0) {
     beta += dl;
@@ -703,6 +743,19 @@ __device__ __forceinline__ void add_row_reg(bool ap, int d, int32_t half, int k0
   cand |= 1ull << k;
   const int kb = k + (ap ? 1 : 0);
   if (kb < W) atomicAdd(&bins[kb], dl);
+}
+
+// Bounds of a narrow column, from the packed copy where there is one (4 bytes
+// for 16).
+__device__ __forceinline__ void narrow_bounds(const WalkCtx& C, int q, double& l, double& u) {
+  if (C.plan.stage_lu) {
+    const uint32_t v = gmem(C.plan.stage_lu)[q];
+    l = (double)(int16_t)(v & 0xFFFFu);
+    u = (double)(int16_t)(v >> 16);
+  } else {
+    l = gmem(C.P.lb)[q];
+    u = gmem(C.P.ub)[q];
+  }
 }
 
 // One workgroup per chunk of a long narrow column: bins, beta, alpha and the
@@ -748,50 +801,44 @@ __device__ __forceinline__ void chunk_task(const WalkCtx& C, int lb, ChunkSmem& 
     const double xb = gmem(x)[q];
     const double l = gmem(P.lb)[q];
     const int W = (int)(gmem(P.ub)[q] - l) + 1, k0 = (int)(xb - l);
-    const gptr<const int32_t> crow = gmem(P.col_row);
-    const gptr<const double> cval = gmem(P.col_val);
     int32_t ib = 0, ia = 0;
+    auto add = [&](const GatherRow& g, int a, int d0, int d1) {
+      add_row_reg(a > 0, d0, (int32_t)g.w0, k0, W, ibins, ib, ia, cand);
+      if (g.w1 != kNoTwin) add_row_reg(a < 0, d1, (int32_t)g.w1, k0, W, ibins, ib, ia, cand);
+    };
+    const gptr<const GatherRow> rows = gmem((const GatherRow*)C.grow);
+    // software pipeline: the next step's entries are in flight while this
+    // step's rows are gathered and binned, two entries per thread and step
     int e = T.e_beg + tid;
-    // software pipeline: the next step's row indices and coefficients are in
-    // flight while this step's rows are gathered and binned
-    int ni0 = 0, ni1 = 0;
-    double na0 = 0.0, na1 = 0.0;
-    if (e < T.e_end) {
-      ni0 = __builtin_nontemporal_load(&crow[e]);
-      na0 = __builtin_nontemporal_load(&cval[e]);
-      if (e + 256 < T.e_end) {
-        ni1 = __builtin_nontemporal_load(&crow[e + 256]);
-        na1 = __builtin_nontemporal_load(&cval[e + 256]);
+    if (C.plan.chunk_ent) {
+      const gptr<const uint32_t> ent = gmem(C.plan.chunk_ent);
+      const int o = C.plan.chunk_e0;
+      uint32_t n0 = 0, n1 = 0;
+      if (e < T.e_end) n0 = __builtin_nontemporal_load(&ent[e - o]);
+      if (e + 256 < T.e_end) n1 = __builtin_nontemporal_load(&ent[e - o + 256]);
+      for (; e < T.e_end; e += 512) {
+        const bool two = e + 256 < T.e_end;
+        const uint32_t e0 = n0, e1 = two ? n1 : n0;
+        const GatherRow g0 = gload(rows, (int64_t)(e0 >> 8));
+        const GatherRow g1 = gload(rows, (int64_t)(e1 >> 8));
+        if (e + 512 < T.e_end) n0 = __builtin_nontemporal_load(&ent[e - o + 512]);
+        if (e + 768 < T.e_end) n1 = __builtin_nontemporal_load(&ent[e - o + 768]);
+        const int a0 = (int)(int8_t)(e0 & 0xFFu), a1 = (int)(int8_t)(e1 & 0xFFu);
+        int p0, p1, q0, q1;
+        row_offsets<true>(g0.r, a0, &p0, &p1);
+        row_offsets<true>(g1.r, a1, &q0, &q1);
+        add(g0, a0, p0, p1);
+        if (two) add(g1, a1, q0, q1);
       }
-    }
-    for (; e < T.e_end; e += 512) {
-      const bool two = e + 256 < T.e_end;
-      const int i0 = ni0;
-      const double a0 = na0;
-      const int i1 = two ? ni1 : i0;
-      const double a1 = two ? na1 : a0;
-      const RowState r0 = rs[i0];
-      const RowState r1 = rs[i1];
-      const int en = e + 512;
-      if (en < T.e_end) {
-        ni0 = __builtin_nontemporal_load(&crow[en]);
-        na0 = __builtin_nontemporal_load(&cval[en]);
-        if (en + 256 < T.e_end) {
-          ni1 = __builtin_nontemporal_load(&crow[en + 256]);
-          na1 = __builtin_nontemporal_load(&cval[en + 256]);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (u == 1 && !two) break;
-        const RowState& r = u ? r1 : r0;
-        const double a = u ? a1 : a0;
-        const bool ap = a > 0.0;
-        const double qv = -r.r / a;
-        const double fl = fmin(fmax(floor(qv), -(double)kStageClamp), (double)kStageClamp);
-        const double ce = fmin(fmax(ceil(qv), -(double)kStageClamp), (double)kStageClamp);
-        add_row_reg(ap, (int)(ap ? fl : ce), (int32_t)r.w0, k0, W, ibins, ib, ia, cand);
-        if (r.w1 >= 0.0f) add_row_reg(!ap, (int)(ap ? ce : fl), (int32_t)r.w1, k0, W, ibins, ib, ia, cand);
+    } else {
+      const gptr<const int32_t> crow = gmem(P.col_row);
+      const gptr<const double> cval = gmem(P.col_val);
+      for (; e < T.e_end; e += 256) {
+        const GatherRow g = gload(rows, (int64_t)crow[e]);
+        const int a = (int)cval[e];
+        int d0, d1;
+        row_offsets<false>(g.r, a, &d0, &d1);
+        add(g, a, d0, d1);
       }
     }
     if (tid == 0 && T.first && st->cut_active) {
@@ -935,10 +982,10 @@ __device__ __forceinline__ void row_terms(bool ap, int d, V one, V half, V& beta
 // a candidate when inside [l, u].
 template <typename V>
 __device__ __forceinline__ void add_row(bool ap, int d, V half, int k0, int W, V* bins, unsigned long long* cand) {
-  const int cs = (ap ? 4 : 1) + (d > 0 ? 1 : 0) - (d < 0 ? 1 : 0);
-  const V b = (V)row_coef(kCoefBeta, cs) * half;
-  const V al = (V)row_coef(kCoefAlpha, cs) * half;
-  const V dl = (V)row_coef(kCoefDelta, cs) * half;
+  const int at = row_case(ap, d);
+  const V b = (V)row_coef(kCoefBeta, at) * half;
+  const V al = (V)row_coef(kCoefAlpha, at) * half;
+  const V dl = (V)row_coef(kCoefDelta, at) * half;
   const int k = k0 + d;
   const int kb = k + (ap ? 1 : 0);
   const int idx = k < 0 ? 0 : ((k >= W || kb >= W) ? kNarrowBins : kb);
@@ -950,53 +997,53 @@ __device__ __forceinline__ void add_row(bool ap, int d, V half, int k0, int W, V
   if (d != 0 && k >= 0 && k < W) atomicOr(cand, 1ull << k);
 }
 
-// add_row for a run of rows of one column: beta, alpha and the candidate
-// mask go to the caller's registers (flushed once per run), the delta to its
-// bin; deltas for bin 0 join beta, those beyond u (the sink bin, never read)
-// are dropped.
+__device__ __forceinline__ int32_t coef_mul(int c, int32_t half) { return __mul24(c, half); }
+__device__ __forceinline__ double coef_mul(int c, double half) { return (double)c * half; }
+
+// add_row for a run of records of one column, from a record's case and offset:
+// beta, alpha and the candidate mask go to the caller's registers (flushed
+// once per run), the delta to its bin; deltas for bin 0 join beta, those
+// beyond u (the sink bin, never read) are dropped.
 template <typename V>
-__device__ __forceinline__ void add_row_run(bool ap, int d, V half, int k0, int W, V* bins, V& beta, V& alpha,
+__device__ __forceinline__ void add_row_run(int at, int d, V half, int k0, int W, V* bins, V& beta, V& alpha,
                                             unsigned long long& cand) {
-  const int cs = (ap ? 4 : 1) + (d > 0 ? 1 : 0) - (d < 0 ? 1 : 0);
-  beta += (V)row_coef(kCoefBeta, cs) * half;
-  alpha += (V)row_coef(kCoefAlpha, cs) * half;
-  const V dl = (V)row_coef(kCoefDelta, cs) * half;
+  beta += coef_mul(row_coef(kCoefBeta, at), half);
+  alpha += coef_mul(row_coef(kCoefAlpha, at), half);
+  const V dl = coef_mul(row_coef(kCoefDelta, at), half);
   const int k = k0 + d;
-  const int kb = k + (ap ? 1 : 0);
+  const int kb = k + row_coef(kCaseAfter, at);
   if (dl != (V)0) {
     if (k < 0)
       beta += dl;
-    else if (k < W && kb < W)
+    else if (kb < W)
       atomicAdd(&bins[kb], dl);
   }
-  if (d != 0 && k >= 0 && k < W) cand |= 1ull << k;
+  if (d != 0 && (unsigned)k < (unsigned)W) cand |= 1ull << k;
 }
 
+// A record's fields.
+__device__ __forceinline__ uint32_t rec_half(bool ap, int d) {
+  return (uint32_t)row_case(ap, d) | (uint32_t)((d >= kStageClamp ? 0 : d) & 0x7F) << 5;
+}
+__device__ __forceinline__ uint64_t make_rec(int lc, bool ap, int d0, bool twin, int d1, uint32_t top) {
+  const uint32_t lo = (uint32_t)lc | rec_half(ap, d0) << 8 | (twin ? rec_half(!ap, d1) : (uint32_t)kCaseNone) << 20;
+  return (uint64_t)lo | (uint64_t)top << 32;
+}
+__device__ __forceinline__ int rec_case0(uint32_t lo) { return (int)__builtin_amdgcn_ubfe(lo, 8, 5); }
+__device__ __forceinline__ int rec_d0(uint32_t lo) { return __builtin_amdgcn_sbfe((int)lo, 13, 7); }
+__device__ __forceinline__ int rec_case1(uint32_t lo) { return (int)__builtin_amdgcn_ubfe(lo, 20, 5); }
+__device__ __forceinline__ int rec_d1(uint32_t lo) { return (int)lo >> 25; }
+
+// A record's row or twin in the form row_terms takes.
+__device__ __forceinline__ bool case_after(int at) { return row_coef(kCaseAfter, at) != 0; }
+__device__ __forceinline__ int case_offset(int at, int d) { return at >= 24 ? kStageClamp : d; }
+
+// One single-entry column's row and twin.
 struct StageRec {
   bool ap, twin;
-  int d0, d1, lc;
+  int d0, d1;
   double w0, w1;
 };
-
-template <typename Rows>
-__device__ __forceinline__ StageRec decode_rec(uint64_t r, bool wts, const Rows& rs) {
-  StageRec o;
-  o.lc = (int)(r & 0xFFu);
-  o.ap = (r >> 8) & 1u;
-  o.twin = (r >> 9) & 1u;
-  o.d0 = (int)((r >> 10) & 0xFFu) - kStageClamp;
-  o.d1 = (int)((r >> 18) & 0xFFu) - kStageClamp;
-  if (wts) {
-    o.w0 = (double)((r >> 32) & 0xFFFFu);
-    o.w1 = (double)(r >> 48);
-  } else {
-    const RowState g = rs[(int)(r >> 32)];
-    o.w0 = (double)g.w0;
-    o.w1 = (double)g.w1;
-  }
-  return o;
-}
-
 
 template <typename V>
 struct StagePackSmem {
@@ -1037,6 +1084,24 @@ __device__ __forceinline__ int stage_segments(const WalkCtx& C, int t, StageSegs
   return G.pre[nrb];
 }
 
+// Half weights of a record's row and twin in value units.
+template <typename Rows>
+__device__ __forceinline__ void rec_weights(uint64_t r, bool, const Rows&, int32_t& w0, int32_t& w1) {
+  w0 = (int32_t)((r >> 32) & 0xFFFFu);
+  w1 = (int32_t)(r >> 48);
+}
+template <typename Rows>
+__device__ __forceinline__ void rec_weights(uint64_t r, bool wts, const Rows& rs, double& w0, double& w1) {
+  if (wts) {
+    w0 = 0.5 * (double)((r >> 32) & 0xFFFFu);
+    w1 = 0.5 * (double)(r >> 48);
+  } else {
+    const RowState g = rs[(int)(r >> 32)];
+    w0 = 0.5 * (double)g.w0;
+    w1 = g.w1 >= 0.0f ? 0.5 * (double)g.w1 : 0.0;
+  }
+}
+
 // A pack of narrow columns from its records: counting sort into LDS bins
 // that also hold beta (bin 0) and alpha (bin xbar - l + 1), so the score of
 // position l + k is the prefix sum of bins 0..k; one lane per column then
@@ -1053,40 +1118,44 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
   const V zero = 0;
   const int nrb = C.plan.n_stage_rb;
   stage_segments(C, tix, G);
-  const gptr<const uint64_t> recs = gmem((const uint64_t*)C.stage_rec);
+  typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+  const gptr<const u64x2> recs = (gptr<const u64x2>)gmem((const uint64_t*)C.stage_rec);
   for (int c0 = 0; c0 < nc; c0 += kCols) {
     const int ncw = min(kCols, nc - c0);
     if (tid < ncw) {
       const int q = T.q_begin + c0 + tid;
-      const double xb = gmem((const double*)C.x)[q], l = gmem(P.lb)[q];
+      const double xb = gmem((const double*)C.x)[q];
+      double l, u;
+      narrow_bounds(C, q, l, u);
       S.xb[tid] = xb;
-      S.W[tid] = (int)(gmem(P.ub)[q] - l) + 1;
+      S.W[tid] = (int)(u - l) + 1;
       S.k0[tid] = (int)(xb - l);
       S.cand[tid] = 0ull;
     }
     for (int i = tid; i < ncw * (kNarrowBins + 1); i += blockDim.x)
       S.bins[i / (kNarrowBins + 1)][i % (kNarrowBins + 1)] = 0;
     __syncthreads();
-    // every thread takes an equal contiguous share of the task's records (in
-    // segment order, crossing row-block segments), kRun records per step;
-    // records of columns outside this window are skipped
-    constexpr int kRun = 4;
+    // every thread takes an equal contiguous share of the task's record pairs
+    // (in segment order, crossing row-block segments, which hold whole pairs),
+    // kRun of them per step, 16 bytes each; records of columns outside this
+    // window (and padding) are skipped
+    constexpr int kRun = 2;
     {
-      const int total = G.pre[nrb];
+      const int total = G.pre[nrb] >> 1;
       const int per = (total + (int)blockDim.x - 1) / (int)blockDim.x;
       const int f0 = min(total, tid * per), f1 = min(total, f0 + per);
       // segment of f0: the last one starting at or before it
       int lo = 0, hi = nrb - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (G.pre[mid] <= f0)
+        if (G.pre[mid] <= 2 * f0)
           lo = mid;
         else
           hi = mid - 1;
       }
       int sg = lo;
-      int base = G.beg[sg] - G.pre[sg];  // record index of flat position f: base + f
-      int send = G.pre[sg + 1];
+      int base = (G.beg[sg] - G.pre[sg]) >> 1;  // pair index of flat pair f: base + f
+      int send = G.pre[sg + 1] >> 1;
       // a thread's run is sorted by column within a segment: beta, alpha and
       // the candidate mask of the current column stay in registers until the
       // column changes
@@ -1103,23 +1172,27 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
         rc_ = 0ull;
       };
       for (int f = f0; f < f1; f += kRun) {
-        uint64_t r[kRun];
+        u64x2 r[kRun];
 #pragma unroll
         for (int u = 0; u < kRun; ++u) {
           const int fu = f + u;
           if (fu < f1) {
             while (fu >= send) {
               ++sg;
-              base = G.beg[sg] - G.pre[sg];
-              send = G.pre[sg + 1];
+              base = (G.beg[sg] - G.pre[sg]) >> 1;
+              send = G.pre[sg + 1] >> 1;
             }
             r[u] = recs[base + fu];
           }
         }
 #pragma unroll
         for (int u = 0; u < kRun; ++u) {
-          if (f + u < f1) {
-            const int lc = (int)(r[u] & 0xFFu) - c0;
+          if (f + u >= f1) break;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const uint64_t rec = h ? r[u].y : r[u].x;
+            const uint32_t lo = (uint32_t)rec;
+            const int lc = (int)(lo & 0xFFu) - c0;
             if (lc < 0 || lc >= ncw) continue;
             if (lc != cur) {
               flush();
@@ -1127,9 +1200,11 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
               k0 = S.k0[lc];
               W = S.W[lc];
             }
-            const StageRec e = decode_rec(r[u], wts, rs);
-            add_row_run(e.ap, e.d0, stage_half(e.w0, zero), k0, W, S.bins[lc], rb_, ra_, rc_);
-            if (e.twin) add_row_run(!e.ap, e.d1, stage_half(e.w1, zero), k0, W, S.bins[lc], rb_, ra_, rc_);
+            V w0, w1;
+            rec_weights(rec, wts, rs, w0, w1);
+            add_row_run(rec_case0(lo), rec_d0(lo), w0, k0, W, S.bins[lc], rb_, ra_, rc_);
+            if (rec_case1(lo) != kCaseNone)
+              add_row_run(rec_case1(lo), rec_d1(lo), w1, k0, W, S.bins[lc], rb_, ra_, rc_);
           }
         }
       }
@@ -1260,20 +1335,15 @@ __device__ __forceinline__ void stage_short_int(const StageShortSmem& S, int lan
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const uint64_t r = S.rec[k][lane];
-    const bool ap = (r >> 8) & 1u;
-    const int d0 = (int)((r >> 10) & 0xFFu) - kStageClamp;
-    const int32_t w0 = (int32_t)((r >> 32) & 0xFFFFu);
-    row_terms(ap, d0, 2 * w0, w0, beta, alpha, dl[2 * k], th[2 * k]);
-    below |= (uint32_t)ap << (2 * k);
-    if ((r >> 9) & 1u) {
-      const int d1 = (int)((r >> 18) & 0xFFu) - kStageClamp;
-      const int32_t w1 = (int32_t)(r >> 48);
-      row_terms(!ap, d1, 2 * w1, w1, beta, alpha, dl[2 * k + 1], th[2 * k + 1]);
-      below |= (uint32_t)(!ap) << (2 * k + 1);
-    } else {
-      dl[2 * k + 1] = 0;
-      th[2 * k + 1] = kNone;
-    }
+    const uint32_t lo = (uint32_t)r;
+    const int at0 = rec_case0(lo), at1 = rec_case1(lo);
+    const bool ap0 = case_after(at0), ap1 = case_after(at1);
+    const int32_t w0 = (int32_t)((r >> 32) & 0xFFFFu), w1 = (int32_t)(r >> 48);
+    row_terms(ap0, case_offset(at0, rec_d0(lo)), 2 * w0, w0, beta, alpha, dl[2 * k], th[2 * k]);
+    below |= (uint32_t)ap0 << (2 * k);
+    // without a twin: weight 0 and an offset above every column
+    row_terms(ap1, case_offset(at1, rec_d1(lo)), 2 * w1, w1, beta, alpha, dl[2 * k + 1], th[2 * k + 1]);
+    below |= (uint32_t)ap1 << (2 * k + 1);
   }
   if (cut) {
     row_terms(cpos, dcut, 2 * wc, wc, beta, alpha, dl[NR - 1], th[NR - 1]);
@@ -1321,17 +1391,16 @@ __device__ __forceinline__ void stage_short_dbl(const StageShortSmem& S, int lan
   uint32_t below = 0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    const StageRec e = decode_rec<Rows>(S.rec[k][lane], false, rs);
-    row_terms(e.ap != 0, e.d0, stage_one(e.w0, zero), stage_half(e.w0, zero), beta, alpha, dl[2 * k], th[2 * k]);
-    below |= (uint32_t)(e.ap != 0) << (2 * k);
-    if (e.twin) {
-      row_terms(e.ap == 0, e.d1, stage_one(e.w1, zero), stage_half(e.w1, zero), beta, alpha, dl[2 * k + 1],
-                th[2 * k + 1]);
-      below |= (uint32_t)(e.ap == 0) << (2 * k + 1);
-    } else {
-      dl[2 * k + 1] = 0.0;
-      th[2 * k + 1] = kNone;
-    }
+    const uint64_t r = S.rec[k][lane];
+    const uint32_t lo = (uint32_t)r;
+    const int at0 = rec_case0(lo), at1 = rec_case1(lo);
+    const bool ap0 = case_after(at0), ap1 = case_after(at1);
+    double h0, h1;
+    rec_weights(r, false, rs, h0, h1);
+    row_terms(ap0, case_offset(at0, rec_d0(lo)), 2.0 * h0, h0, beta, alpha, dl[2 * k], th[2 * k]);
+    below |= (uint32_t)ap0 << (2 * k);
+    row_terms(ap1, case_offset(at1, rec_d1(lo)), 2.0 * h1, h1, beta, alpha, dl[2 * k + 1], th[2 * k + 1]);
+    below |= (uint32_t)ap1 << (2 * k + 1);
   }
   if (cut) {
     row_terms(cpos, dcut, stage_one(wc, zero), stage_half(wc, zero), beta, alpha, dl[NR - 1], th[NR - 1]);
@@ -1374,7 +1443,10 @@ __device__ __forceinline__ void stage_short(const WalkCtx& C, const Rows& rs, bo
   const int D = T.deg;
   // the column's own data is loaded while the records arrive
   const int q = T.q_begin + min(tid, max(nc - 1, 0));
-  const double xb = gmem((const double*)C.x)[q], l = gmem(P.lb)[q], ub = gmem(P.ub)[q], c = gmem(P.obj)[q];
+  const double xb = gmem((const double*)C.x)[q];
+  const double c = st->cut_active ? gmem(P.obj)[q] : 0.0;
+  double l, ub;
+  narrow_bounds(C, q, l, ub);
   S.cnt[tid] = 0;  // stage_segments ends with a barrier
   const int nrb = C.plan.n_stage_rb;
   stage_segments(C, tix, G);
@@ -1462,7 +1534,7 @@ __device__ __forceinline__ void stage_short(const WalkCtx& C, const Rows& rs, bo
 // go to LDS (as GatherRow; weights only when the records carry them), then
 // every entry of the slice becomes the record of the same index, and the
 // slice's single-entry columns (their entry lies in this block) are scored.
-template <typename Rows>
+template <typename Rows, bool kPacked>
 __device__ __forceinline__ void stage_rows_body(const WalkCtx& C, const StageRowTask& T, GatherRow* rows) {
   const Rows rs = rows_of<Rows>(C);
   const bool wts = stage_weights<Rows>(C);
@@ -1473,12 +1545,19 @@ __device__ __forceinline__ void stage_rows_body(const WalkCtx& C, const StageRow
   constexpr int kThreads = 512;
   constexpr int kU = 8;  // entries per thread and step, loaded before any is used
   const int tid = threadIdx.x;
-  uint64_t wd[kU];
+  const gptr<const uint32_t> ent32 = gmem(C.plan.stage_ent32);
+  using Word = typename std::conditional<kPacked, uint32_t, uint64_t>::type;
+  Word wd[kU];
   auto load_step = [&](int base) {
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int i = base + u * kThreads;
-      if (i < T.e_end) wd[u] = __builtin_nontemporal_load(&ent[i]);
+      if (i < T.e_end) {
+        if constexpr (kPacked)
+          wd[u] = __builtin_nontemporal_load(&ent32[i]);
+        else
+          wd[u] = __builtin_nontemporal_load(&ent[i]);
+      }
     }
   };
   // the first step's entries are in flight while the row block is loaded
@@ -1518,19 +1597,23 @@ __device__ __forceinline__ void stage_rows_body(const WalkCtx& C, const StageRow
     for (int u = 0; u < kU; ++u) {
       const int i = base + u * kThreads;
       if (i < T.e_end) {
-        const int local = (int)(wd[u] & 0xFFFFu);
+        int local, lc, a;
+        if constexpr (kPacked) {
+          const uint32_t w = wd[u];
+          local = (int)(w & 0x1FFFu);
+          lc = (int)__builtin_amdgcn_ubfe(w, 13, 8);
+          a = __builtin_amdgcn_sbfe((int)w, 21, 8);
+        } else {
+          local = (int)(wd[u] & 0xFFFFu);
+          lc = (int)((wd[u] >> 16) & 0xFFu);
+          a = ((int32_t)((uint32_t)(wd[u] >> 24) << 8)) >> 8;
+        }
         const GatherRow g = rows[local];
-        const int a = ((int32_t)((uint32_t)(wd[u] >> 24) << 8)) >> 8;
-        const double qv = -(double)g.r / (double)a;
-        const double fl = fmin(fmax(floor(qv), -(double)kStageClamp), (double)kStageClamp);
-        const double ce = fmin(fmax(ceil(qv), -(double)kStageClamp), (double)kStageClamp);
-        const int d0 = (int)(a > 0 ? fl : ce);
-        const int d1 = (int)(a > 0 ? ce : fl);
+        int d0, d1;
+        row_offsets<kPacked>(g.r, a, &d0, &d1);
         const bool twin = g.w1 != kNoTwin;
-        const uint32_t lo = (uint32_t)((wd[u] >> 16) & 0xFFu) | ((a > 0 ? 1u : 0u) << 8) | ((twin ? 1u : 0u) << 9) |
-                            ((uint32_t)(d0 + kStageClamp) << 10) | ((uint32_t)(d1 + kStageClamp) << 18);
-        const uint32_t top = wts ? ((uint32_t)g.w0 | ((uint32_t)g.w1 << 16)) : (uint32_t)(r0 + local);
-        rec[i] = (uint64_t)lo | ((uint64_t)top << 32);
+        const uint32_t top = wts ? ((uint32_t)g.w0 | (twin ? (uint32_t)g.w1 << 16 : 0u)) : (uint32_t)(r0 + local);
+        rec[i] = make_rec(lc, a > 0, d0, twin, d1, top);
       }
     }
   }
@@ -1539,31 +1622,19 @@ __device__ __forceinline__ void stage_rows_body(const WalkCtx& C, const StageRow
   const WalkState* st = C.st;
   const bool cut_on = st->cut_active != 0;
   const double wc = (double)st->wc;
-  const gptr<const int32_t> cptr = gmem(P.col_ptr), crow = gmem(P.col_row);
-  const gptr<const double> cval = gmem(P.col_val), xg = gmem((const double*)C.x), lbg = gmem(P.lb),
-                           ubg = gmem(P.ub), objg = gmem(P.obj);
+  const gptr<const double> xg = gmem((const double*)C.x), objg = gmem(P.obj);
   const gptr<double> xhat = gmem(C.xhat), sco = gmem(C.s);
-  for (int q = T.c_beg + tid; q < T.c_end; q += kThreads) {
-    const int e = cptr[q];
-    const int row = crow[e];
-    const double a = cval[e];
-    const double xb = xg[q], l = lbg[q], u = ubg[q];
-    const double c = cut_on ? objg[q] : 0.0;
-    const GatherRow g = rows[row - r0];
+  auto one = [&](int q, int local, int a, double xb, double l, double u, double c) {
+    const GatherRow g = rows[local];
     StageRec re;
-    re.lc = 0;
-    re.ap = a > 0.0;
-    const double qv = -(double)g.r / a;
-    const double fl = fmin(fmax(floor(qv), -(double)kStageClamp), (double)kStageClamp);
-    const double ce = fmin(fmax(ceil(qv), -(double)kStageClamp), (double)kStageClamp);
-    re.d0 = (int)(re.ap ? fl : ce);
-    re.d1 = (int)(re.ap ? ce : fl);
+    re.ap = a > 0;
+    row_offsets<kPacked>(g.r, a, &re.d0, &re.d1);
     re.twin = g.w1 != kNoTwin;
     if (wts) {
       re.w0 = (double)g.w0;
       re.w1 = (double)g.w1;
     } else {
-      const RowState full = rs[row];
+      const RowState full = rs[r0 + local];
       re.w0 = (double)full.w0;
       re.w1 = (double)full.w1;
     }
@@ -1577,6 +1648,41 @@ __device__ __forceinline__ void stage_rows_body(const WalkCtx& C, const StageRow
     else
       stage_short_col<1, double>(&re, xb, k0, W, cut, c > 0.0, dcut, wc, found, best, bestp);
     write_result(xhat, sco, q, found, best, bestp, xb);
+  };
+  if constexpr (kPacked) {
+    // kOne columns per thread and step; a column's loads do not depend on one
+    // another, and all of a step's are issued before any is used
+    constexpr int kOne = 4;
+    const gptr<const uint32_t> oneg = gmem(C.plan.stage_one);
+    const int o = C.plan.stage_one_begin;
+    for (int q0 = T.c_beg + tid; q0 < T.c_end; q0 += kOne * kThreads) {
+      uint32_t w[kOne];
+      double xb[kOne], l[kOne], u[kOne], c[kOne];
+#pragma unroll
+      for (int k = 0; k < kOne; ++k) {
+        const int q = q0 + k * kThreads;
+        if (q < T.c_end) {
+          w[k] = oneg[q - o];
+          xb[k] = xg[q];
+          narrow_bounds(C, q, l[k], u[k]);
+          c[k] = cut_on ? objg[q] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kOne; ++k) {
+        const int q = q0 + k * kThreads;
+        if (q < T.c_end) one(q, (int)(w[k] & 0x1FFFu), __builtin_amdgcn_sbfe((int)w[k], 16, 8), xb[k], l[k], u[k], c[k]);
+      }
+    }
+  } else {
+    const gptr<const int32_t> cptr = gmem(P.col_ptr), crow = gmem(P.col_row);
+    const gptr<const double> cval = gmem(P.col_val);
+    for (int q = T.c_beg + tid; q < T.c_end; q += kThreads) {
+      const int e = cptr[q];
+      double l, u;
+      narrow_bounds(C, q, l, u);
+      one(q, crow[e] - r0, (int)cval[e], xg[q], l, u, cut_on ? objg[q] : 0.0);
+    }
   }
 }
 
@@ -1594,14 +1700,21 @@ __global__ __launch_bounds__(512) void k_stage_rows(const WalkCtx* __restrict__ 
   const StageRowTask T = C.plan.stage_rtasks[lb];
   if (T.rb < 0) return;
   __shared__ GatherRow rows[kStageRowBlock];
-  if constexpr (std::is_same<Rows, DualRows>::value) {
-    if (C.st->compact_rows)
-      stage_rows_body<CompactRows>(C, T, rows);
-    else
-      stage_rows_body<FullRows>(C, T, rows);
-  } else {
-    stage_rows_body<Rows>(C, T, rows);
-  }
+  auto body = [&](auto packed) {
+    constexpr bool kPacked = decltype(packed)::value;
+    if constexpr (std::is_same<Rows, DualRows>::value) {
+      if (C.st->compact_rows)
+        stage_rows_body<CompactRows, kPacked>(C, T, rows);
+      else
+        stage_rows_body<FullRows, kPacked>(C, T, rows);
+    } else {
+      stage_rows_body<Rows, kPacked>(C, T, rows);
+    }
+  };
+  if (C.plan.stage_packed)
+    body(std::true_type());
+  else
+    body(std::false_type());
 }
 
 // Workgroups of a walk over ntask scoring tasks: kXcds * ceil(ntask / kXcds)
