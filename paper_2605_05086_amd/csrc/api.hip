@@ -775,9 +775,11 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     P->d_inv = d_inv;
   }
   // caller's order -> internal order sends j to inv[j]; back, q to perm[q]
-  CHAP_HIP(build_perm_plan(inv, A, &P->to_internal));
-  CHAP_HIP(build_perm_plan(perm, A, &P->to_caller));
-  CHAP_HIP(A.alloc(&P->bs_stage, 2 * (size_t)n));
+  if (n > kPermDirect) {
+    CHAP_HIP(build_perm_plan(inv, A, &P->to_internal));
+    CHAP_HIP(build_perm_plan(perm, A, &P->to_caller));
+    CHAP_HIP(A.alloc(&P->bs_stage, 2 * (size_t)n));
+  }
   CHAP_HIP(A.upload(&d_pair, P->pair));
   CHAP_HIP(A.upload(&d_nidx, P->nidx));
   D.col_ptr = d_cptr;
@@ -1000,9 +1002,8 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     CHAP_HIP(build_launch(A, one, &P->bs_launch, nullptr));
     P->bs_launch.compact = P->compact_ok ? 2 : 0;
   }
-  CHAP_HIP(P->bs_streams.create());
-  CHAP_HIP(hipEventCreate(&P->pass_ev[0]));
-  CHAP_HIP(hipEventCreate(&P->pass_ev[1]));
+  // timing only: no system-scope fence at the record
+  for (hipEvent_t& e : P->pass_ev) CHAP_HIP(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
   P->pool = std::make_shared<WalkPool>();
   P->pool->n = n;
   P->pool->m = m;
@@ -1022,40 +1023,11 @@ int chap_best_shift(chap_problem* p, const double* d_x, const float* d_w, double
   if (!d_w) return fail(CHAP_EINVAL, "chap_best_shift: null weights");
   if (std::isnan(cutoff_rhs)) return fail(CHAP_EINVAL, "chap_best_shift: cutoff_rhs is NaN");
   hipStream_t s = (hipStream_t)hip_stream;
-  const uint32_t epoch = ++p->bs_epoch == 0 ? ++p->bs_epoch : p->bs_epoch;  // never 0
-  CHAP_HIP(launch_stage_x_plan(p->to_internal, d_x, p->bs_x, p->bs_xc, p->bs_state, epoch, p->bs_stage, s));
-  // the state first (a single pass counts no violated rows, so it reads no
-  // residual), then the residuals with the compact copy and its check
-  const double cut = (cutoff_rhs == HUGE_VAL) ? HUGE_VAL : cutoff_rhs;
-  CHAP_HIP(launch_state_init(p->dev, p->bs_x, p->bs_rs, p->bs_state, p->bs_partial, p->bs_ticket, p->bs_objacc, 1,
-                             0, p->obj_integral, cut, d_w + p->mp, 0, 0, s));
-  CHAP_HIP(launch_residual_scatter(p->dev, p->d_nidx, p->d_pair, d_w, p->bs_x, p->bs_xc, p->bs_state, epoch,
-                                   p->bs_rs, s, p->bs_grow));
-  if (p->n > 0 && !p->bs_exec) {
-    // capture the pass once (its arguments are the problem's own buffers)
-    if (!p->bs_cap) CHAP_HIP(hipStreamCreateWithFlags(&p->bs_cap, hipStreamNonBlocking));
-    CHAP_HIP(hipStreamBeginCapture(p->bs_cap, hipStreamCaptureModeThreadLocal));
-    const hipError_t cap_err = launch_pass(p->bs_launch, p->bs_cap, &p->bs_streams);
-    hipGraph_t graph = nullptr;
-    const hipError_t end_err = hipStreamEndCapture(p->bs_cap, &graph);
-    if (cap_err != hipSuccess || end_err != hipSuccess) {
-      if (graph) (void)hipGraphDestroy(graph);
-      return fail(CHAP_EHIP, std::string("pass capture: ") +
-                                 hipGetErrorString(cap_err != hipSuccess ? cap_err : end_err));
-    }
-    hipGraphExec_t exec = nullptr;
-    const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    if (ie != hipSuccess) {
-      (void)hipGraphDestroy(graph);
-      return fail(CHAP_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
-    }
-    p->bs_graph = graph;
-    p->bs_exec = exec;
-  }
+  CHAP_HIP(launch_single_begin(p, d_x, d_w, cutoff_rhs, s));
   CHAP_HIP(hipEventRecord(p->pass_ev[0], s));
-  if (p->n > 0) CHAP_HIP(hipGraphLaunch(p->bs_exec, s));
+  if (p->n > 0) CHAP_HIP(launch_pass(p->bs_launch, s));
   CHAP_HIP(hipEventRecord(p->pass_ev[1], s));
-  CHAP_HIP(launch_gather2_plan(p->to_caller, p->bs_xhat, p->bs_s, d_shift, d_score, p->bs_stage, s));
+  CHAP_HIP(launch_single_end(p, d_shift, d_score, s));
   p->pass_timed = true;
   return CHAP_OK;
 }
@@ -1074,6 +1046,36 @@ int chap_best_shift_pass_ms(chap_problem* p, double* ms) {
 }  // extern "C"
 
 namespace chap {
+
+hipError_t launch_single_begin(chap_problem* p, const double* d_x, const float* d_w, double cutoff_rhs,
+                               hipStream_t s) {
+  const uint32_t epoch = ++p->bs_epoch == 0 ? ++p->bs_epoch : p->bs_epoch;  // never 0
+  // the state first (a single pass counts no violated rows, so it reads no
+  // residual), then the residuals with the compact copy and its check; only a
+  // cutoff row needs the objective's sum, and a launch of its own for it
+  const bool cut = std::isfinite(cutoff_rhs);
+  SingleInit init;
+  if (!cut) {
+    init.cutoff_w = d_w + p->mp;
+    init.obj_integral = p->obj_integral;
+  }
+  hipError_t e = p->n > kPermDirect
+                     ? launch_stage_x_plan(p->to_internal, d_x, p->bs_x, p->bs_xc, p->bs_state, epoch, p->bs_stage,
+                                           init, s)
+                     : launch_stage_x(p->dev.perm, d_x, p->bs_x, p->bs_xc, p->bs_state, epoch, p->n, init, s);
+  if (e == hipSuccess && cut)
+    e = launch_state_init(p->dev, p->bs_x, p->bs_rs, p->bs_state, p->bs_partial, p->bs_ticket, p->bs_objacc, 1, 0,
+                          p->obj_integral, cutoff_rhs, d_w + p->mp, 0, 0, s);
+  if (e == hipSuccess)
+    e = launch_residual_scatter(p->dev, p->d_nidx, p->d_pair, d_w, p->bs_x, p->bs_xc, p->bs_state, epoch, p->bs_rs,
+                                s, p->bs_grow);
+  return e;
+}
+
+hipError_t launch_single_end(chap_problem* p, double* da, double* db, hipStream_t s) {
+  return p->n > kPermDirect ? launch_gather2_plan(p->to_caller, p->bs_xhat, p->bs_s, da, db, p->bs_stage, s)
+                            : launch_gather2(p->d_inv, p->bs_xhat, p->bs_s, da, db, p->n, s);
+}
 
 hipError_t build_perm_plan(const std::vector<int32_t>& dest, DeviceArena& A, PermPlan* plan) {
   const int32_t n = (int32_t)dest.size();
@@ -1165,7 +1167,7 @@ int init_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, const WalkCtx
     if (n > 0) {
       CHAP_HIP(hipStreamSynchronize(s));
       CHAP_HIP(hipMemcpy(c.xhat, spec.x0, sizeof(double) * (size_t)n, hipMemcpyHostToDevice));
-      CHAP_HIP(launch_stage_x(p->dev.perm, c.xhat, c.x, c.xc, c.st, 1u, n, s));
+      CHAP_HIP(launch_stage_x(p->dev.perm, c.xhat, c.x, c.xc, c.st, 1u, n, SingleInit(), s));
     }
   } else {
     CHAP_HIP(launch_start_point(p->dev, spec.seed, c.x, c.xc, s));

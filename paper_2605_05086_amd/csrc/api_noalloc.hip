@@ -11,6 +11,7 @@
 #include <mutex>
 #include <string>
 
+#include "call_begin.h"
 #include "chap_internal.h"
 
 using namespace chap;
@@ -33,13 +34,29 @@ struct LaunchRecord {
   int32_t off[KS_COUNT][2];
 };
 
-// Writes the launch record into scratch and clears the set-up ticket.
-__global__ __launch_bounds__(256) void k_put_record(LaunchRecord r, LaunchRecord* dst, uint32_t* ticket) {
+// First kernel of a call: the launch record into scratch, the set-up ticket
+// cleared, the state of a call without a cutoff row (workgroup 0), and the
+// point in internal order with its byte copy.
+__global__ __launch_bounds__(256) void k_noalloc_begin(LaunchRecord r, LaunchRecord* dst, uint32_t* ticket,
+                                                       SingleInit init, const int32_t* __restrict__ perm,
+                                                       const double* __restrict__ src, double* __restrict__ x,
+                                                       int8_t* __restrict__ xc, WalkState* st, uint32_t epoch,
+                                                       int32_t n) {
   static_assert(sizeof(LaunchRecord) % 4 == 0, "copied as 32-bit words");
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(&r);
-  uint32_t* out = reinterpret_cast<uint32_t*>(dst);
-  for (int i = threadIdx.x; i < (int)(sizeof(LaunchRecord) / 4); i += blockDim.x) out[i] = src[i];
-  if (threadIdx.x == 0) *ticket = 0u;
+  if (blockIdx.x == 0) {
+    const uint32_t* from = reinterpret_cast<const uint32_t*>(&r);
+    uint32_t* out = reinterpret_cast<uint32_t*>(dst);
+    for (int i = threadIdx.x; i < (int)(sizeof(LaunchRecord) / 4); i += blockDim.x) out[i] = from[i];
+    if (threadIdx.x == 0) {
+      *ticket = 0u;
+      if (init.cutoff_w) single_state(st, init);
+    }
+  }
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  const double v = src[perm[q]];
+  x[q] = v;
+  if (xc) stage_byte(v, q, xc, st, epoch);
 }
 
 // Hands out 256-byte aligned pieces of [base, base + cap); used + size
@@ -134,13 +151,19 @@ int chap_best_shift_noalloc(chap_problem* p, const double* d_x, const float* d_w
     std::lock_guard<std::mutex> lock(g_mu);
     epoch = ++g_epoch[dev] == 0 ? ++g_epoch[dev] : g_epoch[dev];  // never 0
   }
-  hipLaunchKernelGGL(k_put_record, dim3(1), dim3(256), 0, s, r, rec, ticket);
+  const bool cut = std::isfinite(cutoff_rhs);
+  SingleInit init;
+  if (!cut) {
+    init.cutoff_w = d_w + p->mp;
+    init.obj_integral = p->obj_integral;
+  }
+  hipLaunchKernelGGL(k_noalloc_begin, dim3((unsigned)std::max(1, (n + 255) / 256)), dim3(256), 0, s, r, rec, ticket,
+                     init, p->dev.perm, d_x, c.x, xc, c.st, epoch, n);
   CHAP_HIP(hipGetLastError());
-  CHAP_HIP(launch_stage_x(p->dev.perm, d_x, c.x, xc, c.st, epoch, n, s));
-  CHAP_HIP(launch_residual_scatter(p->dev, p->d_nidx, p->d_pair, d_w, c.x, xc, c.st, epoch, c.rs, s));
-  CHAP_HIP(launch_state_init(p->dev, c.x, c.rs, c.st, partial, ticket, objacc, 1, 0, p->obj_integral, cutoff_rhs,
-                             d_w + p->mp, 0, 0, s));
-  if (c.grow) CHAP_HIP(launch_fill_compact_checked(c.rs, c.grow, c.st, m, s));
+  if (cut)
+    CHAP_HIP(launch_state_init(p->dev, c.x, c.rs, c.st, partial, ticket, objacc, 1, 0, p->obj_integral, cutoff_rhs,
+                               d_w + p->mp, 0, 0, s));
+  CHAP_HIP(launch_residual_scatter(p->dev, p->d_nidx, p->d_pair, d_w, c.x, xc, c.st, epoch, c.rs, s, c.grow));
   if (n > 0) CHAP_HIP(launch_pass(L, s, nullptr, false));
   CHAP_HIP(launch_gather2(p->d_inv, c.xhat, c.s, d_shift, d_score, n, s));
   return CHAP_OK;

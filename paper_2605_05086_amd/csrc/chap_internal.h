@@ -13,6 +13,8 @@
 #include "chap.h"
 #include "exact_sum.h"
 
+struct chap_problem;
+
 namespace chap {
 
 // (index+1)-th output of SplitMix64 started at state `seed` (Steele, Lea and
@@ -540,6 +542,7 @@ inline bool pass_defers_combine(const BatchLaunch& L) {
 // places each block's values at their offsets in LDS and writes the block.
 constexpr int kPermChunk = 8192;  // input values per workgroup of the first pass
 constexpr int kPermBlock = 4096;  // output values per workgroup of the second pass
+constexpr int32_t kPermDirect = 1 << 19;  // columns up to which one gather is the faster form
 struct PermPlan {
   int32_t n = 0;
   const uint16_t* lpos = nullptr;  // input e: rank in its chunk's (output block, e) order
@@ -552,12 +555,19 @@ hipError_t build_perm_plan(const std::vector<int32_t>& dest, DeviceArena& A, Per
 
 // ---- launchers (kernels_walk.hip) -----------------------------------------
 // Single-walk set-up kernels.
-// The point of a call in internal order: dst[q] = src[perm[q]] (src already
-// in internal order when perm is null, dst then equal to src or null). With
+// What the first kernel of a single call without a cutoff row writes into the
+// walk state (cutoff_w: the caller's cutoff weight; null: nothing, the state
+// initialisation follows).
+struct SingleInit {
+  const float* cutoff_w = nullptr;
+  int32_t obj_integral = 0;
+  int32_t pad_ = 0;
+};
+// The point of a call in internal order: dst[q] = src[perm[q]]. With
 // xc, also its byte copy: a value that is not an integer in [-128, 127]
 // stores `epoch` in st->x_misfit, and residuals of this call then read dst.
 hipError_t launch_stage_x(const int32_t* perm, const double* src, double* dst, int8_t* xc, WalkState* st,
-                          uint32_t epoch, int32_t n, hipStream_t stream);
+                          uint32_t epoch, int32_t n, const SingleInit& init, hipStream_t stream);
 // Residuals from scratch (weights left as they are). With xc (and
 // st->x_misfit != epoch) the products read the byte copy of x.
 hipError_t launch_residual(const DevProblem& P, const double* x, RowState* rs, hipStream_t stream);
@@ -567,8 +577,8 @@ hipError_t launch_residual_unit(const DevProblem& P, const uint8_t* pair, const 
                                 const WalkState* st, uint32_t epoch, RowState* rs, GatherRow* grow,
                                 hipStream_t stream);
 // Residuals from scratch with the caller's normalised weights w_norm. With
-// grow, also the checked compact copy (launch_fill_compact_checked's work):
-// the state initialisation must have run, and st is then written.
+// grow, also the checked compact copy: the state initialisation must have run,
+// and st->compact_rows is cleared when a residual or weight does not fit.
 hipError_t launch_residual_scatter(const DevProblem& P, const int32_t* nidx, const uint8_t* pair,
                                    const float* w_norm, const double* x, const int8_t* xc, const WalkState* st,
                                    uint32_t epoch, RowState* rs, hipStream_t stream, GatherRow* grow = nullptr);
@@ -586,21 +596,20 @@ hipError_t launch_state_init(const DevProblem& P, const double* x, const RowStat
                              int32_t obj_integral, double cutoff_rhs, const float* cutoff_w,
                              int check_incumbent, int count_violated, hipStream_t stream);
 hipError_t launch_copy_best(const double* x, double* best_x, WalkState* st, int32_t n, hipStream_t stream);
-// grow[i] = compact copy of rs[i]
-hipError_t launch_fill_compact(const RowState* rs, GatherRow* grow, int32_t ms, hipStream_t stream);
-// The same for a single pass with caller weights: clears st->compact_rows
-// (set by the state initialisation) when a residual or weight does not fit.
-hipError_t launch_fill_compact_checked(const RowState* rs, GatherRow* grow, WalkState* st, int32_t ms,
-                                       hipStream_t stream);
 // dst[q] = src[perm[q]] (original order -> internal order)
 hipError_t launch_gather(const int32_t* perm, const double* src, double* dst, int32_t n, hipStream_t stream);
-// launch_stage_x (dst not null, not src) through a plan of the same
-// permutation; stage: n doubles.
+// launch_stage_x through a plan of the same permutation; stage: n doubles.
 hipError_t launch_stage_x_plan(const PermPlan& plan, const double* src, double* dst, int8_t* xc, WalkState* st,
-                               uint32_t epoch, double* stage, hipStream_t stream);
+                               uint32_t epoch, double* stage, const SingleInit& init, hipStream_t stream);
 // launch_gather2 through a plan of the same permutation; stage: 2n doubles.
 hipError_t launch_gather2_plan(const PermPlan& plan, const double* a, const double* b, double* da, double* db,
                                double* stage, hipStream_t stream);
+// The set-up of a single call: its point, its state and its residuals (with
+// the checked compact copy), into the problem's scratch.
+hipError_t launch_single_begin(chap_problem* p, const double* d_x, const float* d_w, double cutoff_rhs,
+                               hipStream_t stream);
+// Its two results from the problem's scratch to the caller's arrays.
+hipError_t launch_single_end(chap_problem* p, double* da, double* db, hipStream_t stream);
 // da[j] = a[inv[j]], db[j] = b[inv[j]] (internal order -> original order)
 hipError_t launch_gather2(const int32_t* inv, const double* a, const double* b, double* da, double* db, int32_t n,
                           hipStream_t stream);
@@ -939,8 +948,8 @@ struct chap_problem {
   int8_t* bs_xc = nullptr;
   uint32_t bs_epoch = 0;
   // chap_best_shift and chap_jump_values: the caller's point into internal
-  // order and the results back, as two-pass permutations over bs_stage
-  // (2n doubles)
+  // order and the results back, on instances of more than kPermDirect columns
+  // as two-pass permutations over bs_stage (2n doubles)
   chap::PermPlan to_internal, to_caller;
   double* bs_stage = nullptr;
   std::vector<int32_t> perm;  // original index of each internal column
@@ -960,13 +969,7 @@ struct chap_problem {
   double c_max = 0.0;
   chap::BatchLaunch bs_launch;
   hipEvent_t pass_ev[2] = {nullptr, nullptr};
-  chap::PassStreams bs_streams;
   bool pass_timed = false;
-  // the pass kernels of chap_best_shift as one HIP graph, captured on the
-  // first call and replayed on the caller's stream
-  hipStream_t bs_cap = nullptr;
-  hipGraph_t bs_graph = nullptr;
-  hipGraphExec_t bs_exec = nullptr;
   // buffers of single walks kept between chap_tabu_run calls
   std::shared_ptr<chap::WalkPool> pool;
   // jump values: wavefront tasks of the longer columns (built on the first
@@ -986,10 +989,6 @@ struct chap_problem {
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : jump_ev)
       if (e) (void)hipEventDestroy(e);
-    if (bs_exec) (void)hipGraphExecDestroy(bs_exec);
-    if (bs_graph) (void)hipGraphDestroy(bs_graph);
-    if (bs_cap) (void)hipStreamDestroy(bs_cap);
-    bs_streams.destroy();
   }
 };
 

@@ -11,6 +11,7 @@
 #include <climits>
 #include <cmath>
 
+#include "call_begin.h"
 #include "chap_internal.h"
 #include "exact_sum.h"
 #include "learned_rows.h"
@@ -481,17 +482,16 @@ __global__ __launch_bounds__(256) void k_start_point(DevProblem P, uint64_t seed
 
 __global__ __launch_bounds__(256) void k_stage_x(const int32_t* __restrict__ perm, const double* __restrict__ src,
                                                  double* __restrict__ dst, int8_t* __restrict__ xc, WalkState* st,
-                                                 uint32_t epoch, int32_t n) {
+                                                 uint32_t epoch, int32_t n, SingleInit init) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q == 0 && init.cutoff_w) single_state(st, init);
   if (q >= n) return;
-  const double v = src[perm ? perm[q] : q];
-  if (dst && dst != src) dst[q] = v;
-  if (xc) {
-    const bool fits = v == floor(v) && v >= -128.0 && v <= 127.0;
-    xc[q] = fits ? (int8_t)v : (int8_t)0;
-    if (!fits) st->x_misfit = epoch;  // every writer stores the same value
-  }
+  const double v = src[perm[q]];
+  dst[q] = v;
+  if (xc) stage_byte(v, q, xc, st, epoch);
 }
+
+constexpr int kInitCopies = 16;
 
 // f = c^T x and V = violated rows as grid reductions; the last workgroup
 // writes the walk state. With objacc (objectives whose FP64 sums may be
@@ -507,16 +507,20 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
                                                     int32_t check_incumbent, int32_t need_obj, int32_t need_v) {
   __shared__ double redd[4];
   __shared__ long long redl[4];
-  __shared__ long long lacc[kExactLimbs];
+  // kInitCopies private sums (lane l uses copy l mod kInitCopies): values of
+  // one magnitude meet in the same limbs, and one copy would queue every lane
+  // of a wavefront at the same three addresses
+  __shared__ long long lacc[kInitCopies][kExactLimbs + 1];
   __shared__ uint32_t last;
   long long* plimb = (long long*)(partial + 2 * kInitBlocks);
   const double eps = P.eps;
   const int gt = blockIdx.x * blockDim.x + threadIdx.x;
   const int gs = gridDim.x * blockDim.x;
   if (objacc) {
-    for (int t = threadIdx.x; t < kExactLimbs; t += blockDim.x) lacc[t] = 0;
+    for (int t = threadIdx.x; t < kInitCopies * (kExactLimbs + 1); t += blockDim.x) (&lacc[0][0])[t] = 0;
     __syncthreads();
   }
+  long long* mine = lacc[threadIdx.x & (kInitCopies - 1)];
   // kU items per thread and step, every load issued before any is used
   constexpr int kU = 4;
   double f = 0.0;
@@ -535,8 +539,8 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
       if (objacc) {
         double p, e;
         exact_product(c[u], xv[u], p, e);
-        exact_atomic_add(lacc, p);
-        exact_atomic_add(lacc, e);
+        exact_atomic_add(mine, p);
+        exact_atomic_add(mine, e);
       } else {
         f += c[u] * xv[u];
       }
@@ -563,8 +567,14 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
     partial[2 * blockIdx.x] = f;
     partial[2 * blockIdx.x + 1] = (double)v;
   }
-  if (objacc)
-    for (int t = threadIdx.x; t < kExactLimbs; t += blockDim.x) plimb[blockIdx.x * kExactLimbs + t] = lacc[t];
+  if (objacc) {
+    __syncthreads();
+    for (int t = threadIdx.x; t < kExactLimbs; t += blockDim.x) {
+      long long sum = 0;
+      for (int c = 0; c < kInitCopies; ++c) sum += lacc[c][t];
+      plimb[blockIdx.x * kExactLimbs + t] = sum;
+    }
+  }
   __threadfence();
   __syncthreads();
   if (threadIdx.x == 0) last = atomicAdd(ticket, 1u);
@@ -572,24 +582,39 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
   if (last != gridDim.x - 1) return;
   __threadfence();
   if (objacc) {
-    for (int t = threadIdx.x; t < kExactLimbs; t += blockDim.x) {
-      long long sum = 0;
-      for (unsigned b = 0; b < gridDim.x; ++b) sum += plimb[b * kExactLimbs + t];
-      lacc[t] = sum;
+    // the workgroups' sums: thread t adds limb t mod kExactLimbs of every
+    // third workgroup, then the three shares of a limb are added
+    constexpr int kShares = 256 / kExactLimbs;
+    const int limb = threadIdx.x % kExactLimbs, share = threadIdx.x / kExactLimbs;
+    long long sum = 0;
+    if (share < kShares) {
+#pragma unroll 8
+      for (unsigned b = share; b < gridDim.x; b += kShares) sum += plimb[b * kExactLimbs + limb];
+      lacc[share][limb] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x < kExactLimbs) {
+      sum = lacc[0][threadIdx.x];
+      for (int c = 1; c < kShares; ++c) sum += lacc[c][threadIdx.x];
+      lacc[0][threadIdx.x] = sum;
     }
     __syncthreads();
   }
   if (threadIdx.x >= 64) return;
-  // one wavefront finishes; every lane computes the same values
+  // one wavefront finishes; every lane computes the same values. The FP64 sums
+  // are exact (of f unless objacc replaces it, and of counts), so their order
+  // does not matter.
   double ft = 0.0, vt = 0.0;
-  for (unsigned b = 0; b < gridDim.x; ++b) {
+  for (unsigned b = threadIdx.x; b < gridDim.x; b += 64) {
     ft += partial[2 * b];
     vt += partial[2 * b + 1];
   }
+  ft = wave_sum_d(ft);
+  vt = wave_sum_d(vt);
   WaveExact acc;
   if (objacc) {
-    acc.a = lacc[threadIdx.x];
-    acc.b = threadIdx.x < kExactLimbs - 64 ? lacc[64 + threadIdx.x] : 0;
+    acc.a = lacc[0][threadIdx.x];
+    acc.b = threadIdx.x < kExactLimbs - 64 ? lacc[0][64 + threadIdx.x] : 0;
     acc.normalize();
     acc.store(objacc);
     ft = acc.round_nearest();
@@ -618,21 +643,8 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
   st->inf_V = v_orig > 0 ? v_orig : LLONG_MAX;
   st->inf_k = v_orig > 0 ? -1 : -2;
   *ticket = 0u;
-  st->k = 0;
-  st->iters = iters;
-  st->tenure = tenure;
   o.store(st);
-  st->sel_k = -1;
-  st->mv_j = -1;
-  st->mv_kind = 2;
-  st->dV = 0ull;
-  // single passes: the compact copy holds the cutoff weight as a count of
-  // half weights only when it is an integer below 2^16 (the rows are
-  // checked where the copy is written)
-  st->compact_rows = (o.wc == floorf(o.wc) && o.wc >= 0.0f && o.wc < 65535.0f) ? 1 : 0;
-  st->aff_ok = 0;
-  st->pass_skip = 0;
-  st->aff_iters = 0;
+  reset_state(st, iters, tenure, o.wc);
 }
 
 // Best positive score overall and among non-tabu variables of the columns the
@@ -1182,7 +1194,8 @@ __global__ __launch_bounds__(kPermPlaceThreads) void k_perm_place(PermPlan pl, c
                                                                   const double* __restrict__ st1,
                                                                   double* __restrict__ out0, double* __restrict__ out1,
                                                                   int8_t* __restrict__ xc, WalkState* ws,
-                                                                  uint32_t epoch) {
+                                                                  uint32_t epoch, SingleInit init) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && init.cutoff_w) single_state(ws, init);
   __shared__ double lds[kArrays][kPermBlock];
   constexpr int kU = kPermBlock / kPermPlaceThreads;
   const double* st[2] = {st0, st1};
@@ -1222,39 +1235,6 @@ __global__ __launch_bounds__(kPermPlaceThreads) void k_perm_place(PermPlan pl, c
     }
   }
   if (misfit) ws->x_misfit = epoch;  // every writer stores the same value
-}
-
-__global__ __launch_bounds__(256) void k_fill_compact(const RowState* __restrict__ rs, GatherRow* __restrict__ grow,
-                                                      int32_t ms) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ms) return;
-  const RowState q = rs[i];
-  GatherRow g;
-  g.r = (int32_t)q.r;
-  g.w0 = (uint16_t)q.w0;
-  g.w1 = q.w1 >= 0.0f ? (uint16_t)q.w1 : kNoTwin;
-  grow[i] = g;
-}
-
-__global__ __launch_bounds__(256) void k_fill_compact_checked(const RowState* __restrict__ rs,
-                                                              GatherRow* __restrict__ grow, WalkState* st,
-                                                              int32_t ms) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    // the cutoff weight enters the staged scores as a count of half weights
-    const float wc = st->wc;
-    if (!(wc == floorf(wc) && wc >= 0.0f && wc < 65535.0f)) st->compact_rows = 0;
-  }
-  if (i >= ms) return;
-  const RowState q = rs[i];
-  const bool ok = q.r == floor(q.r) && fabs(q.r) <= 2147483647.0 && q.w0 == floorf(q.w0) && q.w0 >= 0.0f &&
-                  q.w0 < 65535.0f && (q.w1 < 0.0f || (q.w1 == floorf(q.w1) && q.w1 < 65535.0f));
-  if (!ok) st->compact_rows = 0;  // every writer stores the same value
-  GatherRow g;
-  g.r = ok ? (int32_t)q.r : 0;
-  g.w0 = ok ? (uint16_t)q.w0 : 0;
-  g.w1 = (ok && q.w1 >= 0.0f) ? (uint16_t)q.w1 : kNoTwin;
-  grow[i] = g;
 }
 
 inline int blocks_for(int64_t work, int cap) {
@@ -1536,9 +1516,10 @@ hipError_t launch_start_point(const DevProblem& P, uint64_t seed, double* x, int
 }
 
 hipError_t launch_stage_x(const int32_t* perm, const double* src, double* dst, int8_t* xc, WalkState* st,
-                          uint32_t epoch, int32_t n, hipStream_t stream) {
-  if (n > 0)
-    hipLaunchKernelGGL(k_stage_x, dim3((n + 255) / 256), dim3(256), 0, stream, perm, src, dst, xc, st, epoch, n);
+                          uint32_t epoch, int32_t n, const SingleInit& init, hipStream_t stream) {
+  if (n > 0 || init.cutoff_w)
+    hipLaunchKernelGGL(k_stage_x, dim3((unsigned)std::max(1, (n + 255) / 256)), dim3(256), 0, stream, perm, src, dst,
+                       xc, st, epoch, n, init);
   return hipGetLastError();
 }
 
@@ -1610,14 +1591,14 @@ hipError_t launch_gather(const int32_t* perm, const double* src, double* dst, in
 }
 
 hipError_t launch_stage_x_plan(const PermPlan& plan, const double* src, double* dst, int8_t* xc, WalkState* st,
-                               uint32_t epoch, double* stage, hipStream_t stream) {
+                               uint32_t epoch, double* stage, const SingleInit& init, hipStream_t stream) {
   if (plan.n > 0) {
     const unsigned nc = (unsigned)((plan.n + kPermChunk - 1) / kPermChunk);
     const unsigned nb = (unsigned)((plan.n + kPermBlock - 1) / kPermBlock);
     hipLaunchKernelGGL(k_perm_runs<1>, dim3(nc), dim3(kPermRunsThreads), 0, stream, plan, src, nullptr, stage,
                        nullptr);
     hipLaunchKernelGGL(k_perm_place<1>, dim3(nb), dim3(kPermPlaceThreads), 0, stream, plan, stage, nullptr, dst,
-                       nullptr, xc, st, epoch);
+                       nullptr, xc, st, epoch, init);
   }
   return hipGetLastError();
 }
@@ -1630,7 +1611,7 @@ hipError_t launch_gather2_plan(const PermPlan& plan, const double* a, const doub
     double* stage_b = stage + plan.n;
     hipLaunchKernelGGL(k_perm_runs<2>, dim3(nc), dim3(kPermRunsThreads), 0, stream, plan, a, b, stage, stage_b);
     hipLaunchKernelGGL(k_perm_place<2>, dim3(nb), dim3(kPermPlaceThreads), 0, stream, plan, stage, stage_b, da, db,
-                       nullptr, nullptr, 0u);
+                       nullptr, nullptr, 0u, SingleInit());
   }
   return hipGetLastError();
 }
@@ -1638,18 +1619,6 @@ hipError_t launch_gather2_plan(const PermPlan& plan, const double* a, const doub
 hipError_t launch_gather2(const int32_t* inv, const double* a, const double* b, double* da, double* db, int32_t n,
                           hipStream_t stream) {
   if (n > 0) hipLaunchKernelGGL(k_gather2, dim3((n + 255) / 256), dim3(256), 0, stream, inv, a, b, da, db, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_compact_checked(const RowState* rs, GatherRow* grow, WalkState* st, int32_t ms,
-                                       hipStream_t stream) {
-  hipLaunchKernelGGL(k_fill_compact_checked, dim3(std::max(1, (ms + 255) / 256)), dim3(256), 0, stream, rs, grow, st,
-                     ms);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_compact(const RowState* rs, GatherRow* grow, int32_t ms, hipStream_t stream) {
-  if (ms > 0) hipLaunchKernelGGL(k_fill_compact, dim3((ms + 255) / 256), dim3(256), 0, stream, rs, grow, ms);
   return hipGetLastError();
 }
 
