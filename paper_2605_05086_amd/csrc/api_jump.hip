@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "chap_internal.h"
@@ -46,9 +47,13 @@ int build_jump_plan(chap_problem* p) {
   for (int32_t q = 0; q < n; ++q) cptr[q + 1] = cptr[q] + p->col_entries[q];
   int32_t slot = 0, bslot = 0;
   int64_t nsingle = 0;
+  std::vector<int32_t> singles, groups;
   for (int32_t q = 0; q < n; ++q) {
     const int32_t deg = p->col_entries[q];
-    if (deg <= kJumpLane) continue;
+    if (deg <= kJumpLane) {
+      (deg <= 1 ? singles : groups).push_back(q);
+      continue;
+    }
     const int32_t j = p->perm[q];
     const double l = p->lb[j], u = p->ub[j];
     const bool narrow = p->is_int[j] && std::isfinite(l) && std::isfinite(u) && u - l + 1.0 <= (double)kJumpNarrow;
@@ -105,6 +110,10 @@ int build_jump_plan(chap_problem* p) {
   // cycling through the ranges so that workgroup w (on XCD w mod 8) takes
   // range w mod 8; ranges that run out are padded with empty tasks
   {
+    for (auto& r : range_tasks)  // the longest first: a long task begun last would run alone
+      std::stable_sort(r.begin(), r.end(), [](const JumpBinTask& a, const JumpBinTask& b) {
+        return a.e_end - a.e_beg > b.e_end - b.e_beg;
+      });
     std::vector<size_t> pos(kXcds, 0);
     bool left = true;
     while (left) {
@@ -145,27 +154,31 @@ int build_jump_plan(chap_problem* p) {
   std::vector<JumpTask> sorted(tasks.size());
   for (size_t i = 0; i < order.size(); ++i) sorted[i] = tasks[order[i]];
   DeviceArena& A = p->arena;
-  if (!sorted.empty()) {
-    JumpTask* dt;
-    JumpCol* dc;
-    CHAP_HIP(A.upload(&dt, sorted));
-    CHAP_HIP(A.upload(&dc, cols));
-    CHAP_HIP(A.alloc(&p->jump_part, (size_t)slot * kWave));
-    p->jump_tasks = dt;
-    p->jump_cols = dc;
-  }
-  if (!btasks.empty()) {
-    JumpBinTask* db;
-    CHAP_HIP(A.upload(&db, btasks));
-    CHAP_HIP(A.alloc(&p->jump_bpart, (size_t)bslot * 2 * kWave));
-    p->jump_btasks = db;
-  }
-  p->n_jump_tasks = (int32_t)sorted.size();
-  p->n_jump_cols = (int32_t)cols.size();
-  p->n_jump_plain_tasks = n_plain_tasks;
-  p->n_jump_plain_cols = n_plain_cols;
-  p->n_jump_chunk_cols = n_chunk_cols;
-  p->n_jump_btasks = (int32_t)btasks.size();
+  JumpPlan L;
+  auto upload = [&](auto& to, const auto& v) {
+    typename std::decay<decltype(v)>::type::value_type* d = nullptr;
+    if (!v.empty()) CHAP_HIP(A.upload(&d, v));
+    to = d;
+    return (int)CHAP_OK;
+  };
+  int rc = upload(L.singles, singles);
+  if (rc == CHAP_OK) rc = upload(L.groups, groups);
+  if (rc == CHAP_OK) rc = upload(L.tasks, sorted);
+  if (rc == CHAP_OK) rc = upload(L.cols, cols);
+  if (rc == CHAP_OK) rc = upload(L.btasks, btasks);
+  if (rc != CHAP_OK) return rc;
+  if (!sorted.empty()) CHAP_HIP(A.alloc(&L.part, (size_t)slot * kWave));
+  if (bslot > 0) CHAP_HIP(A.alloc(&L.bpart, (size_t)bslot * 2 * kWave));
+  L.n_singles = (int32_t)singles.size();
+  L.n_groups = (int32_t)groups.size();
+  L.n_tasks = (int32_t)sorted.size();
+  L.n_plain_tasks = n_plain_tasks;
+  L.n_cols = (int32_t)cols.size();
+  L.n_plain_cols = n_plain_cols;
+  L.n_chunk_cols = n_chunk_cols;
+  L.n_btasks = (int32_t)btasks.size();
+  L.small_coef = p->dev.row_c8 != nullptr ? 1 : 0;
+  p->jump = L;
   // timing only: no system-scope fence at the record
   for (hipEvent_t& e : p->jump_ev) CHAP_HIP(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
   p->jump_ready = true;
@@ -189,10 +202,8 @@ int chap_jump_values(chap_problem* p, const double* d_x, const float* d_w, doubl
   hipStream_t s = (hipStream_t)hip_stream;
   CHAP_HIP(launch_single_begin(p, d_x, d_w, cutoff_rhs, s));
   CHAP_HIP(hipEventRecord(p->jump_ev[0], s));
-  CHAP_HIP(launch_jump(p->dev, p->bs_x, p->bs_rs, p->bs_state, p->bs_grow, p->obj_fast, p->jump_tasks,
-                       p->n_jump_tasks, p->n_jump_plain_tasks, p->jump_btasks, p->n_jump_btasks, p->jump_cols,
-                       p->n_jump_cols, p->n_jump_plain_cols, p->n_jump_chunk_cols, p->jump_part,
-                       p->jump_bpart, p->bs_xhat, p->bs_s, s));
+  CHAP_HIP(launch_jump(p->dev, p->jump, p->bs_x, p->bs_rs, p->bs_state, p->bs_grow, p->obj_fast, p->bs_xhat,
+                       p->bs_s, s));
   CHAP_HIP(hipEventRecord(p->jump_ev[1], s));
   CHAP_HIP(launch_single_end(p, d_jump, d_score, s));
   p->jump_timed = true;

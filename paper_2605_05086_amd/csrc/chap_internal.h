@@ -667,7 +667,7 @@ constexpr int kTopkMax = 8192;      // largest proposal set
 constexpr int kSubsetCap = 4096;    // breakpoint capacity of the subset sort workgroup
 constexpr int kSubsetChunk = 2048;  // stored entries per workgroup chunk of the subset pass
 constexpr int kSubsetGrid = 2048;   // workgroups of the subset chunk kernel (grid-stride)
-constexpr int kJumpLane = 8;       // stored entries up to which one lane finds a column's jump value
+constexpr int kJumpLane = 8;       // stored entries up to which eight lanes find a column's jump value
 constexpr int kJumpChunk = 4096;   // entries per wavefront task of a longer column
 constexpr int kJumpBinChunk = 1024;  // entries per wavefront of a column scored from bins
 constexpr int kJumpNarrow = 64;    // integer domains up to this size try every value
@@ -814,11 +814,22 @@ struct JumpBinTask {
 // [the others]; column records as [no bins form (n_plain_cols)] [chunked
 // bins form (n_chunk_cols)] [bins form finished by one bins task], so that
 // exact calls visit only what they need.
-hipError_t launch_jump(const DevProblem& P, const double* x, const RowState* rs, const WalkState* st,
-                       const GatherRow* grow, int32_t obj_small, const JumpTask* tasks, int32_t ntasks,
-                       int32_t n_plain_tasks, const JumpBinTask* btasks, int32_t nbtasks, const JumpCol* cols,
-                       int32_t ncols, int32_t n_plain_cols, int32_t n_chunk_cols, double* part, long long* bpart,
-                       double* jv, double* js, hipStream_t s);
+// Columns of at most one entry (singles) and of 2 .. kJumpLane entries (groups)
+// need no task.
+struct JumpPlan {
+  const int32_t* singles = nullptr;
+  const int32_t* groups = nullptr;
+  const JumpTask* tasks = nullptr;
+  const JumpCol* cols = nullptr;
+  const JumpBinTask* btasks = nullptr;
+  double* part = nullptr;
+  long long* bpart = nullptr;
+  int32_t n_singles = 0, n_groups = 0, n_tasks = 0, n_cols = 0, n_btasks = 0;
+  int32_t n_plain_tasks = 0, n_plain_cols = 0, n_chunk_cols = 0;
+  int32_t small_coef = 0;  // every coefficient is an integer in [-127, 127]
+};
+hipError_t launch_jump(const DevProblem& P, const JumpPlan& L, const double* x, const RowState* rs, const WalkState* st,
+                       const GatherRow* grow, int32_t obj_small, double* jv, double* js, hipStream_t s);
 // The lists of affected rescoring. The affected columns of an iteration are
 // split into its lane-group columns (slist) and the rest (olist, with the
 // subset chunk offsets ooff). When every column outside the lane-group range
@@ -975,13 +986,7 @@ struct chap_problem {
   // jump values: wavefront tasks of the longer columns (built on the first
   // chap_jump_values call), their partial sums, timing events
   bool jump_ready = false;
-  const chap::JumpTask* jump_tasks = nullptr;
-  const chap::JumpCol* jump_cols = nullptr;
-  const chap::JumpBinTask* jump_btasks = nullptr;
-  int32_t n_jump_tasks = 0, n_jump_cols = 0, n_jump_btasks = 0;
-  int32_t n_jump_plain_tasks = 0, n_jump_plain_cols = 0, n_jump_chunk_cols = 0;
-  double* jump_part = nullptr;
-  long long* jump_bpart = nullptr;
+  chap::JumpPlan jump;
   hipEvent_t jump_ev[2] = {nullptr, nullptr};
   bool jump_timed = false;
   ~chap_problem() {

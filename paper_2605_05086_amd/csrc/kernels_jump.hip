@@ -17,26 +17,32 @@
 // its finite bounds and, for an integer variable, xbar +- 1 (V_q is convex
 // and piecewise linear, so its minimum over the domain is among them).
 //
-// Every V_q(t) is one sum in the order above, evaluated directly at t:
-//   k_jump_lane    columns with at most kJumpLane stored entries, one lane
-//                  each, entries in registers, candidates one after another
-//                  (on exact integer data narrow columns too try only the
-//                  kinks' neighbours, bounds and xbar +- 1);
-//   k_jump_tasks   longer columns: one wavefront per (column, tile of 64
-//                  candidates, chunk of kJumpChunk entries), a lane per
-//                  candidate; the wavefront loads 64 entries at a time into
-//                  its LDS slice and every lane adds each entry's terms in
-//                  order (one broadcast read per entry);
-//   k_jump_combine one wavefront per longer column: the chunks' partial sums
-//                  in chunk order, the cutoff term, the argmin over tiles;
-//   k_jump_bins_combine one workgroup per chunked column with a bins form on
-//                  exact data: the chunks' bins, the scan and the argmin.
+// Every V_q(t) is one sum in the order above, evaluated directly at t, by the
+// roles of one launch, k_jump (independent of one another):
+//   single  columns with at most one stored entry, one lane each;
+//   group   columns with 2 .. kJumpLane stored entries, eight lanes each: the
+//           lanes load an entry each into LDS and share the candidates (on
+//           exact integer data narrow columns too try only the kinks'
+//           neighbours, bounds and xbar +- 1);
+//   bins    longer narrow columns on exact integer data: slope and offset
+//           bins, one wavefront per chunk of entries;
+//   tasks   other longer columns: one wavefront per (column, tile of 64
+//           candidates, chunk of kJumpChunk entries), a lane per candidate; the
+//           wavefront loads 64 entries at a time into its LDS slice and every
+//           lane adds each entry's terms in order (one broadcast read per
+//           entry);
+// and of a second one, k_jump_combine:
+//   columns one wavefront per column scored by tasks: the chunks' partial sums
+//           in chunk order, the cutoff term, the argmin over tiles;
+//   bins    one workgroup per chunked bins column: the chunks' bins, the scan
+//           and the argmin.
 // A column of one chunk is summed exactly in the stored order; longer
 // columns add per-chunk partial sums, exact on integer data.
 
 #include <algorithm>
 
 #include "chap_internal.h"
+#include "move_best.h"
 
 namespace chap {
 namespace {
@@ -149,115 +155,220 @@ __device__ __forceinline__ int jump_tiles(bool narrow, int deg) {
   return narrow ? 1 : (2 * deg + kJumpSpecials + kWave - 1) / kWave;
 }
 
-// exact_data: every residual within the bounds fits int32 and the data are
-// integers; with integer weights below 2^16 (st->compact_rows) and a cutoff
-// term of small integers, every V the lane forms is an exact integer below
-// 2^53, and then the kinks' neighbours, the bounds and xbar +- 1 hold the
-// chosen value of a narrow column too (a value strictly between them has
-// neighbours on one line through it; a zero slope makes the neighbour
-// towards xbar tie and win, any other slope makes a neighbour smaller), so
-// narrow columns try those (and the integers next to them) instead of
-// every value.
-__global__ __launch_bounds__(256) void k_jump_lane(DevProblem P, const double* __restrict__ x,
-                                                   const RowState* __restrict__ rs,
-                                                   const GatherRow* __restrict__ grow, const WalkState* __restrict__ st,
-                                                   int32_t exact_data, int32_t obj_small, double* __restrict__ jv,
-                                                   double* __restrict__ js) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= P.n) return;
-  const int beg = P.col_ptr[q], deg = P.col_ptr[q + 1] - beg;
-  if (deg > kJumpLane) return;
-  const double xb = x[q], l = P.lb[q], u = P.ub[q];
-  const bool isint = P.is_int[q] != 0;
-  const bool exact = jump_exact(st, exact_data, obj_small);
-  double r[kJumpLane], a[kJumpLane];
-  float w0[kJumpLane], w1[kJumpLane];
+// What the roles of k_jump share.
+struct JumpCall {
+  DevProblem P;
+  const double* x;
+  const RowState* rs;
+  const GatherRow* grow;  // the call's compact row copy (exact data), or null
+  const WalkState* st;
+  int32_t exact_data, obj_small;
+  const int32_t* singles;  // columns of at most one entry
+  const int32_t* groups;   // columns of 2 .. kJumpLane entries
+  const JumpBinTask* btasks;
+  const JumpTask* tasks;
+  int32_t n_singles, n_groups, nbtasks, ntasks, n_plain;
+  int32_t small_coef;  // every coefficient is an integer in [-127, 127]
+  int32_t blk[3];      // end of the workgroups of bins, tasks, groups (the rest: singles)
+  double* part;
+  long long* bpart;
+  double* jv;
+  double* js;
+};
+
+__device__ __forceinline__ JumpEntry jump_entry(const JumpCall& J, bool exact, int e) {
   // rows from the 8-byte compact copy on exact data (the same values), else
   // the 16-byte row states
-#pragma unroll
-  for (int k = 0; k < kJumpLane; ++k) {
-    r[k] = 0.0;
-    a[k] = 1.0;
-    w0[k] = 0.0f;
-    w1[k] = -1.0f;
-    if (k < deg) {
-      const int i = P.col_row[beg + k];
-      if (exact) {
-        const GatherRow g = grow[i];
-        r[k] = (double)g.r;
-        w0[k] = (float)g.w0;
-        w1[k] = g.w1 == kNoTwin ? -1.0f : (float)g.w1;
-      } else {
-        const RowState s = rs[i];
-        r[k] = s.r;
-        w0[k] = s.w0;
-        w1[k] = s.w1;
-      }
-      a[k] = P.col_val[beg + k];
-    }
+  JumpEntry o;
+  const int i = gmem(J.P.col_row)[e];
+  o.a = gmem(J.P.col_val)[e];
+  if (exact) {
+    const GatherRow g = gload(gmem(J.grow), (int64_t)i);
+    o.r = (double)g.r;
+    o.w0 = (float)g.w0;
+    o.w1 = g.w1 == kNoTwin ? -1.0f : (float)g.w1;
+  } else {
+    const RowState q = gload(gmem(J.rs), (int64_t)i);
+    o.r = q.r;
+    o.w0 = q.w0;
+    o.w1 = q.w1;
   }
-  const double cq = P.obj[q];
-  const bool cact = st->cut_active && cq != 0.0;
+  return o;
+}
+
+__device__ __forceinline__ double add_entry(double v, const JumpEntry& e, double d) {
+  const double y = e.r + e.a * d;
+  v = v + (double)e.w0 * relu(y);
+  if (e.w1 >= 0.0f) v = v + (double)e.w1 * relu(-y);
+  return v;
+}
+
+// The values a column of at most kJumpLane entries tries, numbered: a narrow
+// column off exact data every value of its domain; any other one, per entry
+// and then for the cutoff row when it acts on the column, the values at its
+// kink (an integer variable: floor and ceiling, widened by one on either side
+// for a narrow column; a continuous one: the kink), then l, u and, for an
+// integer variable, xbar - 1 and xbar + 1. Every V formed on exact data is an
+// exact integer below 2^53, and then those values hold the chosen one of a
+// narrow column too (a value strictly between them has neighbours on one line
+// through it; a zero slope makes the neighbour towards xbar tie and win, any
+// other slope makes a neighbour smaller); the widening keeps a rounding of the
+// FP64 kink across an integer from hiding one.
+struct JumpTries {
+  bool every, isint;
+  int per;  // log2 of the values per kink
+  int kinks;
+  __device__ __forceinline__ int count(double l, double u) const {
+    return every ? (int)(u - l) + 1 : (kinks << per) + (isint ? 4 : 2);
+  }
+  // kink(i): the i-th kink
+  template <typename Kink>
+  __device__ __forceinline__ double value(int c, double xb, double l, double u, Kink kink) const {
+    if (every) return l + (double)c;
+    const int i = c >> per;
+    if (i < kinks) {
+      const double k = kink(i);
+      const int o = c & ((1 << per) - 1);
+      if (per == 0) return k;
+      if (per == 1) return o ? ceil(k) : floor(k);
+      return o < 2 ? floor(k) + (double)(o - 1) : ceil(k) + (double)(o - 2);
+    }
+    const int sp = c - (kinks << per);
+    return sp == 0 ? l : (sp == 1 ? u : (sp == 2 ? xb - 1.0 : xb + 1.0));
+  }
+};
+
+__device__ __forceinline__ JumpTries jump_tries(bool isint, bool narrow, bool exact, int kinks) {
+  return JumpTries{narrow && !exact, isint, isint ? (narrow ? 2 : 1) : 0, kinks};
+}
+
+// Columns of at most one entry, a lane each.
+__device__ __forceinline__ void jump_single(const JumpCall& J, bool exact, int b) {
+  const int i = b * 256 + (int)threadIdx.x;
+  if (i >= J.n_singles) return;
+  const int q = gmem(J.singles)[i];
+  const DevProblem& P = J.P;
+  const WalkState* st = J.st;
+  const int beg = gmem(P.col_ptr)[q], deg = gmem(P.col_ptr)[q + 1] - beg;
+  const double xb = gmem(J.x)[q], l = gmem(P.lb)[q], u = gmem(P.ub)[q];
+  const bool isint = gmem(P.is_int)[q] != 0;
+  const double cq = st->cut_active ? gmem(P.obj)[q] : 0.0;
   const double rc = st->rc, wc = (double)st->wc;
+  JumpEntry e{0.0, 1.0, 0.0f, -1.0f};
+  if (deg > 0) e = jump_entry(J, exact, beg);
   auto V = [&](double t) {
     const double d = t - xb;
-    double v = 0.0;
-#pragma unroll
-    for (int k = 0; k < kJumpLane; ++k) {
-      if (k < deg) {
-        const double y = r[k] + a[k] * d;
-        v = v + (double)w0[k] * relu(y);
-        if (w1[k] >= 0.0f) v = v + (double)w1[k] * relu(-y);
-      }
-    }
-    if (cact) v = v + wc * relu(rc + cq * d);
+    double v = deg > 0 ? add_entry(0.0, e, d) : 0.0;
+    if (cq != 0.0) v = v + wc * relu(rc + cq * d);
     return v;
   };
+  const JumpTries T = jump_tries(isint, jump_narrow(isint, l, u), exact, deg + (cq != 0.0 ? 1 : 0));
+  const double k0 = deg > 0 ? xb - e.r / e.a : xb - rc / cq;
+  const double k1 = cq != 0.0 ? xb - rc / cq : 0.0;
   bool found = false;
   double bt = xb, bv = 0.0;
-  auto consider = [&](double t) {
-    if (!(isfinite(t) && t >= l && t <= u && t != xb)) return;
+  const int nc = T.count(l, u);
+  for (int c = 0; c < nc; ++c) {
+    const double t = T.value(c, xb, l, u, [&](int k) { return k == 0 ? k0 : k1; });
+    if (!(isfinite(t) && t >= l && t <= u && t != xb)) continue;
     const double v = V(t);
     if (!found || jump_better(v, t, bv, bt, xb)) {
       found = true;
       bt = t;
       bv = v;
     }
+  }
+  gmem(J.jv)[q] = found ? bt : xb;
+  gmem(J.js)[q] = found ? V(xb) - bv : 0.0;
+}
+
+// Columns of 2 .. kJumpLane entries, kJumpLane lanes each: the longest columns
+// have 36 candidates of 8 terms, which one lane needs several thousand dependent
+// instructions for; the group's lanes take every eighth candidate.
+struct JumpGroupSmem {
+  JumpEntry e[256];
+  double kink[256 + 256 / kJumpLane];
+};
+__device__ __forceinline__ void jump_group(const JumpCall& J, bool exact, int b, JumpGroupSmem& S) {
+  constexpr int G = kJumpLane;
+  const int tid = threadIdx.x, g = tid & (G - 1), base = tid & ~(G - 1);
+  const int i = b * (256 / G) + tid / G;
+  const bool in = i < J.n_groups;
+  const int q = gmem(J.groups)[in ? i : 0];
+  const DevProblem& P = J.P;
+  const WalkState* st = J.st;
+  const int beg = gmem(P.col_ptr)[q], deg = gmem(P.col_ptr)[q + 1] - beg;
+  const double xb = gmem(J.x)[q], l = gmem(P.lb)[q], u = gmem(P.ub)[q];
+  const bool isint = gmem(P.is_int)[q] != 0;
+  const double cq = st->cut_active ? gmem(P.obj)[q] : 0.0;
+  const double rc = st->rc, wc = (double)st->wc;
+  JumpEntry* E = S.e + base;
+  double* kink = S.kink + base + base / G;
+  if (g < deg) {
+    const JumpEntry e = jump_entry(J, exact, beg + g);
+    E[g] = e;
+    kink[g] = xb - e.r / e.a;
+  }
+  if (g == 0 && cq != 0.0) kink[deg] = xb - rc / cq;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  auto V = [&](double t) {
+    const double d = t - xb;
+    double v = 0.0;
+    for (int k = 0; k < deg; ++k) v = add_entry(v, E[k], d);
+    if (cq != 0.0) v = v + wc * relu(rc + cq * d);
+    return v;
   };
-  const bool narrow = jump_narrow(isint, l, u);
-  // a narrow column on exact data: each kink's neighbours, widened by one
-  // on either side so that a rounding of the FP64 kink across an integer
-  // cannot hide one
-  const int pad = narrow ? 1 : 0;
-  auto kink_values = [&](double kink) {
-    if (isint) {
-      for (int o = -pad; o <= 0; ++o) consider(floor(kink) + (double)o);
-      for (int o = 0; o <= pad; ++o) consider(ceil(kink) + (double)o);
-    } else {
-      consider(kink);
+  const JumpTries T = jump_tries(isint, jump_narrow(isint, l, u), exact, deg + (cq != 0.0 ? 1 : 0));
+  // the first of the candidates that are best, as trying them one after
+  // another finds it
+  bool found = false, nan = false;
+  double bt = xb, bv = 0.0;
+  int bc = 0;
+  const int nc = T.count(l, u);
+  auto consider = [&](int c) {
+    const double t = T.value(c, xb, l, u, [&](int k) { return kink[k]; });
+    if (!(isfinite(t) && t >= l && t <= u && t != xb)) return;
+    const double v = V(t);
+    nan = nan || v != v;
+    if (!found || jump_better(v, t, bv, bt, xb)) {
+      found = true;
+      bt = t;
+      bv = v;
+      bc = c;
     }
   };
-  if (narrow && !exact) {
-    const int W = (int)(u - l) + 1;
-    for (int p = 0; p < W; ++p) consider(l + (double)p);
-  } else {
+  for (int c = g; c < nc; c += G) consider(c);
+  if (__ballot(nan)) {
+    // an overflow makes the comparisons depend on the order: one lane tries
+    // every candidate in turn
+    found = false;
+    bt = xb;
+    bv = 0.0;
+    if (g == 0)
+      for (int c = 0; c < nc; ++c) consider(c);
+  }
 #pragma unroll
-    for (int k = 0; k < kJumpLane; ++k)
-      if (k < deg) kink_values(xb - r[k] / a[k]);
-    if (cact) kink_values(xb - rc / cq);
-    consider(l);
-    consider(u);
-    if (isint) {
-      consider(xb - 1.0);
-      consider(xb + 1.0);
+  for (int o = 1; o < G; o <<= 1) {
+    const double ov = __shfl_xor(bv, o, kWave), ot = __shfl_xor(bt, o, kWave);
+    const bool of = __shfl_xor((int)found, o, kWave) != 0;
+    const int oc = __shfl_xor(bc, o, kWave);
+    if (of && (!found || jump_better(ov, ot, bv, bt, xb) || (ov == bv && ot == bt && oc < bc))) {
+      found = true;
+      bt = ot;
+      bv = ov;
+      bc = oc;
     }
   }
-  jv[q] = found ? bt : xb;
-  js[q] = found ? V(xb) - bv : 0.0;
+  if (g != 0 || !in) return;
+  gmem(J.jv)[q] = found ? bt : xb;
+  gmem(J.js)[q] = found ? V(xb) - bv : 0.0;
 }
 
 __device__ void jump_task(const DevProblem& P, const double* __restrict__ x, const RowState* __restrict__ rs,
-                          const WalkState* __restrict__ st, const JumpTask T, double* __restrict__ part) {
+                          const WalkState* __restrict__ st, const JumpTask T, double* __restrict__ part,
+                          JumpEntry* E) {
   const int lane = threadIdx.x & (kWave - 1);
   const int q = T.q;
   const int beg = P.col_ptr[q], deg = P.col_ptr[q + 1] - beg;
@@ -270,8 +381,6 @@ __device__ void jump_task(const DevProblem& P, const double* __restrict__ x, con
   const int e1 = min(beg + deg, e0 + kJumpChunk);
   // each batch of 64 entries goes through this wavefront's LDS slice; every
   // lane then reads entry k at one address (a broadcast)
-  __shared__ JumpEntry S[4][kWave];
-  JumpEntry* E = S[threadIdx.x >> 6];
   double v = 0.0;
   for (int base = e0; base < e1; base += kWave) {
     const int e = base + lane;
@@ -303,29 +412,29 @@ __device__ void jump_task(const DevProblem& P, const double* __restrict__ x, con
   part[(size_t)T.slot * kWave + lane] = v;
 }
 
-// Grid-stride over the tasks, one wavefront per task: every task, or on
-// exact data only the first n_plain (the tasks of columns without a bins
-// form; the others are scored from bins).
-__global__ __launch_bounds__(256) void k_jump_tasks(DevProblem P, const double* __restrict__ x,
-                                                    const RowState* __restrict__ rs, const WalkState* __restrict__ st,
-                                                    int32_t exact_data, int32_t obj_small,
-                                                    const JumpTask* __restrict__ tasks, int32_t ntasks,
-                                                    int32_t n_plain, double* __restrict__ part) {
-  const int nt = jump_exact(st, exact_data, obj_small) ? n_plain : ntasks;
-  for (int id = blockIdx.x * 4 + (threadIdx.x >> 6); id < nt; id += gridDim.x * 4)  // whole wavefronts
-    jump_task(P, x, rs, st, tasks[id], part);
+// floor(n / d) and ceil(n / d) for d > 0 and |n|, |d| < 2^31, clamped to [-1,
+// kJumpNarrow + 1] (positions beyond leave every narrow column). kSmall (d <=
+// 127): a float product with the reciprocal, within 1.2e-5 of the quotient
+// where that is at most 65; 1/512 moves an integer quotient past its own floor
+// and any other lies at least 1/127 from an integer, so the results are exact.
+// Otherwise one FP64 division: an integer quotient is exact, and any other lies
+// at least 1/d from an integer while the rounding moves it by at most |n/d|
+// 2^-53 < 2^-22 / d.
+template <bool kSmall>
+__device__ __forceinline__ int floor_div(long long n, long long d) {
+  constexpr float kTop = (float)(kJumpNarrow + 1);
+  if constexpr (kSmall)
+    return (int)__builtin_amdgcn_fmed3f(
+        floorf(__builtin_fmaf((float)n, __builtin_amdgcn_rcpf((float)d), 1.0f / 512.0f)), -1.0f, kTop);
+  return (int)fmin(fmax(floor((double)n / (double)d), -1.0), (double)kTop);
 }
-
-// floor(n / d) and ceil(n / d) for d > 0 and |n|, |d| < 2^31, through one
-// FP64 division: an integer quotient is exact, and any other lies at least
-// 1/d from an integer while the rounding moves it by at most |n/d| 2^-53 <
-// 2^-22 / d, so floor and ceil are unchanged (64-bit integer division is a
-// long software sequence on the GPU).
-__device__ __forceinline__ long long floor_div(long long n, long long d) {
-  return (long long)floor((double)n / (double)d);
-}
-__device__ __forceinline__ long long ceil_div(long long n, long long d) {
-  return (long long)ceil((double)n / (double)d);
+template <bool kSmall>
+__device__ __forceinline__ int ceil_div(long long n, long long d) {
+  constexpr float kTop = (float)(kJumpNarrow + 1);
+  if constexpr (kSmall)
+    return (int)__builtin_amdgcn_fmed3f(
+        ceilf(__builtin_fmaf((float)n, __builtin_amdgcn_rcpf((float)d), -1.0f / 512.0f)), -1.0f, kTop);
+  return (int)fmin(fmax(ceil((double)n / (double)d), -1.0), (double)kTop);
 }
 
 // One term w max(0, c + a p) over positions p = 0 .. W-1 as bin updates:
@@ -334,53 +443,62 @@ __device__ __forceinline__ long long ceil_div(long long n, long long d) {
 // that is positive at p = 0, and every term with a > 0 positive from p = 0)
 // go to the lane's own k0 and s0, added into the bin once per wavefront:
 // as LDS atomics they would all hit one address.
+template <bool kSmall>
 __device__ __forceinline__ void add_ramp(unsigned long long* K, unsigned long long* S, long long& k0, long long& s0,
-                                         long long c, long long a, long long w, int W) {
+                                         long long c, long long a, int w, int W) {
   if (w == 0) return;
-  if (a > 0) {
-    const long long p0 = floor_div(-c, a) + 1;  // first p with c + a p > 0
-    if (p0 < W) {
-      if (p0 > 0) {
-        atomicAdd(&K[p0], (unsigned long long)(w * c));
-        atomicAdd(&S[p0], (unsigned long long)(w * a));
-      } else {
-        k0 += w * c;
-        s0 += w * a;
-      }
-    }
-  } else {
-    const long long p1 = ceil_div(c, -a);  // first p with c + a p <= 0
-    const int k = (int)(p1 < 0 ? 0 : (p1 > W ? W : p1));
-    if (k > 0) {
-      k0 += w * c;
-      s0 += w * a;
-      if (k < W) {
-        atomicAdd(&K[k], (unsigned long long)(-w * c));
-        atomicAdd(&S[k], (unsigned long long)(-w * a));
-      }
-    }
+  const bool up = a > 0;
+  // the position from which on (a > 0) or up to which the term is positive
+  const int p = up ? floor_div<kSmall>(-c, a) + 1 : ceil_div<kSmall>(c, -a);
+  const long long wc = w * c, wa = kSmall ? (long long)(w * (int)a) : w * a;  // small: below 2^16 * 2^7
+  if (up ? p <= 0 : p > 0) {
+    k0 += wc;
+    s0 += wa;
   }
+  if (p > 0 && p < W) {
+    atomicAdd(&K[p], (unsigned long long)(up ? wc : -wc));
+    atomicAdd(&S[p], (unsigned long long)(up ? wa : -wa));
+  }
+}
+
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ long long dpp_ll(long long v) {  // identity 0
+  const unsigned lo = (unsigned)dpp<kCtrl, kRowMask>((int)v, 0);
+  const unsigned hi = (unsigned)dpp<kCtrl, kRowMask>((int)(v >> 32), 0);
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+// Sums over the lanes up to and with this one.
+__device__ __forceinline__ long long wave_scan(long long v) {
+  v += dpp_ll<kRowShr1, 0xF>(v);
+  v += dpp_ll<kRowShr2, 0xF>(v);
+  v += dpp_ll<kRowShr4, 0xF>(v);
+  v += dpp_ll<kRowShr8, 0xF>(v);
+  v += dpp_ll<kBcast15, 0xA>(v);
+  v += dpp_ll<kBcast31, 0xC>(v);
+  return v;
+}
+__device__ __forceinline__ long long wave_total(long long v) {
+  v = wave_scan(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)v, 63);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(v >> 32), 63);
+  return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
 // The argmin of a narrow column from its bins (lane p holds bin p of the
 // offsets k and slopes sl, summed over the column's chunks): prefix sums
 // across the lanes give V(l + p) exactly, the cutoff term is added in
-// integers; lane 0 writes the jump value and score.
+// integers; lane 0 writes the jump value and score. Every V is an integer in
+// [0, 2^52], so the smallest is the largest 2^53 - V; of the lanes that hold it
+// the nearest below xbar and the nearest above are the two to choose from.
 __device__ __forceinline__ void bins_finish(const DevProblem& P, const WalkState* st, int q, double xb, long long k,
                                             long long sl, double* jv, double* js) {
   const int lane = threadIdx.x & (kWave - 1);
-  const double l = P.lb[q];
-  const int W = (int)(P.ub[q] - l) + 1;
-  const double cq = P.obj[q];
+  const double l = gmem(P.lb)[q];
+  const int W = (int)(gmem(P.ub)[q] - l) + 1;
+  const double cq = gmem(P.obj)[q];
   const bool cact = st->cut_active && cq != 0.0;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const long long yk = __shfl_up(k, o, kWave), ys = __shfl_up(sl, o, kWave);
-    if (lane >= o) {
-      k += yk;
-      sl += ys;
-    }
-  }
+  k = wave_scan(k);
+  sl = wave_scan(sl);
   long long vi = k + (long long)lane * sl;
   const double t = l + (double)lane;
   if (cact) {
@@ -388,33 +506,17 @@ __device__ __forceinline__ void bins_finish(const DevProblem& P, const WalkState
     vi += (long long)st->wc * (y > 0 ? y : 0);
   }
   const double v = (double)vi;
-  bool found = false, have0 = false;
-  double bt = xb, bv = 0.0, v0 = 0.0;
-  if (lane < W) {
-    if (t == xb) {
-      v0 = v;
-      have0 = true;
-    } else {
-      found = true;
-      bt = t;
-      bv = v;
-    }
-  }
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const double ov = __shfl_xor(bv, o, kWave), ot = __shfl_xor(bt, o, kWave);
-    const bool of = __shfl_xor((int)found, o, kWave) != 0;
-    if (of && (!found || jump_better(ov, ot, bv, bt, xb))) {
-      found = true;
-      bt = ot;
-      bv = ov;
-    }
-  }
-  const unsigned long long m0 = __ballot(have0);
-  v0 = __shfl(v0, m0 ? __builtin_ctzll(m0) : 0, kWave);
+  const bool in = lane < W, cur = in && t == xb;
+  const double key = in && !cur ? 9007199254740992.0 - v : 0.0;
+  const double best = wave_max_pos(key);
+  const unsigned long long m = __ballot(key == best && best > 0.0), below = __ballot(t < xb);
+  const unsigned long long ml = m & below, mu = m & ~below, m0 = __ballot(cur);
+  const double tl = l + (double)(63 - __builtin_clzll(ml | 1ull)), tu = l + (double)__builtin_ctzll(mu | (1ull << 63));
+  const bool lower = ml != 0 && (mu == 0 || xb - tl <= tu - xb);
+  const double v0 = m0 ? __shfl(v, __builtin_ctzll(m0 | (1ull << 63)), kWave) : 0.0;
   if (lane == 0) {
-    jv[q] = found ? bt : xb;
-    js[q] = found ? v0 - bv : 0.0;
+    gmem(jv)[q] = m ? (lower ? tl : tu) : xb;
+    gmem(js)[q] = m ? v0 - (9007199254740992.0 - best) : 0.0;
   }
 }
 
@@ -424,73 +526,85 @@ __device__ __forceinline__ void bins_finish(const DevProblem& P, const WalkState
 // eighth of the rows, and the four tasks of a workgroup in the same eighth,
 // which the task order places on one XCD, so the row gathers stay in that
 // XCD's L2.
-__global__ __launch_bounds__(256) void k_jump_bins(DevProblem P, const double* __restrict__ x,
-                                                   const GatherRow* __restrict__ grow, const WalkState* __restrict__ st,
-                                                   int32_t exact_data, int32_t obj_small,
-                                                   const JumpBinTask* __restrict__ tasks, int32_t ntasks,
-                                                   long long* __restrict__ bpart, double* __restrict__ jv,
-                                                   double* __restrict__ js) {
-  if (!jump_exact(st, exact_data, obj_small)) return;
-  const int id = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (id >= ntasks) return;  // whole wavefronts leave together
+struct JumpBinSmem {
+  unsigned long long K[4][kWave], S[4][kWave];
+};
+template <bool kSmall>
+__device__ __forceinline__ void jump_bins(const JumpCall& J, int b, JumpBinSmem& M) {
+  const int id = b * 4 + (threadIdx.x >> 6);
+  if (id >= J.nbtasks) return;  // whole wavefronts leave together
   const int lane = threadIdx.x & (kWave - 1);
-  __shared__ unsigned long long KB[4][kWave], SB[4][kWave];
-  unsigned long long* K = KB[threadIdx.x >> 6];
-  unsigned long long* S = SB[threadIdx.x >> 6];
+  const DevProblem& P = J.P;
+  unsigned long long* K = M.K[threadIdx.x >> 6];
+  unsigned long long* S = M.S[threadIdx.x >> 6];
   K[lane] = 0ull;
   S[lane] = 0ull;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const JumpBinTask T = tasks[id];
+  const JumpBinTask T = J.btasks[id];
   if (T.q < 0) return;  // padding of the row-range interleave
   const int q = T.q;
-  const double xb = x[q], l = P.lb[q];
+  const double xb = gmem(J.x)[q], l = gmem(P.lb)[q];
   const int W = (int)(P.ub[q] - l) + 1;
   long long k0 = 0, s0 = 0;
-  // one entry per lane and step (two or four in flight measured slower:
-  // 363 and 375 against 348 us for the call's kernels on the 20M
-  // instance); rows from the compact copy (exact on this path: integer
-  // residuals and weights)
-  constexpr int kU = 1;
-  for (int e0 = T.e_beg + lane; e0 < T.e_end; e0 += kU * kWave) {
-    GatherRow r[kU];
-    double a[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int e = e0 + u * kWave;
-      if (e < T.e_end) {
-        r[u] = grow[P.col_row[e]];
-        a[u] = P.col_val[e];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      if (e0 + u * kWave >= T.e_end) break;
-      const long long c = (long long)((double)r[u].r + a[u] * (l - xb));  // residual at x_q = l: an integer
-      const long long ai = (long long)a[u];
-      add_ramp(K, S, k0, s0, c, ai, (long long)r[u].w0, W);
-      if (r[u].w1 != kNoTwin) add_ramp(K, S, k0, s0, -c, -ai, (long long)r[u].w1, W);
-    }
+  // one entry per lane and step (two in flight measured slower: 40.0 against
+  // 37.1 us, 2M entries); rows from the compact copy (exact on this path:
+  // integer residuals and weights)
+  for (int e = T.e_beg + lane; e < T.e_end; e += kWave) {
+    const GatherRow r = gload(gmem(J.grow), (int64_t)gmem(P.col_row)[e]);
+    const double a = gmem(P.col_val)[e];
+    const long long c = (long long)((double)r.r + a * (l - xb));  // residual at x_q = l: an integer
+    const long long ai = (long long)a;
+    add_ramp<kSmall>(K, S, k0, s0, c, ai, (int)r.w0, W);
+    if (r.w1 != kNoTwin) add_ramp<kSmall>(K, S, k0, s0, -c, -ai, (int)r.w1, W);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    k0 += __shfl_xor(k0, o, kWave);
-    s0 += __shfl_xor(s0, o, kWave);
-  }
-  if (lane == 0) {
-    atomicAdd(&K[0], (unsigned long long)k0);
-    atomicAdd(&S[0], (unsigned long long)s0);
-  }
+  k0 = wave_total(k0);
+  s0 = wave_total(s0);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const long long k = (long long)K[lane] + (lane == 0 ? k0 : 0), sl = (long long)S[lane] + (lane == 0 ? s0 : 0);
   if (T.slot < 0) {
-    bins_finish(P, st, q, xb, (long long)K[lane], (long long)S[lane], jv, js);  // the whole column
+    bins_finish(P, J.st, q, xb, k, sl, J.jv, J.js);  // the whole column
     return;
   }
-  bpart[(size_t)T.slot * 2 * kWave + lane] = (long long)K[lane];
-  bpart[(size_t)T.slot * 2 * kWave + kWave + lane] = (long long)S[lane];
+  gmem(J.bpart)[(size_t)T.slot * 2 * kWave + lane] = k;
+  gmem(J.bpart)[(size_t)T.slot * 2 * kWave + kWave + lane] = sl;
+}
+
+// Every column's score up to the combines: the roles of the workgroups by J.blk,
+// the longest work first. The bins tasks begin at workgroup 0, which their order
+// over the XCDs counts on. The tasks' workgroups stride over every task, or on
+// exact data over the first n_plain only (those of columns without a bins form).
+// Bounded by its vector instructions (double precision): 1.6e7 of them on 200k
+// integer columns of 2M entries, 34 us, where one lane per short column (29 us;
+// 111 registers and serial candidates), the bins with double-precision quotients
+// and exchanges through LDS (42 us) and an empty tasks launch (5 us) took 76 us
+// one after another. Six wavefronts a SIMD: 37.1 us with five, no spills.
+__global__ __launch_bounds__(256, 6) void k_jump(JumpCall J) {
+  __shared__ union {
+    JumpGroupSmem group;
+    JumpEntry task[4][kWave];
+    JumpBinSmem bins;
+  } M;
+  const bool exact = jump_exact(J.st, J.exact_data, J.obj_small);
+  const int b = blockIdx.x;
+  if (b < J.blk[0]) {
+    if (!exact) return;
+    if (J.small_coef)
+      jump_bins<true>(J, b, M.bins);
+    else
+      jump_bins<false>(J, b, M.bins);
+  } else if (b < J.blk[1]) {
+    const int nt = exact ? J.n_plain : J.ntasks;
+    for (int id = (b - J.blk[0]) * 4 + (threadIdx.x >> 6); id < nt; id += (J.blk[1] - J.blk[0]) * 4)  // whole wavefronts
+      jump_task(J.P, J.x, J.rs, J.st, J.tasks[id], J.part, M.task[threadIdx.x >> 6]);
+  } else if (b < J.blk[2]) {
+    jump_group(J, exact, b - J.blk[1], M.group);
+  } else {
+    jump_single(J, exact, b - J.blk[2]);
+  }
 }
 
 constexpr int kJumpInFlight = 16;  // chunk partials per load round of the combines
@@ -499,13 +613,8 @@ constexpr int kJumpInFlight = 16;  // chunk partials per load round of the combi
 // column record): each wavefront adds every fourth chunk's bins,
 // kJumpInFlight chunks per load round (integer sums, so any order gives the
 // same bins), wavefront 0 adds the four partial sums and finishes.
-__global__ __launch_bounds__(256) void k_jump_bins_combine(DevProblem P, const double* __restrict__ x,
-                                                           const WalkState* __restrict__ st, int32_t exact_data,
-                                                           int32_t obj_small, const JumpCol* __restrict__ cols,
-                                                           const long long* __restrict__ bpart,
-                                                           double* __restrict__ jv, double* __restrict__ js) {
-  const JumpCol J = cols[blockIdx.x];  // the records of chunked columns with a bins form
-  if (J.bn <= 0 || !jump_exact(st, exact_data, obj_small)) return;  // whole workgroup
+__device__ __forceinline__ void bins_combine(const DevProblem& P, const double* x, const WalkState* st, const JumpCol J,
+                                             const long long* __restrict__ bpart, double* jv, double* js) {
   __shared__ long long red[2][3][kWave];
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
   long long k = 0, sl = 0;
@@ -551,7 +660,7 @@ __device__ void jump_combine(const DevProblem& P, const double* __restrict__ x, 
   bool found = false;
   double bt = xb, bv = 0.0, v0 = 0.0;
   bool have0 = false;
-  // bins form on exact data: finished by its bins task or by k_jump_bins_combine
+  // bins form on exact data: finished by its bins task or by bins_combine
   if (J.bn != 0 && jump_exact(st, exact_data, obj_small)) return;
   for (int tile = 0; tile < J.ntiles; ++tile) {
     const JumpCand cd = jump_candidate(P, rs, st, q, beg, deg, xb, l, u, isint, narrow, tile * kWave + lane);
@@ -599,45 +708,65 @@ __device__ void jump_combine(const DevProblem& P, const double* __restrict__ x, 
   }
 }
 
-// Grid-stride over the column records, one wavefront per record: every
-// record, or on exact data only the first n_plain (the columns without a
-// bins form).
+// The first n_chunk workgroups take the chunked columns with a bins form (on
+// exact data), the others stride over the column records, one wavefront per
+// record: every record, or on exact data only the first n_plain (the columns
+// without a bins form).
 __global__ __launch_bounds__(256) void k_jump_combine(DevProblem P, const double* __restrict__ x,
                                                       const RowState* __restrict__ rs,
                                                       const WalkState* __restrict__ st,
                                                       int32_t exact_data, int32_t obj_small,
                                                       const JumpCol* __restrict__ cols, int32_t ncols,
-                                                      int32_t n_plain, const double* __restrict__ part,
-                                                      double* __restrict__ jv, double* __restrict__ js) {
-  const int nc = jump_exact(st, exact_data, obj_small) ? n_plain : ncols;
-  for (int id = blockIdx.x * 4 + (threadIdx.x >> 6); id < nc; id += gridDim.x * 4)  // whole wavefronts
+                                                      int32_t n_plain, int32_t n_chunk, const double* __restrict__ part,
+                                                      const long long* __restrict__ bpart, double* __restrict__ jv,
+                                                      double* __restrict__ js) {
+  const bool exact = jump_exact(st, exact_data, obj_small);
+  if ((int)blockIdx.x < n_chunk) {
+    if (exact) bins_combine(P, x, st, cols[n_plain + blockIdx.x], bpart, jv, js);
+    return;
+  }
+  const int nc = exact ? n_plain : ncols;
+  const int b = blockIdx.x - n_chunk, nb = gridDim.x - n_chunk;
+  for (int id = b * 4 + (threadIdx.x >> 6); id < nc; id += nb * 4)  // whole wavefronts
     jump_combine(P, x, rs, st, exact_data, obj_small, cols[id], part, jv, js);
 }
 
 }  // namespace
 
-hipError_t launch_jump(const DevProblem& P, const double* x, const RowState* rs, const WalkState* st,
-                       const GatherRow* grow, int32_t obj_small, const JumpTask* tasks, int32_t ntasks,
-                       int32_t n_plain_tasks, const JumpBinTask* btasks, int32_t nbtasks, const JumpCol* cols,
-                       int32_t ncols, int32_t n_plain_cols, int32_t n_chunk_cols, double* part, long long* bpart,
-                       double* jv, double* js, hipStream_t s) {
-  const int32_t exact_data = grow != nullptr ? 1 : 0;
-  constexpr int kStrideGrid = 2048;  // workgroups of the grid-stride kernels
-  if (P.n > 0)
-    hipLaunchKernelGGL(k_jump_lane, dim3((P.n + 255) / 256), dim3(256), 0, s, P, x, rs, grow, st, exact_data,
-                       obj_small, jv, js);
-  if (nbtasks > 0)
-    hipLaunchKernelGGL(k_jump_bins, dim3((unsigned)((nbtasks + 3) / 4)), dim3(256), 0, s, P, x, grow, st, exact_data,
-                       obj_small, btasks, nbtasks, bpart, jv, js);
-  if (ntasks > 0)
-    hipLaunchKernelGGL(k_jump_tasks, dim3((unsigned)std::min((ntasks + 3) / 4, kStrideGrid)), dim3(256), 0, s, P, x,
-                       rs, st, exact_data, obj_small, tasks, ntasks, n_plain_tasks, part);
-  if (ncols > 0)
-    hipLaunchKernelGGL(k_jump_combine, dim3((unsigned)std::min((ncols + 3) / 4, kStrideGrid)), dim3(256), 0, s, P, x,
-                       rs, st, exact_data, obj_small, cols, ncols, n_plain_cols, part, jv, js);
-  if (n_chunk_cols > 0)
-    hipLaunchKernelGGL(k_jump_bins_combine, dim3((unsigned)n_chunk_cols), dim3(256), 0, s, P, x, st, exact_data,
-                       obj_small, cols + n_plain_cols, bpart, jv, js);
+hipError_t launch_jump(const DevProblem& P, const JumpPlan& L, const double* x, const RowState* rs, const WalkState* st,
+                       const GatherRow* grow, int32_t obj_small, double* jv, double* js, hipStream_t s) {
+  constexpr int kStrideGrid = 2048;  // most workgroups that stride over tasks or column records
+  JumpCall J{};
+  J.P = P;
+  J.x = x;
+  J.rs = rs;
+  J.grow = grow;
+  J.st = st;
+  J.exact_data = grow != nullptr ? 1 : 0;
+  J.obj_small = obj_small;
+  J.singles = L.singles;
+  J.groups = L.groups;
+  J.btasks = L.btasks;
+  J.tasks = L.tasks;
+  J.n_singles = L.n_singles;
+  J.n_groups = L.n_groups;
+  J.nbtasks = L.n_btasks;
+  J.ntasks = L.n_tasks;
+  J.n_plain = L.n_plain_tasks;
+  J.small_coef = L.small_coef;
+  J.part = L.part;
+  J.bpart = L.bpart;
+  J.jv = jv;
+  J.js = js;
+  J.blk[0] = grow ? (L.n_btasks + 3) / 4 : 0;
+  J.blk[1] = J.blk[0] + std::min((L.n_tasks + 3) / 4, kStrideGrid);
+  J.blk[2] = J.blk[1] + (L.n_groups + 256 / kJumpLane - 1) / (256 / kJumpLane);
+  const int end = J.blk[2] + (L.n_singles + 255) / 256;
+  if (end > 0) hipLaunchKernelGGL(k_jump, dim3((unsigned)end), dim3(256), 0, s, J);
+  if (L.n_cols > 0)
+    hipLaunchKernelGGL(k_jump_combine, dim3((unsigned)(L.n_chunk_cols + std::min((L.n_cols + 3) / 4, kStrideGrid))),
+                       dim3(256), 0, s, P, x, rs, st, J.exact_data, obj_small, L.cols, L.n_cols, L.n_plain_cols,
+                       L.n_chunk_cols, L.part, L.bpart, jv, js);
   return hipGetLastError();
 }
 
