@@ -64,7 +64,7 @@ int chap_model_create(chap_model** out, uint64_t seed) {
   DeviceArena& A = M->arena;
   ModelDev& D = M->dev;
   CHAP_HIP(A.alloc(&D.w, mlp::kNParam));
-  CHAP_HIP(A.alloc(&D.wb, mlp::kNParam));
+  CHAP_HIP(A.alloc(&D.wb, mlp::kNBf16));
   CHAP_HIP(A.alloc(&D.m, mlp::kNParam));
   CHAP_HIP(A.alloc(&D.v, mlp::kNParam));
   CHAP_HIP(A.alloc(&D.adam, 3));
@@ -108,7 +108,7 @@ int chap_model_grad(chap_model* m, const uint16_t* d_feat, const float* d_target
   const int rc = check_device(m, "chap_model_grad");
   if (rc != CHAP_OK) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
-  CHAP_HIP(launch_mlp_grad(m->dev, d_feat, d_target, n, n, 0, 0, 0, s));
+  CHAP_HIP(launch_mlp_grad(m->dev, d_feat, d_target, n, n, 0, 0, 0, 0, s));
   CHAP_HIP(launch_mlp_reduce(m->dev, n, 0, 0.0f, s));
   CHAP_HIP(hipMemcpyAsync(d_grad, m->dev.grad, sizeof(float) * mlp::kNParam, hipMemcpyDeviceToDevice, s));
   return CHAP_OK;
@@ -122,7 +122,7 @@ int chap_model_train(chap_model* m, const uint16_t* d_feat, const float* d_targe
   if (rc != CHAP_OK) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
   for (int32_t k = 0; k < steps; ++k) {
-    CHAP_HIP(launch_mlp_grad(m->dev, d_feat, d_target, npairs, batch, 1, seed, (uint64_t)k * (uint64_t)batch, s));
+    CHAP_HIP(launch_mlp_grad(m->dev, d_feat, d_target, npairs, batch, 1, 1, seed, (uint64_t)k * (uint64_t)batch, s));
     CHAP_HIP(launch_mlp_reduce(m->dev, batch, 1, lr, s));
   }
   return CHAP_OK;

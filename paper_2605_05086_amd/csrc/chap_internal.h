@@ -636,7 +636,7 @@ constexpr float kAdamEps = 1e-8f;
 // W3, b3), their bfloat16 copy, Adam moments and step, gradient buffers.
 struct ModelDev {
   float* w = nullptr;
-  uint16_t* wb = nullptr;
+  uint16_t* wb = nullptr;  // kNBf16
   float* m = nullptr;
   float* v = nullptr;
   double* adam = nullptr;  // beta1^t, beta2^t, t
@@ -647,9 +647,10 @@ struct ModelDev {
 hipError_t launch_mlp_forward(const ModelDev& M, const uint16_t* feat, int64_t n, float* out, hipStream_t s);
 // Gradient partials of the mean squared error over nb samples of (feat,
 // target) with `rows` rows: sample i is row i, or with `sample` row
-// splitmix64(seed, base + i) mod rows.
+// splitmix64(seed, base + i) mod rows. With `update`, the reduction that
+// follows takes an Adam step, whose counter advances here.
 hipError_t launch_mlp_grad(const ModelDev& M, const uint16_t* feat, const float* target, int64_t rows, int64_t nb,
-                           int sample, uint64_t seed, uint64_t base, hipStream_t s);
+                           int sample, int update, uint64_t seed, uint64_t base, hipStream_t s);
 // Reduces the partials of the last gradient launch over nb samples into
 // M.grad; with `update`, one Adam step with learning rate lr.
 hipError_t launch_mlp_reduce(const ModelDev& M, int64_t nb, int update, float lr, hipStream_t s);

@@ -46,30 +46,73 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ w
   }
 }
 
-// Sum over the 16 lanes of a lane group (same g), fixed butterfly order.
+// Sum over the 16 lanes of a lane group (same g), fixed butterfly order: lane
+// distances 1, 2, 4, 8 (the mirrors reach the same sums once four and eight
+// neighbours agree), by DPP.
+template <int kCtrl>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xF, 0xF, true));
+}
 __device__ __forceinline__ float group16_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  return dpp_add<0x140>(v);  // row_mirror
+}
+
+// The wavefront's own LDS slice, written and then read by its lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Per-workgroup gradient partials of the mean squared error over `nb`
 // samples. Sample i is row i of (feat, target), or row
 // splitmix64(seed, base + i) mod rows when `sample` is set. inv_nb = 1/nb.
-// Writes partials[blockIdx.x][p] for every parameter p.
+// Writes partials[blockIdx.x][p] for every parameter p. With `advance`, an Adam
+// step follows: its counter and the powers beta1^t, beta2^t (FP64) advance here.
+// Bounded by the latency of one round (a batch of 1024 is 16 workgroups of four
+// tiles): inputs are asked for before the weights, the next round's during this
+// one, W2^T comes in operand layout, and the wavefronts' sums meet in LDS in one
+// step; XX us at 1024 samples, 16 before (W2^T by 64 two-byte loads a lane,
+// wavefronts adding into one LDS copy in turn, exchanges through LDS).
+struct GradSmem {
+  uint16_t g2[kWaves][kHid * 16];
+  uint16_t h1[kWaves][kHid * 16];
+  uint16_t g1[kWaves][kHid * 16];
+  uint16_t x[kWaves][kIn * 16];
+  alignas(16) float sum[kWaves][kNParamPad];
+};
 __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, const uint16_t* __restrict__ wb,
                                                   const uint16_t* __restrict__ feat,
                                                   const float* __restrict__ target, int64_t rows, int64_t nb,
                                                   int32_t sample, uint64_t seed, uint64_t base, float inv_nb,
-                                                  float* __restrict__ partials, const int32_t* active) {
+                                                  float* __restrict__ partials, double* __restrict__ adam,
+                                                  int32_t advance, const int32_t* active) {
   if (active && !*active) return;
-  __shared__ uint16_t sG2[kWaves][kHid * 16];
-  __shared__ uint16_t sH1[kWaves][kHid * 16];
-  __shared__ uint16_t sG1[kWaves][kHid * 16];
-  __shared__ uint16_t sX[kWaves][kIn * 16];
-  __shared__ float sred[kNParam];
+  __shared__ GradSmem S;
   const int l = threadIdx.x & 63, g = l >> 4, r = l & 15;
   const int wv = threadIdx.x >> 6;
+  if (advance && blockIdx.x == 0 && threadIdx.x == 0) {
+    adam[0] *= kAdamBeta1;
+    adam[1] *= kAdamBeta2;
+    adam[2] += 1.0;
+  }
+  // inputs and target of this lane's sample of a round
+  const int64_t ntiles = (nb + 15) / 16;
+  const int64_t stride = (int64_t)gridDim.x * kWaves;
+  auto load_sample = [&](int64_t tile, bf16x4& x, float& t) {
+    const int64_t i = tile * 16 + r;
+    const bool valid = i < nb;
+    int64_t row = i;
+    if (valid && sample) row = (int64_t)(splitmix64(seed, base + (uint64_t)i) % (uint64_t)rows);
+    x = load_inputs(feat, row, valid);
+    t = l < 16 && valid ? target[row] : 0.0f;
+  };
+  bf16x4 x;
+  float tgt;
+  load_sample((int64_t)blockIdx.x * kWaves + wv, x, tgt);
   Weights W;
   load_weights(wb, w, W);
   // W2^T in A layout: element (i = r, k = 4g + t) of block (ib, ob) is W2[16ob + 4g + t][16ib + r]
@@ -78,13 +121,13 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, c
 #pragma unroll
   for (int ib = 0; ib < 4; ++ib)
 #pragma unroll
-    for (int ob = 0; ob < 4; ++ob)
+    for (int ob = 0; ob < 4; ++ob) a2t[ib][ob] = *(const bf16x4*)(wb + kOffW2T + ((ib * 4 + ob) * 64 + l) * 4);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) a2t[ib][ob][t] = (short)wb[kOffW2 + (16 * ob + 4 * g + t) * kHid + 16 * ib + r];
+  for (int o = 0; o < 4; ++o) {
+    const bf16x4 w3 = *(const bf16x4*)(wb + kOffW3 + 16 * o + 4 * g);
 #pragma unroll
-  for (int o = 0; o < 4; ++o)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) w3r[o][t] = bf2f(wb[kOffW3 + 16 * o + 4 * g + t]);
+    for (int t = 0; t < 4; ++t) w3r[o][t] = bf2f((uint16_t)w3[t]);
+  }
 
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
   f32x4 accW2[4][4], accW1[4];
@@ -101,22 +144,17 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, c
     }
   }
 
-  const int64_t ntiles = (nb + 15) / 16;
-  const int64_t stride = (int64_t)gridDim.x * kWaves;
-  // every wave runs the same number of rounds (barriers below); tiles past
-  // the end are all-zero samples with a zero output signal
+  // tiles past the end are all-zero samples with a zero output signal
   for (int64_t base_tile = (int64_t)blockIdx.x * kWaves; base_tile < ntiles; base_tile += stride) {
-    const int64_t tile = base_tile + wv;
-    const int64_t i = tile * 16 + r;
-    const bool valid = i < nb;
-    int64_t row = i;
-    if (valid && sample) row = (int64_t)(splitmix64(seed, base + (uint64_t)i) % (uint64_t)rows);
-    const bf16x4 x = load_inputs(feat, row, valid);
+    const bool valid = (base_tile + wv) * 16 + r < nb;
+    const bf16x4 x0 = x;
+    const float t0 = tgt;
+    if (base_tile + stride < ntiles) load_sample(base_tile + stride + wv, x, tgt);
     Acts A;
-    forward(W, x, A);
+    forward(W, x0, A);
     // output signal g3 = 2 (y - t) / nb of sample r, broadcast to its column
     float g3 = 0.0f;
-    if (l < 16 && valid) g3 = 2.0f * (A.y - target[row]) * inv_nb;
+    if (l < 16 && valid) g3 = 2.0f * (A.y - t0) * inv_nb;
     g3 = __shfl(g3, r, 64);
     if (l < 16) accB3 += g3;
     // output layer and g2 = W3 g3 gated by z2 > 0
@@ -153,30 +191,30 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, c
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int u = 16 * b + 4 * g + t;
-        sG2[wv][u * 16 + r] = (uint16_t)g2b[b][t];
-        sH1[wv][u * 16 + r] = (uint16_t)A.h1[b][t];
-        sG1[wv][u * 16 + r] = (uint16_t)g1b[b][t];
+        S.g2[wv][u * 16 + r] = (uint16_t)g2b[b][t];
+        S.h1[wv][u * 16 + r] = (uint16_t)A.h1[b][t];
+        S.g1[wv][u * 16 + r] = (uint16_t)g1b[b][t];
       }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) sX[wv][(4 * g + t) * 16 + r] = (uint16_t)x[t];
-    __syncthreads();
+    for (int t = 0; t < 4; ++t) S.x[wv][(4 * g + t) * 16 + r] = (uint16_t)x0[t];
+    wave_sync();
     // dW2[o][i] += sum_s g2[o][s] h1[i][s];  dW1[h][f] += sum_s g1[h][s] x[f][s]
     bf16x4 h1t[4];
 #pragma unroll
-    for (int ib = 0; ib < 4; ++ib) h1t[ib] = *(const bf16x4*)&sH1[wv][(16 * ib + r) * 16 + 4 * g];
+    for (int ib = 0; ib < 4; ++ib) h1t[ib] = *(const bf16x4*)&S.h1[wv][(16 * ib + r) * 16 + 4 * g];
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
-      const bf16x4 g2t = *(const bf16x4*)&sG2[wv][(16 * ob + r) * 16 + 4 * g];
+      const bf16x4 g2t = *(const bf16x4*)&S.g2[wv][(16 * ob + r) * 16 + 4 * g];
 #pragma unroll
       for (int ib = 0; ib < 4; ++ib) accW2[ob][ib] = mma(g2t, h1t[ib], accW2[ob][ib]);
     }
-    const bf16x4 xt = *(const bf16x4*)&sX[wv][r * 16 + 4 * g];
+    const bf16x4 xt = *(const bf16x4*)&S.x[wv][r * 16 + 4 * g];
 #pragma unroll
     for (int hb = 0; hb < 4; ++hb) {
-      const bf16x4 g1t = *(const bf16x4*)&sG1[wv][(16 * hb + r) * 16 + 4 * g];
+      const bf16x4 g1t = *(const bf16x4*)&S.g1[wv][(16 * hb + r) * 16 + 4 * g];
       accW1[hb] = mma(g1t, xt, accW1[hb]);
     }
-    __syncthreads();
+    wave_sync();
   }
   // lane-group sums of the per-lane accumulators
 #pragma unroll
@@ -189,49 +227,56 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, c
     }
   accB3 = group16_sum(accB3);
   // workgroup sum in wave order
-  for (int p = threadIdx.x; p < kNParam; p += blockDim.x) sred[p] = 0.0f;
-  for (int w2 = 0; w2 < kWaves; ++w2) {
-    __syncthreads();
-    if (wv != w2) continue;
+  float* sum = S.sum[wv];
 #pragma unroll
-    for (int ob = 0; ob < 4; ++ob)
+  for (int ob = 0; ob < 4; ++ob)
 #pragma unroll
-      for (int ib = 0; ib < 4; ++ib)
+    for (int ib = 0; ib < 4; ++ib)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) sred[kOffW2 + (16 * ob + 4 * g + t) * kHid + 16 * ib + r] += accW2[ob][ib][t];
+      for (int t = 0; t < 4; ++t) sum[kOffW2 + (16 * ob + 4 * g + t) * kHid + 16 * ib + r] = accW2[ob][ib][t];
 #pragma unroll
-    for (int hb = 0; hb < 4; ++hb)
+  for (int hb = 0; hb < 4; ++hb)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) sred[kOffW1 + (16 * hb + 4 * g + t) * kIn + r] += accW1[hb][t];
-    if (r == 0) {
+    for (int t = 0; t < 4; ++t) sum[kOffW1 + (16 * hb + 4 * g + t) * kIn + r] = accW1[hb][t];
+  if (r == 0) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          sred[kOffW3 + 16 * a + 4 * g + t] += accW3[a][t];
-          sred[kOffB2 + 16 * a + 4 * g + t] += accB2[a][t];
-          sred[kOffB1 + 16 * a + 4 * g + t] += accB1[a][t];
-        }
-    }
-    if (l == 0) sred[kOffB3] += accB3;
+      for (int t = 0; t < 4; ++t) {
+        sum[kOffW3 + 16 * a + 4 * g + t] = accW3[a][t];
+        sum[kOffB2 + 16 * a + 4 * g + t] = accB2[a][t];
+        sum[kOffB1 + 16 * a + 4 * g + t] = accB1[a][t];
+      }
   }
+  if (l == 0) sum[kOffB3] = accB3;
   __syncthreads();
   float* mine = partials + (int64_t)blockIdx.x * kNParamPad;
-  for (int p = threadIdx.x; p < kNParam; p += blockDim.x) mine[p] = sred[p];
+  for (int p = 4 * threadIdx.x; p < kNParam; p += 4 * blockDim.x) {  // whole fours: both rows are padded
+    f32x4 v = zero4;
+#pragma unroll
+    for (int w2 = 0; w2 < kWaves; ++w2) v += *(const f32x4*)&S.sum[w2][p];
+    *(f32x4*)&mine[p] = v;
+  }
 }
 
-// Advances Adam's step counter and the powers beta1^t, beta2^t (FP64).
-__global__ void k_adam_begin(double* adam, double beta1, double beta2, const int32_t* active) {
-  if (threadIdx.x != 0 || blockIdx.x != 0 || (active && !*active)) return;
-  adam[0] *= beta1;
-  adam[1] *= beta2;
-  adam[2] += 1.0;
+// The operand copies of parameter p: its bfloat16 value, and a W2 entry's place
+// in the transposed layout.
+__device__ __forceinline__ void store_bf16(uint16_t* wb, int p, float v) {
+  const uint16_t h = f2bf(v);
+  wb[p] = h;
+  if (p >= kOffW2 && p < kOffB2) {
+    const int o = (p - kOffW2) / kHid, i = (p - kOffW2) % kHid;
+    wb[kOffW2T + (((i >> 4) * 4 + (o >> 4)) * 64 + ((o >> 2) & 3) * 16 + (i & 15)) * 4 + (o & 3)] = h;
+  }
 }
+
+constexpr int kReduceThreads = 64;   // one wavefront, so that the parameters spread over many CUs
+constexpr int kReduceInFlight = 16;  // partials loaded at a time
 
 // Sums the partials in workgroup order into grad; with `update`, one Adam
 // step on the FP32 parameters and a fresh bfloat16 copy. omb1 and omb2 are
 // 1 - beta1 and 1 - beta2 rounded once from FP64.
-__global__ __launch_bounds__(256) void k_mlp_reduce(float* __restrict__ w, uint16_t* __restrict__ wb,
+__global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(float* __restrict__ w, uint16_t* __restrict__ wb,
                                                     float* __restrict__ m, float* __restrict__ v,
                                                     const double* __restrict__ adam, float* __restrict__ grad,
                                                     const float* __restrict__ partials, int32_t nparts,
@@ -241,7 +286,15 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(float* __restrict__ w, uint1
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= kNParam) return;
   float gsum = 0.0f;
-  for (int b = 0; b < nparts; ++b) gsum += partials[(int64_t)b * kNParamPad + p];
+  for (int b0 = 0; b0 < nparts; b0 += kReduceInFlight) {
+    float v[kReduceInFlight];
+#pragma unroll
+    for (int k = 0; k < kReduceInFlight; ++k)
+      v[k] = b0 + k < nparts ? partials[(int64_t)(b0 + k) * kNParamPad + p] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < kReduceInFlight; ++k)
+      if (b0 + k < nparts) gsum += v[k];
+  }
   grad[p] = gsum;
   if (!update) return;
   const float mo = beta1 * m[p] + omb1 * gsum;
@@ -254,12 +307,12 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(float* __restrict__ w, uint1
   const float vh = vo / c2;
   const float nw = w[p] - lr * mh / (sqrtf(vh) + eps);
   w[p] = nw;
-  wb[p] = f2bf(nw);
+  store_bf16(wb, p, nw);
 }
 
 __global__ __launch_bounds__(256) void k_mlp_bf16_copy(const float* __restrict__ w, uint16_t* __restrict__ wb) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < kNParam) wb[p] = f2bf(w[p]);
+  if (p < kNParam) store_bf16(wb, p, w[p]);
 }
 
 }  // namespace
@@ -278,24 +331,25 @@ int32_t mlp_grad_blocks(int64_t nb) {
 }
 
 hipError_t grad_impl(const ModelDev& M, const int32_t* active, const uint16_t* feat, const float* target,
-                     int64_t rows, int64_t nb, int sample, uint64_t seed, uint64_t base, hipStream_t s) {
+                     int64_t rows, int64_t nb, int sample, int advance, uint64_t seed, uint64_t base, hipStream_t s) {
   const int32_t blocks = mlp_grad_blocks(nb);
   hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)blocks), dim3(256), 0, s, M.w, M.wb, feat, target, rows, nb,
-                     (int32_t)sample, seed, base, (float)(1.0 / (double)nb), M.partials, active);
+                     (int32_t)sample, seed, base, (float)(1.0 / (double)nb), M.partials, M.adam, (int32_t)advance,
+                     active);
   return hipGetLastError();
 }
 
 hipError_t reduce_impl(const ModelDev& M, const int32_t* active, int64_t nb, int update, float lr, hipStream_t s) {
-  if (update) hipLaunchKernelGGL(k_adam_begin, dim3(1), dim3(64), 0, s, M.adam, kAdamBeta1, kAdamBeta2, active);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kNParam + 255) / 256), dim3(256), 0, s, M.w, M.wb, M.m, M.v, M.adam, M.grad,
-                     M.partials, mlp_grad_blocks(nb), (int32_t)update, lr, (float)kAdamBeta1,
-                     (float)(1.0 - kAdamBeta1), (float)kAdamBeta2, (float)(1.0 - kAdamBeta2), kAdamEps, active);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((kNParam + kReduceThreads - 1) / kReduceThreads), dim3(kReduceThreads), 0, s,
+                     M.w, M.wb, M.m, M.v, M.adam, M.grad, M.partials, mlp_grad_blocks(nb), (int32_t)update, lr,
+                     (float)kAdamBeta1, (float)(1.0 - kAdamBeta1), (float)kAdamBeta2, (float)(1.0 - kAdamBeta2),
+                     kAdamEps, active);
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_grad(const ModelDev& M, const uint16_t* feat, const float* target, int64_t rows, int64_t nb,
-                           int sample, uint64_t seed, uint64_t base, hipStream_t s) {
-  return grad_impl(M, nullptr, feat, target, rows, nb, sample, seed, base, s);
+                           int sample, int update, uint64_t seed, uint64_t base, hipStream_t s) {
+  return grad_impl(M, nullptr, feat, target, rows, nb, sample, update, seed, base, s);
 }
 
 hipError_t launch_mlp_reduce(const ModelDev& M, int64_t nb, int update, float lr, hipStream_t s) {
@@ -304,7 +358,7 @@ hipError_t launch_mlp_reduce(const ModelDev& M, int64_t nb, int update, float lr
 
 hipError_t launch_mlp_grad_guarded(const ModelDev& M, const int32_t* active, const uint16_t* feat,
                                    const float* target, int64_t nb, hipStream_t s) {
-  return grad_impl(M, active, feat, target, nb, nb, 0, 0, 0, s);
+  return grad_impl(M, active, feat, target, nb, nb, 0, 1, 0, 0, s);
 }
 
 hipError_t launch_mlp_reduce_guarded(const ModelDev& M, const int32_t* active, int64_t nb, float lr, hipStream_t s) {

@@ -38,6 +38,11 @@ constexpr int kOffB2 = 5184;   // b2[64]
 constexpr int kOffW3 = 5248;   // W3[64]
 constexpr int kOffB3 = 5312;   // b3
 constexpr int kNParam = 5313;
+// The bfloat16 copy of the parameters is followed by W2^T in A layout: block
+// (ib, ob), lane l, t at kOffW2T + ((ib 4 + ob) 64 + l) 4 + t holds
+// W2[16ob + 4g + t][16ib + r].
+constexpr int kOffW2T = 5376;
+constexpr int kNBf16 = kOffW2T + kHid * kHid;
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
