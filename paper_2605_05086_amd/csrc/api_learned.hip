@@ -78,12 +78,16 @@ int build_learn_ctx(const chap_problem* p, const chap_learned_options& o, int64_
   CHAP_HIP(A.alloc(&L.feat, (size_t)n * 16));
   CHAP_HIP(A.alloc(&L.moves, (size_t)n));
   CHAP_HIP(A.alloc(&L.xhat_last, (size_t)n));
-  CHAP_HIP(A.alloc(&L.keys[0], (size_t)n));
-  CHAP_HIP(A.alloc(&L.keys[1], (size_t)n));
-  CHAP_HIP(A.alloc(&L.hist, (size_t)2 * 3 * kRadixBins));
-  CHAP_HIP(hipMemset(L.hist, 0, sizeof(uint32_t) * 2 * 3 * kRadixBins));
-  L.nwg = std::max<int32_t>(1, (n + kTopkChunk - 1) / kTopkChunk);
-  CHAP_HIP(A.alloc(&L.wg_cnt, (size_t)2 * L.nwg * 2));
+  // the top-K kernels read keys four at a time
+  CHAP_HIP(A.alloc(&L.keys[0], ((size_t)n + 3) / 4 * 4));
+  CHAP_HIP(A.alloc(&L.keys[1], ((size_t)n + 3) / 4 * 4));
+  CHAP_HIP(A.alloc(&L.hist, (size_t)2 * kHistStride + 1));
+  CHAP_HIP(hipMemset(L.hist, 0, sizeof(uint32_t) * (2 * kHistStride + 1)));
+  const int32_t tiles = std::max<int32_t>(1, (n + kTopkChunk - 1) / kTopkChunk);
+  L.topk_tiles = (tiles + kTopkChunks - 1) / kTopkChunks;
+  L.nwg = (tiles + L.topk_tiles - 1) / L.topk_tiles;
+  CHAP_HIP(A.alloc(&L.wg_cnt, (size_t)L.nwg));
+  CHAP_HIP(A.alloc(&L.stage, (size_t)L.nwg * kTopkChunk * L.topk_tiles));
   L.K[0] = o.topk;
   L.K[1] = o.train_pairs;
   CHAP_HIP(A.alloc(&L.sel[0], (size_t)L.K[0]));

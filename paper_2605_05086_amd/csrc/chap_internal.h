@@ -663,7 +663,9 @@ hipError_t launch_mlp_reduce_guarded(const ModelDev& M, const int32_t* active, i
 
 // ---- learned candidate proposal (kernels_learned.hip) ---------------------
 constexpr int kRadixBins = 2048;    // radix-select digit bins (11, 11, 10 bits)
-constexpr int kTopkChunk = 4096;    // columns per workgroup of the top-K compaction
+constexpr int kHistStride = 10 * kRadixBins;  // histograms of one selection
+constexpr int kTopkChunk = 4096;    // columns per workgroup and step of the top-K kernels
+constexpr int kTopkChunks = 1024;   // most workgroups of the top-K compaction
 constexpr int kTopkMax = 8192;      // largest proposal set
 constexpr int kSubsetCap = 4096;    // breakpoint capacity of the subset sort workgroup
 constexpr int kSubsetChunk = 2048;  // stored entries per workgroup chunk of the subset pass
@@ -733,11 +735,13 @@ struct LearnCtx {
   int32_t* moves;            // moves per column
   double* xhat_last;         // best shift at the last full evaluation
   uint32_t* keys[2];         // 0: network scores, 1: labels
-  uint32_t* hist;            // 2 x 3 x kRadixBins
-  int32_t* wg_cnt;           // 2 x nwg x 2 (greater, equal)
+  uint32_t* hist;            // 2 x kHistStride, the compaction's ticket
+  uint2* wg_cnt;             // nwg x (greater, equal)
+  uint2* stage;              // nwg x kTopkChunk x topk_tiles compacted keys
   int32_t* sel[2];           // selected columns, ascending internal index
   int32_t K[2];
-  int32_t nwg;               // workgroups of the compaction
+  int32_t nwg;               // workgroups of the compaction, at most kTopkChunks
+  int32_t topk_tiles;        // steps of kTopkChunk columns of each
   int32_t sub_cap;           // capacity of sub_parts
   int32_t* sub_off;          // K[0] + 1 chunk offsets of the selected columns
   ChunkPartial* sub_parts;   // per-chunk partial bins of the subset pass

@@ -32,7 +32,7 @@
 // internal index (equal keys: lowest index first). Each kernel of the select
 // re-derives the digits chosen so far from the histograms of the earlier
 // kernels (a few kilobytes from L2), so no single-workgroup kernel sits
-// between them.
+// between them; the compaction's last workgroup puts the list together.
 
 #include <climits>
 #include <cmath>
@@ -40,6 +40,7 @@
 #include "chap_internal.h"
 #include "learned_rows.h"
 #include "mlp_core.h"
+#include "move_best.h"
 
 namespace chap {
 namespace {
@@ -251,6 +252,18 @@ __global__ void k_learn_begin(const WalkCtx* __restrict__ walks, const LearnCtx*
 // Radix top-K
 // ---------------------------------------------------------------------------
 
+// Sums over the lanes up to and with this one, by DPP.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t u) {
+  int v = (int)u;
+  v += dpp<kRowShr1, 0xF>(v, 0);
+  v += dpp<kRowShr2, 0xF>(v, 0);
+  v += dpp<kRowShr4, 0xF>(v, 0);
+  v += dpp<kRowShr8, 0xF>(v, 0);
+  v += dpp<kBcast15, 0xA>(v, 0);
+  v += dpp<kBcast31, 0xC>(v, 0);
+  return (uint32_t)v;
+}
+
 struct Select {
   bool all;          // at most K nonzero keys: take every nonzero key
   uint32_t prefix;   // digits chosen so far (levels below `upto`)
@@ -260,26 +273,45 @@ struct Select {
   int count;         // keys selected (upto == 3 or all)
 };
 
-// Whole workgroup (256 threads): the bin of histogram h (bins from the top)
+// The histograms of a selection: the first digit's in kHistCopies copies (the
+// scores share few first digits, so the scoring workgroups would queue at one
+// copy: 12 ns each), then the other digits'.
+constexpr int kHistCopies = 8;
+static_assert((kHistCopies + 2) * kRadixBins == kHistStride, "as allocated");
+__device__ __forceinline__ int hist_of(int which, int level) {
+  return which * kHistStride + (level == 0 ? 0 : kHistCopies + level - 1) * kRadixBins;
+}
+
+// A thread's bins of one histogram: kBinsPer neighbours, thread 0 the highest.
+constexpr int kBinsPer = kRadixBins / kBlock;
+struct Bins {
+  uint32_t c[kBinsPer];
+};
+template <int kCopies>
+__device__ __forceinline__ Bins load_bins(const uint32_t* __restrict__ h) {
+  static_assert(kBinsPer == 8, "two 16-byte loads");
+  const uint4* p = (const uint4*)(h + kRadixBins - kBinsPer * ((int)threadIdx.x + 1));
+  Bins B{};
+#pragma unroll
+  for (int c = 0; c < kCopies; ++c, p += kRadixBins / 4) {
+    const uint4 lo = p[0], hi = p[1];
+    const uint32_t v[kBinsPer] = {hi.w, hi.z, hi.y, hi.x, lo.w, lo.z, lo.y, lo.x};
+#pragma unroll
+    for (int t = 0; t < kBinsPer; ++t) B.c[t] += v[t];
+  }
+  return B;
+}
+
+// Whole workgroup (256 threads): the bin of a histogram (bins from the top)
 // that holds the rem-th largest key; *left = rank of that key inside the bin.
-__device__ void find_digit(const uint32_t* __restrict__ h, int rem, int* digit, int* left, uint32_t* total) {
+__device__ void find_digit(const Bins& B, int rem, int* digit, int* left, uint32_t* total) {
   __shared__ uint32_t part[kBlock / kWave];
   __shared__ int res[2];
-  constexpr int per = kRadixBins / kBlock;  // 8 bins per thread, thread 0 the highest
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  uint32_t c[per];
   uint32_t sum = 0;
 #pragma unroll
-  for (int t = 0; t < per; ++t) {
-    c[t] = h[kRadixBins - 1 - (tid * per + t)];
-    sum += c[t];
-  }
-  uint32_t inc = sum;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t y = __shfl_up(inc, o, kWave);
-    if (lane >= o) inc += y;
-  }
+  for (int t = 0; t < kBinsPer; ++t) sum += B.c[t];
+  const uint32_t inc = wave_scan(sum);
   __syncthreads();
   if (lane == kWave - 1) part[wv] = inc;
   if (tid == 0) {
@@ -296,30 +328,41 @@ __device__ void find_digit(const uint32_t* __restrict__ h, int rem, int* digit, 
   if (lo < (uint32_t)rem && hi >= (uint32_t)rem) {
     uint32_t cum = lo;
 #pragma unroll
-    for (int t = 0; t < per; ++t) {
-      if (cum < (uint32_t)rem && cum + c[t] >= (uint32_t)rem) {
-        res[0] = kRadixBins - 1 - (tid * per + t);
+    for (int t = 0; t < kBinsPer; ++t) {
+      if (cum < (uint32_t)rem && cum + B.c[t] >= (uint32_t)rem) {
+        res[0] = kRadixBins - 1 - (tid * kBinsPer + t);
         res[1] = rem - (int)cum;
       }
-      cum += c[t];
+      cum += B.c[t];
     }
   }
   __syncthreads();
   *digit = res[0];
   *left = res[1];
   *total = all;
-  __syncthreads();
 }
 
-// Digits of levels < upto (upto = 3: the final threshold) from the
-// histograms of the earlier kernels. Whole workgroup.
-__device__ Select derive(const LearnCtx& L, int which, int upto) {
-  const uint32_t* H = L.hist + which * 3 * kRadixBins;
-  const int K = L.K[which];
+// Digits of levels < kUpto (3: the final threshold) from the histograms of the
+// earlier kernels, which load_levels() has read: the loads do not depend on
+// the digits, so one wait covers them all. Whole workgroup.
+template <int kUpto>
+struct Levels {
+  Bins b[kUpto];
+};
+template <int kUpto>
+__device__ __forceinline__ Levels<kUpto> load_levels(const LearnCtx& L, int which) {
+  Levels<kUpto> V;
+  V.b[0] = load_bins<kHistCopies>(L.hist + hist_of(which, 0));
+#pragma unroll
+  for (int t = 1; t < kUpto; ++t) V.b[t] = load_bins<1>(L.hist + hist_of(which, t));
+  return V;
+}
+template <int kUpto>
+__device__ Select derive(const Levels<kUpto>& V, int K) {
   Select S{false, 0u, K, 0u, 0, 0};
   int d, left;
   uint32_t total;
-  find_digit(H, K, &d, &left, &total);
+  find_digit(V.b[0], K, &d, &left, &total);
   if (total <= (uint32_t)K) {
     S.all = true;
     S.count = (int)total;
@@ -327,13 +370,13 @@ __device__ Select derive(const LearnCtx& L, int which, int upto) {
   }
   S.prefix = (uint32_t)d;
   S.rem = left;
-  if (upto >= 2) {
-    find_digit(H + kRadixBins, S.rem, &d, &left, &total);
+  if constexpr (kUpto >= 2) {
+    find_digit(V.b[1], S.rem, &d, &left, &total);
     S.prefix = (S.prefix << 11) | (uint32_t)d;
     S.rem = left;
   }
-  if (upto >= 3) {
-    find_digit(H + 2 * kRadixBins, S.rem, &d, &left, &total);
+  if constexpr (kUpto >= 3) {
+    find_digit(V.b[2], S.rem, &d, &left, &total);
     S.thresh = (S.prefix << 10) | (uint32_t)d;
     S.need_eq = left;
     S.count = K;
@@ -399,7 +442,7 @@ __global__ __launch_bounds__(256) void k_learn_score(const WalkCtx* __restrict__
       }
     }
   }
-  flush_hist(hist, L.hist);
+  flush_hist(hist, L.hist + hist_of(0, 0) + (blockIdx.x & (kHistCopies - 1)) * kRadixBins);
 }
 
 // Label keys (exact scores of the full pass) plus their first-digit histogram.
@@ -416,7 +459,7 @@ __global__ __launch_bounds__(256) void k_label_keys(const WalkCtx* __restrict__ 
     L.keys[1][q] = key;
     if (key) atomicAdd(&hist[key >> 21], 1u);
   }
-  flush_hist(hist, L.hist + 3 * kRadixBins);
+  flush_hist(hist, L.hist + hist_of(1, 0) + (blockIdx.x & (kHistCopies - 1)) * kRadixBins);
 }
 
 __device__ __forceinline__ uint32_t digit_of(uint32_t key, int level) {
@@ -427,23 +470,46 @@ __device__ __forceinline__ uint32_t prefix_of(uint32_t key, int level) {
   return level == 1 ? (key >> 21) : (key >> 10);
 }
 
-// Histogram of digit `level` (1 or 2) over keys that match the digits above.
-__global__ __launch_bounds__(256) void k_topk_hist(const WalkCtx* __restrict__ walks, const LearnCtx* __restrict__ lc,
-                                                   int32_t which, int32_t level, int32_t n) {
+// A thread's keys of a tile of kTopkChunk columns: four, then every fourth
+// workgroup width on (zero past the end; the array is padded to whole fours).
+constexpr int kKeysPer = kTopkChunk / kBlock;
+
+// Histogram of digit kLevel (1 or 2) over keys that match the digits above, a
+// tile of kTopkChunk columns per workgroup and step, its keys asked for before
+// the digits are derived.
+template <int kLevel>
+__global__ __launch_bounds__(kBlock) void k_topk_hist(const WalkCtx* __restrict__ walks,
+                                                      const LearnCtx* __restrict__ lc, int32_t which, int32_t n) {
   const WalkCtx& C = walks[0];
   const LearnCtx& L = *lc;
   if (!active(C.st, L.ls)) return;
-  const Select S = derive(L, which, level);
-  if (S.all) return;
-  __shared__ uint32_t hist[kRadixBins];
-  for (int b = threadIdx.x; b < kRadixBins; b += blockDim.x) hist[b] = 0;
-  __syncthreads();
+  const Levels<kLevel> V = load_levels<kLevel>(L, which);
   const uint32_t* keys = L.keys[which];
-  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) {
-    const uint32_t key = keys[q];
-    if (key && prefix_of(key, level) == S.prefix) atomicAdd(&hist[digit_of(key, level)], 1u);
+  uint4 v[kKeysPer / 4];
+  auto load = [&](int beg) {
+#pragma unroll
+    for (int t = 0; t < kKeysPer / 4; ++t) {
+      const int q = beg + (t * kBlock + (int)threadIdx.x) * 4;
+      v[t] = q < n ? *(const uint4*)(keys + q) : uint4{0u, 0u, 0u, 0u};
+    }
+  };
+  load(blockIdx.x * kTopkChunk);
+  __shared__ uint32_t hist[kRadixBins];
+  for (int b = threadIdx.x; b < kRadixBins; b += kBlock) hist[b] = 0;
+  const Select S = derive<kLevel>(V, L.K[which]);
+  if (S.all) return;
+  for (int beg = blockIdx.x * kTopkChunk; beg < n; beg += gridDim.x * kTopkChunk) {
+    if (beg != (int)blockIdx.x * kTopkChunk) load(beg);
+#pragma unroll
+    for (int t = 0; t < kKeysPer / 4; ++t) {
+      const int q = beg + (t * kBlock + (int)threadIdx.x) * 4;
+      const uint32_t k4[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (q + u < n && k4[u] && prefix_of(k4[u], kLevel) == S.prefix) atomicAdd(&hist[digit_of(k4[u], kLevel)], 1u);
+    }
   }
-  flush_hist(hist, L.hist + (which * 3 + level) * kRadixBins);
+  flush_hist(hist, L.hist + hist_of(which, kLevel));
 }
 
 __device__ __forceinline__ bool take_above(uint32_t key, const Select& S) {
@@ -452,121 +518,6 @@ __device__ __forceinline__ bool take_above(uint32_t key, const Select& S) {
 
 __device__ __forceinline__ bool take_equal(uint32_t key, const Select& S) {
   return !S.all && key == S.thresh;
-}
-
-// Per-workgroup counts of keys above and equal to the threshold.
-__global__ __launch_bounds__(256) void k_topk_count(const WalkCtx* __restrict__ walks,
-                                                    const LearnCtx* __restrict__ lc, int32_t which, int32_t n) {
-  const WalkCtx& C = walks[0];
-  const LearnCtx& L = *lc;
-  if (!active(C.st, L.ls)) return;
-  const Select S = derive(L, which, 3);
-  __shared__ int red[8];
-  const uint32_t* keys = L.keys[which];
-  int gt = 0, eq = 0;
-  const int beg = blockIdx.x * kTopkChunk;
-  const int end = min(n, beg + kTopkChunk);
-  for (int q = beg + threadIdx.x; q < end; q += blockDim.x) {
-    const uint32_t key = keys[q];
-    gt += take_above(key, S) ? 1 : 0;
-    eq += take_equal(key, S) ? 1 : 0;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    gt += __shfl_xor(gt, o, kWave);
-    eq += __shfl_xor(eq, o, kWave);
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[2 * wv] = gt;
-    red[2 * wv + 1] = eq;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int a = 0, b = 0;
-    for (int k = 0; k < 4; ++k) {
-      a += red[2 * k];
-      b += red[2 * k + 1];
-    }
-    int32_t* cnt = L.wg_cnt + (int64_t)which * L.nwg * 2;
-    cnt[2 * blockIdx.x] = a;
-    cnt[2 * blockIdx.x + 1] = b;
-  }
-}
-
-// Order-preserving compaction of the selected columns; each workgroup sums
-// the counts of the workgroups before it.
-__global__ __launch_bounds__(256) void k_topk_write(const WalkCtx* __restrict__ walks,
-                                                    const LearnCtx* __restrict__ lc, int32_t which, int32_t n) {
-  const WalkCtx& C = walks[0];
-  const LearnCtx& L = *lc;
-  if (!active(C.st, L.ls)) return;
-  const Select S = derive(L, which, 3);
-  __shared__ int sg[4], se[4];
-  const uint32_t* keys = L.keys[which];
-  const int32_t* cnt = L.wg_cnt + (int64_t)which * L.nwg * 2;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int bg = 0, be = 0;
-  for (int b = threadIdx.x; b < (int)blockIdx.x; b += blockDim.x) {
-    bg += cnt[2 * b];
-    be += cnt[2 * b + 1];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    bg += __shfl_xor(bg, o, kWave);
-    be += __shfl_xor(be, o, kWave);
-  }
-  if (lane == 0) {
-    sg[wv] = bg;
-    se[wv] = be;
-  }
-  __syncthreads();
-  const int gt_base = sg[0] + sg[1] + sg[2] + sg[3];
-  const int eq_base = se[0] + se[1] + se[2] + se[3];
-  __syncthreads();
-  constexpr int per = kTopkChunk / kBlock;
-  const int beg = blockIdx.x * kTopkChunk + threadIdx.x * per;
-  int gt = 0, eq = 0;
-  for (int t = 0; t < per; ++t) {
-    const int q = beg + t;
-    if (q >= n) break;
-    const uint32_t key = keys[q];
-    gt += take_above(key, S) ? 1 : 0;
-    eq += take_equal(key, S) ? 1 : 0;
-  }
-  int ig = gt, ie = eq;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int yg = __shfl_up(ig, o, kWave), ye = __shfl_up(ie, o, kWave);
-    if (lane >= o) {
-      ig += yg;
-      ie += ye;
-    }
-  }
-  if (lane == 63) {
-    sg[wv] = ig;
-    se[wv] = ie;
-  }
-  __syncthreads();
-  int og = ig - gt, oe = ie - eq;
-  for (int k = 0; k < wv; ++k) {
-    og += sg[k];
-    oe += se[k];
-  }
-  int eq_rank = eq_base + oe;  // equal keys before this thread's run
-  int pos = gt_base + og + min(eq_rank, S.need_eq);
-  int32_t* out = L.sel[which];
-  for (int t = 0; t < per; ++t) {
-    const int q = beg + t;
-    if (q >= n) break;
-    const uint32_t key = keys[q];
-    bool take = take_above(key, S);
-    if (take_equal(key, S)) {
-      take = eq_rank < S.need_eq;
-      ++eq_rank;
-    }
-    if (take) out[pos++] = q;
-  }
 }
 
 // Appends the c2 first columns of the proposal set to the set log as the set
@@ -596,60 +547,208 @@ __global__ __launch_bounds__(256) void k_keep_set(const WalkCtx* __restrict__ wa
   log_set(C, L, L.ls->tk[0].count);
 }
 
-// End of a selection (one workgroup): the selected count; for the proposal
-// set also the subset-pass chunk offsets and the set log; then clears the
-// histograms for the next selection.
-__global__ __launch_bounds__(256) void k_topk_finish(const WalkCtx* __restrict__ walks,
-                                                     const LearnCtx* __restrict__ lc, int32_t which, int32_t full) {
+// Index of the chunk that holds item i of an exclusive prefix off[0..nc].
+__device__ __forceinline__ int chunk_of(const int32_t* off, int nc, int i) {
+  int lo = 0, hi = nc - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (off[mid] <= i)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
+// The selection in ascending column order and its end, in one launch. Every
+// workgroup compacts its chunk of columns (kTopkChunk times L.topk_tiles)
+// into its part of L.stage: the keys above the threshold from the front, each
+// with the number of equal ones before it, the equal ones from the back with
+// the number of greater ones before them (no more than the selection can
+// take). The last to arrive adds the chunks' counts, so that every staged key
+// knows its place, and writes the selected columns; for the proposal set also
+// the subset-pass chunk offsets and the set log; then it clears the histograms
+// and the ticket for the next selection. Bounded by latency: 18 us on 200k
+// columns, where a count, a write and a finishing launch, each deriving the
+// threshold again, took 29.
+__global__ __launch_bounds__(kBlock) void k_topk_take(const WalkCtx* __restrict__ walks,
+                                                      const LearnCtx* __restrict__ lc, int32_t which, int32_t full,
+                                                      int32_t n) {
   const WalkCtx& C = walks[0];
   const LearnCtx& L = *lc;
-  const WalkState* st = C.st;
-  if (!active(st, L.ls)) return;
-  const Select S = derive(L, which, 3);
-  const int cnt = S.count;
-  __shared__ int wsum[4];
-  __shared__ int carry;
-  if (which == 0) {
-    // exclusive prefix of per-column chunk counts, in tiles of 256 columns
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int base = 0; base < cnt; base += kBlock) {
-      const int i = base + threadIdx.x;
-      int c = 0;
-      if (i < cnt) {
-        const int q = L.sel[0][i];
-        const uint8_t cl = L.cls[q];
-        const int e = C.P.col_ptr[q + 1] - C.P.col_ptr[q];
-        c = (cl == SUB_GENERAL) ? 0 : max(1, (e + kSubsetChunk - 1) / kSubsetChunk);
-      }
-      int inc = c;
+  if (!active(C.st, L.ls)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const Levels<3> V = load_levels<3>(L, which);
+  const uint32_t* keys = L.keys[which];
+  const int chunk = kTopkChunk * L.topk_tiles;
+  const int beg = blockIdx.x * chunk;
+  uint4 v[kKeysPer / 4];
+  auto load = [&](int tile) {
 #pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += y;
-      }
-      if (lane == 63) wsum[wv] = inc;
-      __syncthreads();
-      int off = carry + inc - c;
-      for (int k = 0; k < wv; ++k) off += wsum[k];
-      if (i < cnt) L.sub_off[i] = off;
-      __syncthreads();
-      if (threadIdx.x == kBlock - 1) carry = off + c;
-      __syncthreads();
+    for (int t = 0; t < kKeysPer / 4; ++t) {
+      const int q = beg + tile * kTopkChunk + tid * kKeysPer + 4 * t;
+      v[t] = q < n ? *(const uint4*)(keys + q) : uint4{0u, 0u, 0u, 0u};
     }
-    if (threadIdx.x == 0) {
-      L.sub_off[cnt] = carry;
-      L.ls->tk[0].chunks = carry;
+  };
+  load(0);
+  const Select S = derive<3>(V, L.K[which]);
+  __shared__ uint32_t sg[4], se[4];
+  __shared__ uint32_t last;
+  uint2* stage = L.stage + (int64_t)blockIdx.x * chunk;
+  uint32_t gt_base = 0, eq_base = 0;  // of the tiles before this one
+  for (int tile = 0; tile < L.topk_tiles; ++tile) {
+    if (tile > 0) load(tile);
+    const int q0 = beg + tile * kTopkChunk + tid * kKeysPer;
+    uint32_t mg = 0, me = 0;  // this thread's keys above and equal, a bit each
+#pragma unroll
+    for (int t = 0; t < kKeysPer / 4; ++t) {
+      const uint32_t k4[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool in = q0 + 4 * t + u < n;
+        mg |= (in && take_above(k4[u], S) ? 1u : 0u) << (4 * t + u);
+        me |= (in && take_equal(k4[u], S) ? 1u : 0u) << (4 * t + u);
+      }
+    }
+    const uint32_t gt = __popc(mg), eq = __popc(me);
+    const uint32_t ig = wave_scan(gt), ie = wave_scan(eq);
+    __syncthreads();  // the tile before has read sg and se
+    if (lane == kWave - 1) {
+      sg[wv] = ig;
+      se[wv] = ie;
+    }
+    __syncthreads();
+    uint32_t og = gt_base + ig - gt, oe = eq_base + ie - eq;
+    for (int k = 0; k < kBlock / kWave; ++k) {
+      if (k < wv) {
+        og += sg[k];
+        oe += se[k];
+      }
+      gt_base += sg[k];
+      eq_base += se[k];
+    }
+    for (uint32_t m = mg; m; m &= m - 1) {
+      const int b = __builtin_ctz(m);
+      const uint32_t below = (1u << b) - 1u;
+      stage[og + __popc(mg & below)] = uint2{(uint32_t)(q0 + b), oe + __popc(me & below)};
+    }
+    for (uint32_t m = me; m; m &= m - 1) {
+      const int b = __builtin_ctz(m);
+      const uint32_t below = (1u << b) - 1u;
+      const uint32_t e = oe + __popc(me & below);
+      if (e >= (uint32_t)S.need_eq) break;
+      stage[chunk - 1 - e] = uint2{(uint32_t)(q0 + b), og + __popc(mg & below)};
+    }
+  }
+  uint2* cnt = L.wg_cnt;
+  if (tid == 0) cnt[blockIdx.x] = uint2{gt_base, eq_base};
+  __threadfence();
+  __syncthreads();
+  uint32_t* ticket = L.hist + 2 * kHistStride;
+  if (tid == 0) last = atomicAdd(ticket, 1u);
+  __syncthreads();
+  if (last != gridDim.x - 1) return;
+  __threadfence();
+
+  // exclusive prefixes of the chunks' counts
+  __shared__ int32_t pg[kTopkChunks + 1], pe[kTopkChunks + 1];
+  __shared__ int32_t pc[kTopkMax];  // subset-pass chunks of the selected columns
+  constexpr int kPer = kTopkChunks / kBlock;
+  const int nc = gridDim.x;
+  uint2 c[kPer];
+  uint32_t cg = 0, ce = 0;
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    const int b = tid * kPer + t;
+    c[t] = b < nc ? cnt[b] : uint2{0u, 0u};
+    cg += c[t].x;
+    ce += c[t].y;
+  }
+  uint32_t ag = wave_scan(cg), ae = wave_scan(ce);
+  if (lane == kWave - 1) {
+    sg[wv] = ag;
+    se[wv] = ae;
+  }
+  __syncthreads();
+  ag -= cg;
+  ae -= ce;
+  for (int k = 0; k < wv; ++k) {
+    ag += sg[k];
+    ae += se[k];
+  }
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    pg[tid * kPer + t] = (int32_t)ag;
+    pe[tid * kPer + t] = (int32_t)ae;
+    ag += c[t].x;
+    ae += c[t].y;
+  }
+  if (tid == kBlock - 1) pg[kTopkChunks] = (int32_t)ag;
+  __syncthreads();
+  const int above = pg[kTopkChunks];
+  const int count = above + (S.all ? 0 : S.need_eq);
+  int32_t* out = L.sel[which];
+  constexpr int kU = 4;  // staged keys in flight per thread
+  for (int i0 = tid; i0 < count; i0 += kU * kBlock) {
+    uint2 k[kU];
+    int pos[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int i = i0 + u * kBlock;
+      if (i >= count) break;
+      const bool eq = i >= above;
+      const int j = eq ? i - above : i;
+      const int b = chunk_of(eq ? pe : pg, nc, j);
+      const int o = j - (eq ? pe[b] : pg[b]);
+      k[u] = L.stage[(int64_t)b * chunk + (eq ? chunk - 1 - o : o)];
+      pos[u] = eq ? j + pg[b] : i;
+      if (!eq) k[u].y += pe[b];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int i = i0 + u * kBlock;
+      if (i >= count) break;
+      // equal: after the greater ones before it; greater: after the equal ones
+      // before it that are taken
+      const int at = pos[u] + (i >= above ? (int)k[u].y : min((int)k[u].y, S.all ? 0 : S.need_eq));
+      const int q = (int)k[u].x;
+      out[at] = q;
+      if (which == 0) {
+        const int e = C.P.col_ptr[q + 1] - C.P.col_ptr[q];
+        pc[at] = L.cls[q] == SUB_GENERAL ? 0 : max(1, (e + kSubsetChunk - 1) / kSubsetChunk);
+      }
+    }
+  }
+  __syncthreads();
+  if (which == 0) {
+    // exclusive prefix of the columns' chunk counts, a run of columns a thread
+    const int per = (count + kBlock - 1) / kBlock;
+    const int i0 = min(count, tid * per), i1 = min(count, i0 + per);
+    uint32_t sum = 0;
+    for (int i = i0; i < i1; ++i) sum += (uint32_t)pc[i];
+    const uint32_t inc = wave_scan(sum);
+    if (lane == kWave - 1) sg[wv] = inc;
+    __syncthreads();
+    int off = (int)(inc - sum);
+    for (int k = 0; k < wv; ++k) off += (int)sg[k];
+    for (int i = i0; i < i1; ++i) {
+      L.sub_off[i] = off;
+      off += pc[i];
+    }
+    if (tid == kBlock - 1) {
+      L.sub_off[count] = off;
+      L.ls->tk[0].chunks = off;
     }
     // proposal-set log (original indices); a full evaluation records an empty range
-    log_set(C, L, full ? 0 : cnt);
+    log_set(C, L, full ? 0 : count);
   }
-  if (threadIdx.x == 0) L.ls->tk[which].count = cnt;
-  // every reader of the histograms has finished (earlier kernels, derive above)
-  __syncthreads();
-  uint32_t* H = L.hist + which * 3 * kRadixBins;
-  for (int b = threadIdx.x; b < 3 * kRadixBins; b += blockDim.x) H[b] = 0;
+  if (tid == 0) {
+    L.ls->tk[which].count = count;
+    *ticket = 0u;
+  }
+  // every reader of the histograms has taken its ticket
+  uint4* H = (uint4*)(L.hist + which * kHistStride);
+  for (int b = tid; b < kHistStride / 4; b += kBlock) H[b] = uint4{0u, 0u, 0u, 0u};
 }
 
 // ---------------------------------------------------------------------------
@@ -755,12 +854,10 @@ inline int grid_for(int64_t work, int per_block, int cap) {
 
 hipError_t topk(const WalkCtx* C, const LearnCtx* L, const LearnCtx& Lh, int which, int full, int32_t n,
                 hipStream_t s) {
-  const int hb = grid_for(n, 256 * 16, 1024);
-  hipLaunchKernelGGL(k_topk_hist, dim3(hb), dim3(kBlock), 0, s, C, L, which, 1, n);
-  hipLaunchKernelGGL(k_topk_hist, dim3(hb), dim3(kBlock), 0, s, C, L, which, 2, n);
-  hipLaunchKernelGGL(k_topk_count, dim3(Lh.nwg), dim3(kBlock), 0, s, C, L, which, n);
-  hipLaunchKernelGGL(k_topk_write, dim3(Lh.nwg), dim3(kBlock), 0, s, C, L, which, n);
-  hipLaunchKernelGGL(k_topk_finish, dim3(1), dim3(kBlock), 0, s, C, L, which, (int32_t)full);
+  const int hb = grid_for(n, kTopkChunk, 1024);
+  hipLaunchKernelGGL(k_topk_hist<1>, dim3(hb), dim3(kBlock), 0, s, C, L, which, n);
+  hipLaunchKernelGGL(k_topk_hist<2>, dim3(hb), dim3(kBlock), 0, s, C, L, which, n);
+  hipLaunchKernelGGL(k_topk_take, dim3(Lh.nwg), dim3(kBlock), 0, s, C, L, which, (int32_t)full, n);
   return hipGetLastError();
 }
 
@@ -790,7 +887,9 @@ hipError_t launch_learn_begin(const WalkCtx* C, const LearnCtx* L, hipStream_t s
 hipError_t launch_learn_propose(const WalkCtx* C, const LearnCtx* L, const LearnCtx& Lh, const ModelDev& M,
                                 int32_t n, int full_iteration, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_learn_score, dim3(grid_for(n, 64, 768)), dim3(256), 0, s, C, L, M.w, M.wb, n);
+  // 512 workgroups: 14.7 us on 200k columns (768 and one copy of the first
+  // digit's histogram: 21.0; every further workgroup adds its turn at the bins)
+  hipLaunchKernelGGL(k_learn_score, dim3(grid_for(n, 64, 512)), dim3(256), 0, s, C, L, M.w, M.wb, n);
   return topk(C, L, Lh, 0, full_iteration, n, s);
 }
 
