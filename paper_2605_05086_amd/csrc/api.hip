@@ -3,12 +3,14 @@
 // pass and the graph-captured tabu walk.
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <limits>
 #include <memory>
 #include <numeric>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "chap_internal.h"
@@ -1008,9 +1010,6 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
   P->pool->n = n;
   P->pool->m = m;
   P->pool->mp = P->mp;
-  P->pool->perm = P->perm;
-  P->pool->nidx = P->nidx;
-  P->pool->pair = P->pair;
   CHAP_HIP(hipDeviceSynchronize());
   *out = P.release();
   return CHAP_OK;
@@ -1188,40 +1187,10 @@ int prepare_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, DeviceAren
   int rc = alloc_walk(spec.p, std::max<int64_t>(iters, 1), A, c, scan_all, extra_rec);
   if (rc != CHAP_OK) return rc;
   if (!compact) c.grow = nullptr;
-  rc = init_walk(spec, iters, tenure, c, partial, ticket, s);
-  if (rc != CHAP_OK) return rc;
-  CHAP_HIP(hipStreamSynchronize(s));
-  return CHAP_OK;
+  return init_walk(spec, iters, tenure, c, partial, ticket, s);
 }
 
 namespace {
-
-// Final state in the caller's order: x and best_x from internal order,
-// residuals and weights of the normalised rows (an equality row's twin has
-// residual -r and the second weight), the cutoff row last.
-void fill_state(int32_t n, int32_t m, int32_t mp, const int32_t* perm, const int32_t* nidx, const uint8_t* pair,
-                const double* xin, const double* bxin, const RowState* rs, const WalkState& st, chap_run* R) {
-  R->x.resize(n);
-  std::vector<double> bx(n);
-  for (int32_t q = 0; q < n; ++q) {
-    R->x[perm[q]] = xin[q];
-    bx[perm[q]] = bxin[q];
-  }
-  R->resid.assign((size_t)mp + 1, 0.0);
-  R->w.assign((size_t)mp + 1, 0.0f);
-  for (int32_t i = 0; i < m; ++i) {
-    const int32_t k = nidx[i];
-    R->resid[k] = rs[i].r;
-    R->w[k] = rs[i].w0;
-    if (pair[i]) {
-      R->resid[k + 1] = -rs[i].r;
-      R->w[k + 1] = rs[i].w1;
-    }
-  }
-  R->resid[mp] = st.cut_active ? st.rc : 0.0;
-  R->w[mp] = st.wc;
-  if (R->has_best) R->best_x.swap(bx);
-}
 
 void fill_summary(const WalkState& st, chap_run* R) {
   R->st_end = st;
@@ -1232,38 +1201,65 @@ void fill_summary(const WalkState& st, chap_run* R) {
   R->inf_viol = st.inf_k == -2 ? 0 : st.inf_V;
 }
 
-// The best infeasible point from the final point: the moves after the
-// iteration that reached it are undone in reverse order.
-void rebuild_infeasible(chap_run* R) {
-  R->inf_x.clear();
-  if (R->inf_iter == -2) return;
-  R->inf_x = R->x;
-  for (int64_t k = (int64_t)R->trace.size() - 1; k > R->inf_iter; --k) {
-    const chap_trace_record& t = R->trace[(size_t)k];
-    if (t.var >= 0) R->inf_x[t.var] = t.x_old;
-  }
-}
-
 }  // namespace
 
-int collect_walk(const chap_problem* p, const WalkCtx& c, int64_t iters, double ms, chap_run* R) {
-  const int32_t n = p->n, m = p->m;
-  R->elapsed_ms = ms;
-  R->trace.resize((size_t)iters);
-  if (iters > 0)
-    CHAP_HIP(hipMemcpy(R->trace.data(), c.trace, sizeof(chap_trace_record) * (size_t)iters, hipMemcpyDeviceToHost));
-  std::vector<double> xin(n), bxin(n);
-  if (n > 0) {
-    CHAP_HIP(hipMemcpy(xin.data(), c.x, sizeof(double) * (size_t)n, hipMemcpyDeviceToHost));
-    CHAP_HIP(hipMemcpy(bxin.data(), c.best_x, sizeof(double) * (size_t)n, hipMemcpyDeviceToHost));
+int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
+                  double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out) {
+  const size_t nw = ps.size();
+  // one block: per walk its record, trace, x, residuals, weights
+  auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+  std::vector<size_t> at(nw + 1, 0);
+  auto sizes = [&](size_t i) {
+    return std::array<size_t, 5>{up(sizeof(WalkState)), up(sizeof(chap_trace_record) * (size_t)iters),
+                                 up(sizeof(double) * (size_t)ps[i]->n), up(sizeof(double) * ((size_t)ps[i]->mp + 1)),
+                                 up(sizeof(float) * ((size_t)ps[i]->mp + 1))};
+  };
+  for (size_t i = 0; i < nw; ++i) {
+    at[i + 1] = at[i];
+    for (size_t b : sizes(i)) at[i + 1] += b;
   }
-  std::vector<RowState> rs(m);
-  if (m > 0) CHAP_HIP(hipMemcpy(rs.data(), c.rs, sizeof(RowState) * (size_t)m, hipMemcpyDeviceToHost));
-  WalkState st;
-  CHAP_HIP(hipMemcpy(&st, c.st, sizeof(WalkState), hipMemcpyDeviceToHost));
-  fill_summary(st, R);
-  fill_state(n, m, p->mp, p->perm.data(), p->nidx.data(), p->pair.data(), xin.data(), bxin.data(), rs.data(), st, R);
-  rebuild_infeasible(R);
+  DeviceArena A;
+  char* d;
+  CHAP_HIP(A.alloc(&d, at[nw]));
+  for (size_t i = 0; i < nw; ++i) {
+    const auto z = sizes(i);
+    char* o = d + at[i];
+    StateOut S;
+    S.st = (WalkState*)o;
+    S.trace = (chap_trace_record*)(o += z[0]);
+    S.x = (double*)(o += z[1]);
+    S.resid = (double*)(o += z[2]);
+    S.w = (float*)(o += z[3]);
+    S.best = ctx[i].s;  // free once the walk has ended
+    CHAP_HIP(launch_state_out(ctx[i].P, ps[i]->d_nidx, ps[i]->d_pair, ps[i]->mp, ctx[i], iters, S, s));
+  }
+  const std::unique_ptr<char[]> h(new char[at[nw]]);
+  CHAP_HIP(hipMemcpyAsync(h.get(), d, at[nw], hipMemcpyDeviceToHost, s));
+  CHAP_HIP(hipStreamSynchronize(s));
+  out.clear();
+  for (size_t i = 0; i < nw; ++i) {
+    const auto z = sizes(i);
+    const char* o = h.get() + at[i];
+    std::unique_ptr<chap_run> R(new chap_run());
+    R->elapsed_ms = ms;
+    WalkState st;
+    std::memcpy(&st, o, sizeof(WalkState));
+    fill_summary(st, R.get());
+    auto take = [](auto& v, const char* from, size_t count) {
+      using T = typename std::decay<decltype(v)>::type::value_type;
+      v.assign((const T*)from, (const T*)from + count);
+    };
+    take(R->trace, o += z[0], (size_t)iters);
+    take(R->x, o += z[1], (size_t)ps[i]->n);
+    take(R->resid, o += z[2], (size_t)ps[i]->mp + 1);
+    take(R->w, o += z[3], (size_t)ps[i]->mp + 1);
+    if (R->has_best) {
+      R->best_x.resize((size_t)ps[i]->n);
+      if (ps[i]->n > 0)
+        CHAP_HIP(hipMemcpy(R->best_x.data(), ctx[i].s, sizeof(double) * (size_t)ps[i]->n, hipMemcpyDeviceToHost));
+    }
+    out.push_back(std::move(R));
+  }
   return CHAP_OK;
 }
 
@@ -1272,18 +1268,16 @@ int collect_walk(const chap_problem* p, const WalkCtx& c, int64_t iters, double 
 int materialize(const chap_run* R) {
   if (R->state_ready) return CHAP_OK;
   const WalkPool& M = *R->pool;
-  const WalkCtx& c = R->slot->ctx;
-  std::vector<double> xin(M.n), bxin(M.n);
-  std::vector<RowState> rs(M.m);
-  if (M.n > 0) {
-    CHAP_HIP(hipMemcpy(xin.data(), c.x, sizeof(double) * (size_t)M.n, hipMemcpyDeviceToHost));
-    CHAP_HIP(hipMemcpy(bxin.data(), c.best_x, sizeof(double) * (size_t)M.n, hipMemcpyDeviceToHost));
-  }
-  if (M.m > 0) CHAP_HIP(hipMemcpy(rs.data(), c.rs, sizeof(RowState) * (size_t)M.m, hipMemcpyDeviceToHost));
+  const StateOut& S = R->slot->state;
   chap_run* W = const_cast<chap_run*>(R);
-  fill_state(M.n, M.m, M.mp, M.perm.data(), M.nidx.data(), M.pair.data(), xin.data(), bxin.data(), rs.data(),
-             R->st_end, W);
-  rebuild_infeasible(W);
+  auto read = [](auto& v, const auto* from, size_t count) {
+    v.resize(count);
+    return count > 0 ? hipMemcpy(v.data(), from, sizeof(v[0]) * count, hipMemcpyDeviceToHost) : hipSuccess;
+  };
+  CHAP_HIP(read(W->x, S.x, (size_t)M.n));
+  if (R->has_best) CHAP_HIP(read(W->best_x, S.best, (size_t)M.n));
+  CHAP_HIP(read(W->resid, S.resid, (size_t)M.mp + 1));
+  CHAP_HIP(read(W->w, S.w, (size_t)M.mp + 1));
   R->state_ready = true;
   R->pool->give_back(R->slot);
   return CHAP_OK;
@@ -1345,6 +1339,7 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
     return fail(CHAP_EINVAL, "iters and tenure must be >= 0 with iters + tenure < 2^31");
   const size_t nw = specs.size();
   DeviceArena A;
+  if (nw > 1) A.chunk = (size_t)32 << 20;
   std::vector<WalkCtx> ctx(nw);
   double* partial;
   uint32_t* ticket;
@@ -1360,7 +1355,6 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
       (void)hipStreamDestroy(s);
     }
   } sg{s, {}};
-  CHAP_HIP(sg.ps.create());
   hipEvent_t e_user, e0, e1;
   CHAP_HIP(hipEventCreate(&e_user));
   CHAP_HIP(hipEventCreate(&e0));
@@ -1385,6 +1379,11 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
   std::vector<int32_t> order;
   CHAP_HIP(build_launch(A, ctx, &L, &order));
   L.compact = compact;
+  const PassStreams* ps_side = nullptr;  // creating a stream takes a millisecond
+  if (pass_forks(L)) {
+    CHAP_HIP(sg.ps.create());
+    ps_side = &sg.ps;
+  }
   double ms_total = 0.0;
   std::vector<std::vector<int64_t>> restarts;
   if (iters > 0) {
@@ -1394,7 +1393,7 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
     CHAP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     hipError_t cap_err = hipSuccess;
     for (int64_t q = 0; q < K && cap_err == hipSuccess; ++q) {
-      cap_err = launch_pass(L, s, &sg.ps, true);
+      cap_err = launch_pass(L, s, ps_side, true);
       if (cap_err == hipSuccess) cap_err = launch_walk_step(L, s, true);
     }
     hipError_t end_err = hipStreamEndCapture(s, &graph);
@@ -1481,19 +1480,20 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
       }
     }
   }
-  CHAP_HIP(hipStreamSynchronize(s));
+  std::vector<const chap_problem*> ps(nw);
+  for (size_t i = 0; i < nw; ++i) ps[i] = specs[order[i]].p;  // ctx is in XCD order
+  std::vector<std::unique_ptr<chap_run>> runs;
+  const int rc = collect_walks(ps, ctx, iters, ms_total, s, runs);
+  if (rc != CHAP_OK) return rc;
   out.clear();
   out.resize(nw);
   for (size_t i = 0; i < nw; ++i) {
-    const int32_t w = order[i];  // ctx is in XCD order
-    std::unique_ptr<chap_run> R(new chap_run());
-    const int rc = collect_walk(specs[w].p, ctx[i], iters, ms_total, R.get());
-    if (rc != CHAP_OK) return rc;
+    const int32_t w = order[i];
     if (rsp) {
-      R->restarts = restarts.empty() ? std::vector<int64_t>() : restarts[w];
-      R->restart_run = true;
+      runs[i]->restarts = restarts.empty() ? std::vector<int64_t>() : restarts[w];
+      runs[i]->restart_run = true;
     }
-    out[w] = std::move(R);
+    out[w] = std::move(runs[i]);
   }
   return CHAP_OK;
 }
@@ -1504,6 +1504,10 @@ int slot_setup(const chap_problem* p, WalkSlot& S) {
   if (rc != CHAP_OK) return rc;
   S.grow_buf = S.ctx.grow;
   S.ctx.grow = nullptr;
+  S.state.x = S.ctx.xhat;
+  S.state.best = S.ctx.s;
+  CHAP_HIP(S.A.alloc(&S.state.resid, (size_t)p->mp + 1));
+  CHAP_HIP(S.A.alloc(&S.state.w, (size_t)p->mp + 1));
   CHAP_HIP(S.A.alloc(&S.partial, kInitPartial));
   CHAP_HIP(S.A.alloc(&S.ticket, 1));
   CHAP_HIP(hipMemset(S.ticket, 0, sizeof(uint32_t)));
@@ -1692,6 +1696,7 @@ int run_single(chap_problem* p, uint64_t seed, const double* x0, int64_t iters, 
   CHAP_HIP(hipEventRecord(S.ev[2], S.s));
   // an incumbent found by the last iteration is copied here
   CHAP_HIP(launch_copy_best_batch(S.L, S.s));
+  CHAP_HIP(launch_state_out(p->dev, p->d_nidx, p->d_pair, p->mp, S.ctx, 0, S.state, S.s));
   if (iters > 0)
     CHAP_HIP(hipMemcpyAsync(R->trace.data(), S.trace_buf, sizeof(chap_trace_record) * (size_t)iters,
                             hipMemcpyDeviceToHost, S.s));
@@ -1853,7 +1858,12 @@ int chap_run_best_infeasible(const chap_run* r, double* x, int64_t* violated, in
   if (x && r->inf_iter != -2) {
     const int rc = materialize(r);
     if (rc != CHAP_OK) return rc;
-    std::copy(r->inf_x.begin(), r->inf_x.end(), x);
+    // the final point with the moves after that iteration undone in reverse
+    std::copy(r->x.begin(), r->x.end(), x);
+    for (int64_t k = (int64_t)r->trace.size() - 1; k > r->inf_iter; --k) {
+      const chap_trace_record& t = r->trace[(size_t)k];
+      if (t.var >= 0) x[t.var] = t.x_old;
+    }
   }
   if (violated) *violated = r->inf_viol;
   if (iter) *iter = r->inf_iter;

@@ -273,9 +273,10 @@ int chap_learned_run(chap_problem* p, chap_model* m, const chap_learned_options*
   }
   CHAP_HIP(launch_copy_best_batch(BL, s));
   CHAP_HIP(hipStreamSynchronize(s));
-  std::unique_ptr<chap_run> R(new chap_run());
-  rc = collect_walk(p, c, iters, ms_total, R.get());
+  std::vector<std::unique_ptr<chap_run>> runs;
+  rc = collect_walks({p}, {c}, iters, ms_total, s, runs);
   if (rc != CHAP_OK) return rc;
+  std::unique_ptr<chap_run> R = std::move(runs[0]);
   LearnState ls;
   CHAP_HIP(hipMemcpy(&ls, Lh.ls, sizeof(LearnState), hipMemcpyDeviceToHost));
   R->evals = ls.evals;

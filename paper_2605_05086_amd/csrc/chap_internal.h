@@ -62,8 +62,12 @@ int fail(int code, const std::string& msg);
   } while (0)
 
 // Device allocations owned by one object, freed together.
+// With `chunk` set, requests of up to a quarter of it are cut from blocks of
+// that size (a batch makes a thousand of them).
 struct DeviceArena {
   std::vector<void*> ptrs;
+  size_t chunk = 0, left = 0;
+  char* cur = nullptr;
   DeviceArena() = default;
   DeviceArena(const DeviceArena&) = delete;
   DeviceArena& operator=(const DeviceArena&) = delete;
@@ -73,6 +77,25 @@ struct DeviceArena {
   template <typename T>
   hipError_t alloc(T** out, size_t count) {
     void* p = nullptr;
+    const size_t bytes = (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
+    if (bytes <= chunk / 4) {
+      if (left < bytes) {
+        void* b = nullptr;
+        if (hipMalloc(&b, chunk) == hipSuccess) {
+          ptrs.push_back(b);
+          cur = (char*)b;
+          left = chunk;
+        } else {
+          (void)hipGetLastError();  // no room for a whole block: this request alone
+        }
+      }
+      if (left >= bytes) {
+        *out = (T*)cur;
+        cur += bytes;
+        left -= bytes;
+        return hipSuccess;
+      }
+    }
     hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
     if (e != hipSuccess) return e;
     ptrs.push_back(p);
@@ -528,6 +551,8 @@ struct LearnCtx;
 // combine) scores them while it scans.
 hipError_t launch_pass(const BatchLaunch& L, hipStream_t stream, const PassStreams* ps = nullptr,
                        bool defer_combine = false);
+// Whether a pass with streams uses the side one.
+inline bool pass_forks(const BatchLaunch& L) { return L.total[KS_LONG] > 0 || L.total[KS_CHUNK] > 0; }
 // Only when every walk with long narrow columns is staged (no k_narrow_chunk
 // blocks): the move selection's extra workgroups exist for staged walks only.
 inline bool pass_defers_combine(const BatchLaunch& L) {
@@ -596,6 +621,19 @@ hipError_t launch_state_init(const DevProblem& P, const double* x, const RowStat
                              int32_t obj_integral, double cutoff_rhs, const float* cutoff_w,
                              int check_incumbent, int count_violated, hipStream_t stream);
 hipError_t launch_copy_best(const double* x, double* best_x, WalkState* st, int32_t n, hipStream_t stream);
+// Where a finished walk's state goes, in the caller's order: n, n (written with
+// an incumbent only), mp + 1 and mp + 1 values; st, when set, and trace take
+// the walk's record and `iters` trace records.
+struct StateOut {
+  double* x = nullptr;
+  double* best = nullptr;
+  double* resid = nullptr;
+  float* w = nullptr;
+  WalkState* st = nullptr;
+  chap_trace_record* trace = nullptr;
+};
+hipError_t launch_state_out(const DevProblem& P, const int32_t* nidx, const uint8_t* pair, int32_t mp,
+                            const WalkCtx& c, int64_t iters, const StateOut& o, hipStream_t stream);
 // dst[q] = src[perm[q]] (original order -> internal order)
 hipError_t launch_gather(const int32_t* perm, const double* src, double* dst, int32_t n, hipStream_t stream);
 // launch_stage_x through a plan of the same permutation; stage: n doubles.
@@ -1015,6 +1053,9 @@ struct WalkSlot {
   GatherRow* grow_buf = nullptr;  // compact rows (all-integer instances), used when a run allows them
   chap_trace_record* trace_buf = nullptr;
   int64_t trace_cap = 0;
+  // the finished walk's state in the caller's order; x and best_x lie in the
+  // walk's xhat and s
+  StateOut state;
   double* partial = nullptr;
   uint32_t* ticket = nullptr;
   hipStream_t s = nullptr;
@@ -1054,8 +1095,6 @@ struct WalkSlot {
 // outlive its problem.
 struct WalkPool {
   int32_t n = 0, m = 0, mp = 0;
-  std::vector<int32_t> perm, nidx;
-  std::vector<uint8_t> pair;
   std::vector<std::unique_ptr<WalkSlot>> idle;
   void give_back(std::unique_ptr<WalkSlot>& slot) {
     if (slot && idle.empty()) idle.push_back(std::move(slot));
@@ -1081,11 +1120,10 @@ struct chap_run {
   chap::WalkState st_end{};
   mutable bool state_ready = true;
   // best infeasible point (see WalkState::inf_V): its violated rows, the
-  // iteration after which it was reached, and the point (caller's order,
-  // rebuilt from the final point and the trace when the state is read)
+  // iteration after which it was reached (the point follows from the final
+  // point and the trace)
   int64_t inf_viol = 0;
   int64_t inf_iter = -2;
-  std::vector<double> inf_x;
   // walks of chap_batch_restarts: the iterations at which the walk restarted
   std::vector<int64_t> restarts;
   bool restart_run = false;
@@ -1128,13 +1166,15 @@ int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx
 // c.grow when set), state, incumbent check.
 int init_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, const WalkCtx& c, double* partial,
               uint32_t* ticket, hipStream_t s);
-// alloc_walk + init_walk (the compact copy only when `compact`).
+// alloc_walk + init_walk (the compact copy only when `compact`), on stream s.
 int prepare_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, DeviceArena& A, WalkCtx& c, double* partial,
                  uint32_t* ticket, hipStream_t s, int compact, bool scan_all = false, int32_t extra_rec = 0);
 // 1 when every walk of a run may keep the compact GatherRow copy.
 int compact_walks(const std::vector<WalkSpec>& specs, int64_t iters);
-// Copies a finished walk back into R (host order).
-int collect_walk(const chap_problem* p, const WalkCtx& c, int64_t iters, double ms, chap_run* R);
+// Copies finished walks back into new runs (host order): every walk's state in
+// the caller's order and its trace in one device block, read at once.
+int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
+                  double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out);
 // Device copy of the walk contexts and the per-kernel launch tables; a batch
 // is reordered by XCD (order[i]: caller's index of ctx[i]; may be null).
 hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* L, std::vector<int32_t>* order);

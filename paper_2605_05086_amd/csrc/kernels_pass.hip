@@ -2391,7 +2391,7 @@ hipError_t launch_pass_rows(const BatchLaunch& L, hipStream_t stream, const Pass
     if (first == hipSuccess) first = le;
   };
   // the side stream carries the chunks and the long sorts of unstaged columns
-  const bool fork = ps && (L.total[KS_LONG] > 0 || L.total[KS_CHUNK] > 0);
+  const bool fork = ps && pass_forks(L);
   hipStream_t s_long = stream;
   hipError_t e = hipSuccess;
   if (fork) {
