@@ -39,12 +39,11 @@ __global__ void k_fill_i32(int32_t* a, int32_t v, int64_t n) {
 
 namespace chap {
 
-// Uploads per-walk contexts and the per-kernel block prefix tables. A batch
-// (more than one walk) is placed by XCD: every walk goes to one XCD, chosen
-// greedily by its pass work (largest walks first, to the least loaded XCD),
-// ctx is reordered XCD by XCD (order[i] = caller's index of ctx[i]) and each
-// table gets the first virtual block and block count of every XCD appended
-// (see block_walk); a kernel then launches kXcds x its largest XCD share.
+// Uploads per-walk contexts and, for a batch, the per-kernel tables of the
+// workgroups' walks. A batch (more than one walk) is placed by XCD: every walk
+// goes to one XCD, chosen greedily by its pass work (largest walks first, to
+// the least loaded XCD), ctx is reordered XCD by XCD (order[i] = caller's index
+// of ctx[i]), and a kernel launches kXcds x its largest XCD share.
 hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* L, std::vector<int32_t>* order) {
   const size_t nw = ctx.size();
   L->nw = (int32_t)nw;
@@ -81,29 +80,23 @@ hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* 
   if (e != hipSuccess) return e;
   L->walks = d;
   for (int k = 0; k < KS_COUNT; ++k) {
-    std::vector<int32_t> off(nw + 1, 0);
-    for (size_t w = 0; w < nw; ++w) off[w + 1] = off[w] + kernel_blocks(ctx[w], k);
-    L->total[k] = off.back();
-    L->grid[k] = off.back();
-    if (nw > 1) {
-      int32_t first[kXcds], count[kXcds] = {0};
-      for (int x = 0; x < kXcds; ++x) first[x] = off.back();
-      for (size_t w = 0; w < nw; ++w) {
-        first[xcd[w]] = std::min(first[xcd[w]], off[w]);
-        count[xcd[w]] += off[w + 1] - off[w];
-      }
-      int32_t most = 0;
-      for (int x = 0; x < kXcds; ++x) {
-        off.push_back(first[x]);
-        most = std::max(most, count[x]);
-      }
-      for (int x = 0; x < kXcds; ++x) off.push_back(count[x]);
-      L->grid[k] = kXcds * most;
+    int32_t total = 0, count[kXcds] = {0};
+    for (size_t w = 0; w < nw; ++w) {
+      total += kernel_blocks(ctx[w], k);
+      count[xcd[w]] += kernel_blocks(ctx[w], k);
     }
-    int32_t* doff;
-    e = A.upload(&doff, off);
+    L->total[k] = total;
+    L->grid[k] = nw > 1 ? kXcds * *std::max_element(count, count + kXcds) : total;
+    if (nw == 1 || total == 0) continue;
+    std::vector<int2> table((size_t)L->grid[k], int2{-1, 0});
+    int32_t used[kXcds] = {0};
+    for (size_t w = 0; w < nw; ++w)
+      for (int32_t b = 0; b < kernel_blocks(ctx[w], k); ++b)
+        table[(size_t)(used[xcd[w]]++) * kXcds + (size_t)xcd[w]] = int2{(int32_t)w, b};
+    int2* d_table;
+    e = A.upload(&d_table, table);
     if (e != hipSuccess) return e;
-    L->off[k] = doff;
+    L->off[k] = (const int32_t*)d_table;
   }
   return hipSuccess;
 }
