@@ -27,26 +27,19 @@ std::mutex g_mu;
 void* g_scratch[kMaxDevices] = {};   // device address of `scratch` on each device
 uint32_t g_epoch[kMaxDevices] = {};  // call counter per device (byte copies of x)
 
-// The launch record of one pass: the walk context and the block prefix
-// table of every kernel slot (one walk: 0 and its block count).
-struct LaunchRecord {
-  WalkCtx c;
-  int32_t off[KS_COUNT][2];
-};
-
-// First kernel of a call: the launch record into scratch, the set-up ticket
+// First kernel of a call: the walk record into scratch, the set-up ticket
 // cleared, the state of a call without a cutoff row (workgroup 0), and the
 // point in internal order with its byte copy.
-__global__ __launch_bounds__(256) void k_noalloc_begin(LaunchRecord r, LaunchRecord* dst, uint32_t* ticket,
+__global__ __launch_bounds__(256) void k_noalloc_begin(WalkCtx r, WalkCtx* dst, uint32_t* ticket,
                                                        SingleInit init, const int32_t* __restrict__ perm,
                                                        const double* __restrict__ src, double* __restrict__ x,
                                                        int8_t* __restrict__ xc, WalkState* st, uint32_t epoch,
                                                        int32_t n) {
-  static_assert(sizeof(LaunchRecord) % 4 == 0, "copied as 32-bit words");
+  static_assert(sizeof(WalkCtx) % 4 == 0, "copied as 32-bit words");
   if (blockIdx.x == 0) {
     const uint32_t* from = reinterpret_cast<const uint32_t*>(&r);
     uint32_t* out = reinterpret_cast<uint32_t*>(dst);
-    for (int i = threadIdx.x; i < (int)(sizeof(LaunchRecord) / 4); i += blockDim.x) out[i] = from[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(WalkCtx) / 4); i += blockDim.x) out[i] = from[i];
     if (threadIdx.x == 0) {
       *ticket = 0u;
       if (init.cutoff_w) single_state(st, init);
@@ -127,22 +120,17 @@ int chap_best_shift_noalloc(chap_problem* p, const double* d_x, const float* d_w
   double* partial = cv.take<double>(kInitPartial);
   uint32_t* ticket = cv.take<uint32_t>(1);
   long long* objacc = p->obj_fast ? nullptr : cv.take<long long>(kExactLimbs);
-  LaunchRecord* rec = cv.take<LaunchRecord>(1);
+  WalkCtx* rec = cv.take<WalkCtx>(1);
   if (cv.used > cv.cap)
     return fail(CHAP_EINVAL, "chap_best_shift_noalloc: this problem needs " + std::to_string(cv.used) +
                                  " bytes of scratch, more than the " + std::to_string(kNoAllocBytes) +
                                  " the entry point holds per device (use chap_best_shift)");
-  LaunchRecord r{};
-  r.c = c;
   BatchLaunch L;
   L.nw = 1;
-  L.walks = &rec->c;
+  L.walks = rec;
   for (int k = 0; k < KS_COUNT; ++k) {
-    r.off[k][0] = 0;
-    r.off[k][1] = kernel_blocks(c, k);
-    L.off[k] = rec->off[k];
-    L.total[k] = r.off[k][1];
-    L.grid[k] = r.off[k][1];
+    L.total[k] = kernel_blocks(c, k);
+    L.grid[k] = L.total[k];
   }
   L.compact = p->compact_ok ? 2 : 0;
   hipStream_t s = (hipStream_t)hip_stream;
@@ -157,7 +145,7 @@ int chap_best_shift_noalloc(chap_problem* p, const double* d_x, const float* d_w
     init.cutoff_w = d_w + p->mp;
     init.obj_integral = p->obj_integral;
   }
-  hipLaunchKernelGGL(k_noalloc_begin, dim3((unsigned)std::max(1, (n + 255) / 256)), dim3(256), 0, s, r, rec, ticket,
+  hipLaunchKernelGGL(k_noalloc_begin, dim3((unsigned)std::max(1, (n + 255) / 256)), dim3(256), 0, s, c, rec, ticket,
                      init, p->dev.perm, d_x, c.x, xc, c.st, epoch, n);
   CHAP_HIP(hipGetLastError());
   if (cut)

@@ -834,8 +834,8 @@ struct JumpBinTask {
 // grow: the instance's compact row copy as this call wrote it, when that
 // copy can be exact (all-integer data, residuals within int32), else null
 // (exact_data below is grow != null); obj_small: objective sums are exact
-// small integers. With integer weights (checked on the device) the lane kernel
-// then tries fewer values of narrow columns, with the same results.
+// small integers. With integer weights (checked on the device) the short columns'
+// roles then try fewer values of narrow columns, with the same results.
 // Columns with a bins form are scored from int64 slope and offset bins
 // when the call's data are exact (integer weights; then every V is an
 // integer below 2^53 and any order of summation gives the oracle's value),
