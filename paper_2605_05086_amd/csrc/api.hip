@@ -1199,59 +1199,74 @@ void fill_summary(const WalkState& st, chap_run* R) {
 int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
                   double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out) {
   const size_t nw = ps.size();
-  // one block: per walk its record, trace, x, residuals, weights
+  // a block of at most kCollectBytes (or of one walk): per walk its record,
+  // trace, x, residuals, weights
+  constexpr size_t kCollectBytes = (size_t)64 << 20;
   auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-  std::vector<size_t> at(nw + 1, 0);
   auto sizes = [&](size_t i) {
     return std::array<size_t, 5>{up(sizeof(WalkState)), up(sizeof(chap_trace_record) * (size_t)iters),
                                  up(sizeof(double) * (size_t)ps[i]->n), up(sizeof(double) * ((size_t)ps[i]->mp + 1)),
                                  up(sizeof(float) * ((size_t)ps[i]->mp + 1))};
   };
+  auto bytes = [&](size_t i) {
+    size_t t = 0;
+    for (size_t z : sizes(i)) t += z;
+    return t;
+  };
+  size_t total = 0, most = 0;
   for (size_t i = 0; i < nw; ++i) {
-    at[i + 1] = at[i];
-    for (size_t b : sizes(i)) at[i + 1] += b;
+    total += bytes(i);
+    most = std::max(most, bytes(i));
   }
+  const size_t cap = std::max(most, std::min(total, kCollectBytes));
   DeviceArena A;
   char* d;
-  CHAP_HIP(A.alloc(&d, at[nw]));
-  for (size_t i = 0; i < nw; ++i) {
-    const auto z = sizes(i);
-    char* o = d + at[i];
-    StateOut S;
-    S.st = (WalkState*)o;
-    S.trace = (chap_trace_record*)(o += z[0]);
-    S.x = (double*)(o += z[1]);
-    S.resid = (double*)(o += z[2]);
-    S.w = (float*)(o += z[3]);
-    S.best = ctx[i].s;  // free once the walk has ended
-    CHAP_HIP(launch_state_out(ctx[i].P, ps[i]->d_nidx, ps[i]->d_pair, ps[i]->mp, ctx[i], iters, S, s));
-  }
-  const std::unique_ptr<char[]> h(new char[at[nw]]);
-  CHAP_HIP(hipMemcpyAsync(h.get(), d, at[nw], hipMemcpyDeviceToHost, s));
-  CHAP_HIP(hipStreamSynchronize(s));
+  CHAP_HIP(A.alloc(&d, cap));
+  const std::unique_ptr<char[]> h(new char[cap]);
+  auto take = [](auto& v, const char* from, size_t count) {
+    using T = typename std::decay<decltype(v)>::type::value_type;
+    v.assign((const T*)from, (const T*)from + count);
+  };
   out.clear();
-  for (size_t i = 0; i < nw; ++i) {
-    const auto z = sizes(i);
-    const char* o = h.get() + at[i];
-    std::unique_ptr<chap_run> R(new chap_run());
-    R->elapsed_ms = ms;
-    WalkState st;
-    std::memcpy(&st, o, sizeof(WalkState));
-    fill_summary(st, R.get());
-    auto take = [](auto& v, const char* from, size_t count) {
-      using T = typename std::decay<decltype(v)>::type::value_type;
-      v.assign((const T*)from, (const T*)from + count);
-    };
-    take(R->trace, o += z[0], (size_t)iters);
-    take(R->x, o += z[1], (size_t)ps[i]->n);
-    take(R->resid, o += z[2], (size_t)ps[i]->mp + 1);
-    take(R->w, o += z[3], (size_t)ps[i]->mp + 1);
-    if (R->has_best) {
-      R->best_x.resize((size_t)ps[i]->n);
-      if (ps[i]->n > 0)
-        CHAP_HIP(hipMemcpy(R->best_x.data(), ctx[i].s, sizeof(double) * (size_t)ps[i]->n, hipMemcpyDeviceToHost));
+  for (size_t i0 = 0; i0 < nw;) {
+    size_t i1 = i0, used = 0;
+    for (; i1 < nw && used + bytes(i1) <= cap; ++i1) {
+      const auto z = sizes(i1);
+      char* o = d + used;
+      StateOut S;
+      S.st = (WalkState*)o;
+      S.trace = (chap_trace_record*)(o += z[0]);
+      S.x = (double*)(o += z[1]);
+      S.resid = (double*)(o += z[2]);
+      S.w = (float*)(o += z[3]);
+      S.best = ctx[i1].s;  // free once the walk has ended
+      CHAP_HIP(launch_state_out(ctx[i1].P, ps[i1]->d_nidx, ps[i1]->d_pair, ps[i1]->mp, ctx[i1], iters, S, s));
+      used += bytes(i1);
     }
-    out.push_back(std::move(R));
+    CHAP_HIP(hipMemcpyAsync(h.get(), d, used, hipMemcpyDeviceToHost, s));
+    CHAP_HIP(hipStreamSynchronize(s));
+    const char* base = h.get();
+    for (; i0 < i1; ++i0) {
+      const auto z = sizes(i0);
+      const chap_problem* p = ps[i0];
+      const char* o = base;
+      base += bytes(i0);
+      std::unique_ptr<chap_run> R(new chap_run());
+      R->elapsed_ms = ms;
+      WalkState st;
+      std::memcpy(&st, o, sizeof(WalkState));
+      fill_summary(st, R.get());
+      take(R->trace, o += z[0], (size_t)iters);
+      take(R->x, o += z[1], (size_t)p->n);
+      take(R->resid, o += z[2], (size_t)p->mp + 1);
+      take(R->w, o += z[3], (size_t)p->mp + 1);
+      if (R->has_best) {
+        R->best_x.resize((size_t)p->n);
+        if (p->n > 0)
+          CHAP_HIP(hipMemcpy(R->best_x.data(), ctx[i0].s, sizeof(double) * (size_t)p->n, hipMemcpyDeviceToHost));
+      }
+      out.push_back(std::move(R));
+    }
   }
   return CHAP_OK;
 }

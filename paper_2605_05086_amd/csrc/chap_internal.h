@@ -1159,7 +1159,8 @@ int prepare_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, DeviceAren
 // 1 when every walk of a run may keep the compact GatherRow copy.
 int compact_walks(const std::vector<WalkSpec>& specs, int64_t iters);
 // Copies finished walks back into new runs (host order): every walk's state in
-// the caller's order and its trace in one device block, read at once.
+// the caller's order and its trace go through a bounded device block, as many
+// walks at a time as it holds.
 int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
                   double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out);
 // Device copy of the walk contexts and the per-kernel launch tables; a batch
