@@ -1506,10 +1506,18 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
   return CHAP_OK;
 }
 
+// Workgroups that score lane-group columns in an affected-rescoring iteration.
+constexpr int32_t kAffGroups = 1024;
+int32_t aff_groups(const WalkCtx& c) { return std::min(kAffGroups, std::max(1, c.plan.grp_blk[kGroupClasses])); }
+
 // Buffers, launch table and streams of a new walk slot for problem p.
 int slot_setup(const chap_problem* p, WalkSlot& S) {
-  int rc = alloc_walk(p, 0, S.A, S.ctx, p->opt.rescore_cap > 0);
+  int rc = alloc_walk(p, 0, S.A, S.ctx, p->opt.rescore_cap > 0, p->opt.rescore_cap > 0 ? kAffGroups + kArgmaxBlocks : 0);
   if (rc != CHAP_OK) return rc;
+  // affected rescoring where every column is a lane-group one: the scoring
+  // launch also scans the other columns' kept scores and records the best moves
+  S.aff_scan = p->opt.rescore_cap > 0 && p->n > 0 && p->plan.grp_col[0] == 0 && p->plan.grp_col[kGroupClasses] == p->n;
+  if (S.aff_scan) S.ctx.group_rec = aff_groups(S.ctx);
   S.grow_buf = S.ctx.grow;
   S.ctx.grow = nullptr;
   S.state.x = S.ctx.xhat;
@@ -1524,6 +1532,7 @@ int slot_setup(const chap_problem* p, WalkSlot& S) {
   for (hipEvent_t& e : S.ev) CHAP_HIP(hipEventCreate(&e));
   std::vector<WalkCtx> one{S.ctx};
   CHAP_HIP(build_launch(S.A, one, &S.L, nullptr));
+  if (S.aff_scan) S.L.total[KS_ARGMAX] = 0;
   if (p->opt.rescore_cap > 0) {
     // affected rescoring: the subset pass's record and the lane list, fed
     // with the affected columns of each iteration (or with all columns)
@@ -1605,9 +1614,9 @@ int slot_graph(WalkSlot& S, int64_t K, int compact, hipGraphExec_t* out) {
       cap_err = launch_affected(S.L.walks, S.aff_L, F, S.s);
       if (cap_err == hipSuccess && !F.full_olist) cap_err = launch_pass(S.L, S.s, &S.ps, true);
       if (cap_err == hipSuccess) {
-        const int g[3] = {std::min(1024, std::max(1, S.ctx.plan.grp_blk[kGroupClasses])),
-                          S.aff_other ? std::min(256, F.sub_cap) : 0, S.aff_general ? 32 : 0};
-        cap_err = launch_aff_score(S.L.walks, S.aff_L, F.run, g, 64, compact, S.s);
+        const int g[4] = {aff_groups(S.ctx), S.aff_other ? std::min(256, F.sub_cap) : 0, S.aff_general ? 32 : 0,
+                          S.aff_scan ? S.ctx.argmax_blocks : 0};
+        cap_err = launch_aff_score(S.L.walks, S.aff_L, F, g, 64, compact, S.s);
       }
     } else {
       cap_err = launch_pass(S.L, S.s, &S.ps, true);

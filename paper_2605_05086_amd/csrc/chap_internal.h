@@ -924,11 +924,13 @@ hipError_t launch_hamming(const HamTask* tasks, int32_t ntasks, int32_t* dist, h
 // record.
 hipError_t launch_restart_fix(WalkState* st, const RestartKeep& keep, hipStream_t s);
 // The whole scoring of an affected-rescoring iteration: one launch whose
-// workgroups take two roles: the lane-group columns (g[0]) and the subset
-// chunks (g[1]); then, with g[2] > 0 workgroups, the subset general columns
+// workgroups take the roles of the lane-group columns (g[0]), the subset
+// chunks (g[1]) and, where every column is a lane-group one, the scan of the
+// scores that the iteration keeps (g[3]), with the records of the move
+// selection; then, with g[2] > 0 workgroups, the subset general columns
 // (their LDS sort would keep the other roles at one workgroup per CU); then
 // the subset combine.
-hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[3], int combine_grid,
+hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffLists& A, const int g[4], int combine_grid,
                             int compact, hipStream_t s);
 
 }  // namespace chap
@@ -1061,6 +1063,7 @@ struct WalkSlot {
   LearnCtx aff_Lh{};             // its host copy
   int aff_other = 0;             // the problem has columns outside the lane-group range
   int aff_general = 0;           // the problem has general columns outside the lane-group range
+  bool aff_scan = false;         // the scoring launch scans the other columns' scores
   WalkSlot() = default;
   WalkSlot(const WalkSlot&) = delete;
   WalkSlot& operator=(const WalkSlot&) = delete;

@@ -498,33 +498,43 @@ __global__ __launch_bounds__(256, 8) void k_group(const WalkCtx* __restrict__ wa
 }
 
 // The lane-group columns of an affected-rescoring iteration (b of nb
-// workgroups): the listed ones, a wavefront each, or all of them.
+// workgroups): the listed ones, a wavefront each, or all of them. With `rec`
+// their best moves go there.
 template <typename Rows>
-__device__ __forceinline__ void aff_group_body(const WalkCtx& C, const AffRun* run, int b, int nb, GroupSmem& S) {
+__device__ __forceinline__ void aff_group_body(const WalkCtx& C, const AffRun* run, int b, int nb, GroupSmem& S,
+                                               MoveRecord* rec) {
   const WalkState* st = C.st;
   if (st->k >= st->iters) return;
   const Rows rs = rows_of<Rows>(C);
   const int count = run->n_s;
+  BestPair best;
   if (count < 0) {
-    for (int t = b; t < C.plan.grp_blk[kGroupClasses]; t += nb) group_task<Rows>(C, rs, st, t, S);
-    return;
-  }
-  const int lane = threadIdx.x & (kWave - 1);
-  const int n_flip = C.plan.grp_col[kGroupWidths];
-  for (int i = b * 4 + (int)(threadIdx.x >> 6); i < count; i += nb * 4) {
-    const int q = __builtin_amdgcn_readfirstlane(run->slist[i]);
-    const int beg = C.P.col_ptr[q], deg = C.P.col_ptr[q + 1] - beg;
-    int row = -1;
-    double a = 1.0;
-    if (lane < deg) {
-      row = gmem(C.P.col_row)[beg + lane];
-      a = gmem(C.P.col_val)[beg + lane];
+    for (int t = b; t < C.plan.grp_blk[kGroupClasses]; t += nb) {
+      const GroupScore o = group_task<Rows>(C, rs, st, t, S);
+      if (rec && o.s > 0.0) best.offer(o.s, o.j, o.q, o.tabu);
     }
-    if (q < n_flip)
-      score_group<kWave, true, Rows>(C, rs, st, q, true, row, a, S);
-    else
-      score_group<kWave, false, Rows>(C, rs, st, q, true, row, a, S);
+  } else {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int n_flip = C.plan.grp_col[kGroupWidths];
+    for (int i = b * 4 + (int)(threadIdx.x >> 6); i < count; i += nb * 4) {
+      const int q = __builtin_amdgcn_readfirstlane(run->slist[i]);
+      const int beg = C.P.col_ptr[q], deg = C.P.col_ptr[q + 1] - beg;
+      GroupScore o;
+      if (rec) group_ids(C, st, lane == 0, q, o);
+      int row = -1;
+      double a = 1.0;
+      if (lane < deg) {
+        row = gmem(C.P.col_row)[beg + lane];
+        a = gmem(C.P.col_val)[beg + lane];
+      }
+      if (q < n_flip)
+        o.s = score_group<kWave, true, Rows>(C, rs, st, q, true, row, a, S);
+      else
+        o.s = score_group<kWave, false, Rows>(C, rs, st, q, true, row, a, S);
+      if (rec && o.s > 0.0) best.offer(o.s, o.j, q, o.tabu);
+    }
   }
+  if (rec) block_record<4>(best, rec);
 }
 
 // ---------------------------------------------------------------------------
@@ -2285,33 +2295,48 @@ __global__ __launch_bounds__(256) void k_subset_general(const WalkCtx* __restric
 }
 
 // The scoring of an affected-rescoring iteration in one launch: workgroups
-// [0, g0) score the lane-group columns, the other g1 the subset chunks (each
-// role strides over its own work).
+// [0, g0) score the lane-group columns, the next g1 the subset chunks, the other
+// g2 scan the kept scores of the columns that the iteration does not score
+// (stamp: AffLists::stamp), each role striding over its own work. With the scan
+// (every column a lane-group one) the kernel records the iteration's best moves
+// and nothing is left for a scanning launch: 21.5 us per iteration on 100k
+// columns, 23.0 with one.
 template <typename Rows>
 __global__ __launch_bounds__(256) void k_aff_score(const WalkCtx* __restrict__ walks,
                                                    const LearnCtx* __restrict__ lc, const AffRun* __restrict__ run,
-                                                   int g0, int g1) {
+                                                   const int32_t* __restrict__ stamp, int g0, int g1, int g2) {
   __shared__ union {
     GroupSmem s;
     SubsetChunkSmem c;
   } U;
   const WalkCtx& C = walks[0];
   const int b = (int)blockIdx.x;
-  if (b < g0)
-    aff_group_body<Rows>(C, run, b, g0, U.s);
-  else
+  if (b < g0) {
+    if (g2 > 0 && b == 0 && threadIdx.x == 0) snapshot(C.st, C.st->k < C.st->iters);
+    aff_group_body<Rows>(C, run, b, g0, U.s, g2 > 0 ? C.best + b : nullptr);
+  } else if (b < g0 + g1) {
     subset_chunks_body<Rows>(C, *lc, b - g0, g1, U.c);
+  } else {
+    const WalkState* st = C.st;
+    if (st->k >= st->iters) return;
+    const bool all = run->n_s < 0;
+    const int32_t tag = (int32_t)st->k + 1;
+    BestPair best;
+    scan_scores(C, st->k, st->copy_best != 0, (b - g0 - g1) * 256 + (int)threadIdx.x, g2 * 256, best,
+                [&](int q) { return all || gmem(stamp)[q] == tag; });
+    block_record<4>(best, C.best + b - g1);
+  }
 }
 
 }  // namespace
 
-hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffRun* run, const int g[3], int combine_grid,
+hipError_t launch_aff_score(const WalkCtx* C, const LearnCtx* L, const AffLists& A, const int g[4], int combine_grid,
                             int compact, hipStream_t s) {
-  const unsigned total = (unsigned)(g[0] + g[1]);
+  const unsigned total = (unsigned)(g[0] + g[1] + g[3]);
   if (compact)
-    hipLaunchKernelGGL(k_aff_score<CompactRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1]);
+    hipLaunchKernelGGL(k_aff_score<CompactRows>, dim3(total), dim3(256), 0, s, C, L, A.run, A.stamp, g[0], g[1], g[3]);
   else
-    hipLaunchKernelGGL(k_aff_score<FullRows>, dim3(total), dim3(256), 0, s, C, L, run, g[0], g[1]);
+    hipLaunchKernelGGL(k_aff_score<FullRows>, dim3(total), dim3(256), 0, s, C, L, A.run, A.stamp, g[0], g[1], g[3]);
   if (g[2] > 0) hipLaunchKernelGGL(k_subset_general, dim3((unsigned)g[2]), dim3(256), 0, s, C, L, -1);
   // without columns outside the lane-group range there is nothing to combine
   if (g[1] > 0)

@@ -706,21 +706,12 @@ __global__ __launch_bounds__(256) void k_argmax(const WalkCtx* __restrict__ walk
   const int w_ = block_walk(off, nw, lb);
   if (w_ < 0) return;
   const WalkCtx& C = walks[w_];
-  const gptr<const double> s = gmem((const double*)C.s);
-  const gptr<const int32_t> tabu = gmem((const int32_t*)C.tabu);
-  const gptr<const int32_t> perm = gmem(C.P.perm);
   const WalkState* st = C.st;
-  const gptr<const double> x = gmem((const double*)C.x);
-  const gptr<double> best_x = gmem(C.best_x);
-  const int32_t n = C.P.n;
   const bool active = st->k < st->iters;
   if (lb == 0 && threadIdx.x == 0) snapshot(C.st, active);
   if (!active) return;
   const int64_t k = st->k;
-  const bool copy = st->copy_best != 0;
   BestPair best;
-  const int gt = C.scan_from + lb * blockDim.x + threadIdx.x;
-  const int gs = C.argmax_blocks * blockDim.x;
   const int ncc = combine ? C.plan.n_chunk_cols : 0;
   const int cq0 = ncc > 0 ? C.plan.chunk_cols[0].col : 0;
   if (lb >= C.argmax_blocks) {
@@ -728,33 +719,12 @@ __global__ __launch_bounds__(256) void k_argmax(const WalkCtx* __restrict__ walk
     if (idx < ncc) {
       int q;
       const double v = combine_col(C, idx, threadIdx.x & 63, &q);
-      if ((threadIdx.x & 63) == 0 && v > 0.0) best.offer(v, perm[q], q, k <= (int64_t)tabu[q]);
+      if ((threadIdx.x & 63) == 0 && v > 0.0)
+        best.offer(v, gmem(C.P.perm)[q], q, k <= (int64_t)gmem((const int32_t*)C.tabu)[q]);
     }
   } else {
-    if (copy)
-      for (int q = gt; q < n; q += gs) best_x[q] = x[q];
-    // kU columns per thread and step, every load issued before any is used
-    constexpr int kU = 8;
-    for (int64_t q0 = gt; q0 < n; q0 += (int64_t)kU * gs) {
-      double v[kU];
-      int j[kU], tb[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t q = q0 + (int64_t)u * gs;
-        v[u] = 0.0;
-        if (q < n) {
-          v[u] = s[q];
-          j[u] = perm[q];
-          tb[u] = tabu[q];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t q = q0 + (int64_t)u * gs;
-        if (q < n && v[u] > 0.0 && (uint64_t)(q - cq0) >= (uint64_t)ncc)
-          best.offer(v[u], j[u], (int)q, k <= (int64_t)tb[u]);
-      }
-    }
+    scan_scores(C, k, st->copy_best != 0, C.scan_from + lb * (int)blockDim.x + (int)threadIdx.x,
+                C.argmax_blocks * (int)blockDim.x, best, [&](int q) { return (uint32_t)(q - cq0) < (uint32_t)ncc; });
   }
   block_record<4>(best, C.best + C.group_rec + lb);
 }

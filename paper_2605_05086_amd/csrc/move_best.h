@@ -144,6 +144,46 @@ __device__ __forceinline__ void block_record_one(double s, int j, int q, bool ta
   }
 }
 
+// The kept scores of columns gt, gt + gs, ... of a walk into `best`, but for
+// those with mark(q) (read beside the score); with `copy` also the pending copy
+// of a new incumbent for all of them. kU columns per thread and step, every load
+// issued before any is used.
+template <typename Mark>
+__device__ __forceinline__ void scan_scores(const WalkCtx& C, int64_t k, bool copy, int gt, int gs, BestPair& best,
+                                            Mark mark) {
+  const gptr<const double> s = gmem((const double*)C.s);
+  const gptr<const int32_t> tabu = gmem((const int32_t*)C.tabu);
+  const gptr<const int32_t> perm = gmem(C.P.perm);
+  const int32_t n = C.P.n;
+  if (copy) {
+    const gptr<const double> x = gmem((const double*)C.x);
+    const gptr<double> best_x = gmem(C.best_x);
+    for (int q = gt; q < n; q += gs) best_x[q] = x[q];
+  }
+  constexpr int kU = 8;
+  for (int64_t q0 = gt; q0 < n; q0 += (int64_t)kU * gs) {
+    double v[kU];
+    int j[kU], tb[kU];
+    bool skip[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t q = q0 + (int64_t)u * gs;
+      v[u] = 0.0;
+      if (q < n) {
+        v[u] = s[q];
+        j[u] = perm[q];
+        tb[u] = tabu[q];
+        skip[u] = mark((int)q);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t q = q0 + (int64_t)u * gs;
+      if (q < n && v[u] > 0.0 && !skip[u]) best.offer(v[u], j[u], (int)q, k <= (int64_t)tb[u]);
+    }
+  }
+}
+
 // The iteration the move selection that follows belongs to, and its violated
 // rows: the selection's workgroups read this copy, which none of them writes
 // (one thread of a kernel before it does).
