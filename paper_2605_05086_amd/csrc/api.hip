@@ -996,6 +996,7 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     std::vector<WalkCtx> one{c};
     CHAP_HIP(build_launch(A, one, &P->bs_launch, nullptr));
     P->bs_launch.compact = P->compact_ok ? 2 : 0;
+    P->bs_launch.caller_weights = 1;
   }
   // timing only: no system-scope fence at the record
   for (hipEvent_t& e : P->pass_ev) CHAP_HIP(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));

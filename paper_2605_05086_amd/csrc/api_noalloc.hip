@@ -133,6 +133,7 @@ int chap_best_shift_noalloc(chap_problem* p, const double* d_x, const float* d_w
     L.grid[k] = L.total[k];
   }
   L.compact = p->compact_ok ? 2 : 0;
+  L.caller_weights = 1;
   hipStream_t s = (hipStream_t)hip_stream;
   uint32_t epoch;
   {

@@ -493,6 +493,7 @@ struct BatchLaunch {
   // 0: the pass gathers RowState; 1: every walk keeps a GatherRow copy and the
   // pass gathers it; 2: the copy is used where WalkState::compact_rows says so
   int32_t compact = 0;
+  int32_t caller_weights = 0;  // a single pass: any weight a float holds (a walk's are counts)
   const WalkCtx* walks = nullptr;
   const int32_t* off[KS_COUNT] = {};
   int32_t total[KS_COUNT] = {};

@@ -256,10 +256,24 @@ __device__ __forceinline__ GroupTerm group_term(double t, bool ap, float w, doub
   return g;
 }
 
+// Half of a weight below 2^-125 may be no float: a wavefront that meets one
+// (kTiny) forms the halves of all its terms in FP64, from the whole weights that
+// they hold. Only calls with the caller's weights (kCaller) look for one: the
+// weights of a walk are counts. FP64 terms for every wavefront cost 4 % of a walk
+// on 100k columns, looking 0.5 %.
+constexpr float kTinyWeight = 0x1p-125f;
+__device__ __forceinline__ bool tiny_weight(float w) { return w > 0.0f && w < kTinyWeight; }
+
+template <bool kTiny>
 __device__ __forceinline__ double term_at(const GroupTerm& g, double p, bool right) {
   const float sat = g.sat, left = g.left, rgt = g.right;  // values, not addresses, to select from
+  const bool in = flip_sign(p, g.flip) <= g.t;
+  if constexpr (kTiny) {
+    if (in || sat == 0.0f) return (double)(in ? sat : left);
+    return (double)sat * ((g.flip != 0) == right ? 0.5 : -0.5);
+  }
   const float off = right ? rgt : left;
-  return (double)(flip_sign(p, g.flip) <= g.t ? sat : off);
+  return (double)(in ? sat : off);
 }
 
 // Orders the LDS writes and reads of one wavefront.
@@ -272,8 +286,9 @@ __device__ __forceinline__ void wave_sync() {
 // Column q by the G lanes of its group; row, a: this lane's stored entry (row
 // < 0: none; a column's entries fill its first lanes). Groups without a column
 // (in = false) take part in the exchanges and write nothing. Returns the
-// column's kept score on the group's first lane, 0 on the others.
-template <int G, bool kFlip, typename Rows>
+// column's kept score on the group's first lane, 0 on the others. kCaller: the
+// weights are the caller's (see kTinyWeight).
+template <int G, bool kFlip, bool kCaller, typename Rows>
 __device__ __forceinline__ double score_group(const WalkCtx& C, const Rows& rs, const WalkState* st, int q, bool in,
                                             int row, double a, GroupSmem& S) {
   const DevProblem& P = C.P;
@@ -343,17 +358,26 @@ __device__ __forceinline__ double score_group(const WalkCtx& C, const Rows& rs, 
     right[k] = p[k] > xb;
     v[k] = 0.0;
   }
-  if (third) {
+  bool tiny = false;
+  if constexpr (kCaller)
+    tiny = __any((has && (tiny_weight(r.w0) || tiny_weight(r.w1))) || (c != 0.0 && tiny_weight(st->wc)));
+  if (kCaller && tiny) {
     for (int e = 0; e < nt; ++e) {
       const GroupTerm t = term[e];
 #pragma unroll
-      for (int k = 0; k < kC; ++k) v[k] += term_at(t, p[k], right[k]);
+      for (int k = 0; k < kC; ++k) v[k] += term_at<true>(t, p[k], right[k]);
+    }
+  } else if (third) {
+    for (int e = 0; e < nt; ++e) {
+      const GroupTerm t = term[e];
+#pragma unroll
+      for (int k = 0; k < kC; ++k) v[k] += term_at<false>(t, p[k], right[k]);
     }
   } else {
     for (int e = 0; e < nt; ++e) {
       const GroupTerm t = term[e];
-      v[0] += term_at(t, p[0], right[0]);
-      v[1] += term_at(t, p[1], right[1]);
+      v[0] += term_at<false>(t, p[0], right[0]);
+      v[1] += term_at<false>(t, p[1], right[1]);
     }
   }
   double best = -HUGE_VAL, at = HUGE_VAL;
@@ -394,7 +418,7 @@ __device__ __forceinline__ void group_ids(const WalkCtx& C, const WalkState* st,
   o.tabu = st->k <= (int64_t)gmem((const int32_t*)C.tabu)[q];
 }
 
-template <int G, bool kFlip, typename Rows>
+template <int G, bool kFlip, bool kCaller, typename Rows>
 __device__ __forceinline__ GroupScore group_block(const WalkCtx& C, const Rows& rs, const WalkState* st, int cls,
                                                   int b, GroupSmem& S) {
   const PassPlan& L = C.plan;
@@ -406,7 +430,7 @@ __device__ __forceinline__ GroupScore group_block(const WalkCtx& C, const Rows& 
   const int q = min(qt, end - 1);
   GroupScore o;
   group_ids(C, st, ((int)threadIdx.x & (G - 1)) == 0, q, o);
-  o.s = score_group<G, kFlip, Rows>(C, rs, st, q, qt < end, row, a, S);
+  o.s = score_group<G, kFlip, kCaller, Rows>(C, rs, st, q, qt < end, row, a, S);
   o.q = qt < end ? q : -1;
   return o;
 }
@@ -439,9 +463,9 @@ __device__ __forceinline__ double flip_wave(const WalkCtx& C, const Rows& rs, co
 }
 
 // Workgroup b of the lane-group columns.
-template <typename Rows>
+template <bool kCaller, typename Rows>
 __device__ __forceinline__ GroupScore group_task(const WalkCtx& C, const Rows& rs, const WalkState* st, int b,
-                                           GroupSmem& S) {
+                                                 GroupSmem& S) {
   const int32_t* blk = C.plan.grp_blk;
   int c = 0;
 #pragma unroll
@@ -449,16 +473,16 @@ __device__ __forceinline__ GroupScore group_task(const WalkCtx& C, const Rows& r
     if (b >= blk[k]) c = k;
   b -= blk[c];
   switch (c) {
-    case 0: return group_block<4, true, Rows>(C, rs, st, 0, b, S);
-    case 1: return group_block<8, true, Rows>(C, rs, st, 1, b, S);
-    case 2: return group_block<16, true, Rows>(C, rs, st, 2, b, S);
-    case 3: return group_block<32, true, Rows>(C, rs, st, 3, b, S);
-    case 4: return group_block<64, true, Rows>(C, rs, st, 4, b, S);
-    case 5: return group_block<4, false, Rows>(C, rs, st, 5, b, S);
-    case 6: return group_block<8, false, Rows>(C, rs, st, 6, b, S);
-    case 7: return group_block<16, false, Rows>(C, rs, st, 7, b, S);
-    case 8: return group_block<32, false, Rows>(C, rs, st, 8, b, S);
-    case 9: return group_block<64, false, Rows>(C, rs, st, 9, b, S);
+    case 0: return group_block<4, true, kCaller, Rows>(C, rs, st, 0, b, S);
+    case 1: return group_block<8, true, kCaller, Rows>(C, rs, st, 1, b, S);
+    case 2: return group_block<16, true, kCaller, Rows>(C, rs, st, 2, b, S);
+    case 3: return group_block<32, true, kCaller, Rows>(C, rs, st, 3, b, S);
+    case 4: return group_block<64, true, kCaller, Rows>(C, rs, st, 4, b, S);
+    case 5: return group_block<4, false, kCaller, Rows>(C, rs, st, 5, b, S);
+    case 6: return group_block<8, false, kCaller, Rows>(C, rs, st, 6, b, S);
+    case 7: return group_block<16, false, kCaller, Rows>(C, rs, st, 7, b, S);
+    case 8: return group_block<32, false, kCaller, Rows>(C, rs, st, 8, b, S);
+    case 9: return group_block<64, false, kCaller, Rows>(C, rs, st, 9, b, S);
     default: {
       GroupScore o;
       const int q = C.plan.grp_col[kGroupClasses] + b * 4 + (int)(threadIdx.x >> 6);
@@ -474,7 +498,7 @@ __device__ __forceinline__ GroupScore group_task(const WalkCtx& C, const Rows& r
 
 // Eight wavefronts a SIMD (60 registers): 107.6 us for 64 walks of 28k columns,
 // 113.3 with seven; alone on a walk of 100k columns 10.5 either way.
-template <typename Rows>
+template <bool kCaller, typename Rows>
 __global__ __launch_bounds__(256, 8) void k_group(const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off,
                                                int32_t nw) {
   int lb;
@@ -488,7 +512,7 @@ __global__ __launch_bounds__(256, 8) void k_group(const WalkCtx* __restrict__ wa
   if (!active) return;
   __shared__ GroupSmem S;
   const Rows rs = rows_of<Rows>(C);
-  const GroupScore o = group_task<Rows>(C, rs, st, lb, S);
+  const GroupScore o = group_task<kCaller, Rows>(C, rs, st, lb, S);
   if (!rec) return;
   // the walk's move selection: this workgroup's best moves, and the pending
   // copy of a new incumbent (flagged by the previous iteration, before this
@@ -510,7 +534,7 @@ __device__ __forceinline__ void aff_group_body(const WalkCtx& C, const AffRun* r
   BestPair best;
   if (count < 0) {
     for (int t = b; t < C.plan.grp_blk[kGroupClasses]; t += nb) {
-      const GroupScore o = group_task<Rows>(C, rs, st, t, S);
+      const GroupScore o = group_task<false, Rows>(C, rs, st, t, S);
       if (rec && o.s > 0.0) best.offer(o.s, o.j, o.q, o.tabu);
     }
   } else {
@@ -528,9 +552,9 @@ __device__ __forceinline__ void aff_group_body(const WalkCtx& C, const AffRun* r
         a = gmem(C.P.col_val)[beg + lane];
       }
       if (q < n_flip)
-        o.s = score_group<kWave, true, Rows>(C, rs, st, q, true, row, a, S);
+        o.s = score_group<kWave, true, false, Rows>(C, rs, st, q, true, row, a, S);
       else
-        o.s = score_group<kWave, false, Rows>(C, rs, st, q, true, row, a, S);
+        o.s = score_group<kWave, false, false, Rows>(C, rs, st, q, true, row, a, S);
       if (rec && o.s > 0.0) best.offer(o.s, o.j, q, o.tabu);
     }
   }
@@ -2427,8 +2451,10 @@ hipError_t launch_pass_rows(const BatchLaunch& L, hipStream_t stream, const Pass
     if (e != hipSuccess) return e;
     s_long = ps->side;
   }
-  if (L.total[KS_GROUP] > 0)
-    CHAP_LAUNCH(k_group<Rows>, grid(KS_GROUP), dim3(256), 0, stream, L.walks, L.off[KS_GROUP], nw);
+  if (L.total[KS_GROUP] > 0 && L.caller_weights)
+    CHAP_LAUNCH((k_group<true, Rows>), grid(KS_GROUP), dim3(256), 0, stream, L.walks, L.off[KS_GROUP], nw);
+  else if (L.total[KS_GROUP] > 0)
+    CHAP_LAUNCH((k_group<false, Rows>), grid(KS_GROUP), dim3(256), 0, stream, L.walks, L.off[KS_GROUP], nw);
   // staged columns: the records (alone: they are bound by HBM), then the
   // scoring of every staged task and long-column chunk
   if (L.total[KS_STAGE] > 0)
