@@ -47,6 +47,7 @@ namespace chap {
 hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* L, std::vector<int32_t>* order) {
   const size_t nw = ctx.size();
   L->nw = (int32_t)nw;
+  for (const WalkCtx& c : ctx) L->stage_pairs = L->stage_pairs && c.plan.stage_pairs;
   std::vector<int32_t> xcd(nw, 0), perm(nw);
   std::iota(perm.begin(), perm.end(), 0);
   if (nw > 1) {
@@ -567,6 +568,21 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
         }
       }
   }
+  std::vector<LongTask> longs;
+  int64_t long_total = 0;
+  for (int32_t q = long_begin; q < n; ++q) {
+    const int32_t entries = ne[perm[q]] + 2;
+    int32_t cap = kSortCap[kSortCaps - 1];
+    while (cap < entries) cap <<= 1;
+    LongTask t;
+    t.col = q;
+    t.cap = cap;
+    t.offset = long_total;
+    long_total += cap;
+    longs.push_back(t);
+  }
+  L.n_partials = ccols.empty() ? 0 : ccols.back().first + ccols.back().nparts;
+  L.long_scratch = long_total;
   // staged tasks (narrow packs, then groups of short narrow columns of one
   // degree); the staged entries in (row block, task, column, row) order; the
   // segment table of every task and row block; workgroup slices of each row
@@ -591,26 +607,41 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     const size_t T = stasks.size();
     const int32_t nrb = (int32_t)(((int64_t)m + kStageRowBlock - 1) / kStageRowBlock);
     std::vector<std::vector<uint64_t>> ent_rb(nrb);
-    sseg.assign((T + 1) * (size_t)nrb, 0);
-    for (size_t t = 0; t < T; ++t) {
-      for (int32_t rb = 0; rb < nrb; ++rb) sseg[t * nrb + rb] = (int32_t)ent_rb[rb].size();
-      for (int32_t q = stasks[t].q_begin; q < stasks[t].q_end; ++q) {
-        const uint64_t lc = (uint64_t)(q - stasks[t].q_begin);
-        for (int32_t e = cptr[q]; e < cptr[q + 1]; ++e) {
-          const int32_t i = crow[e], rb = i / kStageRowBlock;
-          const uint64_t a24 = (uint64_t)((uint32_t)(int32_t)cval[e] & 0xFFFFFFu);
-          ent_rb[rb].push_back((uint64_t)(i - rb * kStageRowBlock) | (lc << 16) | (a24 << 24));
+    // a pack's segments hold whole pairs of records at even positions (`pairs`):
+    // its workgroup then reads two records at a time. Returns the entries.
+    auto stage_entries = [&](bool pairs) {
+      int64_t total = 0;
+      const uint64_t pad = (uint64_t)kStagePadSlot << 16 | (uint64_t)1 << 24;
+      for (auto& v : ent_rb) v.clear();
+      sseg.assign((T + 1) * (size_t)nrb, 0);
+      for (size_t t = 0; t < T; ++t) {
+        for (int32_t rb = 0; rb < nrb; ++rb) sseg[t * nrb + rb] = (int32_t)ent_rb[rb].size();
+        for (int32_t q = stasks[t].q_begin; q < stasks[t].q_end; ++q) {
+          const uint64_t lc = (uint64_t)(q - stasks[t].q_begin);
+          for (int32_t e = cptr[q]; e < cptr[q + 1]; ++e) {
+            const int32_t i = crow[e], rb = i / kStageRowBlock;
+            const uint64_t a24 = (uint64_t)((uint32_t)(int32_t)cval[e] & 0xFFFFFFu);
+            ent_rb[rb].push_back((uint64_t)(i - rb * kStageRowBlock) | (lc << 16) | (a24 << 24));
+          }
         }
+        if (pairs && (int32_t)t < npk)
+          for (auto& v : ent_rb)
+            if (v.size() & 1) v.push_back(pad);
       }
-      // a pack's segments hold whole pairs of records, at even positions: its
-      // workgroup reads two records at a time
-      if ((int32_t)t < npk)
-        for (auto& v : ent_rb)
-          if (v.size() & 1) v.push_back((uint64_t)kStagePadSlot << 16 | (uint64_t)1 << 24);
-    }
-    for (int32_t rb = 0; rb < nrb; ++rb) {
-      sseg[T * nrb + rb] = (int32_t)ent_rb[rb].size();
-      if (ent_rb[rb].size() & 1) ent_rb[rb].push_back((uint64_t)kStagePadSlot << 16 | (uint64_t)1 << 24);
+      for (int32_t rb = 0; rb < nrb; ++rb) {
+        sseg[T * nrb + rb] = (int32_t)ent_rb[rb].size();
+        if (pairs && (ent_rb[rb].size() & 1)) ent_rb[rb].push_back(pad);
+        total += (int64_t)ent_rb[rb].size();
+      }
+      return total;
+    };
+    int64_t bare = 0;
+    for (const StageTask& t : stasks) bare += cptr[t.q_end] - cptr[t.q_begin];
+    const int64_t padded = stage_entries(true);
+    if (padded > INT32_MAX ||
+        (noalloc_bytes(P.get(), padded) > kNoAllocBytes && noalloc_bytes(P.get(), bare) <= kNoAllocBytes)) {
+      (void)stage_entries(false);
+      L.stage_pairs = 0;
     }
     std::vector<std::vector<StageRowTask>> per_xcd(kXcds);
     // slices per row block: at most one per kStageSlice entries, and at most
@@ -702,19 +733,6 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     L.n_stage_rb = nrb;
     L.stage = (T > 0 || L.stage_one_end > L.stage_one_begin) ? 1 : 0;
     L.n_stage_units = L.stage ? (int32_t)sunits.size() : 0;
-  }
-  std::vector<LongTask> longs;
-  int64_t long_total = 0;
-  for (int32_t q = long_begin; q < n; ++q) {
-    const int32_t entries = ne[perm[q]] + 2;
-    int32_t cap = kSortCap[kSortCaps - 1];
-    while (cap < entries) cap <<= 1;
-    LongTask t;
-    t.col = q;
-    t.cap = cap;
-    t.offset = long_total;
-    long_total += cap;
-    longs.push_back(t);
   }
   P->perm = perm;
   // learned proposal: binaries and narrow columns of any length; general
@@ -951,7 +969,6 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     CHAP_HIP(A.upload(&dt, tasks));
     L.chunks = dt;
     L.n_chunks = (int32_t)tasks.size();
-    L.n_partials = ccols.back().first + ccols.back().nparts;
     ChunkCol* dc;
     CHAP_HIP(A.upload(&dc, ccols));
     L.chunk_cols = dc;
@@ -962,7 +979,6 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     CHAP_HIP(A.upload(&d, longs));
     L.long_tasks = d;
     L.n_long = (int32_t)longs.size();
-    L.long_scratch = long_total;
   }
   CHAP_HIP(A.alloc(&P->bs_x, (size_t)n));
   CHAP_HIP(A.alloc(&P->bs_xhat, (size_t)n));

@@ -18,7 +18,6 @@ using namespace chap;
 
 namespace {
 
-constexpr size_t kNoAllocBytes = (size_t)64 << 20;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
@@ -66,6 +65,38 @@ struct Carve {
   }
 };
 
+// Every per-call buffer of a pass over p: the walk context's, and the set-up's.
+struct Buffers {
+  int8_t* xc;
+  double* partial;
+  long long* objacc;
+  WalkCtx* rec;
+  uint32_t* ticket;
+};
+
+Buffers carve(const chap_problem* p, int64_t stage_ent, Carve& cv, WalkCtx& c) {
+  const size_t n = (size_t)p->n, m = (size_t)p->m;
+  const PassPlan& plan = p->plan;
+  c.x = cv.take<double>(n);
+  c.xhat = cv.take<double>(n);
+  c.s = cv.take<double>(n);
+  c.rs = cv.take<RowState>(m);
+  c.grow = p->compact_ok ? cv.take<GatherRow>(m) : nullptr;
+  c.st = cv.take<WalkState>(1);
+  c.partials = cv.take<ChunkPartial>((size_t)plan.n_partials);
+  c.long_pos = cv.take<double>((size_t)plan.long_scratch);
+  c.long_delta = cv.take<double>((size_t)plan.long_scratch);
+  c.long_marker = cv.take<int32_t>((size_t)plan.long_scratch);
+  c.stage_rec = cv.take<uint64_t>((size_t)stage_ent);
+  Buffers b;
+  b.xc = p->x_small ? cv.take<int8_t>(n) : nullptr;
+  b.partial = cv.take<double>(kInitPartial);
+  b.objacc = p->obj_fast ? nullptr : cv.take<long long>(kExactLimbs);
+  b.rec = cv.take<WalkCtx>(1);
+  b.ticket = cv.take<uint32_t>(1);
+  return b;
+}
+
 int scratch_of_device(int dev, void** out) {
   if (dev < 0 || dev >= kMaxDevices) return fail(CHAP_EINVAL, "chap_best_shift_noalloc: device index out of range");
   std::lock_guard<std::mutex> lock(g_mu);
@@ -81,6 +112,17 @@ int scratch_of_device(int dev, void** out) {
 }
 
 }  // namespace
+
+namespace chap {
+
+size_t noalloc_bytes(const chap_problem* p, int64_t stage_ent) {
+  Carve cv{nullptr, 0};
+  WalkCtx c{};
+  (void)carve(p, stage_ent, cv, c);
+  return cv.used;
+}
+
+}  // namespace chap
 
 extern "C" {
 
@@ -99,35 +141,20 @@ int chap_best_shift_noalloc(chap_problem* p, const double* d_x, const float* d_w
   void* base = nullptr;
   int rc = scratch_of_device(dev, &base);
   if (rc != CHAP_OK) return rc;
-  const int32_t n = p->n, m = p->m;
-  const PassPlan& plan = p->plan;
+  const int32_t n = p->n;
   Carve cv{(unsigned char*)base, kNoAllocBytes};
   WalkCtx c{};
   c.P = p->dev;
-  c.plan = plan;
-  c.x = cv.take<double>((size_t)n);
-  c.xhat = cv.take<double>((size_t)n);
-  c.s = cv.take<double>((size_t)n);
-  c.rs = cv.take<RowState>((size_t)m);
-  c.grow = p->compact_ok ? cv.take<GatherRow>((size_t)m) : nullptr;
-  c.st = cv.take<WalkState>(1);
-  c.partials = cv.take<ChunkPartial>((size_t)plan.n_partials);
-  c.long_pos = cv.take<double>((size_t)plan.long_scratch);
-  c.long_delta = cv.take<double>((size_t)plan.long_scratch);
-  c.long_marker = cv.take<int32_t>((size_t)plan.long_scratch);
-  c.stage_rec = cv.take<uint64_t>((size_t)plan.n_stage_ent);
-  int8_t* xc = p->x_small ? cv.take<int8_t>((size_t)n) : nullptr;
-  double* partial = cv.take<double>(kInitPartial);
-  uint32_t* ticket = cv.take<uint32_t>(1);
-  long long* objacc = p->obj_fast ? nullptr : cv.take<long long>(kExactLimbs);
-  WalkCtx* rec = cv.take<WalkCtx>(1);
+  c.plan = p->plan;
+  const Buffers b = carve(p, p->plan.n_stage_ent, cv, c);
   if (cv.used > cv.cap)
     return fail(CHAP_EINVAL, "chap_best_shift_noalloc: this problem needs " + std::to_string(cv.used) +
                                  " bytes of scratch, more than the " + std::to_string(kNoAllocBytes) +
                                  " the entry point holds per device (use chap_best_shift)");
   BatchLaunch L;
   L.nw = 1;
-  L.walks = rec;
+  L.walks = b.rec;
+  L.stage_pairs = c.plan.stage_pairs;
   for (int k = 0; k < KS_COUNT; ++k) {
     L.total[k] = kernel_blocks(c, k);
     L.grid[k] = L.total[k];
@@ -146,13 +173,13 @@ int chap_best_shift_noalloc(chap_problem* p, const double* d_x, const float* d_w
     init.cutoff_w = d_w + p->mp;
     init.obj_integral = p->obj_integral;
   }
-  hipLaunchKernelGGL(k_noalloc_begin, dim3((unsigned)std::max(1, (n + 255) / 256)), dim3(256), 0, s, c, rec, ticket,
-                     init, p->dev.perm, d_x, c.x, xc, c.st, epoch, n);
+  hipLaunchKernelGGL(k_noalloc_begin, dim3((unsigned)std::max(1, (n + 255) / 256)), dim3(256), 0, s, c, b.rec,
+                     b.ticket, init, p->dev.perm, d_x, c.x, b.xc, c.st, epoch, n);
   CHAP_HIP(hipGetLastError());
   if (cut)
-    CHAP_HIP(launch_state_init(p->dev, c.x, c.rs, c.st, partial, ticket, objacc, 1, 0, p->obj_integral, cutoff_rhs,
-                               d_w + p->mp, 0, 0, s));
-  CHAP_HIP(launch_residual_scatter(p->dev, p->d_nidx, p->d_pair, d_w, c.x, xc, c.st, epoch, c.rs, s, c.grow));
+    CHAP_HIP(launch_state_init(p->dev, c.x, c.rs, c.st, b.partial, b.ticket, b.objacc, 1, 0, p->obj_integral,
+                               cutoff_rhs, d_w + p->mp, 0, 0, s));
+  CHAP_HIP(launch_residual_scatter(p->dev, p->d_nidx, p->d_pair, d_w, c.x, b.xc, c.st, epoch, c.rs, s, c.grow));
   if (n > 0) CHAP_HIP(launch_pass(L, s, nullptr, false));
   CHAP_HIP(launch_gather2(p->d_inv, c.xhat, c.s, d_shift, d_score, n, s));
   return CHAP_OK;

@@ -395,6 +395,12 @@ struct PassPlan {
   // record of the task in each row block, then the task's records in the
   // blocks before each block (the last value: all of them)
   int32_t stage = 0;
+  // 1: the segments of packs are padded to whole pairs of records at even
+  // positions, which k_stage_score then loads 16 bytes at a time; 0 where the
+  // padding (a few per cent of the records) would be what takes the problem
+  // over the scratch of chap_best_shift_noalloc, or the entries over 2^31. A
+  // batch reads single records when any of its problems is not padded.
+  int32_t stage_pairs = 1;
   int32_t stage_exact = 0;  // the integer breakpoint identity holds (staging eligible)
   int32_t n_stage_tasks = 0;
   int32_t n_stage_packs = 0;
@@ -493,6 +499,7 @@ struct BatchLaunch {
   // 0: the pass gathers RowState; 1: every walk keeps a GatherRow copy and the
   // pass gathers it; 2: the copy is used where WalkState::compact_rows says so
   int32_t compact = 0;
+  int32_t stage_pairs = 1;     // every walk's PassPlan::stage_pairs
   int32_t caller_weights = 0;  // a single pass: any weight a float holds (a walk's are counts)
   const WalkCtx* walks = nullptr;
   const int32_t* off[KS_COUNT] = {};
@@ -1170,5 +1177,9 @@ int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<
 // Device copy of the walk contexts and the per-kernel launch tables; a batch
 // is reordered by XCD (order[i]: caller's index of ctx[i]; may be null).
 hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* L, std::vector<int32_t>* order);
+// Scratch bytes that chap_best_shift_noalloc needs for p with stage_ent staged
+// entries, and what it has.
+size_t noalloc_bytes(const chap_problem* p, int64_t stage_ent);
+constexpr size_t kNoAllocBytes = (size_t)64 << 20;
 int blocks_for_host(int64_t work, int cap);
 }  // namespace chap

@@ -1142,7 +1142,9 @@ __device__ __forceinline__ void rec_weights(uint64_t r, bool wts, const Rows& rs
 // that also hold beta (bin 0) and alpha (bin xbar - l + 1), so the score of
 // position l + k is the prefix sum of bins 0..k; one lane per column then
 // scans its bins and keeps the best candidate (smallest position on ties).
-template <typename Rows, typename V>
+// kPairs: the records of every segment are whole pairs at even positions (see
+// PassPlan::stage_pairs).
+template <bool kPairs, typename Rows, typename V>
 __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, bool wts, int tix, StagePackSmem<V>& S,
                                            StageSegs& G) {
   constexpr int kCols = StagePackSmem<V>::kCols;
@@ -1154,8 +1156,9 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
   const V zero = 0;
   const int nrb = C.plan.n_stage_rb;
   stage_segments(C, tix, G);
-  typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
-  const gptr<const u64x2> recs = (gptr<const u64x2>)gmem((const uint64_t*)C.stage_rec);
+  constexpr int kPer = kPairs ? 2 : 1;  // records per load
+  typedef unsigned long long Unit __attribute__((ext_vector_type(kPer)));
+  const gptr<const Unit> recs = (gptr<const Unit>)gmem((const uint64_t*)C.stage_rec);
   for (int c0 = 0; c0 < nc; c0 += kCols) {
     const int ncw = min(kCols, nc - c0);
     if (tid < ncw) {
@@ -1171,27 +1174,27 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
     for (int i = tid; i < ncw * (kNarrowBins + 1); i += blockDim.x)
       S.bins[i / (kNarrowBins + 1)][i % (kNarrowBins + 1)] = 0;
     __syncthreads();
-    // every thread takes an equal contiguous share of the task's record pairs
-    // (in segment order, crossing row-block segments, which hold whole pairs),
-    // kRun of them per step, 16 bytes each; records of columns outside this
-    // window (and padding) are skipped
-    constexpr int kRun = 2;
+    // every thread takes an equal contiguous share of the task's records (in
+    // segment order, crossing row-block segments), kRun loads of kPer of them
+    // per step; records of columns outside this window (and padding) are
+    // skipped
+    constexpr int kRun = 4 / kPer;
     {
-      const int total = G.pre[nrb] >> 1;
+      const int total = G.pre[nrb] / kPer;
       const int per = (total + (int)blockDim.x - 1) / (int)blockDim.x;
       const int f0 = min(total, tid * per), f1 = min(total, f0 + per);
       // segment of f0: the last one starting at or before it
       int lo = 0, hi = nrb - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (G.pre[mid] <= 2 * f0)
+        if (G.pre[mid] <= kPer * f0)
           lo = mid;
         else
           hi = mid - 1;
       }
       int sg = lo;
-      int base = (G.beg[sg] - G.pre[sg]) >> 1;  // pair index of flat pair f: base + f
-      int send = G.pre[sg + 1] >> 1;
+      int base = (G.beg[sg] - G.pre[sg]) / kPer;  // load index of the f-th load: base + f
+      int send = G.pre[sg + 1] / kPer;
       // a thread's run is sorted by column within a segment: beta, alpha and
       // the candidate mask of the current column stay in registers until the
       // column changes
@@ -1208,15 +1211,15 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
         rc_ = 0ull;
       };
       for (int f = f0; f < f1; f += kRun) {
-        u64x2 r[kRun];
+        Unit r[kRun];
 #pragma unroll
         for (int u = 0; u < kRun; ++u) {
           const int fu = f + u;
           if (fu < f1) {
             while (fu >= send) {
               ++sg;
-              base = (G.beg[sg] - G.pre[sg]) >> 1;
-              send = G.pre[sg + 1] >> 1;
+              base = (G.beg[sg] - G.pre[sg]) / kPer;
+              send = G.pre[sg + 1] / kPer;
             }
             r[u] = recs[base + fu];
           }
@@ -1225,8 +1228,8 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
         for (int u = 0; u < kRun; ++u) {
           if (f + u >= f1) break;
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const uint64_t rec = h ? r[u].y : r[u].x;
+          for (int h = 0; h < kPer; ++h) {
+            const uint64_t rec = r[u][h];
             const uint32_t lo = (uint32_t)rec;
             const int lc = (int)(lo & 0xFFu) - c0;
             if (lc < 0 || lc >= ncw) continue;
@@ -1777,7 +1780,7 @@ union StageScoreSmem {
   StageShortSmem sh;
 };
 
-template <typename Rows>
+template <bool kPairs, typename Rows>
 __device__ __forceinline__ void stage_score_body(const WalkCtx& C, int lb, StageScoreSmem& sm, StageSegs& G) {
   const int32_t unit = gmem(C.plan.stage_units)[lb / kXcds];
   const int role = unit >> 28;
@@ -1793,16 +1796,16 @@ __device__ __forceinline__ void stage_score_body(const WalkCtx& C, int lb, Stage
     const int t = stage_task_of(rb, npk);
     if (t < 0) return;
     if (wts)
-      stage_pack<Rows, int32_t>(C, rs, true, t, sm.pack_i, G);
+      stage_pack<kPairs, Rows, int32_t>(C, rs, true, t, sm.pack_i, G);
     else
-      stage_pack<Rows, double>(C, rs, false, t, sm.pack_d, G);
+      stage_pack<kPairs, Rows, double>(C, rs, false, t, sm.pack_d, G);
     return;
   }
   const int t = stage_task_of(rb, C.plan.n_stage_tasks - npk);
   if (t >= 0) stage_short<Rows>(C, rs, wts, npk + t, sm.sh, G);
 }
 
-template <typename Rows>
+template <bool kPairs, typename Rows>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_stage_score(
     const WalkCtx* __restrict__ walks, const int32_t* __restrict__ off, int32_t nw) {
   int lb;
@@ -1814,11 +1817,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   __shared__ StageSegs G;
   if constexpr (std::is_same<Rows, DualRows>::value) {
     if (C.st->compact_rows)
-      stage_score_body<CompactRows>(C, lb, sm, G);
+      stage_score_body<kPairs, CompactRows>(C, lb, sm, G);
     else
-      stage_score_body<FullRows>(C, lb, sm, G);
+      stage_score_body<kPairs, FullRows>(C, lb, sm, G);
   } else {
-    stage_score_body<Rows>(C, lb, sm, G);
+    stage_score_body<kPairs, Rows>(C, lb, sm, G);
   }
 }
 
@@ -2464,9 +2467,12 @@ hipError_t launch_pass_rows(const BatchLaunch& L, hipStream_t stream, const Pass
   // may hold both, and k_narrow_combine then waits for both (after the join)
   bool combine_after_join = false;
   const bool combine = L.total[KS_COMBINE] > 0 && !(defer_combine && pass_defers_combine(L));
-  if (L.total[KS_STAGE_SCORE] > 0)
-    CHAP_LAUNCH(k_stage_score<Rows>, grid(KS_STAGE_SCORE), dim3(256), 0, stream, L.walks, L.off[KS_STAGE_SCORE],
-                nw);
+  if (L.total[KS_STAGE_SCORE] > 0 && L.stage_pairs)
+    CHAP_LAUNCH((k_stage_score<true, Rows>), grid(KS_STAGE_SCORE), dim3(256), 0, stream, L.walks,
+                L.off[KS_STAGE_SCORE], nw);
+  else if (L.total[KS_STAGE_SCORE] > 0)
+    CHAP_LAUNCH((k_stage_score<false, Rows>), grid(KS_STAGE_SCORE), dim3(256), 0, stream, L.walks,
+                L.off[KS_STAGE_SCORE], nw);
   if (L.total[KS_CHUNK] > 0)
     CHAP_LAUNCH(k_narrow_chunk<Rows>, grid(KS_CHUNK), dim3(256), 0, s_long, L.walks, L.off[KS_CHUNK], nw);
   if (combine) {
