@@ -47,7 +47,10 @@ namespace chap {
 hipError_t build_launch(DeviceArena& A, std::vector<WalkCtx>& ctx, BatchLaunch* L, std::vector<int32_t>* order) {
   const size_t nw = ctx.size();
   L->nw = (int32_t)nw;
-  for (const WalkCtx& c : ctx) L->stage_pairs = L->stage_pairs && c.plan.stage_pairs;
+  for (const WalkCtx& c : ctx) {
+    L->stage_pairs = L->stage_pairs && c.plan.stage_pairs;
+    L->step_shares = L->step_shares || c.apply_blocks >= share_min(c);
+  }
   std::vector<int32_t> xcd(nw, 0), perm(nw);
   std::iota(perm.begin(), perm.end(), 0);
   if (nw > 1) {

@@ -20,6 +20,7 @@ __device__ __forceinline__ void reset_state(WalkState* st, int64_t iters, int32_
   st->mv_j = -1;
   st->mv_kind = 2;
   st->dV = 0ull;
+  st->choice = 0ull;
   // single passes: the compact copy holds the cutoff weight as a count of
   // half weights only when it is an integer below 2^16 (the rows are
   // checked where the copy is written)

@@ -246,6 +246,10 @@ struct __align__(16) WalkState {
   // workgroups of the move kernel that are done (low 16 bits) and, above, the
   // sum of their violation changes (two's complement)
   unsigned long long dV;
+  // an iteration whose choice needed a scan by one workgroup (k_step): its
+  // number + 1 (40 bits), the choice (2 bits), the shares of the application
+  // taken so far (22 bits)
+  unsigned long long choice;
   int32_t compact_rows;   // single passes: the compact row copy is exact for these weights
   // the call (epoch) whose point did not fit the byte copy of x (see
   // launch_stage_x); 0 after the state is cleared
@@ -472,6 +476,13 @@ struct WalkCtx {
   int32_t recompute;
 };
 
+// Workgroups of the move kernel from which they share an application that waits
+// for workgroup 0's scan; below, it does all of it alone. The wait and the shares
+// cost 2 us, what eight workgroups save on 4096 rows each (reweights of 20k rows
+// 27.0 us alone, 27.4 shared; of 40k 28.5 and 27.9; of 100k 32.6 and 28.5); rows
+// that are summed again take far longer.
+__host__ __device__ inline int32_t share_min(const WalkCtx& c) { return c.recompute ? 2 : 8; }
+
 // Kernels of one iteration; each has its own per-walk block counts.
 enum KernelSlot {
   KS_GROUP = 0,
@@ -499,6 +510,7 @@ struct BatchLaunch {
   // 0: the pass gathers RowState; 1: every walk keeps a GatherRow copy and the
   // pass gathers it; 2: the copy is used where WalkState::compact_rows says so
   int32_t compact = 0;
+  int32_t step_shares = 0;     // some walk has share_min() workgroups of the move kernel
   int32_t stage_pairs = 1;     // every walk's PassPlan::stage_pairs
   int32_t caller_weights = 0;  // a single pass: any weight a float holds (a walk's are counts)
   const WalkCtx* walks = nullptr;

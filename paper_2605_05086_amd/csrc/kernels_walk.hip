@@ -741,8 +741,14 @@ __global__ __launch_bounds__(256) void k_argmax(const WalkCtx* __restrict__ walk
 // Tabu/aspiration: a tabu overall best is taken only if its move leaves no
 // violated row; since a move changes at most one violation per normalised
 // entry of its column, that is impossible while V exceeds the column's entry
-// count, and the column is only scanned otherwise, then by workgroup 0, which
-// also does the rest alone (the others must not change rows it still reads).
+// count, and the column is only scanned otherwise, then by workgroup 0. The
+// others must not change rows that it still reads: those that could share the
+// application wait for its choice (one word of the walk state) and then take
+// shares of it as they come, workgroup 0 too, so that every share is done whether
+// or not a waiting workgroup gave up. Where the outcomes ask for few workgroups
+// nobody waits (share_min). With all of it left to workgroup 0 a reweight of 1M
+// rows made an iteration 134 us, now 33; a move of 20k rows summed again took 658
+// us, now 80.
 //
 // Application: the move's rows, or the weights of every violated row (a
 // reweight), over as many workgroups as their number asks for; the others
@@ -767,8 +773,43 @@ struct StepSmem {
   MoveRecord rec[kStepWaves];
   int red[kStepWaves];
   long long total;
+  unsigned long long word;
   int last;
 };
+
+// WalkState::choice. A waiting workgroup asks at most kStepPolls times, half a
+// microsecond apart (a scan takes about 1.5 us per 1024 entries), and then leaves.
+enum { kChoiceNone = 0, kChoiceAll = 1, kChoiceFree = 2 };  // no move, the overall best, the best not tabu
+constexpr int kStepPolls = 4096;
+constexpr int kChoiceShift = 22;
+constexpr unsigned long long kChoiceShares = (1ull << kChoiceShift) - 1;
+__device__ __forceinline__ unsigned long long choice_tag(int64_t k) { return (unsigned long long)(k + 1) << (kChoiceShift + 2); }
+__device__ __forceinline__ bool choice_of(unsigned long long word, int64_t k) {
+  return word >> (kChoiceShift + 2) == choice_tag(k) >> (kChoiceShift + 2);
+}
+
+// The choice of iteration k as workgroup 0 stores it, or -1. Whole workgroup.
+__device__ __forceinline__ int step_await(WalkState* st, int64_t k, StepSmem& S) {
+  if (threadIdx.x == 0) {
+    unsigned long long w = 0;
+    for (int i = 0; i < kStepPolls; ++i) {
+      w = __hip_atomic_load(&st->choice, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (choice_of(w, k)) break;
+      __builtin_amdgcn_s_sleep(16);
+    }
+    S.word = w;
+  }
+  __syncthreads();
+  return choice_of(S.word, k) ? (int)(S.word >> kChoiceShift) & 3 : -1;
+}
+
+// The next share of the application. Whole workgroup.
+__device__ __forceinline__ int step_share(WalkState* st, StepSmem& S) {
+  __syncthreads();
+  if (threadIdx.x == 0) S.word = atomicAdd(&st->choice, 1ull);
+  __syncthreads();
+  return (int)(S.word & kChoiceShares);
+}
 
 // Sum over the workgroup (a thread's violation changes fit 32 bits, and so do
 // a wavefront's).
@@ -900,7 +941,10 @@ __device__ __forceinline__ void step_finish(const WalkCtx& C, const StepMove& M,
 
 // lc: null for an iteration over every column (no admissible move: a
 // reweight); else a proposal iteration over nrec records (no admissible move:
-// a stall, which makes no reweight and idles the rest of its block).
+// a stall, which makes no reweight and idles the rest of its block). kShare: some
+// walk may share an application (the code for it costs a walk of one workgroup
+// 0.15 us an iteration).
+template <bool kShare>
 __global__ __launch_bounds__(kStepThreads) void k_step(const WalkCtx* __restrict__ walks,
                                                        const int32_t* __restrict__ off, int32_t nw,
                                                        const LearnCtx* lc, int32_t nrec) {
@@ -959,25 +1003,52 @@ __global__ __launch_bounds__(kStepThreads) void k_step(const WalkCtx* __restrict
   const int qa = b.all.q;
   const gptr<const double> x = gmem((const double*)C.x), xhat = gmem((const double*)C.xhat),
                            sc = gmem((const double*)C.s);
-  bool solo = false;
+  // the workgroups that the move of a column of deg entries, or (none) an
+  // outcome without a move, is divided among. A row summed again: by a wavefront
+  // while that leaves few rounds, else by kResidualLanes lanes (a short row leaves
+  // most of a wavefront idle)
+  auto deg_of = [&](int q) { return P.col_ptr[q + 1] - P.col_ptr[q]; };
+  auto rows_by_wave = [&](int deg) { return deg <= C.apply_blocks * kStepWaves * 2; };
+  auto blocks_of = [&](bool none, int deg) {
+    if (none) return lc ? 1 : C.apply_blocks;
+    const int per = C.recompute ? (rows_by_wave(deg) ? kStepWaves : kStepThreads / kResidualLanes) : kStepThreads;
+    return max(1, min(C.apply_blocks, (deg + per - 1) / per));
+  };
+  bool solo = false;    // workgroup 0 does the whole iteration
+  bool shares = false;  // the application's shares are taken as the workgroups come
   if (qa >= 0 && b.all.j == b.free.j) {
     M.q = qa;
     M.j = b.all.j;
     M.kind = 0;
   } else if (qa >= 0) {
     const int64_t V = st->sel_V;
-    const int64_t bound = 2 * (int64_t)(P.col_ptr[qa + 1] - P.col_ptr[qa]) + 1;
-    bool aspire = false;
-    if (V <= bound) {
-      if (lb != 0) return;
-      solo = true;
-      aspire = V + step_violations(C, qa, xhat[qa] - x[qa], S) == 0;
+    const int deg = deg_of(qa);
+    const int64_t bound = 2 * (int64_t)deg + 1;
+    int choice = b.free.q >= 0 ? kChoiceFree : kChoiceNone;
+    if (__builtin_expect(V <= bound, 0)) {  // out of the way of the other iterations' code
+      const bool none = b.free.q < 0;
+      const int least = share_min(C);
+      int most = 1;
+      if (kShare && C.apply_blocks >= least)
+        most = max(blocks_of(false, deg), blocks_of(none, none ? 0 : deg_of(b.free.q)));
+      shares = most >= least;
+      solo = !shares;
+      if (lb >= (shares ? most : 1)) return;
+      if (lb == 0) {
+        if (V + step_violations(C, qa, xhat[qa] - x[qa], S) == 0) choice = kChoiceAll;
+        if (shares && tid == 0)
+          __hip_atomic_store(&st->choice, choice_tag(k) | (unsigned long long)choice << kChoiceShift, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        choice = step_await(st, k, S);
+        if (choice < 0) return;
+      }
     }
-    if (aspire) {
+    if (choice == kChoiceAll) {
       M.q = qa;
       M.j = b.all.j;
       M.kind = 1;
-    } else if (b.free.q >= 0) {
+    } else if (choice == kChoiceFree) {
       M.q = b.free.q;
       M.j = b.free.j;
       M.kind = 0;
@@ -994,98 +1065,92 @@ __global__ __launch_bounds__(kStepThreads) void k_step(const WalkCtx* __restrict
     M.score = sc[M.q];
     M.c = gmem(P.obj)[M.q];
   }
-  const int deg = end - beg;
   const bool resum = M.q >= 0 && C.recompute;
-  // a row summed again: by a wavefront while that leaves few rounds, else by
-  // kResidualLanes lanes (a short row leaves most of a wavefront idle)
-  const bool by_wave = resum && deg <= C.apply_blocks * kStepWaves * 2;
-  int nb = C.apply_blocks;
-  if (M.q >= 0) {
-    const int per = resum ? (by_wave ? kStepWaves : kStepThreads / kResidualLanes) : kStepThreads;
-    nb = max(1, min(nb, (deg + per - 1) / per));
-  } else if (M.kind == kStallKind) {
-    nb = 1;
-  }
-  if (solo) nb = 1;
-  if (lb >= nb) return;
-  const int gt = lb * kStepThreads + tid, gs = nb * kStepThreads;
+  const bool by_wave = resum && rows_by_wave(end - beg);
+  const int nb = solo ? 1 : blocks_of(M.q < 0, end - beg);
   RowState* rs = C.rs;
-  int dv = 0;  // this thread's violation changes
-  if (resum) {
-    // every touched row is summed again in its stored order (products side by
-    // side, added in entry order); its state and right-hand side q, rhs
-    auto update = [&](int i, RowState q, double rhs, double acc) {
-      const double r2 = acc - rhs;
-      rs[i].r = r2;
-      if (C.grow) C.grow[i].r = (int32_t)r2;
-      dv += viol_change(q.r, r2, eps);
-      if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
-    };
-    if (by_wave) {
-      for (int e = __builtin_amdgcn_readfirstlane(beg + gt / kWave); e < end; e += gs / kWave) {
-        const int i = __builtin_amdgcn_readfirstlane(P.col_row[e]);
-        const RowState q = rs[i];
-        const double rhs = P.row_rhs[i];
-        const double acc = wave_row_sum(P, C.x, __builtin_amdgcn_readfirstlane(P.row_ptr[i]),
-                                        __builtin_amdgcn_readfirstlane(P.row_ptr[i + 1]), M.q, M.x_new);
-        if (lane == 0) update(i, q, rhs, acc);
-      }
-    } else {
-      const int g = gt & (kResidualLanes - 1);
-      for (int e = beg + gt / kResidualLanes; e < end; e += gs / kResidualLanes) {
-        const int i = P.col_row[e];
-        double acc = 0.0;
-        const int rb = P.row_ptr[i], re = P.row_ptr[i + 1];
-        for (int e0 = rb; e0 < re; e0 += kResidualLanes) {
-          const int f = e0 + g;
-          double prod = 0.0;
-          if (f < re) {
-            const int c = P.row_col[f];
-            prod = P.row_val[f] * ((c == M.q) ? M.x_new : x[c]);
+  // one share of the application; this thread's violation changes
+  auto apply = [&](int share) {
+    const int gt = share * kStepThreads + tid, gs = nb * kStepThreads;
+    int dv = 0;  // this thread's violation changes
+    if (resum) {
+      // every touched row is summed again in its stored order (products side by
+      // side, added in entry order); its state and right-hand side q, rhs
+      auto update = [&](int i, RowState q, double rhs, double acc) {
+        const double r2 = acc - rhs;
+        rs[i].r = r2;
+        if (C.grow) C.grow[i].r = (int32_t)r2;
+        dv += viol_change(q.r, r2, eps);
+        if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
+      };
+      if (by_wave) {
+        for (int e = __builtin_amdgcn_readfirstlane(beg + gt / kWave); e < end; e += gs / kWave) {
+          const int i = __builtin_amdgcn_readfirstlane(P.col_row[e]);
+          const RowState q = rs[i];
+          const double rhs = P.row_rhs[i];
+          const double acc = wave_row_sum(P, C.x, __builtin_amdgcn_readfirstlane(P.row_ptr[i]),
+                                          __builtin_amdgcn_readfirstlane(P.row_ptr[i + 1]), M.q, M.x_new);
+          if (lane == 0) update(i, q, rhs, acc);
+        }
+      } else {
+        const int g = gt & (kResidualLanes - 1);
+        for (int e = beg + gt / kResidualLanes; e < end; e += gs / kResidualLanes) {
+          const int i = P.col_row[e];
+          double acc = 0.0;
+          const int rb = P.row_ptr[i], re = P.row_ptr[i + 1];
+          for (int e0 = rb; e0 < re; e0 += kResidualLanes) {
+            const int f = e0 + g;
+            double prod = 0.0;
+            if (f < re) {
+              const int c = P.row_col[f];
+              prod = P.row_val[f] * ((c == M.q) ? M.x_new : x[c]);
+            }
+            const int cnt = min(kResidualLanes, re - e0);
+            for (int t = 0; t < cnt; ++t) acc = acc + __shfl(prod, t, kResidualLanes);
           }
-          const int cnt = min(kResidualLanes, re - e0);
-          for (int t = 0; t < cnt; ++t) acc = acc + __shfl(prod, t, kResidualLanes);
+          if (g == 0) update(i, rs[i], P.row_rhs[i], acc);
         }
-        if (g == 0) update(i, rs[i], P.row_rhs[i], acc);
       }
-    }
-  } else if (M.q >= 0) {
-    const double d = M.x_new - M.x_old;
-    for (int e = beg + gt; e < end; e += gs) {
-      const int i = P.col_row[e];
-      const RowState q = rs[i];
-      const double r2 = q.r + P.col_val[e] * d;
-      rs[i].r = r2;
-      if (C.grow) C.grow[i].r = (int32_t)r2;
-      dv += viol_change(q.r, r2, eps);
-      if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
-    }
-  } else if (M.kind != kStallKind) {
-    constexpr int kU = 4;  // rows per thread and step, loaded before any is used
-    for (int64_t i0 = gt; i0 < P.ms; i0 += (int64_t)kU * gs) {
-      RowState q[kU];
+    } else if (M.q >= 0) {
+      const double d = M.x_new - M.x_old;
+      for (int e = beg + gt; e < end; e += gs) {
+        const int i = P.col_row[e];
+        const RowState q = rs[i];
+        const double r2 = q.r + P.col_val[e] * d;
+        rs[i].r = r2;
+        if (C.grow) C.grow[i].r = (int32_t)r2;
+        dv += viol_change(q.r, r2, eps);
+        if (q.w1 >= 0.0f) dv += viol_change(-q.r, -r2, eps);
+      }
+    } else if (M.kind != kStallKind) {
+      constexpr int kU = 4;  // rows per thread and step, loaded before any is used
+      for (int64_t i0 = gt; i0 < P.ms; i0 += (int64_t)kU * gs) {
+        RowState q[kU];
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t i = i0 + (int64_t)u * gs;
-        q[u] = i < P.ms ? rs[i] : RowState{0.0, 0.0f, -1.0f};
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t i = i0 + (int64_t)u * gs;
-        if (q[u].r > eps) {
-          rs[i].w0 = q[u].w0 + 1.0f;
-          if (C.grow) C.grow[i].w0 = (uint16_t)(q[u].w0 + 1.0f);
+        for (int u = 0; u < kU; ++u) {
+          const int64_t i = i0 + (int64_t)u * gs;
+          q[u] = i < P.ms ? rs[i] : RowState{0.0, 0.0f, -1.0f};
         }
-        if (q[u].w1 >= 0.0f && -q[u].r > eps) {
-          rs[i].w1 = q[u].w1 + 1.0f;
-          if (C.grow) C.grow[i].w1 = (uint16_t)(q[u].w1 + 1.0f);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int64_t i = i0 + (int64_t)u * gs;
+          if (q[u].r > eps) {
+            rs[i].w0 = q[u].w0 + 1.0f;
+            if (C.grow) C.grow[i].w0 = (uint16_t)(q[u].w0 + 1.0f);
+          }
+          if (q[u].w1 >= 0.0f && -q[u].r > eps) {
+            rs[i].w1 = q[u].w1 + 1.0f;
+            if (C.grow) C.grow[i].w1 = (uint16_t)(q[u].w1 + 1.0f);
+          }
         }
       }
     }
-  }
-  // ---- the last workgroup ends the iteration
-  long long dV = step_sum(dv, S);
-  if (nb > 1) {
+    return dv;
+  };
+  // adds a share's violation changes; true where all shares are done, with the sum
+  auto all_done = [&](int dv, long long& dV) {
+    dV = step_sum(dv, S);
+    if (nb == 1) return true;
     if (tid == 0) {
       const unsigned long long mine = ((unsigned long long)dV << 16) + 1ull;
       const unsigned long long sum = atomicAdd(&st->dV, mine) + mine;
@@ -1093,9 +1158,18 @@ __global__ __launch_bounds__(kStepThreads) void k_step(const WalkCtx* __restrict
       S.total = (long long)sum >> 16;
     }
     __syncthreads();
-    if (!S.last) return;
     dV = S.total;
+    return S.last != 0;
+  };
+  long long dV;
+  int share = kShare && shares ? step_share(st, S) : lb;
+  while (true) {
+    if (share >= nb) return;
+    if (all_done(apply(share), dV)) break;
+    if (!kShare || __builtin_expect(!shares, 1)) return;
+    share = step_share(st, S);
   }
+  // ---- the workgroup of the last share ends the iteration
   if (wv != 0) return;
   step_finish(C, M, dV, T);
   if (lc && lane == 0) {
@@ -1550,21 +1624,26 @@ hipError_t launch_state_init(const DevProblem& P, const double* x, const RowStat
   return hipGetLastError();
 }
 
+static hipError_t launch_step(const BatchLaunch& L, const LearnCtx* lc, int32_t nrec, hipStream_t stream) {
+  const dim3 grid((unsigned)L.grid[KS_STEP]);
+  if (L.step_shares)
+    hipLaunchKernelGGL(k_step<true>, grid, dim3(kStepThreads), 0, stream, L.walks, L.off[KS_STEP], L.nw, lc, nrec);
+  else
+    hipLaunchKernelGGL(k_step<false>, grid, dim3(kStepThreads), 0, stream, L.walks, L.off[KS_STEP], L.nw, lc, nrec);
+  return hipGetLastError();
+}
+
 hipError_t launch_walk_step(const BatchLaunch& L, hipStream_t stream, bool combine) {
   const int nw = L.nw;
   const int32_t comb = (combine && pass_defers_combine(L)) ? 1 : 0;
   if (L.total[KS_ARGMAX] > 0)
     hipLaunchKernelGGL(k_argmax, dim3((unsigned)L.grid[KS_ARGMAX]), dim3(256), 0, stream, L.walks, L.off[KS_ARGMAX],
                        nw, comb);
-  hipLaunchKernelGGL(k_step, dim3((unsigned)L.grid[KS_STEP]), dim3(kStepThreads), 0, stream, L.walks, L.off[KS_STEP],
-                     nw, nullptr, 0);
-  return hipGetLastError();
+  return launch_step(L, nullptr, 0, stream);
 }
 
 hipError_t launch_subset_step(const BatchLaunch& L, const LearnCtx* lc, int32_t nrec, hipStream_t stream) {
-  hipLaunchKernelGGL(k_step, dim3((unsigned)L.grid[KS_STEP]), dim3(kStepThreads), 0, stream, L.walks, L.off[KS_STEP],
-                     L.nw, lc, nrec);
-  return hipGetLastError();
+  return launch_step(L, lc, nrec, stream);
 }
 
 hipError_t launch_subset_none(const WalkCtx* C, const LearnCtx* L, hipStream_t s) {
