@@ -160,8 +160,9 @@ int chap_problem_norm_row_map(const chap_problem *p, int32_t *orig_row, int8_t *
  *   d_shift    device, n doubles, out: xhat_j.
  *   d_score    device, n doubles, out: s_j (> 0, or 0 when no improvement).
  *   hip_stream hipStream_t to run on (NULL = the null stream).
- * Asynchronous: returns once the work is queued (kernels launched one by one).
- * The problem's internal buffers are reused by every call, so calls on one
+ * Asynchronous: returns once the work is queued (kernels launched one by one;
+ * general columns of more than 4094 entries on a stream of the problem's own
+ * that hip_stream waits for). The problem's internal buffers are reused by every call, so calls on one
  * problem must not overlap (queue them on one stream). Errors: CHAP_EINVAL,
  * CHAP_EHIP.
  */

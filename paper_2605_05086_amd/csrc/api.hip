@@ -1016,6 +1016,7 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     CHAP_HIP(build_launch(A, one, &P->bs_launch, nullptr));
     P->bs_launch.compact = P->compact_ok ? 2 : 0;
     P->bs_launch.caller_weights = 1;
+    if (P->bs_launch.total[KS_LONG] > 0) CHAP_HIP(P->bs_streams.create());
   }
   // timing only: no system-scope fence at the record
   for (hipEvent_t& e : P->pass_ev) CHAP_HIP(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
@@ -1037,7 +1038,7 @@ int chap_best_shift(chap_problem* p, const double* d_x, const float* d_w, double
   hipStream_t s = (hipStream_t)hip_stream;
   CHAP_HIP(launch_single_begin(p, d_x, d_w, cutoff_rhs, s));
   CHAP_HIP(hipEventRecord(p->pass_ev[0], s));
-  if (p->n > 0) CHAP_HIP(launch_pass(p->bs_launch, s));
+  if (p->n > 0) CHAP_HIP(launch_pass(p->bs_launch, s, p->bs_streams.side ? &p->bs_streams : nullptr));
   CHAP_HIP(hipEventRecord(p->pass_ev[1], s));
   CHAP_HIP(launch_single_end(p, d_shift, d_score, s));
   p->pass_timed = true;

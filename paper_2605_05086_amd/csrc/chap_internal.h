@@ -1031,6 +1031,11 @@ struct chap_problem {
   int64_t nnz = 0;
   double c_max = 0.0;
   chap::BatchLaunch bs_launch;
+  // side stream of chap_best_shift's pass, on problems with columns that are
+  // sorted in global memory: k_sort_long takes as long as all else together or
+  // longer (2.1 of 2.4 ms on 40 columns of 20k entries beside 100k others), while
+  // the fork and join cost a few microseconds, more than chunks alone save
+  chap::PassStreams bs_streams;
   hipEvent_t pass_ev[2] = {nullptr, nullptr};
   bool pass_timed = false;
   // buffers of single walks kept between chap_tabu_run calls
@@ -1042,6 +1047,7 @@ struct chap_problem {
   hipEvent_t jump_ev[2] = {nullptr, nullptr};
   bool jump_timed = false;
   ~chap_problem() {
+    bs_streams.destroy();
     for (hipEvent_t e : pass_ev)
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : jump_ev)
