@@ -32,7 +32,7 @@
 // internal index (equal keys: lowest index first). Each kernel of the select
 // re-derives the digits chosen so far from the histograms of the earlier
 // kernels (a few kilobytes from L2), so no single-workgroup kernel sits
-// between them; the compaction's last workgroup puts the list together.
+// between them; a last one puts the list together.
 
 #include <climits>
 #include <cmath>
@@ -560,6 +560,15 @@ __device__ __forceinline__ int chunk_of(const int32_t* off, int nc, int i) {
   return lo;
 }
 
+// Store of 8 bytes past the caches of this XCD (an atomic store of device scope):
+// once it has completed, any other workgroup can load it after invalidating its
+// own caches.
+__device__ __forceinline__ void put_agent(uint2* p, uint2 v) {
+  __hip_atomic_store((unsigned long long*)p, (unsigned long long)v.y << 32 | v.x, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+constexpr int kWaitStores = 0x0F70;  // s_waitcnt vmcnt(0)
+
 // The selection in ascending column order and its end, in one launch. Every
 // workgroup compacts its chunk of columns (kTopkChunk times L.topk_tiles)
 // into its part of L.stage: the keys above the threshold from the front, each
@@ -568,9 +577,12 @@ __device__ __forceinline__ int chunk_of(const int32_t* off, int nc, int i) {
 // take). The last to arrive adds the chunks' counts, so that every staged key
 // knows its place, and writes the selected columns; for the proposal set also
 // the subset-pass chunk offsets and the set log; then it clears the histograms
-// and the ticket for the next selection. Bounded by latency: 18 us on 200k
-// columns, where a count, a write and a finishing launch, each deriving the
-// threshold again, took 29.
+// and the ticket for the next selection. What the workgroups hand over goes past
+// their L2 (put_agent), so none of them needs a release fence, which would write
+// back what the scoring left there: with one the whole iteration took 63, 97 and
+// 194 us on 200k, 700k and 2M columns, without 60, 82 and 141. (A launch of its
+// own for the list: 59, 78 and 135, but 2.5 us more in each iteration that does
+// nothing after a stall.)
 __global__ __launch_bounds__(kBlock) void k_topk_take(const WalkCtx* __restrict__ walks,
                                                       const LearnCtx* __restrict__ lc, int32_t which, int32_t full,
                                                       int32_t n) {
@@ -630,25 +642,28 @@ __global__ __launch_bounds__(kBlock) void k_topk_take(const WalkCtx* __restrict_
     for (uint32_t m = mg; m; m &= m - 1) {
       const int b = __builtin_ctz(m);
       const uint32_t below = (1u << b) - 1u;
-      stage[og + __popc(mg & below)] = uint2{(uint32_t)(q0 + b), oe + __popc(me & below)};
+      put_agent(stage + og + __popc(mg & below), uint2{(uint32_t)(q0 + b), oe + __popc(me & below)});
     }
     for (uint32_t m = me; m; m &= m - 1) {
       const int b = __builtin_ctz(m);
       const uint32_t below = (1u << b) - 1u;
       const uint32_t e = oe + __popc(me & below);
       if (e >= (uint32_t)S.need_eq) break;
-      stage[chunk - 1 - e] = uint2{(uint32_t)(q0 + b), og + __popc(mg & below)};
+      put_agent(stage + chunk - 1 - e, uint2{(uint32_t)(q0 + b), og + __popc(mg & below)});
     }
   }
-  uint2* cnt = L.wg_cnt;
-  if (tid == 0) cnt[blockIdx.x] = uint2{gt_base, eq_base};
-  __threadfence();
+  if (tid == 0) put_agent(L.wg_cnt + blockIdx.x, uint2{gt_base, eq_base});
+  // the staged keys and the counts have reached memory (they went past the L2)
+  // before the workgroup takes its ticket; the fence keeps the stores above the
+  // wait
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(kWaitStores);
   __syncthreads();
   uint32_t* ticket = L.hist + 2 * kHistStride;
   if (tid == 0) last = atomicAdd(ticket, 1u);
   __syncthreads();
   if (last != gridDim.x - 1) return;
-  __threadfence();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 
   // exclusive prefixes of the chunks' counts
   __shared__ int32_t pg[kTopkChunks + 1], pe[kTopkChunks + 1];
@@ -660,7 +675,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_take(const WalkCtx* __restrict_
 #pragma unroll
   for (int t = 0; t < kPer; ++t) {
     const int b = tid * kPer + t;
-    c[t] = b < nc ? cnt[b] : uint2{0u, 0u};
+    c[t] = b < nc ? L.wg_cnt[b] : uint2{0u, 0u};
     cg += c[t].x;
     ce += c[t].y;
   }
@@ -887,9 +902,11 @@ hipError_t launch_learn_begin(const WalkCtx* C, const LearnCtx* L, hipStream_t s
 hipError_t launch_learn_propose(const WalkCtx* C, const LearnCtx* L, const LearnCtx& Lh, const ModelDev& M,
                                 int32_t n, int full_iteration, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  // 512 workgroups: 14.7 us on 200k columns (768 and one copy of the first
-  // digit's histogram: 21.0; every further workgroup adds its turn at the bins)
-  hipLaunchKernelGGL(k_learn_score, dim3(grid_for(n, 64, 512)), dim3(256), 0, s, C, L, M.w, M.wb, n);
+  // three workgroups a CU, as many as are resident; two while that leaves a
+  // wavefront few tiles, as each workgroup adds its turn at the histogram's bins.
+  // An iteration with 512 and 768 of them: 57.6 and 58.5 us on 200k columns, 78.4
+  // and 77.2 on 700k, 149 and 134 on 2M (1024: 149, 1536: 140)
+  hipLaunchKernelGGL(k_learn_score, dim3(grid_for(n, 64, n < (1 << 19) ? 512 : 768)), dim3(256), 0, s, C, L, M.w, M.wb, n);
   return topk(C, L, Lh, 0, full_iteration, n, s);
 }
 
