@@ -22,9 +22,9 @@ int check_options(const chap_learned_options& o) {
   return CHAP_OK;
 }
 
-// Device buffers of one learned walk.
+// Device buffers of one learned walk, or (rows_only) what its stored rows need.
 int build_learn_ctx(const chap_problem* p, const chap_learned_options& o, int64_t iters, DeviceArena& A,
-                    LearnCtx& L) {
+                    LearnCtx& L, bool rows_only = false) {
   const int32_t n = p->n;
   L = LearnCtx{};
   std::vector<int32_t> elig;
@@ -78,38 +78,40 @@ int build_learn_ctx(const chap_problem* p, const chap_learned_options& o, int64_
   CHAP_HIP(A.alloc(&L.feat, (size_t)n * 16));
   CHAP_HIP(A.alloc(&L.moves, (size_t)n));
   CHAP_HIP(A.alloc(&L.xhat_last, (size_t)n));
-  // the top-K kernels read keys four at a time
-  CHAP_HIP(A.alloc(&L.keys[0], ((size_t)n + 3) / 4 * 4));
-  CHAP_HIP(A.alloc(&L.keys[1], ((size_t)n + 3) / 4 * 4));
-  CHAP_HIP(A.alloc(&L.hist, (size_t)2 * kHistStride + 1));
-  CHAP_HIP(hipMemset(L.hist, 0, sizeof(uint32_t) * (2 * kHistStride + 1)));
-  const int32_t tiles = std::max<int32_t>(1, (n + kTopkChunk - 1) / kTopkChunk);
-  L.topk_tiles = (tiles + kTopkChunks - 1) / kTopkChunks;
-  L.nwg = (tiles + L.topk_tiles - 1) / L.topk_tiles;
-  CHAP_HIP(A.alloc(&L.wg_cnt, (size_t)L.nwg));
-  CHAP_HIP(A.alloc(&L.stage, (size_t)L.nwg * kTopkChunk * L.topk_tiles));
-  L.K[0] = o.topk;
-  L.K[1] = o.train_pairs;
-  CHAP_HIP(A.alloc(&L.sel[0], (size_t)L.K[0]));
-  CHAP_HIP(A.alloc(&L.sel[1], (size_t)L.K[1]));
-  // subset-pass chunks: at most sum over the selected columns of
-  // ceil(entries / kSubsetChunk) <= nnz / kSubsetChunk + K
-  L.sub_cap = (int32_t)std::min<int64_t>(INT32_MAX, p->nnz / kSubsetChunk + L.K[0] + 1);
-  CHAP_HIP(A.alloc(&L.sub_off, (size_t)L.K[0] + 1));
-  CHAP_HIP(A.alloc(&L.sub_parts, (size_t)L.sub_cap));
-  L.T = o.train_pairs;
-  CHAP_HIP(A.alloc(&L.pair_feat, (size_t)2 * L.T * 16));
-  CHAP_HIP(A.alloc(&L.pair_tgt, (size_t)2 * L.T));
-  if (o.log_pairs > 0) {
-    CHAP_HIP(A.alloc(&L.log_feat, (size_t)o.log_pairs * 16));
-    CHAP_HIP(A.alloc(&L.log_tgt, (size_t)o.log_pairs));
-    L.log_cap = o.log_pairs;
-  }
-  if (o.log_sets) {
-    L.set_log_cap = std::max<int64_t>(1, iters * (int64_t)std::min<int32_t>(o.topk, std::max(L.n_elig, 1)));
-    CHAP_HIP(A.alloc(&L.set_log, (size_t)L.set_log_cap));
-    CHAP_HIP(A.alloc(&L.set_off, (size_t)iters + 1));
-    CHAP_HIP(hipMemset(L.set_off, 0, sizeof(int64_t) * ((size_t)iters + 1)));
+  if (!rows_only) {
+    // the top-K kernels read keys four at a time
+    CHAP_HIP(A.alloc(&L.keys[0], ((size_t)n + 3) / 4 * 4));
+    CHAP_HIP(A.alloc(&L.keys[1], ((size_t)n + 3) / 4 * 4));
+    CHAP_HIP(A.alloc(&L.hist, (size_t)2 * kHistStride + 1));
+    CHAP_HIP(hipMemset(L.hist, 0, sizeof(uint32_t) * (2 * kHistStride + 1)));
+    const int32_t tiles = std::max<int32_t>(1, (n + kTopkChunk - 1) / kTopkChunk);
+    L.topk_tiles = (tiles + kTopkChunks - 1) / kTopkChunks;
+    L.nwg = (tiles + L.topk_tiles - 1) / L.topk_tiles;
+    CHAP_HIP(A.alloc(&L.wg_cnt, (size_t)L.nwg));
+    CHAP_HIP(A.alloc(&L.stage, (size_t)L.nwg * kTopkChunk * L.topk_tiles));
+    L.K[0] = o.topk;
+    L.K[1] = o.train_pairs;
+    CHAP_HIP(A.alloc(&L.sel[0], (size_t)L.K[0]));
+    CHAP_HIP(A.alloc(&L.sel[1], (size_t)L.K[1]));
+    // subset-pass chunks: at most sum over the selected columns of
+    // ceil(entries / kSubsetChunk) <= nnz / kSubsetChunk + K
+    L.sub_cap = (int32_t)std::min<int64_t>(INT32_MAX, p->nnz / kSubsetChunk + L.K[0] + 1);
+    CHAP_HIP(A.alloc(&L.sub_off, (size_t)L.K[0] + 1));
+    CHAP_HIP(A.alloc(&L.sub_parts, (size_t)L.sub_cap));
+    L.T = o.train_pairs;
+    CHAP_HIP(A.alloc(&L.pair_feat, (size_t)2 * L.T * 16));
+    CHAP_HIP(A.alloc(&L.pair_tgt, (size_t)2 * L.T));
+    if (o.log_pairs > 0) {
+      CHAP_HIP(A.alloc(&L.log_feat, (size_t)o.log_pairs * 16));
+      CHAP_HIP(A.alloc(&L.log_tgt, (size_t)o.log_pairs));
+      L.log_cap = o.log_pairs;
+    }
+    if (o.log_sets) {
+      L.set_log_cap = std::max<int64_t>(1, iters * (int64_t)std::min<int32_t>(o.topk, std::max(L.n_elig, 1)));
+      CHAP_HIP(A.alloc(&L.set_log, (size_t)L.set_log_cap));
+      CHAP_HIP(A.alloc(&L.set_off, (size_t)iters + 1));
+      CHAP_HIP(hipMemset(L.set_off, 0, sizeof(int64_t) * ((size_t)iters + 1)));
+    }
   }
   L.full_every = o.full_every;
   L.seed = o.train_seed;
@@ -366,7 +368,7 @@ int chap_features(chap_problem* p, const double* d_x, const float* d_w, double c
   o.log_pairs = 0;
   o.log_sets = 0;
   LearnCtx Lh;
-  int rc = build_learn_ctx(p, o, 1, A, Lh);
+  int rc = build_learn_ctx(p, o, 1, A, Lh, true);
   if (rc != CHAP_OK) return rc;
   WalkCtx* dC;
   LearnCtx* dL;
