@@ -1137,9 +1137,12 @@ int alloc_walk(const chap_problem* p, int64_t trace_cap, DeviceArena& A, WalkCtx
   c.scan_from = grouped;
   c.argmax_blocks = (n > grouped || c.group_rec == 0) ? blocks_for_host(n - grouped, kArgmaxBlocks) : 0;
   c.argmax_comb = p->plan.stage ? (p->plan.n_chunk_cols + 3) / 4 : 0;
-  c.apply_blocks = (int32_t)std::max<int64_t>(
-      1, std::min<int64_t>(((int64_t)std::max(p->m, p->max_col_deg) + kStepRows - 1) / kStepRows, kStepBlocks));
   c.recompute = p->exact_incremental ? 0 : 1;
+  // a reweight's rows, or the rows of the longest column where they are summed
+  // again
+  int64_t blocks = ((int64_t)p->m + kStepRows - 1) / kStepRows;
+  if (c.recompute) blocks = std::max<int64_t>(blocks, ((int64_t)p->max_col_deg + kStepSums - 1) / kStepSums);
+  c.apply_blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(blocks, kStepBlocks));
   CHAP_HIP(A.alloc(&c.x, (size_t)n));
   CHAP_HIP(A.alloc(&c.xhat, (size_t)n));
   CHAP_HIP(A.alloc(&c.s, (size_t)n));
