@@ -583,7 +583,9 @@ __device__ __forceinline__ void jump_bins(const JumpCall& J, int b, JumpBinSmem&
 // and exchanges through LDS (42 us) and an empty tasks launch (5 us) took 76 us
 // one after another. Six wavefronts a SIMD: 37.1 us with five, no spills.
 __global__ __launch_bounds__(256, 6) void k_jump(JumpCall J) {
-  __shared__ union {
+  // aligned so that the tasks' loop reads entries by 16 bytes (1785 against 1920 us
+  // on 1000 continuous columns of 2500 entries)
+  __shared__ union alignas(16) {
     JumpGroupSmem group;
     JumpEntry task[4][kWave];
     JumpBinSmem bins;
