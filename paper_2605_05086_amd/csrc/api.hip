@@ -593,7 +593,7 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
   std::vector<StageTask> stasks;
   std::vector<int32_t> sseg;
   std::vector<uint64_t> sent;
-  std::vector<StageRowTask> srtasks;
+  std::vector<StageRowTask> srtasks, srbatch[2];
   std::vector<int32_t> sunits;
   L.stage_exact = stage ? 1 : 0;
   if (stage) {
@@ -646,11 +646,6 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       (void)stage_entries(false);
       L.stage_pairs = 0;
     }
-    std::vector<std::vector<StageRowTask>> per_xcd(kXcds);
-    // slices per row block: at most one per kStageSlice entries, and at most
-    // the block's share of the workgroups the device holds at once, so that
-    // the record kernel runs in one round instead of a full round and a thin
-    // second one
     int64_t staged = 0, resident = 0;
     {
       int dev = 0, cus = 0;
@@ -661,37 +656,58 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       staged += L.stage_one_end - L.stage_one_begin;
       resident = (int64_t)kStageRowsPerCu * cus;
     }
-    int32_t qone = L.stage_one_begin, slices = 0;
+    std::vector<StageRowTask> whole;  // each row block as one slice
+    int32_t qone = L.stage_one_begin;
     for (int32_t rb = 0; rb < nrb; ++rb) {
       const int32_t e0 = (int32_t)sent.size();
       for (size_t t = 0; t <= T; ++t) sseg[t * nrb + rb] += e0;
       sent.insert(sent.end(), ent_rb[rb].begin(), ent_rb[rb].end());
-      const int32_t e1 = (int32_t)sent.size();
-      const int32_t c0 = qone;
+      StageRowTask rt{};
+      rt.rb = rb;
+      rt.e_beg = e0;
+      rt.e_end = (int32_t)sent.size();
+      rt.c_beg = qone;
       while (qone < L.stage_one_end && crow[cptr[qone]] < (rb + 1) * kStageRowBlock) ++qone;
-      const int32_t c1 = qone;
-      // slices: the block's share of the resident workgroups by its entries and
-      // single-entry columns, but none below kStageSlice entries (or
-      // kStageSliceCols columns) while there are fewer
-      const int32_t by_e = (e1 - e0 + kStageSlice - 1) / kStageSlice;
-      const int32_t by_c = (c1 - c0 + kStageSliceCols - 1) / kStageSliceCols;
-      const int64_t work = (int64_t)(e1 - e0) + (c1 - c0);
-      const int32_t share = (int32_t)std::max<int64_t>(1, resident * work / std::max<int64_t>(staged, 1));
-      const int32_t ns = std::min(std::max(by_e, by_c), share);
-      if (ns == 0) continue;
-      const int32_t se = (e1 - e0 + ns - 1) / ns, sc = (c1 - c0 + ns - 1) / ns;
-      for (int32_t k = 0; k < ns; ++k) {
-        StageRowTask rt{};
-        rt.rb = rb;
-        rt.e_beg = std::min(e1, e0 + k * se);
-        rt.e_end = std::min(e1, e0 + (k + 1) * se);
-        rt.c_beg = std::min(c1, c0 + k * sc);
-        rt.c_end = std::min(c1, c0 + (k + 1) * sc);
-        // the slices of one row block share an XCD's L2 while there are blocks
-        // for every XCD; with few blocks their slices take all XCDs in turn
-        per_xcd[(nrb >= 8 * kXcds ? rb : slices++) % kXcds].push_back(rt);
-      }
+      rt.c_end = qone;
+      whole.push_back(rt);
     }
+    // slices per row block: at most one per `entries` entries or `cols`
+    // single-entry columns, and at most the block's share of `most` workgroups
+    auto slices = [&](int32_t entries, int32_t cols, int64_t most) {
+      std::vector<std::vector<StageRowTask>> per_xcd(kXcds);
+      int32_t turn = 0;
+      for (const StageRowTask& w : whole) {
+        const int32_t ne_ = w.e_end - w.e_beg, nc = w.c_end - w.c_beg;
+        const int32_t share = (int32_t)std::max<int64_t>(1, most * (ne_ + (int64_t)nc) / std::max<int64_t>(staged, 1));
+        const int32_t ns = std::min(std::max((ne_ + entries - 1) / entries, (nc + cols - 1) / cols), share);
+        for (int32_t k = 0; k < ns; ++k) {
+          const int32_t se = (ne_ + ns - 1) / ns, sc = (nc + ns - 1) / ns;
+          StageRowTask rt{};
+          rt.rb = w.rb;
+          rt.e_beg = std::min(w.e_end, w.e_beg + k * se);
+          rt.e_end = std::min(w.e_end, w.e_beg + (k + 1) * se);
+          rt.c_beg = std::min(w.c_end, w.c_beg + k * sc);
+          rt.c_end = std::min(w.c_end, w.c_beg + (k + 1) * sc);
+          // the slices of one row block share an XCD's L2 while there are blocks
+          // for every XCD; with few blocks their slices take all XCDs in turn
+          per_xcd[(nrb >= 8 * kXcds ? w.rb : turn++) % kXcds].push_back(rt);
+        }
+      }
+      std::vector<StageRowTask> list;
+      size_t rounds = 0;
+      for (const auto& v : per_xcd) rounds = std::max(rounds, v.size());
+      for (size_t k = 0; k < rounds; ++k)
+        for (int x = 0; x < kXcds; ++x)
+          list.push_back(k < per_xcd[x].size() ? per_xcd[x][k] : StageRowTask{-1, 0, 0, 0, 0, {0, 0, 0}});
+      return list;
+    };
+    // as many as the device holds at once, so that the record kernel runs in one
+    // round instead of a full round and a thin second one; in a batch, whose walks
+    // are placed on one XCD each, as many as that holds, and longer ones when
+    // walks share an XCD (each workgroup loads its whole row block)
+    srtasks = slices(kStageSlice, kStageSliceCols, resident);
+    srbatch[0] = slices(kStageSlice, kStageSliceCols, resident / kXcds);
+    srbatch[1] = slices(kStageSliceBatch, kStageSliceBatch, resident / kXcds);
     // per task: segment starts, then prefix counts of its records
     {
       const size_t per = 2 * (size_t)nrb + 1;
@@ -707,11 +723,6 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
       }
       sseg.swap(tab);
     }
-    size_t rounds = 0;
-    for (const auto& v : per_xcd) rounds = std::max(rounds, v.size());
-    for (size_t k = 0; k < rounds; ++k)
-      for (int x = 0; x < kXcds; ++x)
-        srtasks.push_back(k < per_xcd[x].size() ? per_xcd[x][k] : StageRowTask{-1, 0, 0, 0, 0, {0, 0, 0}});
     // units of the single scoring launch: chunk and pack units interleaved
     // in proportion to their counts, so that the latency-bound chunk gathers
     // and the VALU-bound pack scoring share every CU, then the short-group
@@ -910,6 +921,12 @@ int chap_problem_create(chap_problem** out, int32_t n, int32_t m, const int64_t*
     CHAP_HIP(A.upload(&dt, stasks));
     CHAP_HIP(A.upload(&dseg, sseg));
     CHAP_HIP(A.upload(&drt, srtasks));
+    for (int k = 0; k < 2; ++k) {
+      StageRowTask* drb;
+      CHAP_HIP(A.upload(&drb, srbatch[k]));
+      L.stage_batch_rtasks[k] = drb;
+      L.n_stage_batch_rtasks[k] = (int32_t)srbatch[k].size();
+    }
     if (fits8) {
       L.stage_packed = 1;
       std::vector<uint32_t> s32(sent.size());
@@ -1361,6 +1378,15 @@ void hamming_tasks(const std::vector<WalkSpec>& specs, const std::vector<WalkCtx
     }
 }
 
+// Sizes of a batch's launches that a walk alone on the device takes larger.
+void share_device(std::vector<WalkCtx>& ctx) {
+  const int k = ctx.size() > (size_t)kXcds ? 1 : 0;
+  for (WalkCtx& c : ctx) {
+    c.plan.stage_rtasks = c.plan.stage_batch_rtasks[k];
+    c.plan.n_stage_rtasks = c.plan.n_stage_batch_rtasks[k];
+  }
+}
+
 // Runs every walk for `iters` iterations: per-walk buffers, set-up kernels,
 // then a HIP graph of `graph_iters` iterations in which each kernel is one
 // launch over all walks. Results are copied back into chap_run objects.
@@ -1407,6 +1433,7 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
     const int rc = prepare_walk(specs[w], iters, tenure, A, ctx[w], partial, ticket, s, compact);
     if (rc != CHAP_OK) return rc;
   }
+  if (nw > 1) share_device(ctx);
   BatchLaunch L;
   std::vector<int32_t> order;
   CHAP_HIP(build_launch(A, ctx, &L, &order));

@@ -338,6 +338,7 @@ constexpr int kStageShort = 256;      // short narrow columns per scoring task
 constexpr int kStageClamp = 64;       // offsets beyond +-64 leave every narrow column
 constexpr int kStageMaxRb = 256;      // row blocks a scoring workgroup can index in LDS
 constexpr int kStageSliceCols = 2048; // single-entry columns per workgroup of k_stage_rows (fewest)
+constexpr int kStageSliceBatch = 8192;  // entries or single-entry columns of a slice in a batch of more walks than XCDs (fewest)
 constexpr int kStagePackCols = 64;    // columns per staged pack (one lane each in the final scan)
 constexpr int kStagePackEntries = 3072;  // target stored entries per staged pack
 
@@ -418,6 +419,11 @@ struct PassPlan {
   const StageTask* stage_tasks = nullptr;
   const int32_t* stage_seg = nullptr;
   const StageRowTask* stage_rtasks = nullptr;
+  // the same for a batch of at most kXcds walks, and of more: with the slices of a
+  // walk alone, each of which loads its whole row block, an iteration of 2, 16 and
+  // 64 walks of 2M entries took 141, 307 and 1168 us; now 119, 259 and 933
+  const StageRowTask* stage_batch_rtasks[2] = {nullptr, nullptr};
+  int32_t n_stage_batch_rtasks[2] = {0, 0};
   const uint64_t* stage_ent = nullptr;
   const uint32_t* stage_ent32 = nullptr;  // instead, where every coefficient fits int8
   // the chunked columns' entries (internal entries from chunk_e0 on) as
