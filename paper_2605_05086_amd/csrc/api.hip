@@ -1380,10 +1380,14 @@ void hamming_tasks(const std::vector<WalkSpec>& specs, const std::vector<WalkCtx
 
 // Sizes of a batch's launches that a walk alone on the device takes larger.
 void share_device(std::vector<WalkCtx>& ctx) {
-  const int k = ctx.size() > (size_t)kXcds ? 1 : 0;
+  const int32_t nw = (int32_t)ctx.size();
+  const int k = nw > kXcds ? 1 : 0;
   for (WalkCtx& c : ctx) {
     c.plan.stage_rtasks = c.plan.stage_batch_rtasks[k];
     c.plan.n_stage_rtasks = c.plan.n_stage_batch_rtasks[k];
+    // the move kernel's workgroups beyond those of a reweight
+    const int32_t base = std::max<int32_t>(1, std::min((c.P.ms + kStepRows - 1) / kStepRows, kStepBlocks));
+    c.apply_blocks = std::max(base, std::min(c.apply_blocks, kStepBlocks / nw));
   }
 }
 
