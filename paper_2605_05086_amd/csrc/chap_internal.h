@@ -405,12 +405,6 @@ struct PassPlan {
   // record of the task in each row block, then the task's records in the
   // blocks before each block (the last value: all of them)
   int32_t stage = 0;
-  // 1: the segments of packs are padded to whole pairs of records at even
-  // positions, which k_stage_score then loads 16 bytes at a time; 0 where the
-  // padding (a few per cent of the records) would be what takes the problem
-  // over the scratch of chap_best_shift_noalloc, or the entries over 2^31. A
-  // batch reads single records when any of its problems is not padded.
-  int32_t stage_pairs = 1;
   int32_t stage_exact = 0;  // the integer breakpoint identity holds (staging eligible)
   int32_t n_stage_tasks = 0;
   int32_t n_stage_packs = 0;
@@ -419,11 +413,6 @@ struct PassPlan {
   const StageTask* stage_tasks = nullptr;
   const int32_t* stage_seg = nullptr;
   const StageRowTask* stage_rtasks = nullptr;
-  // the same for a batch of at most kXcds walks, and of more: with the slices of a
-  // walk alone, each of which loads its whole row block, an iteration of 2, 16 and
-  // 64 walks of 2M entries took 141, 307 and 1168 us; now 119, 259 and 933
-  const StageRowTask* stage_batch_rtasks[2] = {nullptr, nullptr};
-  int32_t n_stage_batch_rtasks[2] = {0, 0};
   const uint64_t* stage_ent = nullptr;
   const uint32_t* stage_ent32 = nullptr;  // instead, where every coefficient fits int8
   // the chunked columns' entries (internal entries from chunk_e0 on) as
@@ -445,6 +434,18 @@ struct PassPlan {
   // on that role's unit (stage_units[u] & kStageUnitMask)
   const int32_t* stage_units = nullptr;
   int32_t n_stage_units = 0;
+  // ---- read by the host only
+  // 1: the segments of packs are padded to whole pairs of records at even
+  // positions, which k_stage_score then loads 16 bytes at a time; 0 where the
+  // padding (a few per cent of the records) would be what takes the problem
+  // over the scratch of chap_best_shift_noalloc, or the entries over 2^31. A
+  // batch reads single records when any of its problems is not padded.
+  int32_t stage_pairs = 1;
+  // stage_rtasks of a batch of at most kXcds walks, and of more: with the slices
+  // of a walk alone, each of which loads its whole row block, an iteration of 2, 16
+  // and 64 walks of 2M entries took 141, 307 and 1168 us; now 119, 259 and 933
+  const StageRowTask* stage_batch_rtasks[2] = {nullptr, nullptr};
+  int32_t n_stage_batch_rtasks[2] = {0, 0};
 };
 
 // Everything the kernels of one walk need: its instance, the instance's pass
