@@ -1402,11 +1402,9 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
   const size_t nw = specs.size();
   DeviceArena A;
   if (nw > 1) A.chunk = (size_t)32 << 20;
-  std::vector<WalkCtx> ctx(nw);
-  double* partial;
-  uint32_t* ticket;
-  CHAP_HIP(A.alloc(&partial, kInitPartial));
-  CHAP_HIP(A.alloc(&ticket, 1));
+  std::vector<WalkCtx> ctx;
+  double* partial = nullptr;
+  uint32_t* ticket = nullptr;
   hipStream_t s;
   CHAP_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
   struct StreamGuard {
@@ -1431,16 +1429,26 @@ int run_walks(const std::vector<WalkSpec>& specs, int64_t iters, int32_t tenure,
   } eg{e_user, e0, e1};
   CHAP_HIP(hipEventRecord(e_user, user));
   CHAP_HIP(hipStreamWaitEvent(s, e_user, 0));
-  CHAP_HIP(hipMemsetAsync(ticket, 0, sizeof(uint32_t), s));
   const int compact = compact_walks(specs, iters);
-  for (size_t w = 0; w < nw; ++w) {
-    const int rc = prepare_walk(specs[w], iters, tenure, A, ctx[w], partial, ticket, s, compact);
-    if (rc != CHAP_OK) return rc;
-  }
-  if (nw > 1) share_device(ctx);
   BatchLaunch L;
   std::vector<int32_t> order;
-  CHAP_HIP(build_launch(A, ctx, &L, &order));
+  auto set_up = [&]() -> int {
+    ctx.assign(nw, WalkCtx{});
+    L = BatchLaunch{};
+    CHAP_HIP(A.alloc(&partial, kInitPartial));
+    CHAP_HIP(A.alloc(&ticket, 1));
+    CHAP_HIP(hipMemsetAsync(ticket, 0, sizeof(uint32_t), s));
+    for (size_t w = 0; w < nw; ++w) {
+      const int rc = prepare_walk(specs[w], iters, tenure, A, ctx[w], partial, ticket, s, compact);
+      if (rc != CHAP_OK) return rc;
+    }
+    if (nw > 1) share_device(ctx);
+    CHAP_HIP(build_launch(A, ctx, &L, &order));
+    return CHAP_OK;
+  };
+  int set_rc = set_up();
+  if (set_rc != CHAP_OK && A.exhausted && hipStreamSynchronize(s) == hipSuccess && A.retry_exact()) set_rc = set_up();
+  if (set_rc != CHAP_OK) return set_rc;
   L.compact = compact;
   const PassStreams* ps_side = nullptr;  // creating a stream takes a millisecond
   if (pass_forks(L)) {

@@ -63,16 +63,29 @@ int fail(int code, const std::string& msg);
 
 // Device allocations owned by one object, freed together.
 // With `chunk` set, requests of up to a quarter of it are cut from blocks of
-// that size (a batch makes a thousand of them).
+// that size (a batch makes a thousand of them). Blocks leave up to a few per cent
+// unused: an owner whose requests did not fit starts again with retry_exact().
 struct DeviceArena {
   std::vector<void*> ptrs;
   size_t chunk = 0, left = 0;
   char* cur = nullptr;
+  bool exhausted = false;  // a request did not fit
   DeviceArena() = default;
   DeviceArena(const DeviceArena&) = delete;
   DeviceArena& operator=(const DeviceArena&) = delete;
   ~DeviceArena() {
     for (void* p : ptrs) (void)hipFree(p);
+  }
+  // After a request that did not fit: frees everything (which waits for the
+  // device) and allocates each request by itself from now on; false where that
+  // would change nothing.
+  bool retry_exact() {
+    if (!exhausted || chunk == 0) return false;
+    for (void* p : ptrs) (void)hipFree(p);
+    ptrs.clear();
+    chunk = left = 0;
+    exhausted = false;
+    return true;
   }
   template <typename T>
   hipError_t alloc(T** out, size_t count) {
@@ -97,7 +110,11 @@ struct DeviceArena {
       }
     }
     hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      exhausted = true;
+      return e;
+    }
     ptrs.push_back(p);
     *out = (T*)p;
     return hipSuccess;
