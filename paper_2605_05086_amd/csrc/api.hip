@@ -1237,6 +1237,55 @@ void fill_summary(const WalkState& st, chap_run* R) {
 
 }  // namespace
 
+namespace {
+
+// The same without device memory of its own: the points through the walk's buffers
+// of its last scores, the rows ordered on the host.
+int collect_in_place(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
+                     double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out) {
+  auto read = [](auto& v, const auto* from, size_t count) {
+    v.resize(count);
+    return count > 0 ? hipMemcpy(v.data(), from, sizeof(v[0]) * count, hipMemcpyDeviceToHost) : hipSuccess;
+  };
+  out.clear();
+  for (size_t i = 0; i < ps.size(); ++i) {
+    const chap_problem* p = ps[i];
+    const WalkCtx& c = ctx[i];
+    StateOut S;
+    S.x = c.xhat;
+    S.best = c.s;
+    CHAP_HIP(launch_state_out(c.P, p->d_nidx, p->d_pair, p->mp, c, iters, S, s));
+    CHAP_HIP(hipStreamSynchronize(s));
+    std::unique_ptr<chap_run> R(new chap_run());
+    R->elapsed_ms = ms;
+    WalkState st;
+    std::vector<RowState> rs;
+    CHAP_HIP(hipMemcpy(&st, c.st, sizeof(WalkState), hipMemcpyDeviceToHost));
+    fill_summary(st, R.get());
+    CHAP_HIP(read(R->trace, c.trace, (size_t)iters));
+    CHAP_HIP(read(R->x, c.xhat, (size_t)p->n));
+    if (R->has_best) CHAP_HIP(read(R->best_x, c.s, (size_t)p->n));
+    CHAP_HIP(read(rs, c.rs, (size_t)p->m));
+    R->resid.resize((size_t)p->mp + 1);
+    R->w.resize((size_t)p->mp + 1);
+    for (size_t k = 0; k < rs.size(); ++k) {
+      const size_t t = (size_t)p->nidx[k];
+      R->resid[t] = rs[k].r;
+      R->w[t] = rs[k].w0;
+      if (p->pair[k]) {
+        R->resid[t + 1] = -rs[k].r;
+        R->w[t + 1] = rs[k].w1;
+      }
+    }
+    R->resid[(size_t)p->mp] = st.cut_active ? st.rc : 0.0;
+    R->w[(size_t)p->mp] = st.wc;
+    out.push_back(std::move(R));
+  }
+  return CHAP_OK;
+}
+
+}  // namespace
+
 int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
                   double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out) {
   const size_t nw = ps.size();
@@ -1262,7 +1311,7 @@ int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<
   const size_t cap = std::max(most, std::min(total, kCollectBytes));
   DeviceArena A;
   char* d;
-  CHAP_HIP(A.alloc(&d, cap));
+  if (A.alloc(&d, cap) != hipSuccess) return collect_in_place(ps, ctx, iters, ms, s, out);
   const std::unique_ptr<char[]> h(new char[cap]);
   auto take = [](auto& v, const char* from, size_t count) {
     using T = typename std::decay<decltype(v)>::type::value_type;

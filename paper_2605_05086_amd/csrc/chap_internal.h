@@ -658,8 +658,8 @@ hipError_t launch_state_init(const DevProblem& P, const double* x, const RowStat
                              int check_incumbent, int count_violated, hipStream_t stream);
 hipError_t launch_copy_best(const double* x, double* best_x, WalkState* st, int32_t n, hipStream_t stream);
 // Where a finished walk's state goes, in the caller's order: n, n (written with
-// an incumbent only), mp + 1 and mp + 1 values; st, when set, and trace take
-// the walk's record and `iters` trace records.
+// an incumbent only), mp + 1 and mp + 1 values (resid null: the points only); st,
+// when set, and trace take the walk's record and `iters` trace records.
 struct StateOut {
   double* x = nullptr;
   double* best = nullptr;
@@ -1218,7 +1218,8 @@ int prepare_walk(const WalkSpec& spec, int64_t iters, int32_t tenure, DeviceAren
 int compact_walks(const std::vector<WalkSpec>& specs, int64_t iters);
 // Copies finished walks back into new runs (host order): every walk's state in
 // the caller's order and its trace go through a bounded device block, as many
-// walks at a time as it holds.
+// walks at a time as it holds, or, where there is no room for that, one at a time
+// through the walks' own buffers.
 int collect_walks(const std::vector<const chap_problem*>& ps, const std::vector<WalkCtx>& ctx, int64_t iters,
                   double ms, hipStream_t s, std::vector<std::unique_ptr<chap_run>>& out);
 // Device copy of the walk contexts and the per-kernel launch tables; a batch

@@ -650,7 +650,8 @@ __global__ __launch_bounds__(256) void k_state_init(DevProblem P, const double* 
 // A finished walk's state in the caller's order: x and, with an incumbent,
 // best_x by the column permutation, the residuals and weights of the normalised
 // rows (an equality row's twin has residual -r and the second weight), the
-// cutoff row last; the walk's record and its trace as they are. Bounded by the
+// cutoff row last; the walk's record and its trace as they are (only the points
+// without o.resid). Bounded by the
 // scattered 8-byte stores; the host did the same in 5 ms at 2M columns, after
 // reading both points and the row states.
 __global__ __launch_bounds__(256) void k_state_out(int32_t n, int32_t m, int32_t mp, const int32_t* __restrict__ perm,
@@ -667,6 +668,7 @@ __global__ __launch_bounds__(256) void k_state_out(int32_t n, int32_t m, int32_t
     o.x[j] = x[q];
     if (best) o.best[j] = best_x[q];
   }
+  if (!o.resid) return;
   for (int64_t k = i; k < m; k += stride) {
     const RowState r = rs[k];
     const int t = nidx[k];
