@@ -419,9 +419,10 @@ def compare_batched(chap, iters, tenure, small, plain=True):
     t0 = time.perf_counter()
     pool = mipgen.batch_pool(total_nnz=2_000_000 if small else 20_000_000)
     probs = [chap.Problem(m) for m in pool]
-    # per-instance plan chosen by chap_autotune (short-column threshold; the
-    # pool's columns are short and general, so the long-column knobs do not
-    # apply), timed on a 32-iteration walk of each instance
+    # per-instance plan chosen by chap_autotune, timed on a 32-iteration walk of
+    # each instance. The pool's columns are general and short: neither the
+    # short-column threshold nor the long-column knobs change their plans, so one
+    # of the two candidates is timed and the default stays
     t1 = time.perf_counter()
     chosen = {}
     for i, m in enumerate(pool):

@@ -162,9 +162,9 @@ int chap_problem_norm_row_map(const chap_problem *p, int32_t *orig_row, int8_t *
  *   hip_stream hipStream_t to run on (NULL = the null stream).
  * Asynchronous: returns once the work is queued (kernels launched one by one;
  * general columns of more than 4094 entries on a stream of the problem's own
- * that hip_stream waits for). The problem's internal buffers are reused by every call, so calls on one
- * problem must not overlap (queue them on one stream). Errors: CHAP_EINVAL,
- * CHAP_EHIP.
+ * that hip_stream waits for). The problem's internal buffers are reused by
+ * every call, so calls on one problem must not overlap (queue them on one
+ * stream). Errors: CHAP_EINVAL, CHAP_EHIP.
  */
 int chap_best_shift(chap_problem *p, const double *d_x, const float *d_w, double cutoff_rhs,
                     double *d_shift, double *d_score, void *hip_stream);
@@ -294,6 +294,8 @@ int chap_batch_run(chap_problem *const *probs, int32_t nprob, const int32_t *wal
  *   cands, ncand  candidate sets (feas_tol is ignored: p's is kept); ncand = 0
  *                 uses a built-in grid of 8 over short_max {4, 8},
  *                 chunk_min = chunk_len {2048, 4096}, graph_iters {32, 64}
+ *                 (a candidate that plans the problem as an earlier one does,
+ *                 such as by short_max off the row-staged form, takes its time)
  *   walk_iters    1 .. 2^20 timed iterations per candidate
  *   best          the fastest candidate (pass it to chap_problem_create)
  *   ms_per_iter   optional, one entry per candidate (8 for the grid)

@@ -1932,23 +1932,47 @@ int chap_autotune(const chap_problem* p, const chap_options* cands, int32_t ncan
   const chap_problem::Raw& R = p->raw;
   double best_ms = HUGE_VAL;
   int32_t best_i = -1;
+  std::vector<double> ms(grid.size(), 0.0);
+  std::vector<char> staged(grid.size(), 0);
+  // a candidate whose plan an earlier one has: only staged problems (and columns
+  // above a chunk_min below kShortMax) are planned by short_max
+  auto same_plan = [&](size_t a, size_t b) {
+    const chap_options &x = grid[a], &y = grid[b];
+    auto eq = [](int32_t u, int32_t v, int32_t dflt) { return (u ? u : dflt) == (v ? v : dflt); };
+    chap_options d;
+    chap_options_default(&d);
+    if (y.short_max < 0 || y.short_max > kShortMax || !eq(x.graph_iters, y.graph_iters, d.graph_iters) ||
+        !eq(x.chunk_min, y.chunk_min, d.chunk_min) || !eq(x.chunk_len, y.chunk_len, d.chunk_len) ||
+        !eq(x.row_stage, y.row_stage, d.row_stage) || x.rescore_cap != y.rescore_cap)
+      return false;
+    return eq(x.short_max, y.short_max, d.short_max) ||
+           (!staged[a] && (y.chunk_min ? y.chunk_min : d.chunk_min) >= kShortMax);
+  };
   for (size_t c = 0; c < grid.size(); ++c) {
-    chap_options o = grid[c];
-    o.feas_tol = p->opt.feas_tol;  // the tolerance is part of the problem, not a tuning knob
-    chap_problem* t = nullptr;
-    int rc = chap_problem_create(&t, p->n, p->m, R.csr_row_ptr.data(), R.csr_col.data(), R.csr_val.data(),
-                                 R.csc_col_ptr.data(), R.csc_row.data(), R.csc_val.data(), R.sense.data(),
-                                 R.rhs.data(), R.lb.data(), R.ub.data(), R.is_int.data(), R.obj.data(), &o);
-    if (rc != CHAP_OK) return rc;
-    std::unique_ptr<chap_problem> guard(t);
-    std::vector<std::unique_ptr<chap_run>> runs;
-    rc = run_walks({WalkSpec{t, 0, nullptr}}, std::min<int64_t>(walk_iters, 8), 10, nullptr, runs);  // warm-up
-    if (rc == CHAP_OK) rc = run_walks({WalkSpec{t, 0, nullptr}}, walk_iters, 10, nullptr, runs);
-    if (rc != CHAP_OK) return rc;
-    const double ms = runs[0]->elapsed_ms / (double)walk_iters;
-    if (ms_per_iter) ms_per_iter[c] = ms;
-    if (ms < best_ms) {
-      best_ms = ms;
+    size_t e = 0;
+    while (e < c && !same_plan(e, c)) ++e;
+    if (e < c) {
+      ms[c] = ms[e];
+      staged[c] = staged[e];
+    } else {
+      chap_options o = grid[c];
+      o.feas_tol = p->opt.feas_tol;  // the tolerance is part of the problem, not a tuning knob
+      chap_problem* t = nullptr;
+      int rc = chap_problem_create(&t, p->n, p->m, R.csr_row_ptr.data(), R.csr_col.data(), R.csr_val.data(),
+                                   R.csc_col_ptr.data(), R.csc_row.data(), R.csc_val.data(), R.sense.data(),
+                                   R.rhs.data(), R.lb.data(), R.ub.data(), R.is_int.data(), R.obj.data(), &o);
+      if (rc != CHAP_OK) return rc;
+      std::unique_ptr<chap_problem> guard(t);
+      std::vector<std::unique_ptr<chap_run>> runs;
+      rc = run_walks({WalkSpec{t, 0, nullptr}}, std::min<int64_t>(walk_iters, 8), 10, nullptr, runs);  // warm-up
+      if (rc == CHAP_OK) rc = run_walks({WalkSpec{t, 0, nullptr}}, walk_iters, 10, nullptr, runs);
+      if (rc != CHAP_OK) return rc;
+      ms[c] = runs[0]->elapsed_ms / (double)walk_iters;
+      staged[c] = t->plan.stage_exact != 0;
+    }
+    if (ms_per_iter) ms_per_iter[c] = ms[c];
+    if (ms[c] < best_ms || (e < c && ms[c] == best_ms)) {  // of equal plans the last
+      best_ms = ms[c];
       best_i = (int32_t)c;
     }
   }
