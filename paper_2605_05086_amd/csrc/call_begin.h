@@ -18,7 +18,6 @@ __device__ __forceinline__ void reset_state(WalkState* st, int64_t iters, int32_
   st->tenure = tenure;
   st->sel_k = -1;
   st->mv_j = -1;
-  st->mv_kind = 2;
   st->dV = 0ull;
   st->choice = 0ull;
   // single passes: the compact copy holds the cutoff weight as a count of

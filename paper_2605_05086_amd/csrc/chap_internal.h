@@ -128,13 +128,6 @@ struct DeviceArena {
   }
 };
 
-// Column classes, decided once at problem creation.
-enum : uint8_t {
-  COL_GENERAL = 0,  // continuous, or integer with more than 64 values / infinite bounds
-  COL_BINARY = 1,   // integer with bounds [0, 1]: the flip is the only move
-  COL_NARROW = 2,   // integer with finite bounds and at most 64 values
-};
-
 constexpr int kShortMax = 8;       // normalised entries a single lane can score
 constexpr int kXcds = 8;           // L2 domains (XCDs) of an MI355X; chunks are cut into as many row ranges
 constexpr int kWave = 64;          // lanes of a gfx950 wavefront
@@ -262,8 +255,6 @@ struct __align__(16) WalkState {
   int64_t sel_V;
   // chosen step (internal column index)
   int32_t mv_j;
-  int32_t mv_kind;
-  double mv_old;
   double mv_new;
   // workgroups of the move kernel that are done (low 16 bits) and, above, the
   // sum of their violation changes (two's complement)
@@ -631,7 +622,6 @@ hipError_t launch_stage_x(const int32_t* perm, const double* src, double* dst, i
                           uint32_t epoch, int32_t n, const SingleInit& init, hipStream_t stream);
 // Residuals from scratch (weights left as they are). With xc (and
 // st->x_misfit != epoch) the products read the byte copy of x.
-hipError_t launch_residual(const DevProblem& P, const double* x, RowState* rs, hipStream_t stream);
 // Residuals from scratch with unit weights, and the compact copy when grow
 // is not null.
 hipError_t launch_residual_unit(const DevProblem& P, const uint8_t* pair, const double* x, const int8_t* xc,

@@ -150,11 +150,6 @@ __device__ __forceinline__ JumpCand jump_candidate(const DevProblem& P, const Ro
   return o;
 }
 
-// Candidates of a longer column: tiles of kWave.
-__device__ __forceinline__ int jump_tiles(bool narrow, int deg) {
-  return narrow ? 1 : (2 * deg + kJumpSpecials + kWave - 1) / kWave;
-}
-
 // What the roles of k_jump share.
 struct JumpCall {
   DevProblem P;

@@ -270,7 +270,6 @@ struct Select {
   int rem;           // keys still to take under the prefix
   uint32_t thresh;   // final key T (upto == 3)
   int need_eq;       // keys == T to take (upto == 3)
-  int count;         // keys selected (upto == 3 or all)
 };
 
 // The histograms of a selection: the first digit's in kHistCopies copies (the
@@ -359,13 +358,12 @@ __device__ __forceinline__ Levels<kUpto> load_levels(const LearnCtx& L, int whic
 }
 template <int kUpto>
 __device__ Select derive(const Levels<kUpto>& V, int K) {
-  Select S{false, 0u, K, 0u, 0, 0};
+  Select S{false, 0u, K, 0u, 0};
   int d, left;
   uint32_t total;
   find_digit(V.b[0], K, &d, &left, &total);
   if (total <= (uint32_t)K) {
     S.all = true;
-    S.count = (int)total;
     return S;
   }
   S.prefix = (uint32_t)d;
@@ -379,7 +377,6 @@ __device__ Select derive(const Levels<kUpto>& V, int K) {
     find_digit(V.b[2], S.rem, &d, &left, &total);
     S.thresh = (S.prefix << 10) | (uint32_t)d;
     S.need_eq = left;
-    S.count = K;
   }
   return S;
 }

@@ -1284,12 +1284,6 @@ __device__ __forceinline__ void stage_pack(const WalkCtx& C, const Rows& rs, boo
   }
 }
 
-__device__ __forceinline__ void cswap_u64(uint64_t& a, uint64_t& b) {
-  const uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
-  a = lo;
-  b = hi;
-}
-
 // One short narrow column with D stored entries (decoded records e[0..D-1])
 // scored directly: value(c) = beta + alpha [c >= 1] + sum of delta [c >= thr]
 // at the candidate offsets c (both bounds, breakpoints inside [l, u]; c = 0
@@ -1766,7 +1760,6 @@ __device__ __forceinline__ int stage_task_of(int lb, int ntask) {
   return t < ntask ? t : -1;
 }
 
-__host__ __device__ inline int32_t stage_blocks(int32_t ntask) { return kXcds * ((ntask + kXcds - 1) / kXcds); }
 
 // The scoring of a staged pass in one launch: the long-column chunks, the packs and the short groups are units of kXcds
 // workgroups of one grid, interleaved so that every CU runs latency-bound

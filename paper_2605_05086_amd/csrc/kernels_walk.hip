@@ -125,7 +125,7 @@ struct ObjState {
 // instances whose row activities are exact integers (P.sums_exact) the
 // order cannot change the sum: each lane adds its own products and the
 // group combines the lanes' sums in three exchanges.
-// Weights: kWeightsKeep leaves them, kWeightsUnit sets every weight to 1,
+// Weights: kWeightsUnit sets every weight to 1,
 // kWeightsScatter copies the caller's normalised weights. With grow, the
 // compact row copy is written too (all-integer instances); with the
 // caller's weights it is checked as well: st->compact_rows, set by the
@@ -133,7 +133,7 @@ struct ObjState {
 // weight (the cutoff's included) does not fit.
 constexpr int kResidualLanes = 8;
 constexpr int kResidualSteps = 4;
-enum { kWeightsKeep = 0, kWeightsUnit = 1, kWeightsScatter = 2 };
+enum { kWeightsUnit, kWeightsScatter };
 
 constexpr int kResidualRound = kResidualLanes * kResidualSteps;
 
@@ -240,8 +240,8 @@ __device__ __forceinline__ double wave_row_sum(const DevProblem& P, const double
   return sum;
 }
 
-// Writes row i's residual r and weights (kWeightsKeep: r only; Unit: 1 and
-// the twin's 1; Scatter: the caller's w0 and w1) and, with grow, its compact
+// Writes row i's residual r and weights (Unit: 1 and the twin's 1;
+// Scatter: the caller's w0 and w1) and, with grow, its compact
 // copy; with the caller's weights the copy is checked as well: the state
 // initialisation has run and checked the cutoff weight, and a residual or
 // weight that does not fit clears st->compact_rows.
@@ -249,35 +249,31 @@ template <int kWeights>
 __device__ __forceinline__ void write_residual(int64_t i, double r, float w0, float w1, bool twin,
                                                RowState* __restrict__ rs, GatherRow* __restrict__ grow,
                                                WalkState* st_w) {
-  if constexpr (kWeights == kWeightsKeep) {
-    rs[i].r = r;
-  } else {
-    RowState q;
-    q.r = r;
-    q.w0 = w0;
-    q.w1 = twin ? w1 : -1.0f;
-    if constexpr (kWeights == kWeightsUnit) {
-      q.w0 = 1.0f;
-      q.w1 = twin ? 1.0f : -1.0f;
-      if (grow) {
-        GatherRow cr;
-        cr.r = (int32_t)r;
-        cr.w0 = 1;
-        cr.w1 = twin ? (uint16_t)1 : kNoTwin;
-        grow[i] = cr;
-      }
-    } else if (grow) {
-      const bool ok = r == floor(r) && fabs(r) <= 2147483647.0 && q.w0 == floorf(q.w0) && q.w0 >= 0.0f &&
-                      q.w0 < 65535.0f && (q.w1 < 0.0f || (q.w1 == floorf(q.w1) && q.w1 < 65535.0f));
-      if (!ok) st_w->compact_rows = 0;  // every writer stores the same value
+  RowState q;
+  q.r = r;
+  q.w0 = w0;
+  q.w1 = twin ? w1 : -1.0f;
+  if constexpr (kWeights == kWeightsUnit) {
+    q.w0 = 1.0f;
+    q.w1 = twin ? 1.0f : -1.0f;
+    if (grow) {
       GatherRow cr;
-      cr.r = ok ? (int32_t)r : 0;
-      cr.w0 = ok ? (uint16_t)q.w0 : 0;
-      cr.w1 = (ok && q.w1 >= 0.0f) ? (uint16_t)q.w1 : kNoTwin;
+      cr.r = (int32_t)r;
+      cr.w0 = 1;
+      cr.w1 = twin ? (uint16_t)1 : kNoTwin;
       grow[i] = cr;
     }
-    rs[i] = q;
+  } else if (grow) {
+    const bool ok = r == floor(r) && fabs(r) <= 2147483647.0 && q.w0 == floorf(q.w0) && q.w0 >= 0.0f &&
+                    q.w0 < 65535.0f && (q.w1 < 0.0f || (q.w1 == floorf(q.w1) && q.w1 < 65535.0f));
+    if (!ok) st_w->compact_rows = 0;  // every writer stores the same value
+    GatherRow cr;
+    cr.r = ok ? (int32_t)r : 0;
+    cr.w0 = ok ? (uint16_t)q.w0 : 0;
+    cr.w1 = (ok && q.w1 >= 0.0f) ? (uint16_t)q.w1 : kNoTwin;
+    grow[i] = cr;
   }
+  rs[i] = q;
 }
 
 // Rows of more than kResLongRow entries are left to the grid's last
@@ -310,7 +306,7 @@ __global__ __launch_bounds__(256) void k_residual(DevProblem P, int32_t group_bl
   bool twin = false;
   if (g == 0) {
     rhs = P.row_rhs[i];
-    if constexpr (kWeights != kWeightsKeep) twin = pair[i] != 0;
+    twin = pair[i] != 0;
     if constexpr (kWeights == kWeightsScatter) {
       const int k = nidx[i];
       w0 = w[k];
@@ -425,8 +421,7 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
     for (int t = threadIdx.x; t < rows; t += kResBlockedThreads) {
       const int64_t i = i0 + t;
       float w0 = 1.0f, w1 = -1.0f;
-      bool twin = false;
-      if constexpr (kWeights != kWeightsKeep) twin = pair[i] != 0;
+      const bool twin = pair[i] != 0;
       if constexpr (kWeights == kWeightsScatter) {
         const int k = nidx[i];
         w0 = w[k];
@@ -445,8 +440,7 @@ __global__ __launch_bounds__(kResBlockedThreads) void k_residual_blocked(
       for (int o = 1; o < kResidualLanes; o <<= 1) sum = sum + __shfl_xor(sum, o, kResidualLanes);
       if (g != 0) continue;
       float w0 = 1.0f, w1 = -1.0f;
-      bool twin = false;
-      if constexpr (kWeights != kWeightsKeep) twin = pair[i] != 0;
+      const bool twin = pair[i] != 0;
       if constexpr (kWeights == kWeightsScatter) {
         const int k = nidx[i];
         w0 = w[k];
@@ -933,8 +927,6 @@ __device__ __forceinline__ void step_finish(const WalkCtx& C, const StepMove& M,
   }
   o.store(st);
   st->mv_j = M.q;
-  st->mv_kind = M.kind;
-  st->mv_old = M.x_old;
   st->mv_new = M.x_new;
   st->aff_ok = aff;
   st->dV = 0ull;
@@ -1556,14 +1548,6 @@ inline dim3 residual_grid(const DevProblem& P) {
 }
 
 }  // namespace
-
-hipError_t launch_residual(const DevProblem& P, const double* x, RowState* rs, hipStream_t stream) {
-  if (P.ms > 0)
-    hipLaunchKernelGGL(k_residual<kWeightsKeep>, residual_grid(P), dim3(256), 0, stream, P,
-                       residual_groups(P.ms), x, nullptr, nullptr,
-                       0u, rs, nullptr, nullptr, nullptr, nullptr);
-  return hipGetLastError();
-}
 
 // The x-block kernel where the problem has its row layout and the call has
 // a byte copy of x (its own fallback covers a point that does not fit).
