@@ -594,7 +594,12 @@ inline bool pass_defers_combine(const BatchLaunch& L) {
 // places each block's values at their offsets in LDS and writes the block.
 constexpr int kPermChunk = 8192;  // input values per workgroup of the first pass
 constexpr int kPermBlock = 4096;  // output values per workgroup of the second pass
-constexpr int32_t kPermDirect = 1 << 19;  // columns up to which one gather is the faster form
+// Columns up to which one gather is the faster form: a call's time by the
+// gather and by the two passes was 56 and 67 us at 300k columns, 70 and 75 at
+// 500k, 73 and 77 at 530k, 90 and 83 at 800k, 101 and 87 at 1M, 132 and 102 at
+// 1.4M (sparse power-law instances, both permutations in it): they meet near
+// 640k, where the gathered words outgrow the 4 MB L2 of an XCD.
+constexpr int32_t kPermDirect = 5 << 17;
 struct PermPlan {
   int32_t n = 0;
   const uint16_t* lpos = nullptr;  // input e: rank in its chunk's (output block, e) order

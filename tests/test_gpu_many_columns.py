@@ -1,7 +1,7 @@
 """Sizes that take later rounds of loops which smaller tests run once: more than
 4096 move records of unstaged columns, more than 524,288 scanned scores, results of
 more than 64 MiB (and one walk of more than that), and single calls whose
-permutations go through staging (more than 2^19 columns). Sparse instances; walks
+permutations go through staging (more than 5 * 2^17 columns). Sparse instances; walks
 and calls equal the oracle's."""
 from __future__ import annotations
 
@@ -45,7 +45,7 @@ def test_results_in_rounds(chap):
             compare_runs(run, refs[which[w]], f"walk {w} of {len(which)}")
 
 
-@pytest.mark.parametrize("n", [524_288, 524_289, 528_385, 1_100_003])
+@pytest.mark.parametrize("n", [524_289, 655_360, 655_361, 659_457, 1_100_003])
 def test_staged_permutations(chap, n):
     import torch
 
